@@ -24,12 +24,13 @@
 #include "misc.h"
 #include "moe.h"
 
-// Scratch of dflash_accept_sampled_noalloc (the entry point for callers that cannot allocate): the rows' softmax
-// statistics, (max, log-sum-exp) of the target rows followed by those of the draft rows.  Every GPU the library runs
-// on holds its own copy of this array until the process ends; host code reaches it through the address that
+// Scratch of dflash_accept_sampled_noalloc (the entry point for callers that cannot allocate): the pieces of the rows'
+// softmax statistics (target rows, then draft rows), followed by the best scores of the vocabulary chunks.  Every GPU the
+// library runs on holds its own copy of this array until the process ends; host code reaches it through the address that
 // hipGetSymbolAddress returns for the current device, never through this name.
 #define DFLASH_NOALLOC_MAX_ROWS 4096
-static __device__ __align__(256) unsigned char scratch[2 * DFLASH_NOALLOC_MAX_ROWS * sizeof(float2)];
+#define DFLASH_NOALLOC_BESTS 4096
+static __device__ __align__(256) unsigned char scratch[(2 * DFLASH_NOALLOC_MAX_ROWS + DFLASH_NOALLOC_BESTS) * sizeof(float2)];
 
 namespace {
 
@@ -241,6 +242,32 @@ inline int arena_rows(int max_rows) { return std::max(1024, 4 * max_rows); }
 
 constexpr int ARGMAX_CHUNKS = 32;   // workgroups that share one vocabulary row in the argmax
 
+// ---- sampled acceptance (dflash_accept, dflash_accept_sampled_noalloc) -----------------------------
+// Workgroups per row of the statistics launch: enough for 4096 of them (16 a CU), not below 1024 columns each, and no
+// more pieces than `room` entries hold.  Workgroups per sequence of the sweep over the vocabulary: 1024 in all, 1024 columns
+// each at least, at most `room` in all.
+inline int lse_chunks(int rows, int V, size_t room) {
+  return (int)std::max<size_t>(1, std::min<size_t>({(size_t)(4096 / rows), (size_t)32, (size_t)(V / 1024), room / rows}));
+}
+inline int accept_chunks(int S, int V, size_t room) {
+  return (int)std::max<size_t>(1, std::min<size_t>({(size_t)(1024 / S), (size_t)64, (size_t)(V / 1024), room / S}));
+}
+// statistics of R rows of `a` and R rows of `b` (may be null with R_b = 0) in `chunks` pieces per row
+inline void launch_lse(hipStream_t st, const float* a, const float* b, int R, int R_b, int V, float inv_T, int chunks, float2* part) {
+  const dim3 grid(chunks, R + R_b), block(256);
+  if (V % 4 == 0 && (((uintptr_t)a | (uintptr_t)b) & 15) == 0)
+    hipLaunchKernelGGL(lse_partial_kernel<true>, grid, block, 0, st, a, b, R, V, inv_T, part);
+  else
+    hipLaunchKernelGGL(lse_partial_kernel<false>, grid, block, 0, st, a, b, R, V, inv_T, part);
+}
+inline void launch_accept_sampled(hipStream_t st, const float* p_logits, const float* q_logits, RowStats ps, RowStats qs, const int32_t* draft,
+                                  const float* uniforms, const uint64_t* key, int S, int B, int V, float inv_T, int32_t* accept_len,
+                                  int32_t* out_tokens, float2* best, size_t room) {
+  const int chunks = accept_chunks(S, V, room);
+  hipLaunchKernelGGL(accept_sampling_kernel, dim3(chunks, S), dim3(256), 0, st, p_logits, q_logits, ps, qs, draft, uniforms, key, V, B, inv_T, accept_len, best);
+  hipLaunchKernelGGL(accept_sampling_finish_kernel, dim3(S), dim3(64), 0, st, best, chunks, draft, B, accept_len, out_tokens);
+}
+
 struct Workspace {
   size_t status, arena, h, a, q, o, act, taps, fuse, ht, logits_d, logits_t, part_o, part_ml, stats_p, stats_q, amax, lsep, rope_t, rope_d, ssq, pf_lens, pf_plens, pf_table, pf_tokens, pf_end_row, pf_end_seq, pf_first, pf_anchor, total;
   size_t moe_sel_e, moe_sel_w, moe_sel_pos, moe_row_of, moe_items, moe_a, moe_act, moe_y;   // routed-expert target only
@@ -290,7 +317,8 @@ Workspace workspace_layout(const dflash_dims& t, const dflash_dims& d, const dfl
   w.stats_p = take((size_t)M * 8);
   w.stats_q = take((size_t)M * 8);
   w.amax = take((size_t)M * std::max(ARGMAX_CHUNKS, t.vocab / 16 + 1) * 8);   // one partial per weight row band at most
-  w.lsep = take((size_t)M * (t.vocab / 16 + 1) * 8);    // per-workgroup softmax statistics of an LM-head launch
+  // per-workgroup softmax statistics of an LM-head launch, or the pieces of both models' rows (lse_partial_kernel)
+  w.lsep = take((size_t)M * std::max(2, t.vocab / 16 + 1) * 8);
   w.rope_t = take((size_t)M * (t.head_dim / 2) * 8);   // rotary tables of the call's rows (target, draft)
   w.rope_d = take((size_t)M * (d.head_dim / 2) * 8);
   w.ssq = take((size_t)M * (D / 16 + 1) * 4);          // pieces of the rows' sums of squares (deferred RMSNorm, few-row path)
@@ -709,17 +737,20 @@ struct Engine {
       const float inv_T = 1.0f / temperature;
       // the (max, log-sum-exp) rows normally come out of the LM-head epilogues; another temperature than the one
       // the draft was sampled at, or a kernel without that epilogue, takes them from the stored logits
-      if (c->stats_p_T != temperature) {
-        hipLaunchKernelGGL(row_lse_kernel, dim3(M), dim3(1024), 0, st, ws<float>(c->ws.logits_t), V, inv_T, ws<float2>(c->ws.stats_p));
+      RowStats ps{ws<float2>(c->ws.stats_p), 0}, qs{ws<float2>(c->ws.stats_q), 0};
+      const size_t room = (size_t)M * std::max(2, V / 16 + 1);   // entries of ws.lsep and, at least, of ws.amax
+      if (c->stats_p_T != temperature || c->stats_q_T != temperature) {
+        float2* part = ws<float2>(c->ws.lsep);
+        const bool both = c->stats_p_T != temperature && c->stats_q_T != temperature;
+        const int chunks = lse_chunks(both ? 2 * M : M, V, room);
+        if (both) launch_lse(st, ws<float>(c->ws.logits_t), ws<float>(c->ws.logits_d), M, M, V, inv_T, chunks, part);
+        else launch_lse(st, ws<float>(c->stats_p_T != temperature ? c->ws.logits_t : c->ws.logits_d), nullptr, M, 0, V, inv_T, chunks, part);
         check();
+        if (c->stats_p_T != temperature) ps = RowStats{part, chunks};
+        if (c->stats_q_T != temperature) qs = RowStats{both ? part + (size_t)M * chunks : part, chunks};
       }
-      if (c->stats_q_T != temperature) {
-        hipLaunchKernelGGL(row_lse_kernel, dim3(M), dim3(1024), 0, st, ws<float>(c->ws.logits_d), V, inv_T, ws<float2>(c->ws.stats_q));
-        check();
-      }
-      hipLaunchKernelGGL(accept_sampling_kernel, dim3(S), dim3(1024), 0, st, ws<float>(c->ws.logits_t), ws<float>(c->ws.logits_d),
-                         ws<float2>(c->ws.stats_p), ws<float2>(c->ws.stats_q), draft_tokens, uniforms, rng_key, V, B, inv_T,
-                         accept_len, out_tokens);
+      launch_accept_sampled(st, ws<float>(c->ws.logits_t), ws<float>(c->ws.logits_d), ps, qs, draft_tokens, uniforms, rng_key, S, B, V, inv_T,
+                            accept_len, out_tokens, ws<float2>(c->ws.amax), room);
       check();
     }
     return hip_err ? DFLASH_EHIP : DFLASH_OK;
@@ -1661,15 +1692,15 @@ int dflash_accept_sampled_noalloc(const float* target_logits, const float* draft
   void* base = nullptr;
   int rc;
   if ((rc = noalloc_scratch(&base))) return rc;
-  float2* stats_p = reinterpret_cast<float2*>(base);
-  float2* stats_q = stats_p + DFLASH_NOALLOC_MAX_ROWS;
+  float2* part = reinterpret_cast<float2*>(base);
+  float2* best = part + 2 * DFLASH_NOALLOC_MAX_ROWS;
   hipStream_t st = (hipStream_t)stream;
   const int M = n_seqs * block_size;
   const float inv_T = 1.0f / temperature;
-  hipLaunchKernelGGL(row_lse_kernel, dim3(M), dim3(1024), 0, st, target_logits, vocab, inv_T, stats_p);
-  hipLaunchKernelGGL(row_lse_kernel, dim3(M), dim3(1024), 0, st, draft_logits, vocab, inv_T, stats_q);
-  hipLaunchKernelGGL(accept_sampling_kernel, dim3(n_seqs), dim3(1024), 0, st, target_logits, draft_logits, stats_p, stats_q, draft_tokens, uniforms,
-                     rng_key, vocab, block_size, inv_T, accept_len, out_tokens);
+  const int chunks = lse_chunks(2 * M, vocab, 2 * DFLASH_NOALLOC_MAX_ROWS);
+  launch_lse(st, target_logits, draft_logits, M, M, vocab, inv_T, chunks, part);
+  launch_accept_sampled(st, target_logits, draft_logits, RowStats{part, chunks}, RowStats{part + (size_t)M * chunks, chunks}, draft_tokens, uniforms,
+                        rng_key, n_seqs, block_size, vocab, inv_T, accept_len, out_tokens, best, DFLASH_NOALLOC_BESTS);
   if (hipGetLastError() != hipSuccess) return fail(nullptr, DFLASH_EHIP, "accept_sampled_noalloc: launch failed");
   return DFLASH_OK;
 }

@@ -1,0 +1,100 @@
+"""Sizes at which single kernels can go wrong (edges of chunks and tiles, remainders, alignment, masked values), each
+against the CPU oracle."""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+
+from oracle import dflash_oracle as O
+from synth import inputs as si
+from tests.helpers import tiny_workload
+from tests.test_gpu_parity import Lockstep, _gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("S,B,V,T,shift", [
+    (1, 2, 8, 1.0, 0),          # one chunk, fewer columns than threads
+    (3, 5, 1003, 0.7, 0),       # rows of odd length: no 16-byte loads
+    (2, 16, 2052, 1.0, 1),      # whole 16-byte rows behind a pointer that is not 16-byte aligned
+    (5, 16, 33000, 0.7, 0),     # several chunks per row and per sequence, ragged last ones
+    (300, 2, 1040, 1.0, 0),     # many sequences: few chunks
+    (1, 16, 151936, 1.0, 0),
+    (256, 16, 64, 1.0, 0),      # the most rows the entry point takes
+])
+def test_sampled_acceptance_on_held_logits(S, B, V, T, shift):
+    """dflash_accept_sampled_noalloc against the oracle's acceptance rule, with masked (-inf) columns and, for some
+    sequences, every slot accepted (uniforms of 0, p = q).  A sequence whose decision hangs on less than 1e-4 (u q against
+    p, or the two best scores: fp32 logits of magnitude ~10 are good to 1e-6, their exponentials to ~1e-5) is left out."""
+    import torch
+    _gpu()
+    from paper_2602_06036_amd import binding as Bd
+    rng = np.random.default_rng([S, B, V])
+    q = (2.5 * rng.standard_normal((S, B, V))).astype(np.float32)
+    p = (2.5 * rng.standard_normal((S, B, V))).astype(np.float32)
+    p[:, :-1] = q[:, 1:] + (0.5 * rng.standard_normal((S, B - 1, V))).astype(np.float32)
+    p[1::3, :-1] = q[1::3, 1:]
+    masked = rng.choice(V, max(1, V // 7), replace=False)
+    p[:, :, masked] = -np.inf
+    q[:, :, masked] = -np.inf
+    d = np.zeros((S, B), np.int32)
+    for s in range(S):
+        for j in range(B):
+            d[s, j] = int(np.argmax(q[s, j] / T + rng.gumbel(size=V)))
+    u = rng.random((S, B)).astype(np.float32)
+    u[1::3] = 0.0
+    key = 987654321
+    dev = "cuda:0"
+
+    def up(x):
+        flat = torch.zeros(x.size + 4, dtype=torch.float32, device=dev)
+        v = flat[shift:shift + x.size].view(x.shape)
+        v.copy_(torch.from_numpy(x))
+        return v
+
+    acc = torch.full((S,), -7, dtype=torch.int32, device=dev)
+    out = torch.full((S, B), -7, dtype=torch.int32, device=dev)
+    for _ in range(2):
+        Bd.dflash_accept_sampled_noalloc(up(p), up(q), torch.from_numpy(d).to(dev), torch.from_numpy(u).to(dev),
+                                         torch.tensor([key], dtype=torch.int64, device=dev), T, acc, out)
+    acc, out = acc.cpu().numpy(), out.cpu().numpy()
+    checked = 0
+    for s in range(S):
+        P, Q = O.softmax(p[s].astype(np.float64) / T), O.softmax(q[s].astype(np.float64) / T)
+        rec = {}
+
+        def draw(w, slot, purpose):
+            with np.errstate(divide="ignore"):
+                rec["scores"] = O.gumbel_scores(np.log(w), key, s, slot, purpose)
+            return int(np.argmax(rec["scores"]))
+
+        a, tok = O.sampling_accept(P, Q, list(d[s]), list(u[s]), draw)
+        gaps = [abs(u[s, j] * Q[j, d[s, j]] / P[j - 1, d[s, j]] - 1.0) for j in range(1, min(a + 2, B))]
+        top = np.sort(rec["scores"][np.isfinite(rec["scores"])])[-2:]
+        if min(gaps) < 1e-4 or (top.size == 2 and top[1] - top[0] < 1e-4):
+            continue
+        checked += 1
+        assert acc[s] == a, (s, acc[s], a)
+        want = [int(x) for x in d[s, 1:a + 1]] + [tok] + [-1] * (B - a - 1)
+        assert list(out[s]) == want, (s, a)
+    assert checked >= 0.9 * S
+
+
+@pytest.mark.parametrize("hd,heads,kv_heads,ffn,lens", [
+    (16, 4, 4, 64, (1, 63)),          # a quarter of the lanes own a head dim; K = 64
+    (48, 4, 2, 1040, (64, 65)),       # down projection with its K over four wavefronts, the last piece short
+    (96, 6, 2, 2048, (15, 200)),      # second half of the head dims ragged; several chunks of keys
+    (128, 2, 1, 512, (129, 16)),
+])
+def test_fp32_head_dims_and_widths(hd, heads, kv_heads, ffn, lens):
+    """fp32 models: generic attention and GEMM kernels over head dims, head groups, widths and context lengths."""
+    w = tiny_workload(seed=hd + ffn, n_layers=2, draft_layers=1, vocab=512, block=8, qk_norm=True, kv_heads=kv_heads, n_seqs=2,
+                      taps=(0, 1), d=hd * heads, heads=heads, hd=hd, ffn=ffn)
+    prompts = [p[:n] for p, n in zip(si.make_prompts(replace(w, ctx_min=200, ctx_max=200)), lens)]
+    ls = Lockstep(w, prompts, max_len=200 + 6 * 8)
+    _, _, mism = ls.prefill()
+    assert not mism
+    for i, plan in enumerate([[0, 7], [7, 3], None]):
+        ls.step(plan=plan, step_idx=i)
+    ls.check_cache([0, 1], [0])
+    assert ls.stats["reseeds"] == 0
