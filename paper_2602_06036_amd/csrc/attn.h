@@ -22,15 +22,26 @@ struct AttnArgs {
 // (o unnormalised, relative to the running max)
 
 // ------------------------------------------------------------------------------------------------
-// Generic kernel (any storage type; plain ALU math).  grid (n_splits, Hkv, S), block 256.
-// A wavefront takes query rows r = wave, wave+4, ... of the B*group rows that share this kv head.
+// Generic kernel (any storage type; plain ALU math).  grid (n_splits, Hkv * row groups, S), block 256.
+// A wavefront takes query rows r = group * 4 + wave, + 4 * groups, ... of the B*group rows that share this kv head.
+// Bound by latency: a chunk is 64 keys or little more, so what counts is that nothing waits that need not.  A lane owns a
+// key for the scores and one or two head dims for P.V; the 64 V rows of a tile are requested together, four keys a load,
+// before their weights are known (8 rows, 136 keys, 4 heads of 64, fp32: 35.9 us with one dependent load per key, 8.9 us like this).
 // ------------------------------------------------------------------------------------------------
+template <typename T>
+__device__ __forceinline__ float4 load_keys4(const T* p) {   // 4 consecutive keys of one head dim of a page
+  if constexpr (sizeof(T) == 4) return *reinterpret_cast<const float4*>(p);
+  const ushort4 u = *reinterpret_cast<const ushort4*>(p);
+  return make_float4(Store<T>::to(u.x), Store<T>::to(u.y), Store<T>::to(u.z), Store<T>::to(u.w));
+}
+
 template <typename T>
 __global__ __launch_bounds__(256) void attn_partial_simple_kernel(const T* __restrict__ q, const T* __restrict__ pool,
                                                                   SeqGeom geo, AttnArgs aa, float* __restrict__ part_o,
                                                                   float2* __restrict__ part_ml) {
-  const int split = blockIdx.x, kvh = blockIdx.y, s = blockIdx.z;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int split = blockIdx.x, kvh = (int)blockIdx.y % aa.n_kv_heads, s = blockIdx.z;
+  const int row_group = (int)blockIdx.y / aa.n_kv_heads, row_groups = (int)gridDim.y / aa.n_kv_heads;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int hd = aa.head_dim, B = geo.block_size;
   const int group = aa.n_q_heads / aa.n_kv_heads;
   const int rows = B * group;
@@ -41,8 +52,9 @@ __global__ __launch_bounds__(256) void attn_partial_simple_kernel(const T* __res
   const int c1 = min(n_tok, c0 + aa.chunk);
   __shared__ float qs[4][128];
   const int32_t* table = geo.block_table + (size_t)s * geo.max_pages_per_seq;
+  const int d0 = min(lane, hd - 1), d1 = min(lane + 64, hd - 1);   // this lane's head dims (clamped: not stored)
 
-  for (int r = wave; r < rows; r += 4) {
+  for (int r = row_group * 4 + wave; r < rows; r += 4 * row_groups) {
     const int slot = r / group, hq = kvh * group + r % group;
     const int m = s * B + slot;
     const size_t pr = ((size_t)m * aa.n_q_heads + hq) * aa.n_splits + split;
@@ -55,19 +67,33 @@ __global__ __launch_bounds__(256) void attn_partial_simple_kernel(const T* __res
       const int pos = t0 + lane;
       const bool vis = pos < c1 && pos <= last_vis;
       int page = -1;
-      if (vis) page = table[pos / DF_PAGE];
-      const bool ok = vis && page >= 0 && page < geo.n_pages;
+      if (pos < c1) page = table[pos / DF_PAGE];
+      const bool page_ok = page >= 0 && page < geo.n_pages;
+      const bool ok = vis && page_ok;
+      const int any_page = page_ok ? page : 0;     // a page that may be read; keys behind it then weigh nothing
+      // the tile's V rows (t0 is a multiple of 64: four whole pages), on their way while the scores are computed
+      float4 v0[16], v1[16];
+#pragma unroll
+      for (int pg = 0; pg < 4; ++pg) {
+        const T* vb = pool + kv_head_base(aa.layer, geo.n_pages, __builtin_amdgcn_readlane(any_page, pg * 16), aa.n_kv_heads, kvh, hd) + DF_PAGE * hd;
+#pragma unroll
+        for (int k4 = 0; k4 < 4; ++k4) {
+          v0[pg * 4 + k4] = load_keys4(vb + v_in_page(k4 * 4, d0));
+          if (hd > 64) v1[pg * 4 + k4] = load_keys4(vb + v_in_page(k4 * 4, d1));
+        }
+      }
       float sc = -INFINITY;
-      if (ok) {
-        const T* kb = pool + kv_head_base(aa.layer, geo.n_pages, page, aa.n_kv_heads, kvh, hd);
+      {
+        const T* kb = pool + kv_head_base(aa.layer, geo.n_pages, any_page, aa.n_kv_heads, kvh, hd);
         const int key = pos % DF_PAGE;
         float acc = 0.f;
+#pragma unroll 4
         for (int d = 0; d < hd; d += 8) {
           const T* kp = kb + k_in_page(key, d);
 #pragma unroll
           for (int e = 0; e < 8; ++e) acc += qs[wave][d + e] * Store<T>::to(kp[e]);
         }
-        sc = acc * aa.scale;
+        if (ok) sc = acc * aa.scale;
       }
       const float tmax = wave_reduce_max(sc);
       if (tmax == -INFINITY) continue;   // uniform across the wavefront
@@ -78,16 +104,15 @@ __global__ __launch_bounds__(256) void attn_partial_simple_kernel(const T* __res
       o0 *= corr;
       o1 *= corr;
       m_run = m_new;
-      const int n_in_tile = min(64, c1 - t0);
-      for (int kk = 0; kk < n_in_tile; ++kk) {
-        const float pk = __shfl(p, kk, 64);
-        if (pk == 0.f) continue;         // uniform
-        const int kpos = t0 + kk;
-        const int pg = table[kpos / DF_PAGE];
-        const T* vb = pool + kv_head_base(aa.layer, geo.n_pages, pg, aa.n_kv_heads, kvh, hd) + DF_PAGE * hd;
-        const int key = kpos % DF_PAGE;
-        if (lane < hd) o0 += pk * Store<T>::to(vb[v_in_page(key, lane)]);
-        if (lane + 64 < hd) o1 += pk * Store<T>::to(vb[v_in_page(key, lane + 64)]);
+      // a key that weighs nothing is left out whatever its V row holds (never written, or another sequence's)
+      auto add = [&](float& o, float pk, float v) { o += pk == 0.f ? 0.f : pk * v; };
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const float p0 = __shfl(p, 4 * i, 64), p1 = __shfl(p, 4 * i + 1, 64), p2 = __shfl(p, 4 * i + 2, 64), p3 = __shfl(p, 4 * i + 3, 64);
+        add(o0, p0, v0[i].x); add(o0, p1, v0[i].y); add(o0, p2, v0[i].z); add(o0, p3, v0[i].w);
+        if (hd > 64) {
+          add(o1, p0, v1[i].x); add(o1, p1, v1[i].y); add(o1, p2, v1[i].z); add(o1, p3, v1[i].w);
+        }
       }
     }
     if (lane == 0) part_ml[pr] = make_float2(m_run, l_run);

@@ -1218,12 +1218,17 @@ template <>
 Engine<float>::Slab Engine<float>::gemm(const float* W, const float* A, int M, int N, int K, int epi, EpiArgs ep, bool) {
   ProfScope prof(c, st, gemm_class(epi, N, c->t.vocab), (double)N * K * 4);
   const int cols = epi == EPI_SWIGLU ? N / 2 : N;
-  const dim3 grid((cols + 3) / 4), block(256);
-  switch (epi) {
-    case EPI_STORE: hipLaunchKernelGGL(gemm_f32_kernel<EPI_STORE>, grid, block, 0, st, W, A, M, N, K, ep); break;
-    case EPI_RESID: hipLaunchKernelGGL(gemm_f32_kernel<EPI_RESID>, grid, block, 0, st, W, A, M, N, K, ep); break;
-    default: hipLaunchKernelGGL(gemm_f32_kernel<EPI_SWIGLU>, grid, block, 0, st, W, A, M, N, K, ep); break;
-  }
+  // four wavefronts per column where K has a 256-wide piece for each and one column per workgroup still leaves the launch
+  // within a few rounds of the CUs; more columns share the activation rows over the workgroup's wavefronts instead
+  const bool split = K >= 1024 && cols <= 2048;
+  auto launch = [&](auto ec) {
+    constexpr int E = decltype(ec)::value;
+    if (split) hipLaunchKernelGGL((gemm_f32_kernel<E, 4>), dim3(cols), dim3(256), 0, st, W, A, M, N, K, ep);
+    else hipLaunchKernelGGL((gemm_f32_kernel<E, 1>), dim3((cols + 3) / 4), dim3(256), 0, st, W, A, M, N, K, ep);
+  };
+  if (epi == EPI_STORE) launch(std::integral_constant<int, EPI_STORE>{});
+  else if (epi == EPI_RESID) launch(std::integral_constant<int, EPI_RESID>{});
+  else launch(std::integral_constant<int, EPI_SWIGLU>{});
   check();
   ++c->gemm_counts[DFLASH_GEMM_F32];
   if (epi == EPI_STORE) return Slab{ep.out, 1, (size_t)M * ep.ld};
@@ -1274,8 +1279,14 @@ void Engine<T>::attention(const dflash_dims& m, const T* pool, int layer, const 
     // algorithmic bytes: every cached K and V row of this layer once (upper bound from the host hint)
     ProfScope prof(c, st, DFLASH_PROF_ATTN, (double)S * max_tokens * 2 * m.n_kv_heads * m.head_dim * sizeof(T));
     if (!attn_mfma_launch<T>(st, ws<T>(c->ws.q), pool, geom(b), aa, S, part_o, part_ml, c->k.attn_wide_min_chunk))
-      hipLaunchKernelGGL(attn_partial_simple_kernel<T>, dim3(p.n_splits, m.n_kv_heads, S), dim3(256), 0, st, ws<T>(c->ws.q), pool,
+    {
+      // query rows of a kv head over several workgroups while that leaves at most two of them a CU (each reads the
+      // chunk's keys for itself, so a launch that fills the chip keeps them together)
+      const int wgs = p.n_splits * m.n_kv_heads * S, rows = B * (m.n_q_heads / m.n_kv_heads);
+      const int groups = std::max(1, std::min(512 / wgs, (rows + 3) / 4));
+      hipLaunchKernelGGL(attn_partial_simple_kernel<T>, dim3(p.n_splits, m.n_kv_heads * groups, S), dim3(256), 0, st, ws<T>(c->ws.q), pool,
                          geom(b), aa, part_o, part_ml);
+    }
     check();
   }
   {
