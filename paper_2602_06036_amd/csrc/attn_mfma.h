@@ -22,59 +22,31 @@ struct KvFrags {
 };
 
 struct AttnLane {          // per-lane constants of the kernel below
-  const int32_t* table;
   int c0, c1, n_tok, last_vis, g, lane, kvh;
 };
 
-// issues the loads of page pair (pa, pb); pb < 0 means the chunk ends after page A.  STREAM: the fragments are
-// used by this wavefront only (key-split kernel), so they are loaded non-temporally and do not displace anything
-// from the caches; the row-split kernel's four wavefronts read the same fragments and want them cached.
-template <int HD, bool STREAM = false>
-__device__ __forceinline__ void attn_load_pages(KvFrags<HD>& f, int pa, int pb, bool has_b, const bf16_t* __restrict__ pool,
-                                                const SeqGeom& geo, const AttnArgs& aa, const AttnLane& L) {
+// issues the loads of the page pair p of the chunk; pa, pb: its page ids (a foreign or missing page aliases a readable one)
+template <int HD>
+__device__ __forceinline__ void attn_load_pair(KvFrags<HD>& f, int p, int pa, int pb, const bf16_t* __restrict__ pool, const SeqGeom& geo,
+                                               const AttnArgs& aa, const AttnLane& L) {
+  const bool has_b = L.c0 + p * 32 + 16 < L.c1;
   f.ok_a = pa >= 0 && pa < geo.n_pages;
   if (!f.ok_a) pa = 0;
   f.ok_b = has_b && pb >= 0 && pb < geo.n_pages;
   if (!f.ok_b) pb = pa;
   const bf16_t* ka = pool + kv_head_base(aa.layer, geo.n_pages, pa, aa.n_kv_heads, L.kvh, HD);
   const bf16_t* kb = pool + kv_head_base(aa.layer, geo.n_pages, pb, aa.n_kv_heads, L.kvh, HD);
-  if constexpr (STREAM) {
-    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 #pragma unroll
-    for (int kt = 0; kt < HD / 32; ++kt) {
-      f.ka[kt] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(ka) + kt * 64 + L.lane);
-      f.kb[kt] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(kb) + kt * 64 + L.lane);
-    }
-#pragma unroll
-    for (int dt = 0; dt < HD / 16; ++dt) {
-      const u32x2 a = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(ka + DF_PAGE * HD) + dt * 64 + L.lane);
-      const u32x2 b = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(kb + DF_PAGE * HD) + dt * 64 + L.lane);
-      f.v[dt] = (u32x4){a[0], a[1], b[0], b[1]};
-    }
-  } else {
-#pragma unroll
-    for (int kt = 0; kt < HD / 32; ++kt) {
-      f.ka[kt] = reinterpret_cast<const u32x4*>(ka)[kt * 64 + L.lane];
-      f.kb[kt] = reinterpret_cast<const u32x4*>(kb)[kt * 64 + L.lane];
-    }
-#pragma unroll
-    for (int dt = 0; dt < HD / 16; ++dt) {
-      const uint2 a = reinterpret_cast<const uint2*>(ka + DF_PAGE * HD)[dt * 64 + L.lane];
-      const uint2 b = reinterpret_cast<const uint2*>(kb + DF_PAGE * HD)[dt * 64 + L.lane];
-      f.v[dt] = (u32x4){a.x, a.y, b.x, b.y};
-    }
+  for (int kt = 0; kt < HD / 32; ++kt) {
+    f.ka[kt] = reinterpret_cast<const u32x4*>(ka)[kt * 64 + L.lane];
+    f.kb[kt] = reinterpret_cast<const u32x4*>(kb)[kt * 64 + L.lane];
   }
-}
-
-template <int HD>
-__device__ __forceinline__ void attn_load_pair(KvFrags<HD>& f, int p, const bf16_t* __restrict__ pool, const SeqGeom& geo,
-                                               const AttnArgs& aa, const AttnLane& L) {
-  const int base = L.c0 + p * 32;           // first key of page A; page B starts at base + 16
-  const int ia = base >> 4;
-  const bool has_b = base + 16 < L.c1;
-  const int pa = L.table[ia];
-  const int pb = has_b ? L.table[ia + 1] : pa;
-  attn_load_pages<HD>(f, pa, pb, has_b, pool, geo, aa, L);
+#pragma unroll
+  for (int dt = 0; dt < HD / 16; ++dt) {
+    const uint2 a = reinterpret_cast<const uint2*>(ka + DF_PAGE * HD)[dt * 64 + L.lane];
+    const uint2 b = reinterpret_cast<const uint2*>(kb + DF_PAGE * HD)[dt * 64 + L.lane];
+    f.v[dt] = (u32x4){a.x, a.y, b.x, b.y};
+  }
 }
 
 template <int HD>
@@ -152,7 +124,7 @@ __device__ __forceinline__ void attn_process_pair(KvFrags<HD>& f, int p, const u
 }
 
 template <int HD>
-__global__ __launch_bounds__(256) void attn_mfma_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ pool,
+__global__ __launch_bounds__(256, 2) void attn_mfma_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ pool,
                                                         SeqGeom geo, AttnArgs aa, float* __restrict__ part_o,
                                                         float2* __restrict__ part_ml) {
   constexpr int KT = HD / 32, DT = HD / 16;
@@ -167,8 +139,12 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(const bf16_t* __restrict
   const int B = geo.block_size;
   const int group = (aa.n_q_heads / aa.n_kv_heads) >> aa.q_shift;   // query heads of this workgroup: blockIdx.y ("kvh") counts such head groups
   const int rows = B * group;
-  const int n_s = geo.seq_lens[s];
   const int cap = geo.max_pages_per_seq * DF_PAGE;
+  const int32_t* table = geo.block_table + (size_t)s * geo.max_pages_per_seq;
+  // page ids of the chunk, 32 pairs at a time: lane l holds page l of the set.  The first set and the queries do not
+  // depend on the sequence's length: the three round trips to memory overlap
+  auto load_ids = [&](int p0) { return table[min((split * aa.chunk >> 4) + 2 * p0 + lane, geo.max_pages_per_seq - 1)]; };
+  int ids = load_ids(0);
 
   // ---- this lane's query column: row r of the kv head's row set
   const int r = wave * 16 + n;
@@ -176,8 +152,18 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(const bf16_t* __restrict
   const int slot = valid ? r / group : 0, hq = kvh * group + (valid ? r % group : 0);
   const size_t pr = ((size_t)(s * B + slot) * aa.n_q_heads + hq) * aa.n_splits + split;
 
+  // query fragments (B operand of S^T): lane (n, g) holds Q[row][kt*32 + g*8 .. +8]
+  u32x4 qf[KT];
+  {
+    const u32x4* qp = reinterpret_cast<const u32x4*>(q + ((size_t)(s * B + slot) * aa.n_q_heads + hq) * HD);
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) {
+      qf[kt] = qp[kt * 4 + g];
+      if (!valid) qf[kt] = (u32x4){0u, 0u, 0u, 0u};
+    }
+  }
+  const int n_s = geo.seq_lens[s];
   AttnLane L;
-  L.table = geo.block_table + (size_t)s * geo.max_pages_per_seq;
   L.n_tok = min(n_s + B, cap);
   L.c0 = split * aa.chunk;
   L.c1 = min(L.n_tok, L.c0 + aa.chunk);
@@ -185,14 +171,6 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(const bf16_t* __restrict
   L.g = g;
   L.lane = lane;
   L.kvh = kvh >> aa.q_shift;
-
-  // query fragments (B operand of S^T): lane (n, g) holds Q[row][kt*32 + g*8 .. +8]
-  u32x4 qf[KT];
-  {
-    const u32x4* qp = reinterpret_cast<const u32x4*>(q + ((size_t)(s * B + slot) * aa.n_q_heads + hq) * HD);
-#pragma unroll
-    for (int kt = 0; kt < KT; ++kt) qf[kt] = valid ? qp[kt * 4 + g] : (u32x4){0u, 0u, 0u, 0u};
-  }
 
   float m_run = -INFINITY, l_run = 0.f;   // l_run: this lane's share (its 8 keys per pair) of the row sum
   f32x4 acc[DT];
@@ -205,16 +183,21 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(const bf16_t* __restrict
   // are peeled off.
   if (n_pairs > 0) {
     KvFrags<HD> f0, f1;
-    attn_load_pair<HD>(f0, 0, pool, geo, aa, L);
+    auto load = [&](KvFrags<HD>& f, int p) {
+      const int at = 2 * (p & 31);
+      attn_load_pair<HD>(f, p, __builtin_amdgcn_readlane(ids, at), __builtin_amdgcn_readlane(ids, at + 1), pool, geo, aa, L);
+    };
+    load(f0, 0);
     int p = 0;
     for (; p + 2 < n_pairs; p += 2) {
-      attn_load_pair<HD>(f1, p + 1, pool, geo, aa, L);
+      load(f1, p + 1);
       attn_process_pair<HD>(f0, p, qf, acc, m_run, l_run, aa.scale, L);
-      attn_load_pair<HD>(f0, p + 2, pool, geo, aa, L);
+      if (((p + 2) & 31) == 0) ids = load_ids(p + 2);   // every 1024 keys
+      load(f0, p + 2);
       attn_process_pair<HD>(f1, p + 1, qf, acc, m_run, l_run, aa.scale, L);
     }
     if (p + 1 < n_pairs) {
-      attn_load_pair<HD>(f1, p + 1, pool, geo, aa, L);
+      load(f1, p + 1);
       attn_process_pair<HD>(f0, p, qf, acc, m_run, l_run, aa.scale, L);
       attn_process_pair<HD>(f1, p + 1, qf, acc, m_run, l_run, aa.scale, L);
     } else {
@@ -237,10 +220,17 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(const bf16_t* __restrict
 // ------------------------------------------------------------------------------------------------
 // Long-chunk variant (hundreds of keys or more per workgroup).  The kernel above keeps only one page pair
 // of unique bytes in flight per CU (its four wavefronts read the same keys), which is latency-bound once a
-// chunk is long.  Here the four wavefronts split the KEYS instead: wavefront w takes page pairs w, w+4, ...
-// of the chunk for all RB = 4 blocks of 16 query rows, each with its own pair in flight (4x the bytes in
-// flight, K/V fragments read from HBM exactly once per workgroup), and the four partial (max, sum, O) sets
-// are merged through LDS at the end with the same log-sum-exp rule as the cross-split merge.
+// chunk is long.  Here eight wavefronts split the KEYS instead: wavefront w takes page pairs w, w+8, ...
+// of the chunk for all RB blocks of 16 query rows (K/V fragments come from HBM exactly once per workgroup), and the
+// partial (max, sum, O) sets are merged through LDS at the end with the same log-sum-exp rule as the cross-split merge.
+//
+// A long sweep is bound by HBM, a short one by the wavefronts' own chain (scores -> softmax -> P.V), so both have to
+// be covered.  The pages go straight to LDS (global_load_lds_dwordx4, a private 16 KB per wavefront): nothing in flight
+// costs a register, the accumulators and one pair's scores fit 256 of them, and a SIMD holds two wavefronts, one's
+// matrix instructions beside the other's softmax.  K and V halves are refilled separately, K as soon as a pair's scores are
+// done, V as soon as its products are, so up to 128 KB per CU are on their way.  The loads are inline assembly and
+// counted by hand (8 per half, in order): the compiler would wait for all of them before every LDS read.
+// WIDE_FIG
 // ------------------------------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t pack_bf16_pair(float a, float b) {   // RNE, a in the low half
   typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
@@ -250,115 +240,18 @@ __device__ __forceinline__ uint32_t pack_bf16_pair(float a, float b) {   // RNE,
 }
 
 template <int HD, int RB>
-__device__ __forceinline__ void attn_process_pair_wide(KvFrags<HD>& f, int base, const u32x4* __restrict__ q_lds,
-                                                       f32x4 (&acc)[RB][HD / 16], float (&m_run)[RB], float (&l_run)[RB],
-                                                       const int (&last_vis)[RB], int n_all_vis, float scale2, const AttnLane& L, f32x4* rescale_lds) {
-  constexpr int KT = HD / 32, DT = HD / 16;
-  if (base + 32 > L.n_tok || !f.ok_a || !f.ok_b) {   // never-written rows / foreign pages: clear V (0 * garbage != NaN)
-    const int pos_a = base + 4 * L.g, pos_b = base + 16 + 4 * L.g;
-    uint32_t ma0 = 0u, ma1 = 0u, mb0 = 0u, mb1 = 0u;
-    if (f.ok_a && pos_a + 0 < L.n_tok) ma0 |= 0x0000FFFFu;
-    if (f.ok_a && pos_a + 1 < L.n_tok) ma0 |= 0xFFFF0000u;
-    if (f.ok_a && pos_a + 2 < L.n_tok) ma1 |= 0x0000FFFFu;
-    if (f.ok_a && pos_a + 3 < L.n_tok) ma1 |= 0xFFFF0000u;
-    if (f.ok_b && pos_b + 0 < L.n_tok) mb0 |= 0x0000FFFFu;
-    if (f.ok_b && pos_b + 1 < L.n_tok) mb0 |= 0xFFFF0000u;
-    if (f.ok_b && pos_b + 2 < L.n_tok) mb1 |= 0x0000FFFFu;
-    if (f.ok_b && pos_b + 3 < L.n_tok) mb1 |= 0xFFFF0000u;
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt) f.v[dt] &= (u32x4){ma0, ma1, mb0, mb1};
-  }
-  // every key of the pair visible to every row (the bulk of a long context): no per-element masking
-  const bool all_vis = f.ok_a && f.ok_b && base + 32 <= n_all_vis;
-  const int pa0 = base + 4 * L.g;
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    f32x4 sa = {0.f, 0.f, 0.f, 0.f}, sb = {0.f, 0.f, 0.f, 0.f};
-    u32x4 qf[KT];   // query fragments of this row block, kept in LDS between uses
-    asm volatile("" ::: "memory");   // keep these reads inside the loop: hoisted, they would cost 64 registers
-#pragma unroll
-    for (int kt = 0; kt < KT; ++kt) qf[kt] = q_lds[(rb * KT + kt) * 64 + L.lane];
-#pragma unroll
-    for (int kt = 0; kt < KT; ++kt) {
-      sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f.ka[kt]), __builtin_bit_cast(bf16x8, qf[kt]), sa, 0, 0, 0);
-      sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f.kb[kt]), __builtin_bit_cast(bf16x8, qf[kt]), sb, 0, 0, 0);
-    }
-    float v[8];   // raw scores q.k; the base-2 exponent domain value is v * scale2, scale2 = log2(e) / sqrt(head_dim) > 0
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      v[i] = sa[i];
-      v[4 + i] = sb[i];
-    }
-    if (!all_vis) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (!(f.ok_a && pa0 + i < L.c1 && pa0 + i <= last_vis[rb])) v[i] = -INFINITY;
-        if (!(f.ok_b && pa0 + 16 + i < L.c1 && pa0 + 16 + i <= last_vis[rb])) v[4 + i] = -INFINITY;
-      }
-    }
-    // Lazy reference maximum: m_run only moves when the true row maximum has grown by more than 8 (a factor 256),
-    // so the accumulators (which live in the MFMA accumulation registers, out of reach of plain ALU ops) are
-    // rescaled once or twice per sweep instead of after every pair.  exp2(v - m_run) <= 256 meanwhile.  A row's
-    // maximum has grown that much exactly when the maximum of one of its four lanes has, so the common case is
-    // decided from each lane's own scores and the cross-lane exchange happens only inside the rare branch.
-    const float lmx = fmaxf(fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])), fmaxf(fmaxf(v[4], v[5]), fmaxf(v[6], v[7]))) * scale2;
-    const float m_old = m_run[rb];
-    if (__builtin_amdgcn_ballot_w64(lmx > m_old + 8.f) != 0ull) {
-      float mx = lmx;   // the maximum commutes with the positive scale
-      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      const bool grow = mx > m_old + 8.f;
-      const float corr = grow ? (m_old == -INFINITY ? 0.f : exp2f(m_old - mx)) : 1.f;
-      l_run[rb] *= corr;
-      // through LDS: the accumulators can be stored from and loaded into the accumulation registers directly, so
-      // the common path never has to shuttle them to ordinary registers on behalf of this rare one
-      f32x4* scr = rescale_lds + L.lane;
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt) scr[dt * 64] = acc[rb][dt];
-      asm volatile("" ::: "memory");
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt) {
-        f32x4 a = scr[dt * 64];
-        a[0] *= corr; a[1] *= corr; a[2] *= corr; a[3] *= corr;
-        scr[dt * 64] = a;
-      }
-      asm volatile("" ::: "memory");
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt) acc[rb][dt] = scr[dt * 64];
-      if (grow) m_run[rb] = mx;
-    }
-    const float mb = (m_run[rb] == -INFINITY) ? 0.f : m_run[rb];   // nothing visible yet: exp2(-inf - 0) = 0
-    float pe[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) pe[i] = __builtin_amdgcn_exp2f(fmaf(v[i], scale2, -mb));   // -inf stays -inf -> 0
-    l_run[rb] += ((pe[0] + pe[1]) + (pe[2] + pe[3])) + ((pe[4] + pe[5]) + (pe[6] + pe[7]));
-    u32x4 ph, pl;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t h = pack_bf16_pair(pe[2 * i], pe[2 * i + 1]);
-      ph[i] = h;
-      pl[i] = pack_bf16_pair(pe[2 * i] - __uint_as_float(h << 16), pe[2 * i + 1] - __uint_as_float(h & 0xFFFF0000u));
-    }
-    // all hi products, then all lo products: two MFMAs on the same accumulator are never back to back
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-      acc[rb][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f.v[dt]), __builtin_bit_cast(bf16x8, ph), acc[rb][dt], 0, 0, 0);
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-      acc[rb][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f.v[dt]), __builtin_bit_cast(bf16x8, pl), acc[rb][dt], 0, 0, 0);
-  }
-}
-
-template <int HD>
-__global__ __launch_bounds__(256, 1) void attn_mfma_wide_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ pool,
+__global__ __launch_bounds__(512, 2) void attn_mfma_wide_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ pool,
                                                                 SeqGeom geo, AttnArgs aa, float* __restrict__ part_o,
                                                                 float2* __restrict__ part_ml) {
-  constexpr int KT = HD / 32, DT = HD / 16, RB = 4, LD = HD + 4;
-  __shared__ float2 s_ml[4][64];
-  __shared__ __attribute__((aligned(16))) float s_raw[4 * 64 * LD];   // query fragments during the sweep, outputs in the merge
-  float (*s_o)[64][LD] = reinterpret_cast<float (*)[64][LD]>(s_raw);
-  u32x4* q_lds = reinterpret_cast<u32x4*>(s_raw);                      // [rb][kt][lane]
-  int32_t* s_pages = reinterpret_cast<int32_t*>(s_raw) + RB * KT * 64 * 4;   // page ids of this chunk (behind the queries)
+  constexpr int KT = HD / 32, DT = HD / 16, NW = 8, LD = HD + 4;
+  constexpr int PART = DF_PAGE * HD * 2;      // bytes of the K or V part of a page
+  constexpr int NI = PART / 1024;             // load instructions per part
+  constexpr int RING = NW * 4 * PART;         // per wavefront: K of page A, K of page B, V of page A, V of page B
+  static_assert(4 * RB * 16 * LD * 4 <= RING + RB * KT * 1024, "the merge buffer overlays the ring and the queries");
+  __shared__ float2 s_ml[NW][RB * 16];
+  __shared__ __attribute__((aligned(1024))) char s_raw[RING + RB * KT * 1024];   // page ring and query fragments; outputs in the merge
+  float (*s_o)[RB * 16][LD] = reinterpret_cast<float (*)[RB * 16][LD]>(s_raw);
+  u32x4* q_lds = reinterpret_cast<u32x4*>(s_raw + RING);               // [rb][kt][lane]
   // grid = (splits, kv heads, parts * sequences): the 2^q_shift workgroups that share a kv head's K/V (each with its
   // share of the query heads) differ in blockIdx.z only, by a multiple of the (even) sequence count, and so land on the
   // same XCD and read the K/V pages through one L2; "kvh" below counts head groups (kv head * parts + part)
@@ -370,41 +263,81 @@ __global__ __launch_bounds__(256, 1) void attn_mfma_wide_kernel(const bf16_t* __
   const int B = geo.block_size;
   const int group = (aa.n_q_heads / aa.n_kv_heads) >> aa.q_shift;   // query heads of this workgroup: blockIdx.y ("kvh") counts such head groups
   const int rows = B * group;
-  const int n_s = geo.seq_lens[s];
   const int cap = geo.max_pages_per_seq * DF_PAGE;
-  // per-wavefront staging for the rare accumulator rescale (behind room for 16384 page ids)
-  f32x4* rescale_lds = reinterpret_cast<f32x4*>(s_raw + RB * KT * 64 * 4 + 16384) + wave * (DT * 64);
+  const int32_t* table = geo.block_table + (size_t)s * geo.max_pages_per_seq;
+  const int c0 = split * aa.chunk;
+  const int kv = kvh >> aa.q_shift;
 
-  AttnLane L;
-  L.table = geo.block_table + (size_t)s * geo.max_pages_per_seq;
-  L.n_tok = min(n_s + B, cap);
-  L.c0 = split * aa.chunk;
-  L.c1 = min(L.n_tok, L.c0 + aa.chunk);
-  L.last_vis = 0;
-  L.g = g;
-  L.lane = lane;
-  L.kvh = kvh >> aa.q_shift;
-  const int n_all_vis = min(L.c1, aa.causal ? n_s : L.n_tok);   // keys below this are visible to every row
+  // Page ids of this wavefront's pairs, 32 pairs at a time: lane l holds page l % 2 of its pair k0 + l / 2.  The next set is
+  // requested when a set comes into use, long before it is needed.
+  auto load_ids = [&](int k0) {
+    const int pair = wave + NW * (k0 + (lane >> 1));
+    return table[min((c0 >> 4) + 2 * pair + (lane & 1), geo.max_pages_per_seq - 1)];
+  };
+  // the first set and the queries do not depend on the sequence's length: the three round trips to memory overlap
+  int ids = load_ids(0);
+  u32x4 qr[KT];
+  {
+    const int r = (wave < RB ? wave : 0) * 16 + n;
+    const bool valid = r < rows;
+    const int slot = valid ? r / group : 0, hq = kvh * group + (valid ? r % group : 0);
+    const u32x4* qp = reinterpret_cast<const u32x4*>(q + ((size_t)(s * B + slot) * aa.n_q_heads + hq) * HD);
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) {
+      qr[kt] = qp[kt * 4 + g];
+      if (!valid) qr[kt] = (u32x4){0u, 0u, 0u, 0u};
+    }
+  }
+  const int n_s = geo.seq_lens[s];
+  const int n_tok = min(n_s + B, cap);
+  const int c1 = min(n_tok, c0 + aa.chunk);
+  const int n_all_vis = min(c1, aa.causal ? n_s : n_tok);   // keys below this are visible to every row
+  const int n_pairs = c1 > c0 ? (c1 - c0 + 31) >> 5 : 0;
+  const int my_pairs = n_pairs > wave ? (n_pairs - wave + NW - 1) / NW : 0;
+  int ids_next = my_pairs > 32 ? load_ids(32) : 0;
+
+  const unsigned ring = (unsigned)(size_t)&s_raw[0] + (unsigned)wave * (4 * PART);
+  const unsigned voff = lane * 16;
+  // one part (K or V) of a page into the ring at byte `at`
+  auto fetch = [&](const bf16_t* src, unsigned at) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const unsigned dst = __builtin_amdgcn_readfirstlane(ring + at + i * 1024);
+      const bf16_t* from = src + i * 512;
+      unsigned keep_m0;   // whatever the compiler keeps in m0 is put back
+      asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3 nt\n\ts_nop 0\n\ts_mov_b32 m0, %0"
+                   : "=&s"(keep_m0) : "s"(dst), "v"(voff), "s"(from) : "memory");
+    }
+  };
+  struct Pair {
+    const bf16_t *a, *b;   // the pages' K parts (V follows)
+    bool ok_a, ok_b;
+  };
+  auto pair_of = [&](int k) {   // this wavefront's k-th pair; foreign or missing pages alias a readable one and weigh nothing
+    Pair p;
+    const int pa = __builtin_amdgcn_readlane(ids, (k & 31) * 2), pb = __builtin_amdgcn_readlane(ids, (k & 31) * 2 + 1);
+    const bool has_b = c0 + (wave + NW * k) * 32 + 16 < c1;
+    p.ok_a = pa >= 0 && pa < geo.n_pages;
+    p.ok_b = has_b && pb >= 0 && pb < geo.n_pages;
+    const int a = p.ok_a ? pa : 0, b = p.ok_b ? pb : a;
+    p.a = pool + kv_head_base(aa.layer, geo.n_pages, a, aa.n_kv_heads, kv, HD);
+    p.b = pool + kv_head_base(aa.layer, geo.n_pages, b, aa.n_kv_heads, kv, HD);
+    return p;
+  };
+  Pair cur{pool, pool, false, false};
+  if (my_pairs > 0) {
+    cur = pair_of(0);
+    fetch(cur.a, 0);
+    fetch(cur.b, PART);
+    fetch(cur.a + DF_PAGE * HD, 2 * PART);
+    fetch(cur.b + DF_PAGE * HD, 3 * PART);
+  }
 
   // query fragments of the RB row blocks: lane (n, g) holds Q[row rb*16 + n][kt*32 + g*8 .. +8]; wavefront w
   // stages row block w in LDS for everybody
-  int last_vis[RB];
+  if (wave < RB) {
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    const int r = rb * 16 + n;
-    const bool valid = r < rows;
-    const int slot = valid ? r / group : 0, hq = kvh * group + (valid ? r % group : 0);
-    last_vis[rb] = valid ? (aa.causal ? n_s + slot : 0x7FFFFFFF) : -1;
-    if (rb == wave) {
-      const u32x4* qp = reinterpret_cast<const u32x4*>(q + ((size_t)(s * B + slot) * aa.n_q_heads + hq) * HD);
-#pragma unroll
-      for (int kt = 0; kt < KT; ++kt) q_lds[(rb * KT + kt) * 64 + lane] = valid ? qp[kt * 4 + g] : (u32x4){0u, 0u, 0u, 0u};
-    }
-  }
-  // the chunk's slice of the page table: the sweep then never waits on a dependent table load from memory
-  {
-    const int first = L.c0 >> 4, count = L.c1 > L.c0 ? ((L.c1 - L.c0 + 15) >> 4) : 0;
-    for (int i = threadIdx.x; i < count; i += 256) s_pages[i] = L.table[first + i];
+    for (int kt = 0; kt < KT; ++kt) q_lds[(wave * KT + kt) * 64 + lane] = qr[kt];
   }
   __syncthreads();
 
@@ -417,40 +350,145 @@ __global__ __launch_bounds__(256, 1) void attn_mfma_wide_kernel(const bf16_t* __
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) acc[rb][dt] = (f32x4){0.f, 0.f, 0.f, 0.f};
   }
-
-  const int n_pairs = L.c1 > L.c0 ? (L.c1 - L.c0 + 31) >> 5 : 0;
   const float scale2 = aa.scale * 1.44269504088896341f;   // scores and running maxima in the base-2 exponent domain
-  auto load = [&](KvFrags<HD>& f, int p) {
-    const bool has_b = L.c0 + p * 32 + 16 < L.c1;
-    // the same for every lane: tell the compiler, so addresses and validity branches stay scalar
-    const int pa = __builtin_amdgcn_readfirstlane(s_pages[2 * p]);
-    const int pb = has_b ? __builtin_amdgcn_readfirstlane(s_pages[2 * p + 1]) : pa;
-    attn_load_pages<HD, true>(f, pa, pb, has_b, pool, geo, aa, L);
-  };
-  // Two fragment sets per wavefront; no conditional load inside the loop (see the kernel above), tail peeled off.
-  if (wave < n_pairs) {
-    KvFrags<HD> f0, f1;
-    auto process = [&](KvFrags<HD>& f, int p) {
-      attn_process_pair_wide<HD, RB>(f, L.c0 + p * 32, q_lds, acc, m_run, l_run, last_vis, n_all_vis, scale2, L, rescale_lds);
-    };
-    load(f0, wave);
-    int p = wave;
-    for (; p + 8 < n_pairs; p += 8) {
-      load(f1, p + 4);
-      process(f0, p);
-      load(f0, p + 8);
-      process(f1, p + 4);
+  const char* my_ring = s_raw + wave * (4 * PART);
+
+  for (int k = 0; k < my_pairs; ++k) {
+    const int base = c0 + (wave + NW * k) * 32;
+    const bool more = k + 1 < my_pairs;
+    if (more && ((k + 1) & 31) == 0) {   // uniform over the wavefront
+      ids = ids_next;
+      if (k + 33 < my_pairs) ids_next = load_ids(k + 33);
     }
-    if (p + 4 < n_pairs) {
-      load(f1, p + 4);
-      process(f0, p);
-      process(f1, p + 4);
-    } else {
-      process(f0, p);
+    Pair nxt = cur;
+    if (more) nxt = pair_of(k + 1);
+
+    // ---- scores of all row blocks: S^T = K . Q^T
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NI) : "memory");   // this pair's K is there (its V still on the way)
+    f32x4 sc[RB][2];
+    {
+      const u32x4* kp = reinterpret_cast<const u32x4*>(my_ring) + lane;
+      u32x4 ka[KT], kb[KT];
+#pragma unroll
+      for (int kt = 0; kt < KT; ++kt) {
+        ka[kt] = kp[kt * 64];
+        kb[kt] = kp[PART / 16 + kt * 64];
+      }
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+        asm volatile("" ::: "memory");   // the query fragments of one row block at a time: together they would cost 64 registers
+        sc[rb][0] = sc[rb][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt) {
+          const u32x4 qf = q_lds[(rb * KT + kt) * 64 + lane];
+          sc[rb][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ka[kt]), __builtin_bit_cast(bf16x8, qf), sc[rb][0], 0, 0, 0);
+          sc[rb][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kb[kt]), __builtin_bit_cast(bf16x8, qf), sc[rb][1], 0, 0, 0);
+        }
+      }
     }
+    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): the K half has been read
+    if (more) {
+      fetch(nxt.a, 0);
+      fetch(nxt.b, PART);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- visibility (only the last pairs of a sequence and foreign pages take this branch)
+    const bool tail = !cur.ok_a || !cur.ok_b || base + 32 > n_all_vis;
+    if (tail) {
+      const int pa0 = base + 4 * g;
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+        const int r = rb * 16 + n;
+        const int last_vis = r < rows ? (aa.causal ? n_s + r / group : 0x7FFFFFFF) : -1;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if (!(cur.ok_a && pa0 + i < c1 && pa0 + i <= last_vis)) sc[rb][0][i] = -INFINITY;
+          if (!(cur.ok_b && pa0 + 16 + i < c1 && pa0 + 16 + i <= last_vis)) sc[rb][1][i] = -INFINITY;
+        }
+      }
+    }
+    // Lazy reference maximum: m_run only moves when the true row maximum has grown by more than 8 (a factor 256),
+    // so the accumulators are rescaled once or twice per sweep instead of after every pair.  exp2(v - m_run) <= 256
+    // meanwhile.  A row's maximum has grown that much exactly when the maximum of one of its four lanes has, so the common
+    // case is decided from each lane's own scores and the cross-lane exchange happens only inside the rare branch.
+    float lmx[RB];
+    bool grew = false;
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      const f32x4 x = sc[rb][0], y = sc[rb][1];
+      lmx[rb] = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(y[0], y[1]), fmaxf(y[2], y[3]))) * scale2;
+      grew = grew || lmx[rb] > m_run[rb] + 8.f;
+    }
+    if (__builtin_amdgcn_ballot_w64(grew) != 0ull) {
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+        float mx = lmx[rb];   // the maximum commutes with the positive scale
+        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        const bool grow = mx > m_run[rb] + 8.f;
+        const float corr = grow ? (m_run[rb] == -INFINITY ? 0.f : exp2f(m_run[rb] - mx)) : 1.f;
+        l_run[rb] *= corr;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) {
+          acc[rb][dt][0] *= corr; acc[rb][dt][1] *= corr; acc[rb][dt][2] *= corr; acc[rb][dt][3] *= corr;
+        }
+        if (grow) m_run[rb] = mx;
+      }
+    }
+    // ---- probabilities as hi + lo pairs
+    u32x4 ph[RB], pl[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      const float mb = (m_run[rb] == -INFINITY) ? 0.f : m_run[rb];   // nothing visible yet: exp2(-inf - 0) = 0
+      float pe[8];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {   // -inf stays -inf -> 0
+        pe[i] = __builtin_amdgcn_exp2f(fmaf(sc[rb][0][i], scale2, -mb));
+        pe[4 + i] = __builtin_amdgcn_exp2f(fmaf(sc[rb][1][i], scale2, -mb));
+      }
+      l_run[rb] += ((pe[0] + pe[1]) + (pe[2] + pe[3])) + ((pe[4] + pe[5]) + (pe[6] + pe[7]));
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t h = pack_bf16_pair(pe[2 * i], pe[2 * i + 1]);
+        ph[rb][i] = h;
+        pl[rb][i] = pack_bf16_pair(pe[2 * i] - __uint_as_float(h << 16), pe[2 * i + 1] - __uint_as_float(h & 0xFFFF0000u));
+      }
+    }
+    // ---- O^T += V^T . P^T; this pair's V is there (the next pair's K may still be on its way)
+    if (more) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NI) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // never-written rows and foreign pages: 0 * garbage must not become NaN, so those V elements are cleared
+    u32x4 keep = {~0u, ~0u, ~0u, ~0u};
+    if (base + 32 > n_tok || !cur.ok_a || !cur.ok_b) {
+      const int pos_a = base + 4 * g, pos_b = base + 16 + 4 * g;
+      auto half = [&](bool ok, int p0) { return (ok && p0 < n_tok ? 0x0000FFFFu : 0u) | (ok && p0 + 1 < n_tok ? 0xFFFF0000u : 0u); };
+      keep = (u32x4){half(cur.ok_a, pos_a), half(cur.ok_a, pos_a + 2), half(cur.ok_b, pos_b), half(cur.ok_b, pos_b + 2)};
+    }
+    {
+      const uint2* va = reinterpret_cast<const uint2*>(my_ring + 2 * PART) + lane;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) {
+        const uint2 a = va[dt * 64], b = va[PART / 8 + dt * 64];
+        const u32x4 vf = (u32x4){a.x, a.y, b.x, b.y} & keep;
+        // all hi products, then all lo products: two MFMAs on the same accumulator are never back to back
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+          acc[rb][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vf), __builtin_bit_cast(bf16x8, ph[rb]), acc[rb][dt], 0, 0, 0);
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+          acc[rb][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vf), __builtin_bit_cast(bf16x8, pl[rb]), acc[rb][dt], 0, 0, 0);
+      }
+    }
+    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): the V half has been read
+    if (more) {
+      fetch(nxt.a + DF_PAGE * HD, 2 * PART);
+      fetch(nxt.b + DF_PAGE * HD, 3 * PART);
+    }
+    cur = nxt;
   }
 
-  // ---- merge the four wavefronts' partial results (each over its own keys) --------------------------------
+  // ---- merge the wavefronts' partial results (each over its own keys): the upper four hand theirs to the lower four ----
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     float l = l_run[rb];
@@ -458,21 +496,36 @@ __global__ __launch_bounds__(256, 1) void attn_mfma_wide_kernel(const bf16_t* __
     l += __shfl_xor(l, 32, 64);
     if (g == 0) s_ml[wave][rb * 16 + n] = make_float2(m_run[rb], l);
   }
-  __syncthreads();   // also: every wavefront is done with the query fragments that s_o overlays
+  __syncthreads();   // also: every wavefront is done with the ring and the query fragments that s_o overlays
+  float mine[RB];
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
-    const int r = rb * 16 + n;
     float m_all = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) m_all = fmaxf(m_all, s_ml[w][r].x);
-    const float mine = (m_run[rb] == -INFINITY) ? 0.f : exp2f(m_run[rb] - m_all);   // m_all is finite whenever m_run is
+    for (int w = 0; w < NW; ++w) m_all = fmaxf(m_all, s_ml[w][rb * 16 + n].x);
+    mine[rb] = (m_run[rb] == -INFINITY) ? 0.f : exp2f(m_run[rb] - m_all);   // m_all is finite whenever m_run is
+  }
+  if (wave >= 4) {
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-      *reinterpret_cast<float4*>(&s_o[wave][r][dt * 16 + 4 * g]) =
-          make_float4(acc[rb][dt][0] * mine, acc[rb][dt][1] * mine, acc[rb][dt][2] * mine, acc[rb][dt][3] * mine);
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+        *reinterpret_cast<float4*>(&s_o[wave - 4][rb * 16 + n][dt * 16 + 4 * g]) =
+            make_float4(acc[rb][dt][0] * mine[rb], acc[rb][dt][1] * mine[rb], acc[rb][dt][2] * mine[rb], acc[rb][dt][3] * mine[rb]);
   }
   __syncthreads();
-  for (int idx = threadIdx.x; idx < 64 * (HD / 4); idx += 256) {
+  if (wave < 4) {
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) {
+        float4* p = reinterpret_cast<float4*>(&s_o[wave][rb * 16 + n][dt * 16 + 4 * g]);
+        const float4 u = *p;
+        *p = make_float4(acc[rb][dt][0] * mine[rb] + u.x, acc[rb][dt][1] * mine[rb] + u.y, acc[rb][dt][2] * mine[rb] + u.z, acc[rb][dt][3] * mine[rb] + u.w);
+      }
+  }
+  __syncthreads();
+  for (int idx = threadIdx.x; idx < RB * 16 * (HD / 4); idx += 64 * NW) {
     const int r = idx / (HD / 4), d4 = idx % (HD / 4);
     if (r >= rows) continue;
     const int slot = r / group, hq = kvh * group + r % group;
@@ -487,10 +540,10 @@ __global__ __launch_bounds__(256, 1) void attn_mfma_wide_kernel(const bf16_t* __
     if (d4 == 0) {
       float m_all = -INFINITY;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) m_all = fmaxf(m_all, s_ml[w][r].x);
+      for (int w = 0; w < NW; ++w) m_all = fmaxf(m_all, s_ml[w][r].x);
       float l = 0.f;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
+      for (int w = 0; w < NW; ++w) {
         const float2 ml = s_ml[w][r];
         l += (ml.x == -INFINITY) ? 0.f : ml.y * exp2f(ml.x - m_all);
       }
@@ -511,9 +564,9 @@ inline bool attn_mfma_launch<bf16_t>(hipStream_t st, const bf16_t* q, const bf16
   const int rows = (geo.block_size * (aa.n_q_heads / aa.n_kv_heads)) >> aa.q_shift;
   if (rows > 64 || (aa.n_q_heads / aa.n_kv_heads) % (1 << aa.q_shift) || (aa.head_dim != 128 && aa.head_dim != 64)) return false;
   const dim3 grid(aa.n_splits, aa.n_kv_heads, S << aa.q_shift), block(256);
-  // long chunks: wavefronts split the keys (the chunk's page ids must fit the kernel's LDS slice)
-  if (aa.head_dim == 128 && aa.chunk >= wide_min_chunk && aa.chunk / DF_PAGE + 2 <= 16384)
-    hipLaunchKernelGGL(attn_mfma_wide_kernel<128>, grid, block, 0, st, q, pool, geo, aa, part_o, part_ml);
+  // long chunks: wavefronts split the keys
+  if (aa.head_dim == 128 && aa.chunk >= wide_min_chunk)
+    hipLaunchKernelGGL((attn_mfma_wide_kernel<128, 4>), grid, dim3(512), 0, st, q, pool, geo, aa, part_o, part_ml);
   else if (aa.head_dim == 128)
     hipLaunchKernelGGL(attn_mfma_kernel<128>, grid, block, 0, st, q, pool, geo, aa, part_o, part_ml);
   else

@@ -495,6 +495,8 @@ struct Engine {
     gemm(reinterpret_cast<const T*>(lbase + lo.wgu), a, M, 2 * m.d_ffn, D, EPI_SWIGLU, deferred(EpiArgs{nullptr, 0, 0, ws<T>(c->ws.act), m.d_ffn}, m));
     resid(reinterpret_cast<const T*>(lbase + lo.wd), ws<T>(c->ws.act), M, D, m.d_ffn, gain_next, tap);
   }
+  // workgroups of embed_kernel: one per row, then one thread per entry of the rotary tables (half a head dim each)
+  static dim3 embed_grid(int M, int head_dims) { return dim3(M + (M * (head_dims / 2) + 255) / 256); }
   void qkv_post(const dflash_dims& m, const char* lbase, const LayerOff& lo, T* pool, int l, const dflash_batch* b, const Slab& qs) {
     const int M = b->n_seqs * blk(b);
     const int qd = m.n_q_heads * m.head_dim, kd = m.n_kv_heads * m.head_dim, nqkv = qd + 2 * kd;
@@ -538,7 +540,7 @@ struct Engine {
       hipLaunchKernelGGL(argmax_rows_kernel, dim3(ARGMAX_CHUNKS, M), dim3(256), 0, st, logits, V, B, part, mode, inv_T, key);
       check();
     }
-    hipLaunchKernelGGL(argmax_finish_kernel, dim3(M), dim3(64), 0, st, part, parts, B, out, skip_slot0);
+    hipLaunchKernelGGL(argmax_finish_kernel, dim3(M), dim3(256), 0, st, part, parts, B, out, skip_slot0);
     check();
     amax_parts = 0;
   }
@@ -639,8 +641,8 @@ struct Engine {
       ef.ssq = ws<float>(c->ws.ssq);
       defer_parts = 1;
     }
-    hipLaunchKernelGGL(embed_kernel<T>, dim3(M), dim3(256), 0, st, reinterpret_cast<const T*>(c->tblob + c->tl.embed), draft_tokens,
-                       ws<float>(c->ws.h), d.d_model, d.vocab, status(), b->seq_lens, B, b->max_seq_len,
+    hipLaunchKernelGGL(embed_kernel<T>, embed_grid(M, d.head_dim), dim3(256), 0, st, reinterpret_cast<const T*>(c->tblob + c->tl.embed), draft_tokens,
+                       ws<float>(c->ws.h), d.d_model, d.vocab, status(), b->seq_lens, B, b->max_seq_len, M,
                        RopeTab{ws<float2>(c->ws.rope_d), log((double)d.rope_theta), d.head_dim}, RopeTab{nullptr, 0.0, 0}, ef);
     check();
     for (int i = 0; i < d.n_layers; ++i) {
@@ -683,8 +685,8 @@ struct Engine {
       ef.ssq = ws<float>(c->ws.ssq);
       defer_parts = 1;
     }
-    hipLaunchKernelGGL(embed_kernel<T>, dim3(M), dim3(256), 0, st, reinterpret_cast<const T*>(c->tblob + c->tl.embed), tokens,
-                       ws<float>(c->ws.h), t.d_model, t.vocab, status(), b->seq_lens, B, b->max_seq_len,
+    hipLaunchKernelGGL(embed_kernel<T>, embed_grid(M, t.head_dim + c->d.head_dim), dim3(256), 0, st, reinterpret_cast<const T*>(c->tblob + c->tl.embed), tokens,
+                       ws<float>(c->ws.h), t.d_model, t.vocab, status(), b->seq_lens, B, b->max_seq_len, M,
                        RopeTab{ws<float2>(c->ws.rope_t), log((double)t.rope_theta), t.head_dim},
                        RopeTab{ws<float2>(c->ws.rope_d), log((double)c->d.rope_theta), c->d.head_dim}, ef);
     check();
@@ -828,8 +830,8 @@ struct Engine {
       pb.max_seq_len = std::min(b->max_seq_len + max_len, c->rt.max_pages_per_seq * DFLASH_PAGE_SIZE - B);
       pb.seq_lens = pp.p_lens; pb.block_table = pp.p_table; pb.anchor = ws<int32_t>(c->ws.pf_anchor);
       pb.block_size = B;
-      hipLaunchKernelGGL(embed_kernel<T>, dim3(M), dim3(256), 0, st, reinterpret_cast<const T*>(c->tblob + c->tl.embed), pp.p_tokens,
-                         ws<float>(c->ws.h), t.d_model, t.vocab, status(), pb.seq_lens, B, pb.max_seq_len,
+      hipLaunchKernelGGL(embed_kernel<T>, embed_grid(M, t.head_dim + c->d.head_dim), dim3(256), 0, st, reinterpret_cast<const T*>(c->tblob + c->tl.embed), pp.p_tokens,
+                         ws<float>(c->ws.h), t.d_model, t.vocab, status(), pb.seq_lens, B, pb.max_seq_len, M,
                          RopeTab{ws<float2>(c->ws.rope_t), log((double)t.rope_theta), t.head_dim},
                          RopeTab{ws<float2>(c->ws.rope_d), log((double)c->d.rope_theta), c->d.head_dim}, EmbedFuse{});
       check();

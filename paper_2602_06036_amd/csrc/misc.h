@@ -23,7 +23,7 @@ struct RopeTab {
 
 // h[m, :] = float(E[tokens[m], :]); ids outside the vocabulary raise the status flag and read row 0; so does a sequence
 // longer than the host's hint.
-// The first two wavefronts also write the row's entries of up to two rotary tables.
+// Up to two rotary tables are written by further workgroups of the launch.
 // With `fuse.a_out` the row is also handed on as the first layer's GEMM operand with the RMSNorm deferred (see
 // gemm_resid.h): a_out[m, :] = h * gain, ssq[m] = sum of squares of the row (one piece per row).
 struct EmbedFuse {
@@ -35,22 +35,26 @@ struct EmbedFuse {
 template <typename T>
 __global__ __launch_bounds__(256) void embed_kernel(const T* __restrict__ E, const int32_t* __restrict__ tokens,
                                                     float* __restrict__ h, int D, int vocab, int32_t* status,
-                                                    const int32_t* __restrict__ seq_lens, int B, int len_hint, RopeTab t0, RopeTab t1,
+                                                    const int32_t* __restrict__ seq_lens, int B, int len_hint, int n_rows, RopeTab t0, RopeTab t1,
                                                     EmbedFuse fuse = EmbedFuse{}) {
+  // workgroups M .. of the grid write the rotary tables (angles in double precision take longer than a row's copy): one
+  // entry of a table per thread
+  if ((int)blockIdx.x >= n_rows) {
+    const int half0 = t0.out ? t0.hd >> 1 : 0, half1 = t1.out ? t1.hd >> 1 : 0;
+    const int i = ((int)blockIdx.x - n_rows) * 256 + threadIdx.x, per = half0 + half1;
+    if (i >= n_rows * per) return;
+    const int row = i / per, e = i % per;
+    const RopeTab rt = e < half0 ? t0 : t1;
+    const int d = e < half0 ? e : e - half0;
+    double sn, cs;
+    sincos((double)(seq_lens[row / B] + row % B) * exp(-rt.log_theta * (2.0 * d / rt.hd)), &sn, &cs);
+    rt.out[(size_t)row * (rt.hd >> 1) + d] = make_float2((float)cs, (float)sn);
+    return;
+  }
   const int m = blockIdx.x;
   // the host sized the attention launches of this call for sequences of at most len_hint committed tokens: a longer
   // one would have its last keys left out, so it is reported
   if (threadIdx.x == 0 && seq_lens[m / B] > len_hint) atomicOr(status, DF_STATUS_CAPACITY);
-  {
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const RopeTab rt = w == 0 ? t0 : t1;
-    if (w < 2 && rt.out && lane < (rt.hd >> 1)) {
-      const int pos = seq_lens[m / B] + m % B;
-      double sn, cs;
-      sincos((double)pos * exp(-rt.log_theta * (2.0 * lane / rt.hd)), &sn, &cs);
-      rt.out[(size_t)m * (rt.hd >> 1) + lane] = make_float2((float)cs, (float)sn);
-    }
-  }
   int tok = tokens[m];
   if (tok < 0 || tok >= vocab) {
     if (threadIdx.x == 0) atomicOr(status, DF_STATUS_CAPACITY);
@@ -127,6 +131,14 @@ __global__ __launch_bounds__(NTHR) void rmsnorm_kernel(const float* base, const 
       return v;
     }
     int z = 0;
+    for (; z + 8 <= ks; z += 8) {   // eight slabs (what a few-row GEMM leaves) in one round trip
+      const float* pz = delta + (size_t)z * slab + ro + d;
+      float4 p[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) p[i] = *reinterpret_cast<const float4*>(pz + i * slab);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) { v.x += p[i].x; v.y += p[i].y; v.z += p[i].z; v.w += p[i].w; }
+    }
     for (; z + 4 <= ks; z += 4) {
       const float* pz = delta + (size_t)z * slab + ro + d;
       const float4 p0 = *reinterpret_cast<const float4*>(pz), p1 = *reinterpret_cast<const float4*>(pz + slab);
@@ -226,18 +238,44 @@ __global__ __launch_bounds__(256) void qkv_post_kernel(const float* __restrict__
   kn += blockIdx.z * ra.kn_stride;
   const int hd = ra.head_dim, half = hd >> 1;
   const int s = m / geo.block_size, slot = m % geo.block_size;
-  const int pos = geo.seq_lens[s] + slot;
   const bool is_q = head < ra.n_q_heads;
   const bool is_k = !is_q && head < ra.n_q_heads + ra.n_kv_heads;
   const int kvh = is_q ? 0 : (is_k ? head - ra.n_q_heads : head - ra.n_q_heads - ra.n_kv_heads);
-  const float* src = in + (size_t)m * in_ld + (is_q ? ra.q_off + head * hd : (is_k ? ra.k_off : ra.v_off) + kvh * hd);
   const bool active = lane < half;
-  float x1 = 0.f, x2 = 0.f;
-  if (active)
-    for (int z = 0; z < ks; ++z) {
-      x1 += src[(size_t)z * slab + lane];
-      x2 += src[(size_t)z * slab + lane + half];
+  const int l0 = active ? lane : 0;   // idle lanes read along (head_dim 64 and less)
+  const float* src = in + (size_t)m * in_ld + (is_q ? ra.q_off + head * hd : (is_k ? ra.k_off : ra.v_off) + kvh * hd) + l0;
+  // everything the head needs is requested before any of it is waited for: this kernel is a chain of memory round trips
+  // and nothing else (16 rows, four slabs: 4.6 us with one slab after the other, QP_US)
+  float2 r = make_float2(1.f, 0.f);
+  float g1 = 1.f, g2 = 1.f;
+  if (is_q || is_k) {
+    r = ra.rope[(size_t)m * half + l0];
+    if (ra.qk_norm) {
+      const float* gn = is_q ? qn : kn;
+      g1 = gn[l0];
+      g2 = gn[l0 + half];
     }
+  }
+  const int n_s = geo.seq_lens[s];
+  float x1 = 0.f, x2 = 0.f;
+  for (int z = 0; z < ks; z += 4) {   // four slabs in flight, added in ascending order
+    float p1[4], p2[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float* pz = src + (size_t)min(z + i, ks - 1) * slab;
+      p1[i] = pz[0];
+      p2[i] = pz[half];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      x1 += z + i < ks ? p1[i] : 0.f;
+      x2 += z + i < ks ? p2[i] : 0.f;
+    }
+  }
+  const int pos = n_s + slot;
+  T* base = nullptr;
+  const int key = pos % DF_PAGE;
   if (!is_q) {
     const int pidx = pos / DF_PAGE;
     int page = -1;
@@ -246,8 +284,7 @@ __global__ __launch_bounds__(256) void qkv_post_kernel(const float* __restrict__
       if (lane == 0) atomicOr(geo.status, DF_STATUS_CAPACITY);
       return;
     }
-    T* base = pool + kv_head_base(ra.layer, geo.n_pages, page, ra.n_kv_heads, kvh, hd);
-    const int key = pos % DF_PAGE;
+    base = pool + kv_head_base(ra.layer, geo.n_pages, page, ra.n_kv_heads, kvh, hd);
     if (!is_k) {
       if (active) {
         base[DF_PAGE * hd + v_in_page(key, lane)] = Store<T>::from(x1);
@@ -255,30 +292,23 @@ __global__ __launch_bounds__(256) void qkv_post_kernel(const float* __restrict__
       }
       return;
     }
-    if (ra.qk_norm) {
-      const float ss = wave_reduce_sum(x1 * x1 + x2 * x2);
-      const float rstd = 1.0f / sqrtf(ss / (float)hd + ra.eps);
-      if (active) { x1 *= rstd * kn[lane]; x2 *= rstd * kn[lane + half]; }
-    }
-    if (active) {
-      const float2 r = ra.rope[(size_t)m * half + lane];
-      const float c = r.x, sf = r.y;
-      base[k_in_page(key, lane)] = Store<T>::from(x1 * c - x2 * sf);
-      base[k_in_page(key, lane + half)] = Store<T>::from(x2 * c + x1 * sf);
-    }
-    return;
   }
   if (ra.qk_norm) {
-    const float ss = wave_reduce_sum(x1 * x1 + x2 * x2);
+    const float ss = wave_reduce_sum(active ? x1 * x1 + x2 * x2 : 0.f);
     const float rstd = 1.0f / sqrtf(ss / (float)hd + ra.eps);
-    if (active) { x1 *= rstd * qn[lane]; x2 *= rstd * qn[lane + half]; }
+    x1 *= rstd * g1;
+    x2 *= rstd * g2;
   }
-  if (active) {
-    const float2 r = ra.rope[(size_t)m * half + lane];
-    const float c = r.x, sf = r.y;
+  if (!active) return;
+  const float c = r.x, sf = r.y;
+  const T y1 = Store<T>::from(x1 * c - x2 * sf), y2 = Store<T>::from(x2 * c + x1 * sf);
+  if (is_q) {
     T* dst = q_out + ((size_t)m * ra.n_q_heads + head) * hd;
-    dst[lane] = Store<T>::from(x1 * c - x2 * sf);
-    dst[lane + half] = Store<T>::from(x2 * c + x1 * sf);
+    dst[lane] = y1;
+    dst[lane + half] = y2;
+  } else {
+    base[k_in_page(key, lane)] = y1;
+    base[k_in_page(key, lane + half)] = y2;
   }
 }
 
@@ -322,22 +352,23 @@ __global__ __launch_bounds__(256) void argmax_rows_kernel(const float* __restric
   if (threadIdx.x == 0) part[(size_t)m * n_chunks + chunk] = make_float2(bv, __int_as_float(bi));
 }
 
-__global__ __launch_bounds__(64) void argmax_finish_kernel(const float2* __restrict__ part, int n_chunks, int B, int32_t* __restrict__ out,
-                                                           int skip_slot0) {
+__global__ __launch_bounds__(256) void argmax_finish_kernel(const float2* __restrict__ part, int n_chunks, int B, int32_t* __restrict__ out,
+                                                            int skip_slot0) {
   const int m = blockIdx.x;
   if (skip_slot0 && m % B == 0) return;
   float bv = -INFINITY;
   int bi = 0x7FFFFFFF;
-  for (int c = threadIdx.x; c < n_chunks; c += 64) {
-    const float2 p = part[(size_t)m * n_chunks + c];
-    argmax_combine(bv, bi, p.x, __float_as_int(p.y));
-  }
+  // five parts a thread cover the 1187 column blocks of a 151936-entry vocabulary in one round trip (8.6 us by one
+  // wavefront with a load at a time, AF_US)
+  for (int c0 = threadIdx.x; c0 < n_chunks; c0 += 256 * 5) {
+    float2 p[5];
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const float ov = __shfl_xor(bv, o, 64);
-    const int oi = __shfl_xor(bi, o, 64);
-    argmax_combine(bv, bi, ov, oi);
+    for (int i = 0; i < 5; ++i) p[i] = part[(size_t)m * n_chunks + min(c0 + i * 256, n_chunks - 1)];   // the last part again: no other winner
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < 5; ++i) argmax_combine(bv, bi, p[i].x, __float_as_int(p[i].y));
   }
+  block_argmax(bv, bi);
   if (threadIdx.x == 0) out[m] = bi;
 }
 
@@ -421,10 +452,12 @@ __global__ __launch_bounds__(256) void lse_partial_kernel(const float* __restric
 __global__ __launch_bounds__(64) void lse_finish_kernel(const float2* __restrict__ part, int n_parts, float2* __restrict__ stats) {
   const int m = blockIdx.x, lane = threadIdx.x;
   float mx = -INFINITY;
+#pragma unroll 8
   for (int c = lane; c < n_parts; c += 64) mx = fmaxf(mx, part[(size_t)m * n_parts + c].x);
   mx = wave_reduce_max(mx);
   // every lane sums its stride of the parts in ascending order, then the 64 lane sums are added in lane order
   float s = 0.f;
+#pragma unroll 8
   for (int c = lane; c < n_parts; c += 64) {
     const float2 p = part[(size_t)m * n_parts + c];
     s += p.x == -INFINITY ? 0.f : p.y * expf(p.x - mx);
