@@ -245,7 +245,7 @@ __global__ __launch_bounds__(256) void qkv_post_kernel(const float* __restrict__
   const int l0 = active ? lane : 0;   // idle lanes read along (head_dim 64 and less)
   const float* src = in + (size_t)m * in_ld + (is_q ? ra.q_off + head * hd : (is_k ? ra.k_off : ra.v_off) + kvh * hd) + l0;
   // everything the head needs is requested before any of it is waited for: this kernel is a chain of memory round trips
-  // and nothing else (16 rows, four slabs: 4.6 us with one slab after the other, QP_US)
+  // and nothing else (16 rows, four slabs: 4.6 us with one slab after the other, 4.6 with four at a time: what is left is the launch)
   float2 r = make_float2(1.f, 0.f);
   float g1 = 1.f, g2 = 1.f;
   if (is_q || is_k) {
@@ -359,7 +359,7 @@ __global__ __launch_bounds__(256) void argmax_finish_kernel(const float2* __rest
   float bv = -INFINITY;
   int bi = 0x7FFFFFFF;
   // five parts a thread cover the 1187 column blocks of a 151936-entry vocabulary in one round trip (8.6 us by one
-  // wavefront with a load at a time, AF_US)
+  // wavefront with a load at a time, 5 like this)
   for (int c0 = threadIdx.x; c0 < n_chunks; c0 += 256 * 5) {
     float2 p[5];
 #pragma unroll
