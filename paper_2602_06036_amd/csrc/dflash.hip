@@ -909,10 +909,65 @@ inline int pick_ksplit(int n_blocks, int KT, int M, int arena, int target) {
   return ks;
 }
 
+// The weight-streaming kernel's launch for up to 64 rows: weight tiles and activation bands per workgroup, k tiles per
+// prefetch stage, K ranges.
+struct StreamPlan {
+  int nt = 0, mt = 0, u = 0, ks = 1;   // nt = 0: another kernel's shape
+};
+inline StreamPlan stream_plan(const Knobs& kn, int M, int N, int K, bool split, int arena) {
+  const int nt = N / 16, KT = K / 32;
+  StreamPlan p;
+  // a launch of 192 workgroups leaves a quarter of the CUs idle: among 8, 6 or 4 weight tiles per wavefront and any K split
+  // (not only powers of two) take the fullest last round; ties go to more tiles, then to fewer K ranges.  (Four tiles pay
+  // where nothing else fills the chip: an unsplit 16384-column LM head, 128 workgroups with 8, took 31 us at 16 rows and 49 at
+  // 64, now 23 and 39.)
+  auto fullest = [&]() {
+    double best = -1.0;
+    for (int cand : {8, 6, 4}) {
+      if (nt % cand) continue;
+      const int nb = nt / cand;
+      for (int k = 1; k <= (split ? kMaxKSplit : 1); ++k) {
+        if (k > 1 && (KT / (k * 4) < 2 || k * M > arena)) break;
+        const int wgs = nb * k, rounds = (wgs + 255) / 256;
+        const double fill = (double)wgs / (rounds * 256.0) - 0.02 * (rounds - 1);   // a single round beats several
+        if (fill > best + 1e-9) { best = fill; p.nt = cand; p.ks = k; }
+      }
+    }
+  };
+  auto powers = [&](int t) {
+    p.nt = t;
+    p.ks = split ? pick_ksplit(nt / t, KT, M, arena, kn.gemm_target_wgs) : 1;
+  };
+  if (M <= 16) {
+    const int NT8 = kn.gemm_nt8, U = kn.gemm_u;   // U: k-tiles per prefetch stage
+    p.mt = 1;
+    if (kn.gemm_fill == 1 && NT8 && nt >= 8 * NT8 && (nt % 8 == 0 || nt % 6 == 0)) {
+      fullest();
+      p.u = 2;
+    } else if (NT8 && nt % 8 == 0 && nt >= 8 * NT8) {
+      powers(8);
+      p.u = U >= 2 ? 2 : 1;
+    } else if (nt % 4 == 0) {
+      powers(4);
+      p.u = U >= 4 ? 4 : (U >= 2 ? 2 : 1);
+    } else {
+      powers(nt % 2 == 0 ? 2 : 1);
+      p.u = 4;
+    }
+  } else if (M <= 64 && nt % 8 == 0) {
+    // still bandwidth-bound: the same streaming kernel with two or four activation bands per weight tile
+    p.mt = M <= 32 ? 2 : 4;
+    p.u = 1;
+    if (kn.gemm_fill4 == 1) fullest();
+    else powers(8);
+    if (p.nt == 8 && kn.gemm_u4 >= 2) p.u = 2;   // (measured slower)
+  }
+  return p;
+}
+
 template <>
 Engine<bf16_t>::Slab Engine<bf16_t>::gemm(const bf16_t* W, const bf16_t* A, int M, int N, int K, int epi, EpiArgs ep, bool allow_split) {
   ProfScope prof(c, st, gemm_class(epi, N, c->t.vocab), (double)N * K * 2);
-  const int U = c->k.gemm_u;   // k-tiles per prefetch stage
   const int nt = N / 16, KT = K / 32;
   int kepi = epi;
   if (epi == EPI_RESID) {   // partial slabs into the arena; the next RMSNorm adds them to the residual stream
@@ -925,80 +980,18 @@ Engine<bf16_t>::Slab Engine<bf16_t>::gemm(const bf16_t* W, const bf16_t* A, int 
   if (ep.amax && (split || epi != EPI_STORE)) ep.amax = nullptr;   // the fused argmax needs complete sums
   if (ep.lse && (split || epi != EPI_STORE)) ep.lse = nullptr;      // so do the fused softmax statistics
   if (ep.amax && lm_skip_store) ep.out = nullptr;
-  if (M <= 16) {
-    const int NT8 = c->k.gemm_nt8, FILL = c->k.gemm_fill;
-    if (FILL == 1 && NT8 && nt >= 8 * NT8 && (nt % 8 == 0 || nt % 6 == 0)) {
-      // a launch of 192 workgroups leaves a quarter of the CUs idle: among 8 or 6 weight tiles per wavefront and
-      // any K split (not only powers of two) take the fullest last round; ties go to 8 tiles, then to fewer K ranges
-      int best_nt = 0, best_ks = 1;
-      double best_fill = -1.0;
-      for (int cand : {8, 6}) {
-        if (nt % cand) continue;
-        const int nb = nt / cand;
-        for (int k = 1; k <= (split ? kMaxKSplit : 1); ++k) {
-          if (k > 1 && (KT / (k * 4) < 2 || k * M > arena)) break;
-          const int wgs = nb * k, rounds = (wgs + 255) / 256;
-          const double fill = (double)wgs / (rounds * 256.0) - 0.02 * (rounds - 1);   // a single round beats several
-          if (fill > best_fill + 1e-9) { best_fill = fill; best_nt = cand; best_ks = k; }
-        }
-      }
-      ks = best_ks;
-      ep.slab = (size_t)M * ep.ld;
-      if (best_nt == 8) launch_bf16<8, 1, 2>(st, W, A, M, N, K, kepi, ep, ks);
-      else launch_bf16<6, 1, 2>(st, W, A, M, N, K, kepi, ep, ks);
-    } else if (NT8 && nt % 8 == 0 && nt >= 8 * NT8) {
-      if (split) ks = pick_ksplit(nt / 8, KT, M, arena, c->k.gemm_target_wgs);
-      ep.slab = (size_t)M * ep.ld;
-      if (U >= 2) launch_bf16<8, 1, 2>(st, W, A, M, N, K, kepi, ep, ks);
-      else launch_bf16<8, 1, 1>(st, W, A, M, N, K, kepi, ep, ks);
-    } else if (nt % 4 == 0) {
-      if (split) ks = pick_ksplit(nt / 4, KT, M, arena, c->k.gemm_target_wgs);
-      ep.slab = (size_t)M * ep.ld;
-      if (U >= 4) launch_bf16<4, 1, 4>(st, W, A, M, N, K, kepi, ep, ks);
-      else if (U >= 2) launch_bf16<4, 1, 2>(st, W, A, M, N, K, kepi, ep, ks);
-      else launch_bf16<4, 1, 1>(st, W, A, M, N, K, kepi, ep, ks);
-    } else if (nt % 2 == 0) {
-      if (split) ks = pick_ksplit(nt / 2, KT, M, arena, c->k.gemm_target_wgs);
-      ep.slab = (size_t)M * ep.ld;
-      launch_bf16<2, 1, 4>(st, W, A, M, N, K, kepi, ep, ks);
-    } else {
-      if (split) ks = pick_ksplit(nt, KT, M, arena, c->k.gemm_target_wgs);
-      ep.slab = (size_t)M * ep.ld;
-      launch_bf16<1, 1, 4>(st, W, A, M, N, K, kepi, ep, ks);
-    }
-  } else if (M <= 64 && nt % 8 == 0) {
-    // still bandwidth-bound: the same streaming kernel with two or four activation bands per weight tile.  As for a
-    // single band, 8 or 6 weight tiles per wavefront and the K split are chosen for the fullest rounds of the 256 CUs
-    // (gate/up of the 8B shape: 192 workgroups with 8 tiles, 256 with 6)
-    const int FILL4 = c->k.gemm_fill4;   // any value but 1: 8 tiles and power-of-two K splits only
-    int best_nt = 8;
-    if (FILL4 == 1) {
-      double best_fill = -1.0;
-      for (int cand : {8, 6}) {
-        if (nt % cand) continue;
-        const int nb = nt / cand;
-        for (int k = 1; k <= (split ? kMaxKSplit : 1); ++k) {
-          if (k > 1 && (KT / (k * 4) < 2 || k * M > arena)) break;
-          const int wgs = nb * k, rounds = (wgs + 255) / 256;
-          const double fill = (double)wgs / (rounds * 256.0) - 0.02 * (rounds - 1);
-          if (fill > best_fill + 1e-9) { best_fill = fill; best_nt = cand; ks = k; }
-        }
-      }
-    } else if (split) {
-      ks = pick_ksplit(nt / 8, KT, M, arena, c->k.gemm_target_wgs);
-    }
+  if (const StreamPlan sp = stream_plan(c->k, M, N, K, split, arena); sp.nt) {
+    ks = sp.ks;
     ep.slab = (size_t)M * ep.ld;
-    const int U4 = c->k.gemm_u4;   // k-tiles per prefetch stage for 16 < M <= 64 (2 measured slower)
-    if (M <= 32) {
-      if (best_nt == 6) launch_bf16<6, 2, 1>(st, W, A, M, N, K, kepi, ep, ks);
-      else if (U4 >= 2) launch_bf16<8, 2, 2>(st, W, A, M, N, K, kepi, ep, ks);
-      else launch_bf16<8, 2, 1>(st, W, A, M, N, K, kepi, ep, ks);
-    } else {
+    const int shape = sp.nt * 100 + sp.mt * 10 + sp.u;
+    switch (shape) {
+#define DF_STREAM(NT, MT, U) case NT * 100 + MT * 10 + U: launch_bf16<NT, MT, U>(st, W, A, M, N, K, kepi, ep, ks); break
+      DF_STREAM(8, 1, 2); DF_STREAM(8, 1, 1); DF_STREAM(6, 1, 2); DF_STREAM(4, 1, 4); DF_STREAM(4, 1, 2); DF_STREAM(4, 1, 1);
+      DF_STREAM(2, 1, 4); DF_STREAM(1, 1, 4); DF_STREAM(8, 2, 2); DF_STREAM(8, 2, 1); DF_STREAM(6, 2, 1); DF_STREAM(4, 2, 1);
       // (the single-buffered two-workgroups-per-CU form of this kernel that the routed experts use was measured here
       // too: 58.7 us against 48.2 for gate/up at 64 rows -- a dense launch has fewer workgroups than CUs)
-      if (best_nt == 6) launch_bf16<6, 4, 1>(st, W, A, M, N, K, kepi, ep, ks);
-      else if (U4 >= 2) launch_bf16<8, 4, 2>(st, W, A, M, N, K, kepi, ep, ks);
-      else launch_bf16<8, 4, 1>(st, W, A, M, N, K, kepi, ep, ks);
+      DF_STREAM(8, 4, 2); DF_STREAM(8, 4, 1); DF_STREAM(6, 4, 1); DF_STREAM(4, 4, 1);
+#undef DF_STREAM
     }
   } else if (M > 64 && nt % 2 == 0) {
     // compute-bound: LDS-staged tiles of 256, 192 or 128 weight rows x 128 activation rows.  Pick the shape and
