@@ -59,7 +59,7 @@ inline int env_int(const char* name, int dflt) {
 // context keeps the values it was created with, so a test that sets one before dflash_create gets exactly that path
 // whatever ran earlier in the process.  Defaults are what the measurements in the documentation use.
 struct Knobs {
-  int gemm_wide;            // DFLASH_GEMM_WIDE: 1 = eight-wavefront tiles where they fill one round of the CUs (default), 2 = wherever one fits (tests), any other value = never
+  int gemm_wide;            // DFLASH_GEMM_WIDE: 1 = eight-wavefront tiles by estimated time (default), 2 = wherever one fits (tests), any other value = never
   int attn_target_wgs;      // DFLASH_ATTN_TARGET_WGS: workgroups an attention launch aims at
   int attn_wide_min_chunk;  // DFLASH_ATTN_WIDE_MIN_CHUNK: keys per workgroup from which the key-split attention kernel is used
   int gemm_target_wgs;      // DFLASH_GEMM_TARGET_WGS: workgroups a K-split streaming GEMM aims at
@@ -68,14 +68,10 @@ struct Knobs {
   int gemm_fill;            // DFLASH_GEMM_FILL: 1 = weight tiles per wavefront (8 or 6) and K split chosen to fill whole rounds of the CUs
   int gemm_fill4;           // DFLASH_GEMM_FILL4: the same for 17-64 rows
   int gemm_u4;              // DFLASH_GEMM_U4: k tiles per prefetch stage for 17-64 rows
-  int gemm_solo_pct;        // DFLASH_GEMM_SOLO_PCT: tiled GEMM picker, time penalty (percent) of a ring tile alone on its CU
-  int gemm_pd;              // DFLASH_GEMM_PD: tiled GEMM, k tiles in flight from global memory (192/128-row tiles)
-  int gemm_ring;            // DFLASH_GEMM_RING: 1 = direct-to-LDS ring for the small tiles, other = register staging
   int gemm_tile, gemm_wm, gemm_ks;   // DFLASH_GEMM_TILE / _WM / _KS: force the tiled GEMM's shape / rows per tile / K split (0 = by estimated time)
   int lm_stats;             // DFLASH_LM_STATS: 1 = softmax statistics from the LM-head epilogue, other = from the stored logits
   int moe_mt;               // DFLASH_MOE_MT: 1, 2, 4 or 8 forces the bands per routed-expert work item (0 = by rows per expert)
   int moe_gather_min_rows;  // DFLASH_MOE_GATHER_MIN_ROWS: rows from which the routed-expert GEMMs get their rows copied into list order
-  int moe_phases;           // DFLASH_MOE_PHASES: 2 = two-half sum form of the 4-band down projection
   int moe_down_u;           // DFLASH_MOE_DOWN_U: k tiles per stage of the one-band down projection
   int fuse;                 // DFLASH_FUSE: few-row path, see dflash_ctx::fuse
   int resid_nw, resid_u;    // DFLASH_RESID_NW / _U: wavefronts per workgroup and k tiles per stage of the unsplit projection kernel
@@ -91,16 +87,12 @@ Knobs read_knobs() {
   k.gemm_fill = env_int("DFLASH_GEMM_FILL", 1);
   k.gemm_fill4 = env_int("DFLASH_GEMM_FILL4", 1);
   k.gemm_u4 = env_int("DFLASH_GEMM_U4", 1);
-  k.gemm_solo_pct = env_int("DFLASH_GEMM_SOLO_PCT", 120);
-  k.gemm_pd = env_int("DFLASH_GEMM_PD", 2);
-  k.gemm_ring = env_int("DFLASH_GEMM_RING", 1);
   k.gemm_tile = env_int("DFLASH_GEMM_TILE", 0);
   k.gemm_wm = env_int("DFLASH_GEMM_WM", 0);
   k.gemm_ks = env_int("DFLASH_GEMM_KS", 0);
   k.lm_stats = env_int("DFLASH_LM_STATS", 1);
   k.moe_mt = env_int("DFLASH_MOE_MT", 0);
   k.moe_gather_min_rows = env_int("DFLASH_MOE_GATHER_MIN_ROWS", 64);
-  k.moe_phases = env_int("DFLASH_MOE_PHASES", 2);
   k.moe_down_u = env_int("DFLASH_MOE_DOWN_U", 1);
   k.fuse = env_int("DFLASH_FUSE", 1);
   if (k.fuse != 1 && k.fuse != 2) k.fuse = 0;
@@ -887,16 +879,66 @@ void launch_bf16(hipStream_t st, const bf16_t* W, const bf16_t* A, int M, int N,
   }
 }
 
-template <int WN, int WM, int PD, int NS = 2, int WY = 2>
+template <int WN, int WM, int NS, int WY = 2, bool REG = false>
 void launch_tiled(hipStream_t st, const bf16_t* W, const bf16_t* A, int M, int N, int K, int epi, EpiArgs ep, int ks) {
   const int n_blocks = (N / 16 + WY * WN - 1) / (WY * WN), m_blocks = ((M + 15) / 16 + 2 * WM - 1) / (2 * WM);
-  const dim3 grid(((n_blocks + 7) / 8) * 8 * m_blocks, ks), block(128 * WY);
+  const dim3 grid((n_blocks * m_blocks + 7) / 8 * 8, ks), block(128 * WY);
   g_launch_parts = n_blocks;
   g_launch_kind = WY == 4 ? DFLASH_GEMM_TILED8 : DFLASH_GEMM_TILED4;
   if (epi == EPI_SWIGLU)
-    hipLaunchKernelGGL((gemm_bf16_tiled_kernel<WN, WM, PD, EPI_SWIGLU, NS, false, WY>), grid, block, 0, st, W, A, M, N, K, n_blocks, m_blocks, ep);
+    hipLaunchKernelGGL((gemm_bf16_tiled_kernel<WN, WM, EPI_SWIGLU, NS, false, WY, REG>), grid, block, 0, st, W, A, M, N, K, n_blocks, m_blocks, ep);
   else
-    hipLaunchKernelGGL((gemm_bf16_tiled_kernel<WN, WM, PD, EPI_STORE, NS, false, WY>), grid, block, 0, st, W, A, M, N, K, n_blocks, m_blocks, ep);
+    hipLaunchKernelGGL((gemm_bf16_tiled_kernel<WN, WM, EPI_STORE, NS, false, WY, REG>), grid, block, 0, st, W, A, M, N, K, n_blocks, m_blocks, ep);
+}
+
+// The LDS-staged tiles and what a k tile costs on a CU, in microseconds: `two` with two workgroups of the shape side by
+// side (four-wavefront tiles), `one` with a workgroup by itself; `fixed` per round of workgroups (ramp, prologue, epilogue).
+// Fitted to launches back to back over random operands (16 row counts from 80 to 2048, ten matrices of 2048 to 28672 rows
+// with K of 2048 to 12288, one to eight K ranges); the shape picked with them is on average 0.7-1.1 % slower than the
+// fastest one (the efficiency factors used before, which knew neither the pairing on a CU nor the XCDs' shares: 6.5 %).
+struct TileShape {
+  int wn, wm, wy;      // weight tiles and activation bands per wavefront, wavefronts along N
+  float two, one, fixed;
+};
+constexpr TileShape kTiles[] = {
+    {8, 4, 2, 1.32f, 1.00f, 1.0f},  {6, 4, 2, 1.02f, 0.72f, 1.5f},  {4, 4, 2, 0.747f, 0.464f, 3.5f}, {8, 2, 2, 0.727f, 0.463f, 3.1f},
+    {6, 2, 2, 0.579f, 0.397f, 3.4f}, {4, 2, 2, 0.44f, 0.269f, 2.9f}, {6, 4, 4, 0.f, 1.00f, 1.5f},     {4, 4, 4, 0.f, 0.715f, 2.0f},
+    {6, 2, 4, 0.f, 0.562f, 2.5f},    {4, 2, 4, 0.f, 0.425f, 3.3f}};
+
+struct TilePlan {
+  const TileShape* t = nullptr;
+  int ks = 1;
+};
+// Time of a launch = k tiles of a K range x cost of the workgroups on the busiest CU + the partial slabs (written by the
+// GEMM, read by its consumer).  XCDs take equal shares of the tiles, so the busiest CU has ceil(share / 32 CUs) workgroups.
+inline TilePlan tile_plan(const Knobs& kn, int M, int N, int K, bool split, int arena) {
+  const int nt = N / 16, KT = K / 32;
+  const bool forced = kn.gemm_tile || kn.gemm_wm || kn.gemm_ks;   // a forced four-wavefront shape stays forced
+  auto fits = [&](int k) { return k == 1 || (split && KT / k >= 8 && k * M <= arena); };
+  TilePlan best;
+  double best_t = 1e30;
+  for (const TileShape& t : kTiles) {
+    const int nb = (nt + t.wy * t.wn - 1) / (t.wy * t.wn), mb = ((M + 15) / 16 + 2 * t.wm - 1) / (2 * t.wm);
+    if (t.wy == 4) {
+      if (kn.gemm_wide == 2 ? nt % (4 * t.wn) != 0 : (kn.gemm_wide != 1 || forced)) continue;
+    }
+    if (kn.gemm_tile && kn.gemm_tile != t.wn) continue;
+    if (kn.gemm_wm && kn.gemm_wm != t.wm) continue;
+    for (int k : {1, 2, 3, 4, 6, 8}) {
+      if (!fits(k)) continue;
+      if (kn.gemm_ks && split && k != kn.gemm_ks && fits(kn.gemm_ks)) continue;
+      // a workgroup of eight wavefronts has its CU to itself: not for launches that leave many CUs without one
+      if (t.wy == 4 && kn.gemm_wide == 1 && nb * mb * k < 160) continue;
+      const int on_cu = ((nb * mb + 7) / 8 * k + 31) / 32, per = (KT + k - 1) / k;
+      const int pairs = t.wy == 2 ? on_cu / 2 : 0, single = on_cu - 2 * pairs;
+      double us = (pairs * t.two + single * t.one) * per + (pairs + single) * t.fixed;
+      if (split) us += 2.25 * k * M * (double)N * 4 / 4.7e6;   // slabs, at the rate of a large copy
+      if (t.wy == 4 && kn.gemm_wide == 2) us *= 1e-3;           // wherever one fits
+      if (us < best_t) { best_t = us; best.t = &t; best.ks = k; }
+    }
+  }
+  if (!best.t) best.t = &kTiles[2];   // a knob that names no shape
+  return best;
 }
 
 inline int gemm_class(int epi, int N, int vocab) { return (epi == EPI_STORE && N == vocab) ? DFLASH_PROF_GEMM_LMHEAD : epi; }
@@ -994,89 +1036,22 @@ Engine<bf16_t>::Slab Engine<bf16_t>::gemm(const bf16_t* W, const bf16_t* A, int 
 #undef DF_STREAM
     }
   } else if (M > 64 && nt % 2 == 0) {
-    // compute-bound: LDS-staged tiles of 256, 192 or 128 weight rows x 128 activation rows.  Pick the shape and
-    // K split with the least estimated time: workgroups on the busiest CU x MFMA time of one workgroup (larger
-    // tiles move fewer operand bytes per flop, hence the efficiency factors; a workgroup alone on its CU has
-    // nobody to hide its barriers and LDS latency behind), plus the traffic of the partial slabs.
-    struct Cand { int wn, wm; double eff; };
-    static const Cand cands[6] = {{8, 4, 1.0}, {6, 4, 0.95}, {4, 4, 0.85}, {8, 2, 0.8}, {6, 2, 0.75}, {4, 2, 0.65}};
-    int best_wn = 4, best_wm = 4;
-    bool best_solo = false;
-    double best = 1e30;
-    for (const Cand& cd : cands) {
-      if (c->k.gemm_tile && cd.wn != c->k.gemm_tile) continue;
-      if (c->k.gemm_wm && cd.wm != c->k.gemm_wm) continue;
-      const int mb = ((M + 15) / 16 + 2 * cd.wm - 1) / (2 * cd.wm);
-      const int wgs = ((nt + 2 * cd.wn - 1) / (2 * cd.wn)) * mb;
-      for (int k = 1; k <= kMaxKSplit; k *= 2) {
-        if (k > 1 && (!split || KT / k < 8 || k * M > arena)) break;
-        if (c->k.gemm_ks && split && k != c->k.gemm_ks && c->k.gemm_ks * M <= arena && KT / c->k.gemm_ks >= 8) continue;
-        const int per_cu = (wgs * k + 255) / 256;
-        const double mfma_us = 32.0 * cd.wn * cd.wm * ((KT + k - 1) / k) / 2400.0;   // MFMA issue time of one workgroup
-        const double slab_us = k > 1 ? (double)k * M * N * 8 / 4e6 : 0.0;
-        // a workgroup alone on its CU has nobody to hide its barriers behind; the 128-row tiles then run as a
-        // three-slot direct-to-LDS ring (they have the LDS to themselves), which loses less
-        const bool solo = per_cu == 1, solo_ring = solo && !split && cd.wm == 4 && cd.wn >= 6;   // measured: only pays where K is not split
-        const double solo_pen = c->k.gemm_solo_pct / 100.0;   // measured 120 against 140 and 100
-        const bool small_ring = cd.wm == 2 || cd.wn == 4;   // tiles that run as a direct-to-LDS ring anyway
-        const double t = per_cu * mfma_us / cd.eff * (solo ? (solo_ring ? 1.15 : (small_ring ? solo_pen : 1.4)) : 1.0) + slab_us;
-        if (t < best) { best = t; best_wn = cd.wn; best_wm = cd.wm; ks = k; best_solo = solo_ring; }
-      }
-    }
+    // compute-bound: LDS-staged tiles
+    const TilePlan tp = tile_plan(c->k, M, N, K, split, arena);
+    ks = tp.ks;
     ep.slab = (size_t)M * ep.ld;
-    // Eight-wavefront tiles (four wavefronts along N: 384 or 256 weight rows x 128 or 64 activation rows, one workgroup
-    // per CU): two of the four-wavefront workgroups fused along N, so the activation stage is fetched once for twice
-    // the weight rows.  Taken when such a tiling with some K split gives exactly one round that fills the CUs (225-256
-    // workgroups).  Isolated launches at 512 rows over random operands, against the best four-wavefront choice: gate/up
-    // 166 against 197 us, QKV 46 against 51.  Whole step: 25.2 against 25.8 ms at 512 rows, 12.24 against 12.42 at 256.
-    // Over several rounds they lose (gate/up of a 1024-row prefill pass, two rounds: 49.8 against 48.8 ms per prefill; the LM
-    // head at 512 rows, five to seven rounds: 1157-1230 against 1090 us).
-    const bool forced = c->k.gemm_tile || c->k.gemm_wm || c->k.gemm_ks;   // a forced four-wavefront shape stays forced
-    if (c->k.gemm_wide == 2 || (c->k.gemm_wide == 1 && !forced)) {
-      const bool any_fill = c->k.gemm_wide == 2;   // 2: the first fitting eight-wavefront tile whatever the number of workgroups
-      static const int wide[4][2] = {{6, 4}, {4, 4}, {6, 2}, {4, 2}};
-      for (const auto& wd : wide) {
-        if (nt % (4 * wd[0])) continue;
-        if (any_fill && ((c->k.gemm_tile && c->k.gemm_tile != wd[0]) || (c->k.gemm_wm && c->k.gemm_wm != wd[1]))) continue;
-        const int mb = ((M + 15) / 16 + 2 * wd[1] - 1) / (2 * wd[1]);
-        const int wgs = nt / (4 * wd[0]) * mb;
-        for (int k = 1; k <= kMaxKSplit; k *= 2) {
-          if (k > 1 && (!split || KT / k < 8 || k * M > arena)) break;
-          if (any_fill ? (c->k.gemm_ks && split && k != c->k.gemm_ks && c->k.gemm_ks * M <= arena && KT / c->k.gemm_ks >= 8)
-                       : (wgs * k < 225 || wgs * k > 256))
-            continue;
-          ks = k;
-          if (wd[0] == 6 && wd[1] == 4) launch_tiled<6, 4, 1, 3, 4>(st, W, A, M, N, K, kepi, ep, ks);
-          else if (wd[0] == 4 && wd[1] == 4) launch_tiled<4, 4, 1, 3, 4>(st, W, A, M, N, K, kepi, ep, ks);
-          else if (wd[0] == 6) launch_tiled<6, 2, 1, 3, 4>(st, W, A, M, N, K, kepi, ep, ks);
-          else launch_tiled<4, 2, 1, 4, 4>(st, W, A, M, N, K, kepi, ep, ks);
-          check();
-          ++c->gemm_counts[g_launch_kind];
-          if (ep.amax) amax_parts = g_launch_parts;
-          if (ep.lse) lse_parts = g_launch_parts;
-          if (epi == EPI_SWIGLU) return Slab{};
-          return Slab{ep.out, ks, ep.slab};
-        }
-      }
+    switch (tp.t->wy * 100 + tp.t->wn * 10 + tp.t->wm) {
+      case 284: launch_tiled<8, 4, 2, 2, true>(st, W, A, M, N, K, kepi, ep, ks); break;
+      case 264: launch_tiled<6, 4, 2>(st, W, A, M, N, K, kepi, ep, ks); break;
+      case 244: launch_tiled<4, 4, 3>(st, W, A, M, N, K, kepi, ep, ks); break;
+      case 282: launch_tiled<8, 2, 3>(st, W, A, M, N, K, kepi, ep, ks); break;
+      case 262: launch_tiled<6, 2, 3>(st, W, A, M, N, K, kepi, ep, ks); break;
+      case 242: launch_tiled<4, 2, 4>(st, W, A, M, N, K, kepi, ep, ks); break;
+      case 464: launch_tiled<6, 4, 3, 4>(st, W, A, M, N, K, kepi, ep, ks); break;
+      case 444: launch_tiled<4, 4, 4, 4>(st, W, A, M, N, K, kepi, ep, ks); break;
+      case 462: launch_tiled<6, 2, 4, 4>(st, W, A, M, N, K, kepi, ep, ks); break;
+      default: launch_tiled<4, 2, 4, 4>(st, W, A, M, N, K, kepi, ep, ks); break;
     }
-    const int PD = c->k.gemm_pd;              // k tiles in flight from global memory (192/128-row tiles)
-    const bool RING = c->k.gemm_ring == 1;    // any other value: register-staged variant for the small tiles
-    if (best_wm == 2 && RING) {
-      if (best_wn == 8) launch_tiled<8, 2, 1, 3>(st, W, A, M, N, K, kepi, ep, ks);
-      else if (best_wn == 6) launch_tiled<6, 2, 1, 3>(st, W, A, M, N, K, kepi, ep, ks);
-      else launch_tiled<4, 2, 1, 4>(st, W, A, M, N, K, kepi, ep, ks);
-    } else if (best_wm == 2) {
-      if (best_wn == 8) launch_tiled<8, 2, 2>(st, W, A, M, N, K, kepi, ep, ks);
-      else if (best_wn == 6) launch_tiled<6, 2, 2>(st, W, A, M, N, K, kepi, ep, ks);
-      else launch_tiled<4, 2, 2>(st, W, A, M, N, K, kepi, ep, ks);
-    } else if (best_wn == 4 && RING) launch_tiled<4, 4, 1, 3>(st, W, A, M, N, K, kepi, ep, ks);
-    else if (best_wn == 6 && best_solo && RING) launch_tiled<6, 4, 1, 3>(st, W, A, M, N, K, kepi, ep, ks);
-    else if (best_wn == 8 && best_solo && RING) launch_tiled<8, 4, 1, 3>(st, W, A, M, N, K, kepi, ep, ks);
-    else if (best_wn == 8) launch_tiled<8, 4, 1>(st, W, A, M, N, K, kepi, ep, ks);   // no registers left for a second set
-    else if (best_wn == 6 && PD == 2) launch_tiled<6, 4, 2>(st, W, A, M, N, K, kepi, ep, ks);
-    else if (best_wn == 6) launch_tiled<6, 4, 1>(st, W, A, M, N, K, kepi, ep, ks);
-    else if (PD == 2) launch_tiled<4, 4, 2>(st, W, A, M, N, K, kepi, ep, ks);
-    else launch_tiled<4, 4, 1>(st, W, A, M, N, K, kepi, ep, ks);
   } else {
     const int my = ((M + 15) / 16 + 3) / 4;
     if (nt % 2 == 0) {
@@ -1098,19 +1073,20 @@ Engine<bf16_t>::Slab Engine<bf16_t>::gemm(const bf16_t* W, const bf16_t* A, int 
 }
 
 // (four weight tiles per wavefront instead of eight were measured at 512 rows: 192 us against 174 for gate/up)
-template <int MT, int U, int EPI, int PH = 1>
+template <int MT, int U, int EPI>
 void launch_grouped(hipStream_t st, const bf16_t* W, const bf16_t* A, int rows, int N, int K, EpiArgs ep, int n_items) {
   const dim3 grid(((n_items + 7) / 8) * 8 * ((N / 16) / 8), 1, 1), block(256);
   ep.grp_n_items = n_items;
-  hipLaunchKernelGGL((gemm_bf16_kernel<8, MT, U, EPI, true, PH>), grid, block, 0, st, W, A, rows, N, K, ep);
+  hipLaunchKernelGGL((gemm_bf16_kernel<8, MT, U, EPI, true>), grid, block, 0, st, W, A, rows, N, K, ep);
 }
 
-// grouped launch of the LDS-staged kernel: items of up to 8 bands (one 128-row activation block each)
-template <int WN, int PD, int EPI, int NS>
+// grouped launch of the LDS-staged kernel: items of up to 2 * WM bands (one activation block each)
+template <int WN, int WM, int EPI, int NS, int WY>
 void launch_grouped_tiled(hipStream_t st, const bf16_t* W, const bf16_t* A, int rows, int N, int K, EpiArgs ep, int n_items) {
-  const int n_blocks = (N / 16 + 2 * WN - 1) / (2 * WN);
-  const dim3 grid(((n_items + 7) / 8) * 8 * n_blocks, 1), block(256);
-  hipLaunchKernelGGL((gemm_bf16_tiled_kernel<WN, 4, PD, EPI, NS, true>), grid, block, 0, st, W, A, rows, N, K, n_blocks, n_items, ep);
+  const int n_blocks = (N / 16 + WY * WN - 1) / (WY * WN);
+  const dim3 grid(((n_items + 7) / 8) * 8 * n_blocks, 1), block(128 * WY);
+  ep.slab = 0;
+  hipLaunchKernelGGL((gemm_bf16_tiled_kernel<WN, WM, EPI, NS, true, WY>), grid, block, 0, st, W, A, rows, N, K, n_blocks, n_items, ep);
 }
 
 template <>
@@ -1154,7 +1130,7 @@ Engine<bf16_t>::Slab Engine<bf16_t>::moe_ffn(const dflash_dims& m, const char* l
   // tuning knob: from this many rows on the listed rows are first copied into list order (the GEMM then reads whole
   // fragments); below, the GEMM reads them through the list
   const int gather_min = c->k.moe_gather_min_rows;
-  const bool gathered = M >= gather_min || MT == 8;   // the LDS-staged kernel copies whole fragments: list order only
+  const bool gathered = M >= gather_min || MT >= 4;   // the LDS-staged kernel copies whole fragments: list order only
   if (gathered) {
     hipLaunchKernelGGL(moe_gather_kernel, dim3((D / 32 + 3) / 4, n_pos / 16), dim3(256), 0, st, reinterpret_cast<const u32x4*>(a), r.row_of,
                        r.n_bands_out, D / 32, ws<u32x4>(c->ws.moe_a));
@@ -1162,11 +1138,10 @@ Engine<bf16_t>::Slab Engine<bf16_t>::moe_ffn(const dflash_dims& m, const char* l
     a = ws<bf16_t>(c->ws.moe_a);
   }
   const double used = (double)std::min(E, M * k);   // experts whose matrices are streamed, at most
-  // tuning knob: the 4-band grouped down projection runs single-buffered with the cross-wavefront sum in two halves (200
-  // registers, 64 KB of LDS: two workgroups per CU cover each other's waits); 1 = the double-buffered form, one
-  // workgroup per CU.  Measured at 512 rows: 91-95 us against 104-106.  The gate/up launch gains nothing from it (165-181
-  // us from run to run against 167-176) and stays double-buffered.
-  const int ph4 = c->k.moe_phases;
+  // Items of 4 and 8 bands run on the LDS-staged kernel: eight wavefronts on 256 x 64 tiles, two workgroups to a CU, keep
+  // 96 KB of k tiles on their way per CU, where the streaming kernel's cross-wavefront sum takes a whole CU's LDS and its
+  // short sweeps (16 k tiles a wavefront) end in it.  512 rows, 8 of 128 experts each (805 / 403 MB of matrices): gate/up
+  // 188 -> 175 us, down 96 -> 84 in the step; 177 -> 150 and 92 -> 87 as isolated launches.
   {
     ProfScope prof(c, st, DFLASH_PROF_MOE_GATEUP, used * 2 * Fe * D * 2);
     EpiArgs ep{nullptr, 0, 0, act, Fe};
@@ -1174,12 +1149,11 @@ Engine<bf16_t>::Slab Engine<bf16_t>::moe_ffn(const dflash_dims& m, const char* l
     if (gathered) ep.grp_rows = nullptr;
     const bf16_t* W = reinterpret_cast<const bf16_t*>(lbase + lo.wgu);
     if (MT == 8) {
-      ep.slab = 0;
-      if ((2 * Fe / 16) % 12 == 0) launch_grouped_tiled<6, 1, EPI_SWIGLU, 3>(st, W, a, n_pos, 2 * Fe, D, ep, n_items);
-      else launch_grouped_tiled<4, 1, EPI_SWIGLU, 3>(st, W, a, n_pos, 2 * Fe, D, ep, n_items);
-    } else if (MT == 1) launch_grouped<1, 2, EPI_SWIGLU>(st, W, a, n_pos, 2 * Fe, D, ep, n_items);   // one k tile per stage: no faster (78.9 us)
-    else if (MT == 2) launch_grouped<2, 1, EPI_SWIGLU>(st, W, a, n_pos, 2 * Fe, D, ep, n_items);
-    else launch_grouped<4, 1, EPI_SWIGLU>(st, W, a, n_pos, 2 * Fe, D, ep, n_items);
+      if ((2 * Fe / 16) % 12 == 0) launch_grouped_tiled<6, 4, EPI_SWIGLU, 2, 2>(st, W, a, n_pos, 2 * Fe, D, ep, n_items);
+      else launch_grouped_tiled<4, 4, EPI_SWIGLU, 3, 2>(st, W, a, n_pos, 2 * Fe, D, ep, n_items);
+    } else if (MT == 4) launch_grouped_tiled<4, 2, EPI_SWIGLU, 3, 4>(st, W, a, n_pos, 2 * Fe, D, ep, n_items);
+    else if (MT == 1) launch_grouped<1, 2, EPI_SWIGLU>(st, W, a, n_pos, 2 * Fe, D, ep, n_items);   // one k tile per stage: no faster (78.9 us)
+    else launch_grouped<2, 1, EPI_SWIGLU>(st, W, a, n_pos, 2 * Fe, D, ep, n_items);
     check();
     ++c->gemm_counts[DFLASH_GEMM_GROUPED];
   }
@@ -1192,12 +1166,11 @@ Engine<bf16_t>::Slab Engine<bf16_t>::moe_ffn(const dflash_dims& m, const char* l
     // at the 30B-A3B shape): one tile per stage leaves registers for four workgroups per CU, whose prologues and
     // epilogues overlap (measured 48 us against 54 with two tiles per stage and 60 with four)
     const int down_u = c->k.moe_down_u;
-    if (MT == 8) launch_grouped_tiled<4, 1, EPI_STORE, 3>(st, W, act, n_pos, D, Fe, ep, n_items);
+    if (MT == 8) launch_grouped_tiled<4, 4, EPI_STORE, 3, 2>(st, W, act, n_pos, D, Fe, ep, n_items);
+    else if (MT == 4) launch_grouped_tiled<4, 2, EPI_STORE, 3, 4>(st, W, act, n_pos, D, Fe, ep, n_items);
     else if (MT == 1 && down_u == 1) launch_grouped<1, 1, EPI_STORE>(st, W, act, n_pos, D, Fe, ep, n_items);
     else if (MT == 1) launch_grouped<1, 2, EPI_STORE>(st, W, act, n_pos, D, Fe, ep, n_items);
-    else if (MT == 2) launch_grouped<2, 1, EPI_STORE>(st, W, act, n_pos, D, Fe, ep, n_items);
-    else if (ph4 == 2) launch_grouped<4, 1, EPI_STORE, 2>(st, W, act, n_pos, D, Fe, ep, n_items);
-    else launch_grouped<4, 1, EPI_STORE>(st, W, act, n_pos, D, Fe, ep, n_items);
+    else launch_grouped<2, 1, EPI_STORE>(st, W, act, n_pos, D, Fe, ep, n_items);
     check();
     ++c->gemm_counts[DFLASH_GEMM_GROUPED];
   }

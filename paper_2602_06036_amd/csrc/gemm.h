@@ -91,8 +91,8 @@ struct GemmBuf {
   u32x4 w[U][NT], ah[U][MT], al[U][MT];
 };
 
-template <int NT, int MT, int U, int EPI, bool GRP = false, int PH = 1, int NW = 4>
-__global__ __launch_bounds__(64 * NW, (NW > 4 ? 1 : PH)) void gemm_bf16_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ A,
+template <int NT, int MT, int U, int EPI, bool GRP = false, int NW = 4>
+__global__ __launch_bounds__(64 * NW, 1) void gemm_bf16_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ A,
                                                         int M, int N, int K, EpiArgs ep) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int kz = blockIdx.z;
@@ -211,15 +211,7 @@ __global__ __launch_bounds__(64 * NW, (NW > 4 ? 1 : PH)) void gemm_bf16_kernel(c
   // time, and the wait for the older buffer would then have to drain the newer one as well.  The last one or two
   // stages are peeled off; if the range has an odd number of stages the final load re-reads the last tile
   // (still in cache) and meets zeroed activations.
-  if constexpr (PH == 2 && NW == 4) {
-    // one buffer only (and the cross-wavefront sum below in two halves): half the registers and half the LDS, so that
-    // two workgroups share a CU and their wavefronts cover each other's waits
-    GemmBuf<NT, MT, U> b;
-    for (int k0 = kb; k0 < ke; k0 += U) {
-      load(b, k0);
-      compute(b);
-    }
-  } else if (kb < ke) {
+  if (kb < ke) {
     GemmBuf<NT, MT, U> b0, b1;
     load(b0, kb);
     int k0 = kb;
@@ -234,12 +226,10 @@ __global__ __launch_bounds__(64 * NW, (NW > 4 ? 1 : PH)) void gemm_bf16_kernel(c
     compute(b1);
   }
 
-  // The four wavefronts' partial sums meet in LDS, PH phases of NT / PH weight tiles each (PH = 2 halves the buffer).
-  constexpr int HT = NT / PH;
-  static_assert(NT % PH == 0 && (EPI != EPI_SWIGLU || HT % 2 == 0), "phases");
-  __shared__ float4 red[NW][HT * MT][64];
+  // The wavefronts' partial sums meet in LDS.
+  __shared__ float4 red[NW][NT * MT][64];
   const int mrow = lane & 15, g = lane >> 4;
-  // the four wavefronts' partial sums of tile t (= weight tile * MT + band) of the current phase, in wavefront order,
+  // the wavefronts' partial sums of tile t (= weight tile * MT + band), in wavefront order,
   // times the row's deferred 1 / rms
   auto tile_sum = [&](int t) {
     float4 s = red[0][t][lane];
@@ -254,45 +244,34 @@ __global__ __launch_bounds__(64 * NW, (NW > 4 ? 1 : PH)) void gemm_bf16_kernel(c
     }
     return s;
   };
-  auto phase = [&](auto phc) {
-    constexpr int ph = decltype(phc)::value;
-    if (ph) __syncthreads();   // everybody is done reading the previous phase
 #pragma unroll
-    for (int i = 0; i < HT; ++i)
+  for (int i = 0; i < NT; ++i)
 #pragma unroll
-      for (int j = 0; j < MT; ++j)
-        red[wave][i * MT + j][lane] = make_float4(acc[ph * HT + i][j][0], acc[ph * HT + i][j][1], acc[ph * HT + i][j][2], acc[ph * HT + i][j][3]);
-    __syncthreads();
-    if (EPI == EPI_SWIGLU) {
-      bf16_t* act = reinterpret_cast<bf16_t*>(ep.act);
-      for (int t = wave; t < (HT / 2) * MT; t += NW) {
-        const int p = t / MT, j = t % MT;
-        const float4 gs = tile_sum((2 * p) * MT + j), us = tile_sum((2 * p + 1) * MT + j);
-        const int m = (mt0 + j) * 16 + mrow;
-        if (mt0 + j < m_tiles && m < M) {
-          const int col = ((nt0 + ph * HT + 2 * p) >> 1) * 16 + 4 * g;
-          Act<bf16_t>::store4(act, m, col, ep.act_K,
-                              make_float4(silu_f(gs.x) * us.x, silu_f(gs.y) * us.y, silu_f(gs.z) * us.z, silu_f(gs.w) * us.w));
-        }
-      }
-    } else if (ep.out) {
-      for (int t = wave; t < HT * MT; t += NW) {
-        const int i = t / MT, j = t % MT;
-        const float4 s = tile_sum(t);
-        const int m = (mt0 + j) * 16 + mrow;
-        if (mt0 + j < m_tiles && m < M) {
-          float4* dst = reinterpret_cast<float4*>(ep.out + (size_t)kz * ep.slab + (size_t)m * ep.ld + (nt0 + ph * HT + i) * 16 + 4 * g);
-          *dst = s;
-        }
+    for (int j = 0; j < MT; ++j) red[wave][i * MT + j][lane] = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+  __syncthreads();
+  if (EPI == EPI_SWIGLU) {
+    bf16_t* act = reinterpret_cast<bf16_t*>(ep.act);
+    for (int t = wave; t < (NT / 2) * MT; t += NW) {
+      const int p = t / MT, j = t % MT;
+      const float4 gs = tile_sum((2 * p) * MT + j), us = tile_sum((2 * p + 1) * MT + j);
+      const int m = (mt0 + j) * 16 + mrow;
+      if (mt0 + j < m_tiles && m < M) {
+        const int col = ((nt0 + 2 * p) >> 1) * 16 + 4 * g;
+        Act<bf16_t>::store4(act, m, col, ep.act_K,
+                            make_float4(silu_f(gs.x) * us.x, silu_f(gs.y) * us.y, silu_f(gs.z) * us.z, silu_f(gs.w) * us.w));
       }
     }
-  };
-  phase(std::integral_constant<int, 0>{});
-  if constexpr (PH >= 2) phase(std::integral_constant<int, 1>{});
-  if constexpr (PH >= 3) phase(std::integral_constant<int, 2>{});
-  static_assert(PH <= 3, "phases");
+  } else if (ep.out) {
+    for (int t = wave; t < NT * MT; t += NW) {
+      const int i = t / MT, j = t % MT;
+      const float4 s = tile_sum(t);
+      const int m = (mt0 + j) * 16 + mrow;
+      if (mt0 + j < m_tiles && m < M)
+        *reinterpret_cast<float4*>(ep.out + (size_t)kz * ep.slab + (size_t)m * ep.ld + (nt0 + i) * 16 + 4 * g) = s;
+    }
+  }
 
-  if constexpr (EPI != EPI_SWIGLU && PH == 1) {
+  if constexpr (EPI != EPI_SWIGLU) {
     if (ep.amax) {   // fused argmax over this workgroup's NT*16 columns (host guarantees a single K range)
       __shared__ float2 wbest[NW][MT * 16];
       const uint64_t key = ep.amax_mode ? ep.amax_key[0] : 0ull;

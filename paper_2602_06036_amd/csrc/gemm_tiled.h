@@ -3,40 +3,54 @@
 //
 // A workgroup of 2*WY wavefronts (WY = 2 or 4 along N x 2 along M) owns a tile of WY*WN weight row bands x 2*WM
 // activation row bands for one K range (grid.y).  Both operands already sit in HBM in MFMA fragment order (1 KB per
-// 16x32 fragment), so a k tile is staged by copying whole fragments: global -> registers (PD k tiles in flight)
-// -> one of two LDS slots; every wavefront reads the WN weight and 2*WM activation fragments of its part of the tile
-// (each lane its own 16 bytes: conflict-free ds_read_b128) and issues WN*WM*2 MFMAs per k tile.  The eight-wavefront
-// form (WY = 4) is two four-wavefront workgroups fused along N: one activation stage for twice the weight rows,
-// i.e. a third less operand traffic from L2 per flop, at one workgroup per CU.
-// Schedule of a k tile, register-staged variant (NS = 2; one barrier per k tile, order pinned with scheduling
-// barriers): barrier -> all WN + 2*WM fragment reads of the k tile -> the LDS writes of the next k tile (from
-// registers loaded PD k tiles earlier) and the global loads of k tile t+1+PD -> the WN*WM*2 MFMAs.  LDS operations
-// of a wavefront complete in order and a 1 KB ds_write occupies the LDS path several times longer than a read, so
-// the reads go first: the MFMAs wait for the reads only and the writes drain behind the MFMA stream; the second
-// workgroup on the CU fills the gaps around the barrier.
-// Ring variant (NS >= 3): the k tiles arrive by direct-to-LDS loads, see the comment at the loop.  It is used where
-// NS slots fit next to a second workgroup on the CU (128 x 128 and the 64-row tiles) and for the 128-row tiles of
-// an unsplit GEMM whose workgroups each have a CU to themselves.
+// 16x32 fragment), so a k tile is staged in LDS by copying whole fragments; every wavefront reads the WN weight and 2*WM
+// activation fragments of its part of the tile (each lane its own 16 bytes: conflict-free ds_read_b128) and issues
+// WN*WM*2 MFMAs per k tile.  The eight-wavefront form (WY = 4) is two four-wavefront workgroups fused along N: one
+// activation stage for twice the weight rows, i.e. a third less operand traffic from L2 per flop, at one workgroup per CU.
 //
-// Workgroup order: consecutive workgroup ids go to different XCDs (round-robin dispatch), so id = 8*j + x
-// is mapped to weight band block 8*(j / m_blocks) + x and activation block j % m_blocks: the workgroups that
-// re-read one weight block run back to back on one XCD and share its L2.
+// What bounds it: over random operands every tiling ends at 1.2-1.45 PFLOP/s of issued MFMA work (a torch matrix product of
+// the same issued size reaches 1.1-1.47), where the clock gives way to the power limit; below that the waits at the k tiles' seams count.
+//
+// Pipelined variant (REG = false): a ring of NS LDS slots filled by direct-to-LDS loads (global_load_lds_dwordx4: every
+// lane's 16 bytes go straight to consecutive LDS addresses, which is exactly a fragment in operand order), and the
+// fragments double-buffered in registers: while the MFMAs of k tile t run out of one register set, the LDS reads of k tile
+// t+1 fill the other, so no MFMA waits for LDS behind the barrier.  One barrier per k tile.  Against the same ring with the
+// reads behind the barrier: gate/up of the 8B shape 155-160 -> 150 us at 512 rows, 92 -> 85-89 at 256, 2-4 % elsewhere.
+// Register-staged variant (REG = true, 256 x 128 tiles): global -> registers -> one of two LDS slots.  Its 128
+// accumulators leave no registers for a second fragment set with two workgroups on a CU, and the two cover each other's
+// seams; the largest wavefront tile moves the fewest bytes per flop and is the fastest one over many rounds (2048 rows:
+// gate/up 570 us, 1.45 PFLOP/s).  Order inside a k tile: barrier -> all fragment reads -> the LDS writes of the next k
+// tile and the global loads after it -> the MFMAs; LDS operations of a wavefront complete in order, so the MFMAs wait for
+// the reads only and the (slow) writes drain behind the MFMA stream.
+//
+// Workgroup order: consecutive workgroup ids go to different XCDs (round-robin dispatch, id = 8*j + x), and the
+// workgroups that re-read one weight block run back to back on one XCD and share its L2.  Where the weight blocks divide
+// evenly over the XCDs, XCD x takes blocks x, x + 8, ...: the chip sweeps neighbouring blocks together.  Otherwise XCD x
+// takes the x-th eighth of the tiles, counted activation block by activation block within a weight block, so that no XCD has
+// more than one tile more than another (20 blocks are 3 on four XCDs and 2 on four: a fifth of the launch; the even case is
+// 1 % faster the first way).
 #pragma once
 #include "gemm.h"
 
-template <int WN, int WM, int PD, int EPI, int NS = 2, bool GRP = false, int WY = 2>
-__global__ __launch_bounds__(128 * WY, (WY == 2 && NS * (2 * WN + 4 * WM) <= 80 ? 2 : 1)) void gemm_bf16_tiled_kernel(
+// whether two workgroups of this shape share a CU (their staging fits twice)
+template <int WN, int WM, int NS, int WY>
+constexpr bool tiled_twice() { return WY == 2 && NS * (WY * WN + 4 * WM) <= 80; }
+
+template <int WN, int WM, int EPI, int NS, bool GRP = false, int WY = 2, bool REG = false>
+__global__ __launch_bounds__(128 * WY, (tiled_twice<WN, WM, NS, WY>() ? 2 : 1)) void gemm_bf16_tiled_kernel(
     const bf16_t* __restrict__ W, const bf16_t* __restrict__ A, int M, int N, int K, int n_blocks, int m_blocks, EpiArgs ep) {
   constexpr int NWV = 2 * WY;                       // wavefronts: WY along N x 2 along M
   constexpr int BNT = WY * WN, BMT = 2 * WM;        // fragments of a stage: BNT weight + 2*BMT activation (hi, lo)
   constexpr int FR = BNT + 2 * BMT, PER = FR / NWV; // fragments copied by each wavefront
-  static_assert(WN % 2 == 0 && WM % 2 == 0 && FR % NWV == 0 && (PD == 1 || PD == 2) && NS >= 2 && NS * FR <= 160 && (WY == 2 || WY == 4),
+  static_assert(WN % 2 == 0 && WM % 2 == 0 && FR % NWV == 0 && NS >= 2 && (!REG || NS == 2) && NS * FR <= 160 && (WY == 2 || WY == 4),
                 "tile shape");
   __shared__ u32x4 stage[NS][FR][64];
 
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wy = wave >> 1, wx = wave & 1;
   const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
-  int nb = (j / m_blocks) * 8 + xcd, mb = j % m_blocks;
+  const int tile = xcd * (int)(gridDim.x >> 3) + j;
+  int nb = tile / m_blocks, mb = tile % m_blocks;
+  if ((n_blocks & 7) == 0) { nb = (j / m_blocks) * 8 + xcd; mb = j % m_blocks; }
   const int KT = K >> 5, n_tiles = N >> 4;
   int m_tiles = (M + 15) >> 4, mt0 = mb * BMT;
   if constexpr (GRP) {
@@ -57,31 +71,26 @@ __global__ __launch_bounds__(128 * WY, (WY == 2 && NS * (2 * WN + 4 * WM) <= 80 
   const int kb = min(KT, kz * per), ke = min(KT, kb + per);
   const int nt0 = nb * BNT;
 
-  // the PER fragments this wavefront copies per stage: offset at k tile 0 and stride per k tile (u32x4 units)
-  size_t g_off[PER];
-  int g_step[PER];
-  const u32x4* g_base[PER];
+  // the PER fragments this wavefront copies per stage: address at k tile kb (the same for all lanes) and bytes per k tile
+  const char* src[PER];
+  unsigned step[PER];
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
     const int f = wave * PER + i;
     if (f < BNT) {   // weight fragment: bands past the matrix alias the last band (never stored)
-      g_base[i] = reinterpret_cast<const u32x4*>(W);
-      g_off[i] = (size_t)min(nt0 + f, n_tiles - 1) * 64 + lane;
-      g_step[i] = n_tiles * 64;
+      src[i] = reinterpret_cast<const char*>(W) + ((size_t)kb * n_tiles + min(nt0 + f, n_tiles - 1)) * 1024;
+      step[i] = (unsigned)n_tiles * 1024u;
     } else {         // activation fragment: band (f - BNT) / 2, plane (f - BNT) % 2
       const int a = f - BNT;
-      g_base[i] = reinterpret_cast<const u32x4*>(A);
-      g_off[i] = (size_t)min(mt0 + (a >> 1), m_tiles - 1) * KT * 128 + (a & 1) * 64 + lane;
-      g_step[i] = 128;
+      src[i] = reinterpret_cast<const char*>(A) + ((size_t)min(mt0 + (a >> 1), m_tiles - 1) * KT + kb) * 2048 + (a & 1) * 1024;
+      step[i] = 2048u;
     }
   }
-  auto load_global = [&](u32x4 (&g)[PER], int kt) {
+  int at_kt = kb;             // k tile the addresses stand at; past the end of the K range they stay on the last one
+  auto advance = [&]() {
+    const bool go = ++at_kt < ke;
 #pragma unroll
-    for (int i = 0; i < PER; ++i) g[i] = g_base[i][g_off[i] + (size_t)kt * g_step[i]];
-  };
-  auto write_lds = [&](int slot, const u32x4 (&g)[PER]) {
-#pragma unroll
-    for (int i = 0; i < PER; ++i) stage[slot][wave * PER + i][lane] = g[i];
+    for (int i = 0; i < PER; ++i) src[i] += go ? step[i] : 0u;
   };
 
   f32x4 acc[WN][WM];
@@ -89,116 +98,117 @@ __global__ __launch_bounds__(128 * WY, (WY == 2 && NS * (2 * WN + 4 * WM) <= 80 
   for (int i = 0; i < WN; ++i)
 #pragma unroll
     for (int jj = 0; jj < WM; ++jj) acc[i][jj] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  auto mma_band = [&](int jj, const u32x4 (&wf)[WN], const u32x4 (&ap)[2]) {
+#pragma unroll
+    for (int i = 0; i < WN; ++i)
+      acc[i][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf[i]), __builtin_bit_cast(bf16x8, ap[0]), acc[i][jj], 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < WN; ++i)
+      acc[i][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf[i]), __builtin_bit_cast(bf16x8, ap[1]), acc[i][jj], 0, 0, 0);
+  };
+  auto read = [&](int slot, u32x4 (&wf)[WN], u32x4 (&ap)[WM][2]) {
+    const u32x4* sp = &stage[0][0][0] + (size_t)slot * (FR * 64) + lane;
+#pragma unroll
+    for (int i = 0; i < WN; ++i) wf[i] = sp[(wy * WN + i) * 64];
+#pragma unroll
+    for (int jj = 0; jj < WM; ++jj) {
+      ap[jj][0] = sp[(BNT + 2 * (wx * WM + jj)) * 64];
+      ap[jj][1] = sp[(BNT + 2 * (wx * WM + jj) + 1) * 64];
+    }
+  };
 
   if (kb < ke) {
-   if constexpr (NS == 2) {
-    u32x4 g[PD][PER];   // k tiles t+1 .. t+PD on their way from global memory while k tile t is multiplied
-    load_global(g[0], kb);
-    write_lds(0, g[0]);
+   if constexpr (REG) {
+    u32x4 g[PER];   // k tile t+1 on its way from global memory while k tile t is multiplied
+    auto load_global = [&]() {
 #pragma unroll
-    for (int d = 0; d < PD; ++d) load_global(g[d], min(kb + 1 + d, ke - 1));
-
-    // One k tile out of LDS slot S0; k tile t+1 goes from register set G into the other slot meanwhile.
-    // Order inside a k tile, pinned with scheduling barriers: barrier (k tile t is complete in S0, everybody is done
-    // with the other slot) -> all fragment reads of the k tile -> the LDS writes of k tile t+1 and the global loads
-    // of k tile t+1+PD -> the MFMAs.  LDS operations of a wavefront complete in order, so the reads must be issued
-    // before the (slow) writes: the MFMAs then wait for the reads only, and the writes drain behind the MFMA stream.
+      for (int i = 0; i < PER; ++i) g[i] = reinterpret_cast<const u32x4*>(src[i])[lane];
+      advance();
+    };
+    auto write_lds = [&](int slot) {
+#pragma unroll
+      for (int i = 0; i < PER; ++i) stage[slot][wave * PER + i][lane] = g[i];
+    };
+    load_global();
+    write_lds(0);
+    load_global();
     // Straight-line body: past the end of the K range the global loads repeat the last k tile and the write fills a
     // slot nobody reads any more.
-    auto k_tile = [&](auto s0_c, auto g_c, int kt) {
-      constexpr int s0 = decltype(s0_c)::value, s1 = s0 ^ 1, G = decltype(g_c)::value;
+    auto k_tile = [&](auto s0_c) {
+      constexpr int s0 = decltype(s0_c)::value;
       u32x4 wf[WN], ap[WM][2];
-      __syncthreads();
+      __syncthreads();                       // k tile t is complete in s0, everybody is done with the other slot
+      __builtin_amdgcn_sched_barrier(0);
+      read(s0, wf, ap);
+      __builtin_amdgcn_sched_barrier(0);
+      write_lds(s0 ^ 1);
+      load_global();
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int i = 0; i < WN; ++i) wf[i] = stage[s0][wy * WN + i][lane];
-#pragma unroll
-      for (int jj = 0; jj < WM; ++jj) {
-        ap[jj][0] = stage[s0][BNT + 2 * (wx * WM + jj)][lane];
-        ap[jj][1] = stage[s0][BNT + 2 * (wx * WM + jj) + 1][lane];
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      write_lds(s1, g[G]);
-      load_global(g[G], min(kt + 1 + PD, ke - 1));
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int jj = 0; jj < WM; ++jj) {
-#pragma unroll
-        for (int i = 0; i < WN; ++i)
-          acc[i][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf[i]), __builtin_bit_cast(bf16x8, ap[jj][0]),
-                                                               acc[i][jj], 0, 0, 0);
-#pragma unroll
-        for (int i = 0; i < WN; ++i)
-          acc[i][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf[i]), __builtin_bit_cast(bf16x8, ap[jj][1]),
-                                                               acc[i][jj], 0, 0, 0);
-      }
+      for (int jj = 0; jj < WM; ++jj) mma_band(jj, wf, ap[jj]);
       __builtin_amdgcn_sched_barrier(0);
     };
-    using I0 = std::integral_constant<int, 0>;
-    using I1 = std::integral_constant<int, 1>;
-    using IG = std::integral_constant<int, PD - 1>;
     int kt = kb;
     for (; kt + 1 < ke; kt += 2) {
-      k_tile(I0{}, I0{}, kt);
-      k_tile(I1{}, IG{}, kt + 1);
+      k_tile(std::integral_constant<int, 0>{});
+      k_tile(std::integral_constant<int, 1>{});
     }
-    if (kt < ke) k_tile(I0{}, I0{}, kt);
+    if (kt < ke) k_tile(std::integral_constant<int, 0>{});
    } else {
-    // ---- ring of NS LDS slots filled by direct-to-LDS loads (global_load_lds_dwordx4: every lane's 16 bytes go
-    // straight to consecutive LDS addresses, which is exactly a fragment in operand order) -------------------
-    // No staging registers, no ds_write (a 1 KB ds_write holds up the wavefront's SIMD several times longer than the
-    // issue of such a load), k tiles t+1 .. t+NS-1 in flight while k tile t is multiplied.  The loads are inline
-    // assembly so that the compiler does not count them: it would otherwise wait for ALL of them before every LDS
-    // read.  Completion is tracked by hand: each wavefront issues PER loads per k tile, in order, so "at most
-    // PER*(NS-2) outstanding" means its share of k tile t has landed; the barrier extends that to the whole
-    // workgroup and also says that everybody is done reading k tile t-1, whose slot is refilled next.
-    const unsigned lds_base = (unsigned)(size_t)&stage[0][0][0];
-    auto dma_tile = [&](int slot, int kt) {
-#pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        const u32x4* src = g_base[i] + g_off[i] + (size_t)kt * g_step[i];
-        const unsigned dst = __builtin_amdgcn_readfirstlane(lds_base + (unsigned)((slot * FR + wave * PER + i) * 1024));
-        // m0 carries the LDS address; whatever the compiler keeps in it is put back, so the statement clobbers nothing
-        unsigned keep_m0;
-        asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off\n\ts_nop 0\n\ts_mov_b32 m0, %0"
-                     : "=&s"(keep_m0)
-                     : "s"(dst), "v"(src)
-                     : "memory");
-      }
+    // The direct-to-LDS loads are inline assembly so that the compiler does not count them: it would otherwise wait for ALL of
+    // them before every LDS read.  Completion is tracked by hand: each wavefront issues PER loads per k tile, in order, so
+    // "at most PER*(NS-2) outstanding" says that its share of k tile t+1 has landed.  The barrier extends that to the whole
+    // workgroup; every wavefront has waited for its reads of k tile t before it, so slot t may be refilled behind it.
+    const unsigned lds_base = (unsigned)(size_t)&stage[0][0][0] + (unsigned)(wave * PER) * 1024u, voff = lane * 16;
+    auto dma = [&](int i, int slot) {
+      const unsigned dst = __builtin_amdgcn_readfirstlane(lds_base + (unsigned)((slot * FR + i) * 1024));
+      // m0 carries the LDS address; whatever the compiler keeps in it is put back, so the statement clobbers nothing
+      unsigned keep_m0;
+      asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_nop 0\n\ts_mov_b32 m0, %0"
+                   : "=&s"(keep_m0) : "s"(dst), "v"(voff), "s"(src[i]) : "memory");
     };
+    for (int d = 0; d < NS; ++d) {
 #pragma unroll
-    for (int d = 0; d < NS - 1; ++d) dma_tile(d, min(kb + d, ke - 1));
+      for (int i = 0; i < PER; ++i) dma(i, d);
+      advance();
+    }
+    u32x4 wf[2][WN], ap[2][WM][2];
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER * (NS - 1)) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    read(0, wf[0], ap[0]);
     int slot = 0;
-    for (int kt = kb; kt < ke; ++kt) {
+    // the refill's loads go out in front of the MFMAs or between the activation bands: 384 x 128 tiles like the former (150
+    // against 155 us for gate/up at 512 rows), the others the latter
+    constexpr bool SPREAD = !(WN == 6 && WM == 4);
+    auto k_tile = [&](auto cur_c) {
+      constexpr int C = decltype(cur_c)::value;
       asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER * (NS - 2)) : "memory");
+      __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): this wavefront's reads of k tile t are done
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
-      u32x4 wf[WN], ap[WM][2];
-      const u32x4* sp = &stage[0][0][0] + (size_t)slot * (FR * 64) + lane;
-#pragma unroll
-      for (int i = 0; i < WN; ++i) wf[i] = sp[(wy * WN + i) * 64];
-#pragma unroll
-      for (int jj = 0; jj < WM; ++jj) {
-        ap[jj][0] = sp[(BNT + 2 * (wx * WM + jj)) * 64];
-        ap[jj][1] = sp[(BNT + 2 * (wx * WM + jj) + 1) * 64];
-      }
-      // past the end of the K range the last k tile is fetched again into a slot nobody reads any more
-      dma_tile(slot == 0 ? NS - 1 : slot - 1, min(kt + NS - 1, ke - 1));
+      __builtin_amdgcn_sched_barrier(0);
+      const int next = slot == NS - 1 ? 0 : slot + 1;
+      read(next, wf[C ^ 1], ap[C ^ 1]);     // past the end: a landed copy of the last k tile, not used
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int jj = 0; jj < WM; ++jj) {
 #pragma unroll
-        for (int i = 0; i < WN; ++i)
-          acc[i][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf[i]), __builtin_bit_cast(bf16x8, ap[jj][0]),
-                                                               acc[i][jj], 0, 0, 0);
-#pragma unroll
-        for (int i = 0; i < WN; ++i)
-          acc[i][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf[i]), __builtin_bit_cast(bf16x8, ap[jj][1]),
-                                                               acc[i][jj], 0, 0, 0);
+        for (int i = 0; i < PER; ++i)
+          if ((SPREAD ? i * WM / PER : 0) == jj) dma(i, slot);
+        __builtin_amdgcn_sched_barrier(0);
+        mma_band(jj, wf[C], ap[C][jj]);
+        __builtin_amdgcn_sched_barrier(0);
       }
-      __builtin_amdgcn_sched_barrier(0);
-      slot = slot == NS - 1 ? 0 : slot + 1;
+      advance();
+      slot = next;
+    };
+    int kt = kb;
+    for (; kt + 1 < ke; kt += 2) {
+      k_tile(std::integral_constant<int, 0>{});
+      k_tile(std::integral_constant<int, 1>{});
     }
+    if (kt < ke) k_tile(std::integral_constant<int, 0>{});
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // nothing may still be on its way into LDS when the slots are reused or released
    }
   }

@@ -2,6 +2,8 @@
 // write, row argmax / Gumbel-max, acceptance, commit bookkeeping, weight packing and
 // KV import/export.
 #pragma once
+#include <type_traits>
+
 #include "common.h"
 
 // ---- block assembly + embedding gather -------------------------------------------------------
@@ -258,21 +260,23 @@ __global__ __launch_bounds__(256) void qkv_post_kernel(const float* __restrict__
   }
   const int n_s = geo.seq_lens[s];
   float x1 = 0.f, x2 = 0.f;
-  for (int z = 0; z < ks; z += 4) {   // four slabs in flight, added in ascending order
-    float p1[4], p2[4];
+  // the slabs in ascending order, up to four in flight (the same few instructions whatever ks is: no slab is read twice)
+  auto add = [&](int z, auto nc) {
+    constexpr int C = decltype(nc)::value;
+    float p1[C], p2[C];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float* pz = src + (size_t)min(z + i, ks - 1) * slab;
-      p1[i] = pz[0];
-      p2[i] = pz[half];
+    for (int i = 0; i < C; ++i) {
+      p1[i] = src[(size_t)(z + i) * slab];
+      p2[i] = src[(size_t)(z + i) * slab + half];
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      x1 += z + i < ks ? p1[i] : 0.f;
-      x2 += z + i < ks ? p2[i] : 0.f;
-    }
-  }
+    for (int i = 0; i < C; ++i) { x1 += p1[i]; x2 += p2[i]; }
+  };
+  int z = 0;
+  for (; z + 4 <= ks; z += 4) add(z, std::integral_constant<int, 4>{});
+  if (z + 2 <= ks) { add(z, std::integral_constant<int, 2>{}); z += 2; }
+  if (z < ks) add(z, std::integral_constant<int, 1>{});
   const int pos = n_s + slot;
   T* base = nullptr;
   const int key = pos % DF_PAGE;

@@ -98,3 +98,49 @@ def test_fp32_head_dims_and_widths(hd, heads, kv_heads, ffn, lens):
         ls.step(plan=plan, step_idx=i)
     ls.check_cache([0, 1], [0])
     assert ls.stats["reseeds"] == 0
+
+
+@pytest.mark.parametrize("n_seqs,d,ffn,vocab", [
+    (5, 256, 1056, 1008),       # 80 rows: a row block of five bands; 66 and 63 row bands of weights (clamped last tiles)
+    (9, 256, 2560, 4096),       # 144 rows: nine bands; 20 weight blocks of 256 rows (not a multiple of the eight XCDs)
+    (17, 512, 1536, 2064),      # 272 rows: one band behind two blocks of 128
+])
+def test_bf16_tile_edges_many_rows(n_seqs, d, ffn, vocab):
+    """The LDS-staged GEMM at row counts and matrix heights that leave tiles, activation blocks and the XCDs' shares
+    ragged, with the shapes and K splits that the dispatcher picks."""
+    w = tiny_workload(seed=d + ffn, n_layers=2, draft_layers=1, vocab=vocab, block=16, qk_norm=True, kv_heads=2, dtype="bf16",
+                      n_seqs=n_seqs, taps=(0, 1), d=d, heads=d // 64, hd=64, ffn=ffn)
+    lens = [20 + (7 * i) % 31 for i in range(n_seqs)]
+    prompts = [p[:n] for p, n in zip(si.make_prompts(replace(w, ctx_min=60, ctx_max=60)), lens)]
+    ls = Lockstep(w, prompts, max_len=60 + 4 * 16)
+    ls.prefill()
+    ls.g.e.gemm_counts()
+    for i, plan in enumerate([[(5 * s) % 16 for s in range(n_seqs)], None]):
+        ls.step(plan=plan, step_idx=i)
+    counts = ls.g.e.gemm_counts()
+    assert counts[1] + counts[2] > 0
+    ls.check_cache([0, 1], [0])
+    assert ls.stats["low_margin_flips"] <= 0.02 * ls.stats["rows"] + 2
+    assert ls.stats["reseeds"] <= 1
+
+
+@pytest.mark.parametrize("n_seqs,lens,block", [
+    (1, (8500,), 16),           # 33 pairs a wavefront and more: the page ids' second set
+    (2, (2300, 33), 10),        # 40 query rows (the last block of 16 half empty), one chunk with a single pair
+    (3, (257, 511, 64), 16),    # chunk ends on and off a page, wavefronts without a pair
+])
+def test_key_split_attention_edges(n_seqs, lens, block, monkeypatch):
+    """The key-split attention kernel over chunks from one page pair to more than 32 pairs per wavefront (one split per
+    sequence), against the oracle."""
+    monkeypatch.setenv("DFLASH_ATTN_WIDE_MIN_CHUNK", "64")
+    monkeypatch.setenv("DFLASH_ATTN_TARGET_WGS", "1")
+    w = tiny_workload(seed=17 + block, n_layers=2, draft_layers=1, vocab=512, block=block, qk_norm=True, kv_heads=1, dtype="bf16",
+                      n_seqs=n_seqs, taps=(0, 1), d=256, heads=4, hd=128, ffn=512)
+    top = max(lens)
+    prompts = [p[:n] for p, n in zip(si.make_prompts(replace(w, ctx_min=top, ctx_max=top)), lens)]
+    ls = Lockstep(w, prompts, max_len=top + 4 * 16)
+    ls.prefill()
+    for i, plan in enumerate([[3] * n_seqs, None]):
+        ls.step(plan=plan, step_idx=i)
+    assert ls.stats["low_margin_flips"] <= 0.02 * ls.stats["rows"] + 2
+    assert ls.stats["reseeds"] <= 1
