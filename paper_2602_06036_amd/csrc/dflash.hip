@@ -588,10 +588,19 @@ struct Engine {
   // stats_T > 0: the epilogue also leaves the softmax statistics of logits / stats_T, combined into stats_out; returns
   // whether that happened (kernels without the fused epilogue leave it to row_lse_kernel)
   // few: the final norm is already deferred into ws.a / ws.ssq by the last layer's down projection
+  // logits_out (nullable): the caller's buffer, written by the same epilogue where its alignment allows the epilogue's stores
+  static bool stores_to(const float* p) { return p && (sizeof(T) == 4 || ((uintptr_t)p & 15) == 0); }
+  int copy_logits(float* logits_out, const float* logits, int M) {   // any other buffer
+    if (!logits_out || stores_to(logits_out)) return DFLASH_OK;
+    if (hipMemcpyAsync(logits_out, logits, (size_t)M * c->t.vocab * 4, hipMemcpyDeviceToDevice, st) != hipSuccess)
+      return CTX_FAIL(c, DFLASH_EHIP, "logits copy failed");
+    return DFLASH_OK;
+  }
   bool lm_head(const float* final_gain, float eps, int M, float* logits, bool want_logits, int B, int mode, float inv_T,
-               const uint64_t* key, float stats_T = 0.f, float2* stats_out = nullptr, bool few = false) {
+               const uint64_t* key, float stats_T = 0.f, float2* stats_out = nullptr, bool few = false, float* logits_out = nullptr) {
     const dflash_dims& t = c->t;
     EpiArgs ep{logits, t.vocab, 0, nullptr, 0};
+    if (stores_to(logits_out)) ep.out2 = logits_out;
     if (few) {
       ep = deferred(ep, t);
       ep.ssq_eps = eps;
@@ -652,15 +661,12 @@ struct Engine {
     const float inv_T = mode ? 1.0f / temperature : 1.0f;
     const bool want_logits = logits_out || mode;        // sampling: dflash_accept needs the proposal distribution
     const bool st_q = lm_head(reinterpret_cast<const float*>(c->dblob + c->dl.gf), d.rms_eps, M, logits, want_logits, B, mode, inv_T, rng_key,
-                              mode ? temperature : 0.f, ws<float2>(c->ws.stats_q), few);
+                              mode ? temperature : 0.f, ws<float2>(c->ws.stats_q), few, logits_out);
     c->stats_q_T = st_q ? temperature : 0.f;
     c->have_logits_d = want_logits || amax_parts == 0;
     c->draft_temperature = temperature;
     argmax(logits, d.vocab, M, B, draft_tokens, 1, mode, inv_T, rng_key);
-    if (logits_out) {
-      if (hipMemcpyAsync(logits_out, logits, (size_t)M * d.vocab * 4, hipMemcpyDeviceToDevice, st) != hipSuccess)
-        return CTX_FAIL(c, DFLASH_EHIP, "logits copy failed");
-    }
+    if (int rc = copy_logits(logits_out, logits, M)) return rc;
     return hip_err ? DFLASH_EHIP : DFLASH_OK;
   }
 
@@ -709,15 +715,12 @@ struct Engine {
     const bool want_logits = logits_out || c->draft_temperature > 0.f;   // sampling: dflash_accept needs the target distribution
     const float sT = c->draft_temperature > 0.f ? c->draft_temperature : 0.f;
     const bool st_p = lm_head(reinterpret_cast<const float*>(c->tblob + c->tl.gf), t.rms_eps, M, logits, want_logits, B, 0, 1.0f, nullptr, sT,
-                              ws<float2>(c->ws.stats_p), few);
+                              ws<float2>(c->ws.stats_p), few, logits_out);
     c->stats_p_T = st_p ? sT : 0.f;
     c->have_logits_t = want_logits || amax_parts == 0;
     if (tgt_argmax) argmax(logits, t.vocab, M, B, tgt_argmax, 0, 0, 1.0f, (const uint64_t*)nullptr);
     else amax_parts = 0;
-    if (logits_out) {
-      if (hipMemcpyAsync(logits_out, logits, (size_t)M * t.vocab * 4, hipMemcpyDeviceToDevice, st) != hipSuccess)
-        return CTX_FAIL(c, DFLASH_EHIP, "logits copy failed");
-    }
+    if (int rc = copy_logits(logits_out, logits, M)) return rc;
     return hip_err ? DFLASH_EHIP : DFLASH_OK;
   }
 

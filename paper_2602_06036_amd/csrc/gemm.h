@@ -43,6 +43,9 @@ struct EpiArgs {
   const float* ssq = nullptr;
   int ssq_parts = 0;
   float ssq_inv_D = 0.f, ssq_eps = 0.f;
+  // STORE with a single K range, LM head only: the result goes here as well (the caller's logits beside the workspace's; a
+  // copy afterwards read them all again: 4 to 10 us a call)
+  float* out2 = nullptr;
 };
 
 // score of logit y at (row m, column col) for the fused argmax
@@ -266,8 +269,11 @@ __global__ __launch_bounds__(64 * NW, 1) void gemm_bf16_kernel(const bf16_t* __r
       const int i = t / MT, j = t % MT;
       const float4 s = tile_sum(t);
       const int m = (mt0 + j) * 16 + mrow;
-      if (mt0 + j < m_tiles && m < M)
-        *reinterpret_cast<float4*>(ep.out + (size_t)kz * ep.slab + (size_t)m * ep.ld + (nt0 + i) * 16 + 4 * g) = s;
+      if (mt0 + j < m_tiles && m < M) {
+        const size_t at = (size_t)m * ep.ld + (nt0 + i) * 16 + 4 * g;
+        *reinterpret_cast<float4*>(ep.out + (size_t)kz * ep.slab + at) = s;
+        if (ep.out2) *reinterpret_cast<float4*>(ep.out2 + at) = s;
+      }
     }
   }
 
@@ -396,6 +402,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
         ep.out[(size_t)m * ep.ld + col] += s0;
       } else {
         ep.out[(size_t)m * ep.ld + col] = s0;
+        if (ep.out2) ep.out2[(size_t)m * ep.ld + col] = s0;
       }
     }
   }

@@ -235,7 +235,9 @@ __global__ __launch_bounds__(128 * WY, (tiled_twice<WN, WM, NS, WY>() ? 2 : 1)) 
         const int nt = nt0 + wy * WN + i;
         if (nt >= n_tiles || !ep.out) continue;
         const f32x4 s = acc[i][jj];
-        *reinterpret_cast<float4*>(ep.out + (size_t)kz * ep.slab + (size_t)m * ep.ld + nt * 16 + 4 * gq) = make_float4(s[0], s[1], s[2], s[3]);
+        const size_t at = (size_t)m * ep.ld + nt * 16 + 4 * gq;
+        *reinterpret_cast<float4*>(ep.out + (size_t)kz * ep.slab + at) = make_float4(s[0], s[1], s[2], s[3]);
+        if (ep.out2) *reinterpret_cast<float4*>(ep.out2 + at) = make_float4(s[0], s[1], s[2], s[3]);
       }
     }
   }

@@ -144,3 +144,32 @@ def test_key_split_attention_edges(n_seqs, lens, block, monkeypatch):
         ls.step(plan=plan, step_idx=i)
     assert ls.stats["low_margin_flips"] <= 0.02 * ls.stats["rows"] + 2
     assert ls.stats["reseeds"] <= 1
+
+
+@pytest.mark.parametrize("dtype,n_seqs", [("f32", 2), ("bf16", 1), ("bf16", 3), ("bf16", 6)])
+def test_logits_reach_buffers_of_any_alignment(dtype, n_seqs):
+    """logits_out is written by the LM head's epilogue (fp32, few-row, streaming and LDS-staged kernels) where 16-byte stores
+    reach it and copied otherwise: the same values for an aligned buffer, one that is 4 bytes off, and in the workspace."""
+    import torch
+    from paper_2602_06036_amd import binding as Bd
+    GpuModel = _gpu()
+    w = tiny_workload(seed=3, n_layers=2, draft_layers=1, vocab=512, block=16, qk_norm=True, kv_heads=2, dtype=dtype, n_seqs=n_seqs,
+                      taps=(0,), d=256, heads=4, hd=64, ffn=512)
+    wt, wd = si.make_weights(w, 4)
+    g = GpuModel(w, wt, wd, 80, n_seqs=n_seqs)
+    prompts = si.make_prompts(replace(w, ctx_min=20, ctx_max=40))
+    g.prefill(prompts)
+    n = n_seqs * 16 * 512
+    flat = torch.zeros(2 * n + 4, dtype=torch.float32, device=g.dev)
+    for fn, toks in ((Bd.dflash_draft_block, g.draft_tokens), (Bd.dflash_verify, g.draft_tokens)):
+        outs = []
+        for shift in (0, 1):
+            buf = flat[shift:shift + n].view(n_seqs, 16, 512).zero_()
+            if fn is Bd.dflash_draft_block:
+                fn(g.e, g.batch(), toks, logits_out=buf)
+            else:
+                fn(g.e, g.batch(), toks, g.tgt_argmax, buf)
+            outs.append(buf.clone())
+        assert torch.isfinite(outs[0]).all() and outs[0].abs().max() > 0
+        assert torch.equal(outs[0], outs[1])
+    g.e.close()
