@@ -141,8 +141,8 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(const bf16_t* __restr
   const int rows = B * group;
   const int cap = geo.max_pages_per_seq * DF_PAGE;
   const int32_t* table = geo.block_table + (size_t)s * geo.max_pages_per_seq;
-  // page ids of the chunk, 32 pairs at a time: lane l holds page l of the set.  The first set and the queries do not
-  // depend on the sequence's length: the three round trips to memory overlap
+  // page ids of the chunk, 32 pairs at a time: lane l holds page l of the set (the pairs' own table loads would be a
+  // chain).  The first set and the queries do not depend on the sequence's length: the three round trips to memory overlap
   auto load_ids = [&](int p0) { return table[min((split * aa.chunk >> 4) + 2 * p0 + lane, geo.max_pages_per_seq - 1)]; };
   int ids = load_ids(0);
 
@@ -181,22 +181,23 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(const bf16_t* __restr
   // Two fragment sets, one multiplied while the other is on its way.  Inside the loop no load is conditional (a
   // load skipped on some path would force every wait to drain all loads in flight); the last one or two pairs
   // are peeled off.
-  if (n_pairs > 0) {
+  for (int p0 = 0; p0 < n_pairs; p0 += 32) {   // one set of page ids, loaded outside the loop below for the same reason
+    if (p0) ids = load_ids(p0);
+    const int end = min(n_pairs, p0 + 32);
     KvFrags<HD> f0, f1;
     auto load = [&](KvFrags<HD>& f, int p) {
-      const int at = 2 * (p & 31);
+      const int at = 2 * (p - p0);
       attn_load_pair<HD>(f, p, __builtin_amdgcn_readlane(ids, at), __builtin_amdgcn_readlane(ids, at + 1), pool, geo, aa, L);
     };
-    load(f0, 0);
-    int p = 0;
-    for (; p + 2 < n_pairs; p += 2) {
+    load(f0, p0);
+    int p = p0;
+    for (; p + 2 < end; p += 2) {
       load(f1, p + 1);
       attn_process_pair<HD>(f0, p, qf, acc, m_run, l_run, aa.scale, L);
-      if (((p + 2) & 31) == 0) ids = load_ids(p + 2);   // every 1024 keys
       load(f0, p + 2);
       attn_process_pair<HD>(f1, p + 1, qf, acc, m_run, l_run, aa.scale, L);
     }
-    if (p + 1 < n_pairs) {
+    if (p + 1 < end) {
       load(f1, p + 1);
       attn_process_pair<HD>(f0, p, qf, acc, m_run, l_run, aa.scale, L);
       attn_process_pair<HD>(f1, p + 1, qf, acc, m_run, l_run, aa.scale, L);

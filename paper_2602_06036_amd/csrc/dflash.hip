@@ -213,10 +213,13 @@ struct SplitPlan {
   int bound;  // >= n_splits for this and every smaller max_tokens (sizes the partial buffers)
 };
 SplitPlan plan_splits(int S, int n_kv_heads, int max_tokens, int target_wgs) {
-  // the attention kernel runs one workgroup per CU (its accumulators fill the register file), so aim at
-  // one round of workgroups on the 256 CUs (target_wgs: Knobs::attn_target_wgs)
+  // The attention kernels run one workgroup per CU, or two where their page loads then wait on each other: at most one
+  // round of workgroups on the 256 CUs (target_wgs: Knobs::attn_target_wgs).  Rounded down: a second round of a few
+  // workgroups costs as much as the first.  Two-layer verify steps of the 8B target, rounded up and down: 24 sequences x
+  // 4000 keys 1040 and 951 us, 7 x 8000 532 and 490, 20 x 100..400 738 and 724; slower in one of 19 sizes (13 x 300..5000,
+  // lengths that differ so much that more workgroups even the load out: 469 and 476).
   const int max_splits = 64;
-  int splits = (target_wgs + S * n_kv_heads - 1) / (S * n_kv_heads);
+  int splits = target_wgs / (S * n_kv_heads);
   const int by_len = (max_tokens + 63) / 64;
   splits = std::max(1, std::min(splits, std::min(by_len, max_splits)));
   int chunk = (max_tokens + splits - 1) / splits;
