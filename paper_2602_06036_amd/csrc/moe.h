@@ -29,20 +29,37 @@ struct MoeRoute {
   int32_t* n_bands_out;           // [1] bands of the list this launch built
 };
 
+// Value of another lane of the same sixteen, rotated by N: one VALU instruction, where a shuffle is an LDS round trip.
+template <int N>
+__device__ __forceinline__ float row_rotate(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x120 + N, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float wave_max(float x) {   // over the wavefront, the same in every lane; no NaN
+  x = fmaxf(x, row_rotate<8>(x));
+  x = fmaxf(x, row_rotate<4>(x));
+  x = fmaxf(x, row_rotate<2>(x));
+  x = fmaxf(x, row_rotate<1>(x));
+  auto at = [&](int l) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), l)); };
+  return fmaxf(fmaxf(at(0), at(16)), fmaxf(at(32), at(48)));
+}
+
 // One wavefront picks row t's experts: lane j < k ends up with the j-th best (expert, weight); returns the expert.
+// A serial chain of k rounds, each a maximum over the wavefront by rotations inside sixteen lanes and the place of its
+// first holder by a ballot; as a butterfly of (value, index) shuffles a round took twelve dependent LDS operations.
+// 16 rows, 128 experts, top 8, 8 slabs: the routing kernel 7.9 us, with shuffles 11.2.
 __device__ __forceinline__ int moe_topk_row(const MoeRoute& a, int t, int lane, float& weight) {
   float v[4] = {0.f, 0.f, 0.f, 0.f};   // lane holds experts lane, lane + 64, ...
-  for (int z0 = 0; z0 < a.ks; z0 += 4) {   // four slabs' loads in flight at a time, added in ascending order
-    float part[4][4];
+  for (int z0 = 0; z0 < a.ks; z0 += 8) {   // eight slabs' loads in flight at a time, added in ascending order
+    float part[8][4];
 #pragma unroll
-    for (int zz = 0; zz < 4; ++zz)
+    for (int zz = 0; zz < 8; ++zz)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int e = lane + 64 * i;
         part[zz][i] = (e < a.E && z0 + zz < a.ks) ? a.logits[(size_t)(z0 + zz) * a.stride + (size_t)t * a.E + e] : 0.f;
       }
 #pragma unroll
-    for (int zz = 0; zz < 4; ++zz)
+    for (int zz = 0; zz < 8; ++zz)
 #pragma unroll
       for (int i = 0; i < 4; ++i) v[i] += part[zz][i];
   }
@@ -55,26 +72,26 @@ __device__ __forceinline__ int moe_topk_row(const MoeRoute& a, int t, int lane, 
   float mine = 0.f, top = 0.f;
   int mine_e = 0;
   for (int j = 0; j < a.k; ++j) {
-    float bv = v[0];
-    int bi = lane;
+    const float best = wave_max(fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
+    int e = 0;   // the lowest index that holds it
 #pragma unroll
-    for (int i = 1; i < 4; ++i)
-      if (v[i] > bv) { bv = v[i]; bi = lane + 64 * i; }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-      const float ov = __shfl_xor(bv, o, 64);
-      const int oi = __shfl_xor(bi, o, 64);
-      if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+    for (int i = 3; i >= 0; --i) {
+      const unsigned long long at = __ballot(v[i] == best);
+      if (at) e = 64 * i + (int)__builtin_ctzll(at);
     }
-    if (j == 0) top = bv;
-    if (lane == j) { mine = bv; mine_e = bi; }
+    if (j == 0) top = best;
+    if (lane == j) { mine = best; mine_e = e; }
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      if (bi == lane + 64 * i) v[i] = -INFINITY;
+      if (e == lane + 64 * i) v[i] = -INFINITY;
   }
-  float ex = lane < a.k ? __expf(mine - top) : 0.f, sum = ex;
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) sum += __shfl_xor(sum, o, 64);
+  static_assert(MOE_MAX_TOPK <= 16, "the weights' sum is taken inside sixteen lanes");
+  const float ex = lane < a.k ? __expf(mine - top) : 0.f;
+  float sum = ex;
+  sum += row_rotate<8>(sum);
+  sum += row_rotate<4>(sum);
+  sum += row_rotate<2>(sum);
+  sum += row_rotate<1>(sum);
   weight = ex / sum;
   return mine_e;
 }
@@ -134,30 +151,30 @@ __global__ __launch_bounds__(1024) void moe_route_kernel(MoeRoute a) {
   }
   __syncthreads();
   if (wave == 0) {   // exclusive scans over the experts (bands, work items): lane owns experts 4*lane .. 4*lane+3
-    int nb[4], ni[4], sb = 0, si = 0, su = 0;
+    // bands in the low half of a word, items in the high half: at most rows * top_k / 16 + experts < 2^15 of either
+    int cnt[4], sum = 0, used = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int e = 4 * lane + i;
-      nb[i] = e < a.E ? (tot[e] + 15) >> 4 : 0;
-      ni[i] = (nb[i] + a.MT - 1) / a.MT;
-      sb += nb[i]; si += ni[i]; su += nb[i] > 0;
+      const int nb = e < a.E ? (tot[e] + 15) >> 4 : 0;
+      cnt[i] = nb | ((nb + a.MT - 1) / a.MT) << 16;
+      sum += cnt[i];
+      used += __popcll(__ballot(nb > 0));
     }
-    int ib = sb, ii = si;
+    int upto = sum;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
-      const int ob = __shfl_up(ib, o, 64), oi = __shfl_up(ii, o, 64);
-      if (lane >= o) { ib += ob; ii += oi; }
+      const int below = __shfl_up(upto, o, 64);
+      if (lane >= o) upto += below;
     }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) su += __shfl_xor(su, o, 64);
-    int eb = ib - sb, ei = ii - si;
+    int at = upto - sum;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int e = 4 * lane + i;
-      if (e < a.E) { base[e] = eb * 16; item0[e] = ei; }
-      eb += nb[i]; ei += ni[i];
+      if (e < a.E) { base[e] = (at & 0xffff) * 16; item0[e] = at >> 16; }
+      at += cnt[i];
     }
-    if (lane == 63) { n_items = ii; n_bands = ib; n_used = su; }
+    if (lane == 63) { n_items = upto >> 16; n_bands = upto & 0xffff; n_used = used; }
   }
   __syncthreads();
   if (tid < a.E && tot[tid] > 0) {
@@ -178,10 +195,11 @@ __global__ __launch_bounds__(1024) void moe_route_kernel(MoeRoute a) {
   }
   if (tid == 0) {
     a.n_bands_out[0] = n_bands;
-    a.counters[0] += 1ull;
-    a.counters[1] += (unsigned long long)n_used;
-    a.counters[2] += (unsigned long long)n_bands;
-    a.counters[3] += (unsigned long long)n_items;
+    // atomics for their form, not for other writers: nothing waits for an old value
+    atomicAdd(&a.counters[0], 1ull);
+    atomicAdd(&a.counters[1], (unsigned long long)n_used);
+    atomicAdd(&a.counters[2], (unsigned long long)n_bands);
+    atomicAdd(&a.counters[3], (unsigned long long)n_items);
     a.counters[4] = (unsigned long long)a.MT;   // not a total: the bands per work item of this launch
   }
 }

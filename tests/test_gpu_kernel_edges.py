@@ -173,3 +173,30 @@ def test_logits_reach_buffers_of_any_alignment(dtype, n_seqs):
         assert torch.isfinite(outs[0]).all() and outs[0].abs().max() > 0
         assert torch.equal(outs[0], outs[1])
     g.e.close()
+
+
+@pytest.mark.parametrize("experts,top_k,n_seqs", [(16, 4, 1), (80, 8, 2), (48, 6, 5), (256, 16, 4), (256, 15, 6)])
+def test_equal_router_logits_go_to_the_lowest_expert(experts, top_k, n_seqs):
+    """Router rows equal in groups of four give four bitwise equal logits each: every row's choices are whole groups in
+    ascending order (the last one cut off where four does not divide top_k), expert counts below, between and at the
+    multiples of 64, choices made in the routing kernel (up to 64 rows) and before it."""
+    import torch
+    from paper_2602_06036_amd import binding as Bd
+    GpuModel = _gpu()
+    w = si.small_moe_workload(n_seqs=n_seqs, ctx_min=12, ctx_max=20, seed=5, n_experts=experts, top_k=top_k, d_expert=64)
+    wt, wd = si.make_weights(w, 8)
+    for l in range(w.target.n_layers):
+        wt.t[f"L{l}.wr"] = np.ascontiguousarray(np.repeat(wt.t[f"L{l}.wr"][::4], 4, axis=0))
+    g = GpuModel(w, wt, wd, 64, n_seqs=n_seqs)
+    g.prefill(si.make_prompts(w))
+    g.draft_tokens.copy_(torch.arange(n_seqs * 16, device=g.dev).view(n_seqs, 16) * 37 % 4096)
+    trace = g.e.moe_trace()
+    Bd.dflash_verify(g.e, g.batch(), g.draft_tokens, g.tgt_argmax)
+    got = trace.cpu().numpy()[:, : n_seqs * 16].reshape(-1, top_k)
+    assert (got >= 0).all() and (got < experts).all()
+    assert (got % 4 == np.arange(top_k) % 4).all()
+    first = got[:, ::4]
+    assert (np.repeat(first, 4, axis=1)[:, :top_k] // 4 == got // 4).all()
+    assert all(len(set(r)) == len(r) for r in first)
+    assert len(np.unique(first)) > top_k // 4 + 1
+    g.e.close()
