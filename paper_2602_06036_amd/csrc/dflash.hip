@@ -589,7 +589,7 @@ struct Engine {
   // final norm + LM head with the row argmax fused into the GEMM epilogue where the kernel supports it (then
   // amax_parts > 0 and, unless want_logits, the [M, V] logits are never written); argmax() finishes the job
   // stats_T > 0: the epilogue also leaves the softmax statistics of logits / stats_T, combined into stats_out; returns
-  // whether that happened (kernels without the fused epilogue leave it to row_lse_kernel)
+  // whether that happened (kernels without the fused epilogue leave it to lse_partial_kernel)
   // few: the final norm is already deferred into ws.a / ws.ssq by the last layer's down projection
   // logits_out (nullable): the caller's buffer, written by the same epilogue where its alignment allows the epilogue's stores
   static bool stores_to(const float* p) { return p && (sizeof(T) == 4 || ((uintptr_t)p & 15) == 0); }

@@ -452,7 +452,7 @@ __global__ __launch_bounds__(256) void lse_partial_kernel(const float* __restric
 }
 
 // combines the per-workgroup (max, sum) partials that the LM-head epilogue left for row m, in ascending order of the
-// column blocks: stats[m] = (max, log-sum-exp) of logits * inv_T, the pair row_lse_kernel computes from stored logits
+// column blocks: stats[m] = (max, log-sum-exp) of logits * inv_T, the pair lse_partial_kernel computes from stored logits
 __global__ __launch_bounds__(64) void lse_finish_kernel(const float2* __restrict__ part, int n_parts, float2* __restrict__ stats) {
   const int m = blockIdx.x, lane = threadIdx.x;
   float mx = -INFINITY;
