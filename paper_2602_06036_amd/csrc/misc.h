@@ -247,7 +247,8 @@ __global__ __launch_bounds__(256) void qkv_post_kernel(const float* __restrict__
   const int l0 = active ? lane : 0;   // idle lanes read along (head_dim 64 and less)
   const float* src = in + (size_t)m * in_ld + (is_q ? ra.q_off + head * hd : (is_k ? ra.k_off : ra.v_off) + kvh * hd) + l0;
   // everything the head needs is requested before any of it is waited for: this kernel is a chain of memory round trips
-  // and nothing else (16 rows, four slabs: 4.6 us with one slab after the other, 4.6 with four at a time: what is left is the launch)
+  // and nothing else (a step of the 8B shape at batch 1, 41 launches: 4416 us with one slab after the other and the gains
+  // and angles behind them, 4388 like this; by itself a launch takes 4.6 us either way)
   float2 r = make_float2(1.f, 0.f);
   float g1 = 1.f, g2 = 1.f;
   if (is_q || is_k) {
@@ -298,14 +299,16 @@ __global__ __launch_bounds__(256) void qkv_post_kernel(const float* __restrict__
     }
   }
   if (ra.qk_norm) {
-    const float ss = wave_reduce_sum(active ? x1 * x1 + x2 * x2 : 0.f);
+    // which product of a sum is rounded by itself is written out here and below: left to the compiler it changes with the code
+    // around it, and a last bit here is a bf16 step of one stored value in some ten thousand
+    const float ss = wave_reduce_sum(active ? fmaf(x2, x2, x1 * x1) : 0.f);
     const float rstd = 1.0f / sqrtf(ss / (float)hd + ra.eps);
     x1 *= rstd * g1;
     x2 *= rstd * g2;
   }
   if (!active) return;
   const float c = r.x, sf = r.y;
-  const T y1 = Store<T>::from(x1 * c - x2 * sf), y2 = Store<T>::from(x2 * c + x1 * sf);
+  const T y1 = Store<T>::from(fmaf(x1, c, -(x2 * sf))), y2 = Store<T>::from(fmaf(x2, c, x1 * sf));
   if (is_q) {
     T* dst = q_out + ((size_t)m * ra.n_q_heads + head) * hd;
     dst[lane] = y1;

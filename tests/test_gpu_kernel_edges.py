@@ -100,6 +100,45 @@ def test_fp32_head_dims_and_widths(hd, heads, kv_heads, ffn, lens):
     assert ls.stats["reseeds"] == 0
 
 
+@pytest.mark.parametrize("hd,qk_norm", [(64, False), (64, True), (128, False), (128, True)])
+def test_rotated_keys_are_rounded_in_the_stated_order(hd, qk_norm):
+    """q/k norm and rotation, bit for bit: with W_k = W_v = 1 the cached V rows are the vectors that the kernel normalises and
+    rotates into the K rows.  Every operation is rounded to fp32, products that a sum takes in unrounded are the ones the kernel
+    names (evaluated here with 64 significand bits and rounded once)."""
+    from paper_2602_06036_amd import binding as Bd
+    GpuModel = _gpu()
+    d, f32 = 256, np.float32
+    w = tiny_workload(seed=hd, n_layers=1, draft_layers=1, vocab=512, block=16, qk_norm=qk_norm, kv_heads=d // hd, n_seqs=2, taps=(0,),
+                      d=d, heads=d // hd, hd=hd, ffn=256)
+    wt, wd = si.make_weights(w, 4)
+    wt.t["L0.wk"], wt.t["L0.wv"] = np.eye(d, dtype=f32), np.eye(d, dtype=f32)
+    g = GpuModel(w, wt, wd, 80, n_seqs=2)
+    g.prefill([p[:n] for p, n in zip(si.make_prompts(replace(w, ctx_min=48, ctx_max=48)), (48, 37))])
+
+    def fma(a, b, c):
+        return (a.astype(np.longdouble) * b + c).astype(f32)
+
+    half = hd // 2
+    freq = np.exp(-np.log(np.float64(f32(w.target.rope_theta))) * (2.0 * np.arange(half) / hd))
+    for s, n in enumerate((48, 37)):
+        k, x = (r.cpu().numpy() for r in Bd.dflash_kv_read(g.e, g.batch(), Bd.DFLASH_POOL_TARGET, 0, s, 0, n))
+        x1, x2 = x[..., :half], x[..., half:]
+        if qk_norm:
+            ss = np.zeros(x1.shape[:-1] + (64,), f32)
+            ss[..., :half] = fma(x2, x2, x1 * x1)
+            for o in (32, 16, 8, 4, 2, 1):
+                ss = ss + ss[..., np.arange(64) ^ o]
+            rstd = f32(1) / np.sqrt(ss[..., :half] / f32(hd) + f32(w.target.rms_eps))
+            x1, x2 = x1 * (rstd * wt.t["L0.kn"][:half]), x2 * (rstd * wt.t["L0.kn"][half:])
+        ang = np.arange(n)[:, None, None] * freq
+        c, sn = np.cos(ang).astype(f32), np.sin(ang).astype(f32)
+        want = np.concatenate([fma(x1, c, -(x2 * sn)), fma(x2, c, x1 * sn)], -1)
+        assert k.dtype == want.dtype == f32
+        wrong = int((k != want).sum())
+        assert wrong == 0, (wrong, k.size)
+    g.e.close()
+
+
 @pytest.mark.parametrize("n_seqs,d,ffn,vocab", [
     (5, 256, 1056, 1008),       # 80 rows: a row block of five bands; 66 and 63 row bands of weights (clamped last tiles)
     (9, 256, 2560, 4096),       # 144 rows: nine bands; 20 weight blocks of 256 rows (not a multiple of the eight XCDs)
