@@ -586,24 +586,36 @@ struct Engine {
   // its bands belong to -> weighted sum per token, left as a slab that the next RMSNorm adds to the residual stream.
   Slab moe_ffn(const dflash_dims& m, const char* lbase, const LayerOff& lo, int M);
 
+  // Whether the epilogue's stores may go to the caller's buffer p: memory of this device, 16-byte aligned where the stores are 16
+  // bytes wide.  Anything else that a copy reaches (host memory, pinned or not, another device's) gets a copy: a store from a
+  // kernel faults there, or crosses the bus line by line.  The query takes 0.3 us on the host.
+  static bool stores_to(const float* p) {
+    if (!p || (sizeof(T) == 2 && ((uintptr_t)p & 15) != 0)) return false;
+    hipPointerAttribute_t at;
+    int dev = -1;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess || hipGetDevice(&dev) != hipSuccess) {
+      (void)hipGetLastError();   // answered, not left for the next launch's check
+      return false;
+    }
+    return at.type == hipMemoryTypeDevice && at.device == dev;
+  }
+  int copy_logits(float* logits_out, const float* logits, int M) {
+    if (!logits_out) return DFLASH_OK;
+    if (hipMemcpyAsync(logits_out, logits, (size_t)M * c->t.vocab * 4, hipMemcpyDeviceToDevice, st) != hipSuccess)
+      return CTX_FAIL(c, DFLASH_EHIP, "logits copy failed");
+    return DFLASH_OK;
+  }
   // final norm + LM head with the row argmax fused into the GEMM epilogue where the kernel supports it (then
   // amax_parts > 0 and, unless want_logits, the [M, V] logits are never written); argmax() finishes the job
   // stats_T > 0: the epilogue also leaves the softmax statistics of logits / stats_T, combined into stats_out; returns
   // whether that happened (kernels without the fused epilogue leave it to lse_partial_kernel)
   // few: the final norm is already deferred into ws.a / ws.ssq by the last layer's down projection
-  // logits_out (nullable): the caller's buffer, written by the same epilogue where its alignment allows the epilogue's stores
-  static bool stores_to(const float* p) { return p && (sizeof(T) == 4 || ((uintptr_t)p & 15) == 0); }
-  int copy_logits(float* logits_out, const float* logits, int M) {   // any other buffer
-    if (!logits_out || stores_to(logits_out)) return DFLASH_OK;
-    if (hipMemcpyAsync(logits_out, logits, (size_t)M * c->t.vocab * 4, hipMemcpyDeviceToDevice, st) != hipSuccess)
-      return CTX_FAIL(c, DFLASH_EHIP, "logits copy failed");
-    return DFLASH_OK;
-  }
+  // logits_to (nullable): the caller's buffer (see stores_to), written by the same epilogue
   bool lm_head(const float* final_gain, float eps, int M, float* logits, bool want_logits, int B, int mode, float inv_T,
-               const uint64_t* key, float stats_T = 0.f, float2* stats_out = nullptr, bool few = false, float* logits_out = nullptr) {
+               const uint64_t* key, float stats_T = 0.f, float2* stats_out = nullptr, bool few = false, float* logits_to = nullptr) {
     const dflash_dims& t = c->t;
     EpiArgs ep{logits, t.vocab, 0, nullptr, 0};
-    if (stores_to(logits_out)) ep.out2 = logits_out;
+    ep.out2 = logits_to;
     if (few) {
       ep = deferred(ep, t);
       ep.ssq_eps = eps;
@@ -663,13 +675,14 @@ struct Engine {
     const int mode = temperature > 0.f ? 1 : 0;
     const float inv_T = mode ? 1.0f / temperature : 1.0f;
     const bool want_logits = logits_out || mode;        // sampling: dflash_accept needs the proposal distribution
+    float* logits_to = stores_to(logits_out) ? logits_out : nullptr;
     const bool st_q = lm_head(reinterpret_cast<const float*>(c->dblob + c->dl.gf), d.rms_eps, M, logits, want_logits, B, mode, inv_T, rng_key,
-                              mode ? temperature : 0.f, ws<float2>(c->ws.stats_q), few, logits_out);
+                              mode ? temperature : 0.f, ws<float2>(c->ws.stats_q), few, logits_to);
     c->stats_q_T = st_q ? temperature : 0.f;
     c->have_logits_d = want_logits || amax_parts == 0;
     c->draft_temperature = temperature;
     argmax(logits, d.vocab, M, B, draft_tokens, 1, mode, inv_T, rng_key);
-    if (int rc = copy_logits(logits_out, logits, M)) return rc;
+    if (int rc = copy_logits(logits_to ? nullptr : logits_out, logits, M)) return rc;
     return hip_err ? DFLASH_EHIP : DFLASH_OK;
   }
 
@@ -716,14 +729,15 @@ struct Engine {
       return hip_err ? DFLASH_EHIP : DFLASH_OK;
     }
     const bool want_logits = logits_out || c->draft_temperature > 0.f;   // sampling: dflash_accept needs the target distribution
+    float* logits_to = stores_to(logits_out) ? logits_out : nullptr;
     const float sT = c->draft_temperature > 0.f ? c->draft_temperature : 0.f;
     const bool st_p = lm_head(reinterpret_cast<const float*>(c->tblob + c->tl.gf), t.rms_eps, M, logits, want_logits, B, 0, 1.0f, nullptr, sT,
-                              ws<float2>(c->ws.stats_p), few, logits_out);
+                              ws<float2>(c->ws.stats_p), few, logits_to);
     c->stats_p_T = st_p ? sT : 0.f;
     c->have_logits_t = want_logits || amax_parts == 0;
     if (tgt_argmax) argmax(logits, t.vocab, M, B, tgt_argmax, 0, 0, 1.0f, (const uint64_t*)nullptr);
     else amax_parts = 0;
-    if (int rc = copy_logits(logits_out, logits, M)) return rc;
+    if (int rc = copy_logits(logits_to ? nullptr : logits_out, logits, M)) return rc;
     return hip_err ? DFLASH_EHIP : DFLASH_OK;
   }
 

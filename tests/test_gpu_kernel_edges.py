@@ -214,6 +214,60 @@ def test_logits_reach_buffers_of_any_alignment(dtype, n_seqs):
     g.e.close()
 
 
+@pytest.mark.parametrize("dtype,n_seqs", [("f32", 1), ("bf16", 1), ("bf16", 6)])
+def test_logits_reach_host_memory(dtype, n_seqs):
+    """A buffer that a copy reaches and a kernel's stores may not: host memory, pinned and pageable, through the C calls."""
+    import ctypes as C
+    import torch
+    from paper_2602_06036_amd import binding as Bd
+    GpuModel = _gpu()
+    w = tiny_workload(seed=3, n_layers=2, draft_layers=1, vocab=512, block=16, qk_norm=True, kv_heads=2, dtype=dtype, n_seqs=n_seqs,
+                      taps=(0,), d=256, heads=4, hd=64, ffn=512)
+    wt, wd = si.make_weights(w, 4)
+    g = GpuModel(w, wt, wd, 80, n_seqs=n_seqs)
+    g.prefill(si.make_prompts(replace(w, ctx_min=20, ctx_max=40)))
+    shape = (n_seqs, 16, 512)
+    st, b, toks = torch.cuda.current_stream().cuda_stream, g.batch(), g.draft_tokens
+    pinned, pageable = torch.empty(shape, pin_memory=True), torch.empty(shape)
+    for call in (lambda p: g.e.l.dflash_draft_block(g.e.ctx, C.byref(b), 0.0, None, toks.data_ptr(), p, st),
+                 lambda p: g.e.l.dflash_verify(g.e.ctx, C.byref(b), toks.data_ptr(), g.tgt_argmax.data_ptr(), p, st)):
+        on_device = torch.zeros(shape, device=g.dev)
+        assert call(on_device.data_ptr()) == Bd.DFLASH_OK
+        for host in (pinned, pageable):
+            host.zero_()
+            assert call(host.data_ptr()) == Bd.DFLASH_OK
+            torch.cuda.synchronize()
+            assert on_device.abs().max() > 0 and torch.equal(host, on_device.cpu())
+    g.e.close()
+
+
+@pytest.mark.parametrize("dtype,n_seqs", [("f32", 1), ("bf16", 1), ("bf16", 6)])
+def test_logits_under_capture(dtype, n_seqs):
+    """The caller's logits of a captured verification, replayed with eager work in between: the eager call's, each time."""
+    import torch
+    from paper_2602_06036_amd import binding as Bd
+    GpuModel = _gpu()
+    w = tiny_workload(seed=4, n_layers=2, draft_layers=1, vocab=512, block=16, qk_norm=True, kv_heads=2, dtype=dtype, n_seqs=n_seqs,
+                      taps=(0,), d=256, heads=4, hd=64, ffn=512)
+    wt, wd = si.make_weights(w, 4)
+    g = GpuModel(w, wt, wd, 80, n_seqs=n_seqs)
+    g.prefill(si.make_prompts(replace(w, ctx_min=20, ctx_max=40)))
+    b, want = g.batch(), torch.zeros((n_seqs, 16, 512), device=g.dev)
+    Bd.dflash_verify(g.e, b, g.draft_tokens, g.tgt_argmax, want)
+    out, graph, side = torch.zeros_like(want), torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        Bd.dflash_verify(g.e, b, g.draft_tokens, g.tgt_argmax, out)
+    for _ in range(3):
+        out.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        Bd.dflash_draft_block(g.e, b, torch.zeros_like(g.draft_tokens))
+    g.e.close()
+
+
 @pytest.mark.parametrize("experts,top_k,n_seqs", [(16, 4, 1), (80, 8, 2), (48, 6, 5), (256, 16, 4), (256, 15, 6)])
 def test_equal_router_logits_go_to_the_lowest_expert(experts, top_k, n_seqs):
     """Router rows equal in groups of four give four bitwise equal logits each: every row's choices are whole groups in
