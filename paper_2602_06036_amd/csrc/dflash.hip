@@ -23,6 +23,7 @@
 #include "gemm_tiled.h"
 #include "misc.h"
 #include "moe.h"
+#include "plan.h"
 
 // Scratch of dflash_accept_sampled_noalloc (the entry point for callers that cannot allocate): the pieces of the rows'
 // softmax statistics (target rows, then draft rows), followed by the best scores of the vocabulary chunks.  Every GPU the
@@ -48,58 +49,6 @@ int fail(char* dst, int code, const char* fmt, ...) {
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 inline size_t esize(int dtype) { return dtype == DFLASH_BF16 ? 2 : 4; }
 inline int round_rows(int dtype, int M) { return dtype == DFLASH_BF16 ? (M + 15) & ~15 : M; }
-
-inline int env_int(const char* name, int dflt) {
-  const char* e = getenv(name);
-  const int v = e ? atoi(e) : 0;
-  return v > 0 ? v : dflt;
-}
-
-// Tuning and testing knobs, read from the environment whenever a context is created (or a workspace is sized): a
-// context keeps the values it was created with, so a test that sets one before dflash_create gets exactly that path
-// whatever ran earlier in the process.  Defaults are what the measurements in the documentation use.
-struct Knobs {
-  int gemm_wide;            // DFLASH_GEMM_WIDE: 1 = eight-wavefront tiles by estimated time (default), 2 = wherever one fits (tests), any other value = never
-  int attn_target_wgs;      // DFLASH_ATTN_TARGET_WGS: workgroups an attention launch aims at
-  int attn_wide_min_chunk;  // DFLASH_ATTN_WIDE_MIN_CHUNK: keys per workgroup from which the key-split attention kernel is used
-  int gemm_target_wgs;      // DFLASH_GEMM_TARGET_WGS: workgroups a K-split streaming GEMM aims at
-  int gemm_u;               // DFLASH_GEMM_U: k tiles per prefetch stage (one band of rows)
-  int gemm_nt8;             // DFLASH_GEMM_NT8: matrices with at least 8 * this row bands use 8 weight tiles per activation fragment
-  int gemm_fill;            // DFLASH_GEMM_FILL: 1 = weight tiles per wavefront (8 or 6) and K split chosen to fill whole rounds of the CUs
-  int gemm_fill4;           // DFLASH_GEMM_FILL4: the same for 17-64 rows
-  int gemm_u4;              // DFLASH_GEMM_U4: k tiles per prefetch stage for 17-64 rows
-  int gemm_tile, gemm_wm, gemm_ks;   // DFLASH_GEMM_TILE / _WM / _KS: force the tiled GEMM's shape / rows per tile / K split (0 = by estimated time)
-  int lm_stats;             // DFLASH_LM_STATS: 1 = softmax statistics from the LM-head epilogue, other = from the stored logits
-  int moe_mt;               // DFLASH_MOE_MT: 1, 2, 4 or 8 forces the bands per routed-expert work item (0 = by rows per expert)
-  int moe_gather_min_rows;  // DFLASH_MOE_GATHER_MIN_ROWS: rows from which the routed-expert GEMMs get their rows copied into list order
-  int moe_down_u;           // DFLASH_MOE_DOWN_U: k tiles per stage of the one-band down projection
-  int fuse;                 // DFLASH_FUSE: few-row path, see dflash_ctx::fuse
-  int resid_nw, resid_u;    // DFLASH_RESID_NW / _U: wavefronts per workgroup and k tiles per stage of the unsplit projection kernel
-};
-Knobs read_knobs() {
-  Knobs k;
-  k.gemm_wide = env_int("DFLASH_GEMM_WIDE", 1);
-  k.attn_target_wgs = env_int("DFLASH_ATTN_TARGET_WGS", 256);
-  k.attn_wide_min_chunk = env_int("DFLASH_ATTN_WIDE_MIN_CHUNK", 512);
-  k.gemm_target_wgs = env_int("DFLASH_GEMM_TARGET_WGS", 256);
-  k.gemm_u = env_int("DFLASH_GEMM_U", 2);
-  k.gemm_nt8 = env_int("DFLASH_GEMM_NT8", 1);
-  k.gemm_fill = env_int("DFLASH_GEMM_FILL", 1);
-  k.gemm_fill4 = env_int("DFLASH_GEMM_FILL4", 1);
-  k.gemm_u4 = env_int("DFLASH_GEMM_U4", 1);
-  k.gemm_tile = env_int("DFLASH_GEMM_TILE", 0);
-  k.gemm_wm = env_int("DFLASH_GEMM_WM", 0);
-  k.gemm_ks = env_int("DFLASH_GEMM_KS", 0);
-  k.lm_stats = env_int("DFLASH_LM_STATS", 1);
-  k.moe_mt = env_int("DFLASH_MOE_MT", 0);
-  k.moe_gather_min_rows = env_int("DFLASH_MOE_GATHER_MIN_ROWS", 64);
-  k.moe_down_u = env_int("DFLASH_MOE_DOWN_U", 1);
-  k.fuse = env_int("DFLASH_FUSE", 1);
-  if (k.fuse != 1 && k.fuse != 2) k.fuse = 0;
-  k.resid_nw = env_int("DFLASH_RESID_NW", 4);
-  k.resid_u = env_int("DFLASH_RESID_U", 8);
-  return k;
-}
 
 struct LayerOff {
   size_t wqkv, wo, wgu, wd, wr, g1, g2, qn, kn, end;
@@ -208,45 +157,10 @@ inline int attn_q_shift(const dflash_dims& m, int block_size) {
   return (m.dtype == DFLASH_BF16 && (m.head_dim == 128 || m.head_dim == 64) && group % (1 << sh) == 0) ? sh : -1;
 }
 
-struct SplitPlan {
-  int n_splits, chunk;
-  int bound;  // >= n_splits for this and every smaller max_tokens (sizes the partial buffers)
-};
-SplitPlan plan_splits(int S, int n_kv_heads, int max_tokens, int target_wgs) {
-  // The attention kernels run one workgroup per CU, or two where their page loads then wait on each other: at most one
-  // round of workgroups on the 256 CUs (target_wgs: Knobs::attn_target_wgs).  Rounded down: a second round of a few
-  // workgroups costs as much as the first.  Two-layer verify steps of the 8B target, rounded up and down: 24 sequences x
-  // 4000 keys 1040 and 951 us, 7 x 8000 532 and 490, 20 x 100..400 738 and 724; slower in one of 19 sizes (13 x 300..5000,
-  // lengths that differ so much that more workgroups even the load out: 469 and 476).
-  const int max_splits = 64;
-  int splits = target_wgs / (S * n_kv_heads);
-  const int by_len = (max_tokens + 63) / 64;
-  splits = std::max(1, std::min(splits, std::min(by_len, max_splits)));
-  int chunk = (max_tokens + splits - 1) / splits;
-  chunk = (chunk + 63) & ~63;
-  SplitPlan p;
-  p.bound = splits;
-  p.chunk = chunk;
-  p.n_splits = (max_tokens + chunk - 1) / chunk;
-  return p;
-}
-
 // ---- workspace ------------------------------------------------------------------------------------
-// rows of partial results the split-K arena holds for a context of at most max_rows activation rows
-inline int arena_rows(int max_rows) { return std::max(1024, 4 * max_rows); }
-
 constexpr int ARGMAX_CHUNKS = 32;   // workgroups that share one vocabulary row in the argmax
 
 // ---- sampled acceptance (dflash_accept, dflash_accept_sampled_noalloc) -----------------------------
-// Workgroups per row of the statistics launch: enough for 4096 of them (16 a CU), not below 1024 columns each, and no
-// more pieces than `room` entries hold.  Workgroups per sequence of the sweep over the vocabulary: 1024 in all, 1024 columns
-// each at least, at most `room` in all.
-inline int lse_chunks(int rows, int V, size_t room) {
-  return (int)std::max<size_t>(1, std::min<size_t>({(size_t)(4096 / rows), (size_t)32, (size_t)(V / 1024), room / rows}));
-}
-inline int accept_chunks(int S, int V, size_t room) {
-  return (int)std::max<size_t>(1, std::min<size_t>({(size_t)(1024 / S), (size_t)64, (size_t)(V / 1024), room / S}));
-}
 // statistics of R rows of `a` and R rows of `b` (may be null with R_b = 0) in `chunks` pieces per row
 inline void launch_lse(hipStream_t st, const float* a, const float* b, int R, int R_b, int V, float inv_T, int chunks, float2* part) {
   const dim3 grid(chunks, R + R_b), block(256);
@@ -882,7 +796,6 @@ struct Engine {
 };
 
 // ---- GEMM dispatch ----------------------------------------------------------------------------------
-constexpr int kMaxKSplit = 16;
 
 thread_local int g_launch_parts = 0;   // column blocks of the last bf16 GEMM launch (= fused-argmax partials per row)
 thread_local int g_launch_kind = 0;    // kernel family of that launch (DFLASH_GEMM_* of dflash_gemm_counts)
@@ -911,121 +824,7 @@ void launch_tiled(hipStream_t st, const bf16_t* W, const bf16_t* A, int M, int N
     hipLaunchKernelGGL((gemm_bf16_tiled_kernel<WN, WM, EPI_STORE, NS, false, WY, REG>), grid, block, 0, st, W, A, M, N, K, n_blocks, m_blocks, ep);
 }
 
-// The LDS-staged tiles and what a k tile costs on a CU, in microseconds: `two` with two workgroups of the shape side by
-// side (four-wavefront tiles), `one` with a workgroup by itself; `fixed` per round of workgroups (ramp, prologue, epilogue).
-// Fitted to launches back to back over random operands (16 row counts from 80 to 2048, ten matrices of 2048 to 28672 rows
-// with K of 2048 to 12288, one to eight K ranges); the shape picked with them is on average 0.7-1.1 % slower than the
-// fastest one (the efficiency factors used before, which knew neither the pairing on a CU nor the XCDs' shares: 6.5 %).
-struct TileShape {
-  int wn, wm, wy;      // weight tiles and activation bands per wavefront, wavefronts along N
-  float two, one, fixed;
-};
-constexpr TileShape kTiles[] = {
-    {8, 4, 2, 1.32f, 1.00f, 1.0f},  {6, 4, 2, 1.02f, 0.72f, 1.5f},  {4, 4, 2, 0.747f, 0.464f, 3.5f}, {8, 2, 2, 0.727f, 0.463f, 3.1f},
-    {6, 2, 2, 0.579f, 0.397f, 3.4f}, {4, 2, 2, 0.44f, 0.269f, 2.9f}, {6, 4, 4, 0.f, 1.00f, 1.5f},     {4, 4, 4, 0.f, 0.715f, 2.0f},
-    {6, 2, 4, 0.f, 0.562f, 2.5f},    {4, 2, 4, 0.f, 0.425f, 3.3f}};
-
-struct TilePlan {
-  const TileShape* t = nullptr;
-  int ks = 1;
-};
-// Time of a launch = k tiles of a K range x cost of the workgroups on the busiest CU + the partial slabs (written by the
-// GEMM, read by its consumer).  XCDs take equal shares of the tiles, so the busiest CU has ceil(share / 32 CUs) workgroups.
-inline TilePlan tile_plan(const Knobs& kn, int M, int N, int K, bool split, int arena) {
-  const int nt = N / 16, KT = K / 32;
-  const bool forced = kn.gemm_tile || kn.gemm_wm || kn.gemm_ks;   // a forced four-wavefront shape stays forced
-  auto fits = [&](int k) { return k == 1 || (split && KT / k >= 8 && k * M <= arena); };
-  TilePlan best;
-  double best_t = 1e30;
-  for (const TileShape& t : kTiles) {
-    const int nb = (nt + t.wy * t.wn - 1) / (t.wy * t.wn), mb = ((M + 15) / 16 + 2 * t.wm - 1) / (2 * t.wm);
-    if (t.wy == 4) {
-      if (kn.gemm_wide == 2 ? nt % (4 * t.wn) != 0 : (kn.gemm_wide != 1 || forced)) continue;
-    }
-    if (kn.gemm_tile && kn.gemm_tile != t.wn) continue;
-    if (kn.gemm_wm && kn.gemm_wm != t.wm) continue;
-    for (int k : {1, 2, 3, 4, 6, 8}) {
-      if (!fits(k)) continue;
-      if (kn.gemm_ks && split && k != kn.gemm_ks && fits(kn.gemm_ks)) continue;
-      // a workgroup of eight wavefronts has its CU to itself: not for launches that leave many CUs without one
-      if (t.wy == 4 && kn.gemm_wide == 1 && nb * mb * k < 160) continue;
-      const int on_cu = ((nb * mb + 7) / 8 * k + 31) / 32, per = (KT + k - 1) / k;
-      const int pairs = t.wy == 2 ? on_cu / 2 : 0, single = on_cu - 2 * pairs;
-      double us = (pairs * t.two + single * t.one) * per + (pairs + single) * t.fixed;
-      if (split) us += 2.25 * k * M * (double)N * 4 / 4.7e6;   // slabs, at the rate of a large copy
-      if (t.wy == 4 && kn.gemm_wide == 2) us *= 1e-3;           // wherever one fits
-      if (us < best_t) { best_t = us; best.t = &t; best.ks = k; }
-    }
-  }
-  if (!best.t) best.t = &kTiles[2];   // a knob that names no shape
-  return best;
-}
-
 inline int gemm_class(int epi, int N, int vocab) { return (epi == EPI_STORE && N == vocab) ? DFLASH_PROF_GEMM_LMHEAD : epi; }
-
-// K split across workgroups: aim at enough workgroups that every CU keeps several wavefronts streaming,
-// keep at least 2 k-tiles per wavefront, and stay inside the arena.
-inline int pick_ksplit(int n_blocks, int KT, int M, int arena, int target) {
-  int ks = 1;
-  while (ks < kMaxKSplit && n_blocks * ks * 2 <= target && KT / (ks * 2 * 4) >= 2 && ks * 2 * M <= arena) ks *= 2;
-  return ks;
-}
-
-// The weight-streaming kernel's launch for up to 64 rows: weight tiles and activation bands per workgroup, k tiles per
-// prefetch stage, K ranges.
-struct StreamPlan {
-  int nt = 0, mt = 0, u = 0, ks = 1;   // nt = 0: another kernel's shape
-};
-inline StreamPlan stream_plan(const Knobs& kn, int M, int N, int K, bool split, int arena) {
-  const int nt = N / 16, KT = K / 32;
-  StreamPlan p;
-  // a launch of 192 workgroups leaves a quarter of the CUs idle: among 8, 6 or 4 weight tiles per wavefront and any K split
-  // (not only powers of two) take the fullest last round; ties go to more tiles, then to fewer K ranges.  (Four tiles pay
-  // where nothing else fills the chip: an unsplit 16384-column LM head, 128 workgroups with 8, took 31 us at 16 rows and 49 at
-  // 64, now 23 and 39.)
-  auto fullest = [&]() {
-    double best = -1.0;
-    for (int cand : {8, 6, 4}) {
-      if (nt % cand) continue;
-      const int nb = nt / cand;
-      for (int k = 1; k <= (split ? kMaxKSplit : 1); ++k) {
-        if (k > 1 && (KT / (k * 4) < 2 || k * M > arena)) break;
-        const int wgs = nb * k, rounds = (wgs + 255) / 256;
-        const double fill = (double)wgs / (rounds * 256.0) - 0.02 * (rounds - 1);   // a single round beats several
-        if (fill > best + 1e-9) { best = fill; p.nt = cand; p.ks = k; }
-      }
-    }
-  };
-  auto powers = [&](int t) {
-    p.nt = t;
-    p.ks = split ? pick_ksplit(nt / t, KT, M, arena, kn.gemm_target_wgs) : 1;
-  };
-  if (M <= 16) {
-    const int NT8 = kn.gemm_nt8, U = kn.gemm_u;   // U: k-tiles per prefetch stage
-    p.mt = 1;
-    if (kn.gemm_fill == 1 && NT8 && nt >= 8 * NT8 && (nt % 8 == 0 || nt % 6 == 0)) {
-      fullest();
-      p.u = 2;
-    } else if (NT8 && nt % 8 == 0 && nt >= 8 * NT8) {
-      powers(8);
-      p.u = U >= 2 ? 2 : 1;
-    } else if (nt % 4 == 0) {
-      powers(4);
-      p.u = U >= 4 ? 4 : (U >= 2 ? 2 : 1);
-    } else {
-      powers(nt % 2 == 0 ? 2 : 1);
-      p.u = 4;
-    }
-  } else if (M <= 64 && nt % 8 == 0) {
-    // still bandwidth-bound: the same streaming kernel with two or four activation bands per weight tile
-    p.mt = M <= 32 ? 2 : 4;
-    p.u = 1;
-    if (kn.gemm_fill4 == 1) fullest();
-    else powers(8);
-    if (p.nt == 8 && kn.gemm_u4 >= 2) p.u = 2;   // (measured slower)
-  }
-  return p;
-}
 
 template <>
 Engine<bf16_t>::Slab Engine<bf16_t>::gemm(const bf16_t* W, const bf16_t* A, int M, int N, int K, int epi, EpiArgs ep, bool allow_split) {
