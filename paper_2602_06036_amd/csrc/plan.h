@@ -112,6 +112,7 @@ inline TilePlan tile_plan(const Knobs& kn, int M, int N, int K, bool split, int 
   const int nt = N / 16, KT = K / 32;
   const bool forced = kn.gemm_tile || kn.gemm_wm || kn.gemm_ks;   // a forced four-wavefront shape stays forced
   auto fits = [&](int k) { return k == 1 || (split && KT / k >= 8 && k * M <= arena); };
+  const bool force_ks = kn.gemm_ks && split && fits(kn.gemm_ks);   // any number of ranges that fits
   TilePlan best;
   double best_t = 1e30;
   for (const TileShape& t : kTiles) {
@@ -121,9 +122,10 @@ inline TilePlan tile_plan(const Knobs& kn, int M, int N, int K, bool split, int 
     }
     if (kn.gemm_tile && kn.gemm_tile != t.wn) continue;
     if (kn.gemm_wm && kn.gemm_wm != t.wm) continue;
-    for (int k : {1, 2, 3, 4, 6, 8}) {
+    const int tried[] = {1, 2, 3, 4, 6, 8};
+    for (int i = 0; i < (force_ks ? 1 : 6); ++i) {
+      const int k = force_ks ? kn.gemm_ks : tried[i];
       if (!fits(k)) continue;
-      if (kn.gemm_ks && split && k != kn.gemm_ks && fits(kn.gemm_ks)) continue;
       // a workgroup of eight wavefronts has its CU to itself: not for launches that leave many CUs without one
       if (t.wy == 4 && kn.gemm_wide == 1 && nb * mb * k < 160) continue;
       const int on_cu = ((nb * mb + 7) / 8 * k + 31) / 32, per = (KT + k - 1) / k;
@@ -134,7 +136,10 @@ inline TilePlan tile_plan(const Knobs& kn, int M, int N, int K, bool split, int 
       if (us < best_t) { best_t = us; best.t = &t; best.ks = k; }
     }
   }
-  if (!best.t) best.t = &kTiles[2];   // a knob that names no shape
+  if (!best.t) {   // a knob that names no shape
+    best.t = &kTiles[2];
+    if (force_ks) best.ks = kn.gemm_ks;
+  }
   return best;
 }
 
