@@ -957,10 +957,11 @@ Engine<bf16_t>::Slab Engine<bf16_t>::moe_ffn(const dflash_dims& m, const char* l
     a = ws<bf16_t>(c->ws.moe_a);
   }
   const double used = (double)std::min(E, M * k);   // experts whose matrices are streamed, at most
-  // Items of 4 and 8 bands run on the LDS-staged kernel: eight wavefronts on 256 x 64 tiles, two workgroups to a CU, keep
-  // 96 KB of k tiles on their way per CU, where the streaming kernel's cross-wavefront sum takes a whole CU's LDS and its
-  // short sweeps (16 k tiles a wavefront) end in it.  512 rows, 8 of 128 experts each (805 / 403 MB of matrices): gate/up
-  // 188 -> 175 us, down 96 -> 84 in the step; 177 -> 150 and 92 -> 87 as isolated launches.
+  // Items of 4 and 8 bands run on the LDS-staged kernel.  Of 4 bands: eight wavefronts on 256 x 64 tiles (four on 128 x 64 where
+  // half_height_expert_tiles says so), two workgroups to a CU, keep 96 KB of k tiles on their way per CU, where the streaming
+  // kernel's cross-wavefront sum takes a whole CU's LDS and its short sweeps (16 k tiles a wavefront) end in it.  512 rows, 8 of
+  // 128 experts each (805 / 403 MB of matrices): gate/up 188 -> 175 us, down 96 -> 84 in the step; 177 -> 150 and 92 -> 87 as
+  // isolated launches.
   {
     ProfScope prof(c, st, DFLASH_PROF_MOE_GATEUP, used * 2 * Fe * D * 2);
     EpiArgs ep{nullptr, 0, 0, act, Fe};
@@ -970,8 +971,10 @@ Engine<bf16_t>::Slab Engine<bf16_t>::moe_ffn(const dflash_dims& m, const char* l
     if (MT == 8) {
       if ((2 * Fe / 16) % 12 == 0) launch_grouped_tiled<6, 4, EPI_SWIGLU, 2, 2>(st, W, a, n_pos, 2 * Fe, D, ep, n_items);
       else launch_grouped_tiled<4, 4, EPI_SWIGLU, 3, 2>(st, W, a, n_pos, 2 * Fe, D, ep, n_items);
-    } else if (MT == 4) launch_grouped_tiled<4, 2, EPI_SWIGLU, 3, 4>(st, W, a, n_pos, 2 * Fe, D, ep, n_items);
-    else if (MT == 1) launch_grouped<1, 2, EPI_SWIGLU>(st, W, a, n_pos, 2 * Fe, D, ep, n_items);   // one k tile per stage: no faster (78.9 us)
+    } else if (MT == 4) {
+      if (half_height_expert_tiles(2 * Fe / 16)) launch_grouped_tiled<4, 2, EPI_SWIGLU, 4, 2>(st, W, a, n_pos, 2 * Fe, D, ep, n_items);
+      else launch_grouped_tiled<4, 2, EPI_SWIGLU, 3, 4>(st, W, a, n_pos, 2 * Fe, D, ep, n_items);
+    } else if (MT == 1) launch_grouped<1, 2, EPI_SWIGLU>(st, W, a, n_pos, 2 * Fe, D, ep, n_items);   // one k tile per stage: no faster (78.9 us)
     else launch_grouped<2, 1, EPI_SWIGLU>(st, W, a, n_pos, 2 * Fe, D, ep, n_items);
     check();
     ++c->gemm_counts[DFLASH_GEMM_GROUPED];
@@ -986,6 +989,7 @@ Engine<bf16_t>::Slab Engine<bf16_t>::moe_ffn(const dflash_dims& m, const char* l
     // epilogues overlap (measured 48 us against 54 with two tiles per stage and 60 with four)
     const int down_u = c->k.moe_down_u;
     if (MT == 8) launch_grouped_tiled<4, 4, EPI_STORE, 3, 2>(st, W, act, n_pos, D, Fe, ep, n_items);
+    else if (MT == 4 && half_height_expert_tiles(D / 16)) launch_grouped_tiled<4, 2, EPI_STORE, 4, 2>(st, W, act, n_pos, D, Fe, ep, n_items);
     else if (MT == 4) launch_grouped_tiled<4, 2, EPI_STORE, 3, 4>(st, W, act, n_pos, D, Fe, ep, n_items);
     else if (MT == 1 && down_u == 1) launch_grouped<1, 1, EPI_STORE>(st, W, act, n_pos, D, Fe, ep, n_items);
     else if (MT == 1) launch_grouped<1, 2, EPI_STORE>(st, W, act, n_pos, D, Fe, ep, n_items);

@@ -207,6 +207,13 @@ inline StreamPlan stream_plan(const Knobs& kn, int M, int N, int K, bool split, 
   return p;
 }
 
+// Weight rows per tile of a four-band routed-expert item: 256 (eight wavefronts), or 128 (four) for the short matrices of an odd
+// number of 128-row blocks, where the half-empty last 256-row block is a twelfth of the launch or more.  `nt`: 16-row bands of
+// the matrix.  Two-layer verifications of 512 rows, 8 of 128 experts, 2048 wide, with 256 and with 128 rows per tile: d_expert 64
+// 402 and 388 us, 320 586 and 574, 448 665 and 658, 576 747 and 733, 704 842 and 812 (8 % empty), but 960 939 and 955 (6 %) and 1344
+// 1181 and 1192; 192 is 480 and 486 there, 659 and 625 at 896 rows.
+inline bool half_height_expert_tiles(int nt) { return nt % 16 != 0 && nt < 96; }
+
 // ---- sampled acceptance ------------------------------------------------------------------------------------
 // Workgroups per row of the statistics launch: enough for 4096 of them (16 a CU), not below 1024 columns each, and no
 // more pieces than `room` entries hold.  Workgroups per sequence of the sweep over the vocabulary: 1024 in all, 1024 columns

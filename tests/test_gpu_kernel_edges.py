@@ -8,7 +8,7 @@ import pytest
 from oracle import dflash_oracle as O
 from synth import inputs as si
 from tests.helpers import tiny_workload
-from tests.test_gpu_parity import Lockstep, _gpu
+from tests.test_gpu_parity import ROUTE_CLEAR, Lockstep, _gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -293,3 +293,23 @@ def test_equal_router_logits_go_to_the_lowest_expert(experts, top_k, n_seqs):
     assert all(len(set(r)) == len(r) for r in first)
     assert len(np.unique(first)) > top_k // 4 + 1
     g.e.close()
+
+
+@pytest.mark.parametrize("d_expert,d_model,seed", [
+    (192, 640, 202),      # gate/up 24 bands, down 40: 128-row tiles
+    (832, 512, 201),      # gate/up 104 bands: 256-row tiles, the last one half empty; down 32
+    (64, 1792, 200),      # gate/up 8 bands: one 128-row tile; down 112: 256-row tiles, the last one half empty
+])
+def test_four_band_expert_items_of_odd_heights(d_expert, d_model, seed):
+    """Routed-expert items of four bands (160 rows, 4 of 16 experts) on matrices that 256-row tiles do not divide."""
+    w = si.small_moe_workload(n_seqs=10, ctx_min=12, ctx_max=30, seed=seed, n_experts=16, top_k=4, d_expert=d_expert)
+    w = replace(w, target=replace(w.target, d_model=d_model, n_layers=2), draft=replace(w.draft, d_model=d_model, n_layers=1))
+    ls = Lockstep(w, si.make_prompts(w), max_len=30 + 3 * 16)
+    ls.prefill()
+    assert min(ls.route_gaps) > ROUTE_CLEAR
+    ls.g.e.moe_stats()
+    for i, plan in enumerate([None, list(np.arange(10) % 16)]):
+        ls.step(plan=plan, step_idx=i)
+    assert ls.g.e.moe_stats()[4] == 4
+    ls.check_cache([0, 1], [0])
+    assert ls.stats["route_ties"] <= 2 and ls.stats["reseeds"] <= 1 + ls.stats["route_ties"]
