@@ -16,7 +16,7 @@ inline int env_int(const char* name, int dflt) {
 // context keeps the values it was created with, so a test that sets one before dflash_create gets exactly that path
 // whatever ran earlier in the process.  Defaults are what the measurements in the documentation use.
 struct Knobs {
-  int gemm_wide;            // DFLASH_GEMM_WIDE: 1 = eight-wavefront tiles by estimated time (default), 2 = wherever one fits (tests), any other value = never
+  int gemm_wide;            // DFLASH_GEMM_WIDE: 1 = eight-wavefront tiles by estimated time (default), 2 = always (tests), any other value = never
   int attn_target_wgs;      // DFLASH_ATTN_TARGET_WGS: workgroups an attention launch aims at
   int attn_wide_min_chunk;  // DFLASH_ATTN_WIDE_MIN_CHUNK: keys per workgroup from which the key-split attention kernel is used
   int gemm_target_wgs;      // DFLASH_GEMM_TARGET_WGS: workgroups a K-split streaming GEMM aims at
@@ -117,9 +117,7 @@ inline TilePlan tile_plan(const Knobs& kn, int M, int N, int K, bool split, int 
   double best_t = 1e30;
   for (const TileShape& t : kTiles) {
     const int nb = (nt + t.wy * t.wn - 1) / (t.wy * t.wn), mb = ((M + 15) / 16 + 2 * t.wm - 1) / (2 * t.wm);
-    if (t.wy == 4) {
-      if (kn.gemm_wide == 2 ? nt % (4 * t.wn) != 0 : (kn.gemm_wide != 1 || forced)) continue;
-    }
+    if (t.wy == 4 && kn.gemm_wide != 2 && (kn.gemm_wide != 1 || forced)) continue;
     if (kn.gemm_tile && kn.gemm_tile != t.wn) continue;
     if (kn.gemm_wm && kn.gemm_wm != t.wm) continue;
     const int tried[] = {1, 2, 3, 4, 6, 8};
@@ -132,7 +130,7 @@ inline TilePlan tile_plan(const Knobs& kn, int M, int N, int K, bool split, int 
       const int pairs = t.wy == 2 ? on_cu / 2 : 0, single = on_cu - 2 * pairs;
       double us = (pairs * t.two + single * t.one) * per + (pairs + single) * t.fixed;
       if (split) us += 2.25 * k * M * (double)N * 4 / 4.7e6;   // slabs, at the rate of a large copy
-      if (t.wy == 4 && kn.gemm_wide == 2) us *= 1e-3;           // wherever one fits
+      if (t.wy == 4 && kn.gemm_wide == 2) us *= 1e-3;           // before any four-wavefront shape
       if (us < best_t) { best_t = us; best.t = &t; best.ks = k; }
     }
   }

@@ -30,3 +30,20 @@ def tiny_workload(seed=0, n_layers=2, draft_layers=1, vocab=1024, block=8, qk_no
     taps = taps if taps is not None else (0,)
     return si.Workload("tiny", dtype, t, dd, tuple(taps), vocab - 1, block, n_seqs, ctx[0], ctx[1],
                        0.0, seed)
+
+
+# Forced shapes of the LDS-staged GEMM over row counts and heights that leave tiles, activation blocks and the XCDs' shares ragged:
+# (sequences of 16 rows, FFN width, vocabulary, DFLASH_GEMM_WIDE, _TILE, _WM, _KS).  Rows of the model: d_model 256, QKV 512.
+TILE_EDGES = [
+    (5, 1056, 1056, 1, 8, 4, 3), (9, 2112, 2080, 1, 8, 4, 0),
+    (17, 1312, 2080, 1, 6, 4, 0), (5, 2112, 1056, 1, 6, 4, 6),
+    (9, 1056, 1056, 1, 4, 4, 0), (17, 2112, 2048, 1, 4, 4, 3),
+    (5, 1312, 2080, 1, 8, 2, 0), (17, 1056, 1056, 1, 8, 2, 2),
+    (9, 1312, 2080, 1, 6, 2, 5), (5, 1056, 1056, 1, 4, 2, 0),
+    (9, 1056, 2080, 2, 6, 4, 3), (17, 1312, 1056, 2, 6, 4, 0),
+    (5, 2112, 1056, 2, 4, 4, 6), (9, 1312, 2080, 2, 4, 4, 0),
+    (17, 1056, 2080, 2, 6, 2, 2), (5, 2112, 2080, 2, 6, 2, 6),
+    (9, 2112, 1056, 2, 4, 2, 3), (17, 1312, 2080, 2, 4, 2, 0),
+]
+# (vocabulary, rows, weight tiles per wavefront) of LM heads that the streaming GEMM takes with eight, six and four weight tiles
+STREAM_HEADS = [(v, m, nt) for v, nt in ((32768, 8), (24576, 6), (4096, 4)) for m in (16, 32, 48)]

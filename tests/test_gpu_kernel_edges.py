@@ -7,7 +7,7 @@ import pytest
 
 from oracle import dflash_oracle as O
 from synth import inputs as si
-from tests.helpers import tiny_workload
+from tests.helpers import STREAM_HEADS, TILE_EDGES, tiny_workload
 from tests.test_gpu_parity import ROUTE_CLEAR, Lockstep, _gpu
 
 pytestmark = pytest.mark.gpu
@@ -139,26 +139,61 @@ def test_rotated_keys_are_rounded_in_the_stated_order(hd, qk_norm):
     g.e.close()
 
 
-@pytest.mark.parametrize("n_seqs,d,ffn,vocab", [
-    (5, 256, 1056, 1008),       # 80 rows: a row block of five bands; 66 and 63 row bands of weights (clamped last tiles)
-    (9, 256, 2560, 4096),       # 144 rows: nine bands; 20 weight blocks of 256 rows (not a multiple of the eight XCDs)
-    (17, 512, 1536, 2064),      # 272 rows: one band behind two blocks of 128
-])
-def test_bf16_tile_edges_many_rows(n_seqs, d, ffn, vocab):
-    """The LDS-staged GEMM at row counts and matrix heights that leave tiles, activation blocks and the XCDs' shares
-    ragged, with the shapes and K splits that the dispatcher picks."""
+def _many_rows(n_seqs, d, ffn, vocab):
+    """Prefill, a planned and a free greedy step and a sampled one; returns the launches per kernel family of the steps."""
     w = tiny_workload(seed=d + ffn, n_layers=2, draft_layers=1, vocab=vocab, block=16, qk_norm=True, kv_heads=2, dtype="bf16",
                       n_seqs=n_seqs, taps=(0, 1), d=d, heads=d // 64, hd=64, ffn=ffn)
-    lens = [20 + (7 * i) % 31 for i in range(n_seqs)]
-    prompts = [p[:n] for p, n in zip(si.make_prompts(replace(w, ctx_min=60, ctx_max=60)), lens)]
-    ls = Lockstep(w, prompts, max_len=60 + 4 * 16)
+    lens = [3 + (7 * i) % 31 for i in range(n_seqs)]
+    prompts = [p[:n] for p, n in zip(si.make_prompts(replace(w, ctx_min=40, ctx_max=40)), lens)]
+    ls = Lockstep(w, prompts, max_len=40 + 4 * 16)
     ls.prefill()
     ls.g.e.gemm_counts()
-    for i, plan in enumerate([[(5 * s) % 16 for s in range(n_seqs)], None]):
-        ls.step(plan=plan, step_idx=i)
+    ls.step(plan=[(5 * s) % 16 for s in range(n_seqs)], step_idx=0)
+    ls.step(step_idx=1)
+    ls.step(temperature=0.8, step_idx=2, key=11)
     counts = ls.g.e.gemm_counts()
-    assert counts[1] + counts[2] > 0
     ls.check_cache([0, 1], [0])
+    assert ls.stats["low_margin_flips"] <= 0.02 * ls.stats["rows"] + 2
+    assert ls.stats["reseeds"] <= 1
+    return counts
+
+
+@pytest.mark.parametrize("n_seqs,d,ffn,vocab", [
+    (5, 256, 1056, 1008),       # 80 rows; an LM head of 63 row bands, which the LDS-staged kernel does not take
+    (9, 256, 2560, 4096),       # 144 rows
+    (17, 512, 1536, 2064),      # 272 rows; an LM head of 129 row bands
+])
+def test_bf16_tile_edges_many_rows(n_seqs, d, ffn, vocab):
+    """The GEMMs of many rows with the shapes and K splits that the dispatcher picks for small matrices: four-wavefront 128 x 64 tiles."""
+    counts = _many_rows(n_seqs, d, ffn, vocab)
+    assert counts[1] > 0 and counts[2] == 0 and (counts[0] > 0) == (vocab % 32 != 0)
+
+
+@pytest.mark.parametrize("n_seqs,ffn,vocab,wide,tile,wm,ks", TILE_EDGES)
+def test_forced_tiles_over_ragged_sizes(n_seqs, ffn, vocab, wide, tile, wm, ks, monkeypatch):
+    """Every tile shape of the LDS-staged GEMM, SwiGLU, K-split and LM-head epilogues (argmax, Gumbel-max, softmax statistics), with
+    clamped last weight blocks, partly filled activation blocks and both mappings to the XCDs; the geometries are listed and checked
+    in test_launch_plans_cpu.py."""
+    for k, v in (("WIDE", wide), ("TILE", tile), ("WM", wm), ("KS", ks)):
+        monkeypatch.setenv("DFLASH_GEMM_" + k, str(v))
+    counts = _many_rows(n_seqs, 256, ffn, vocab)
+    assert counts[wide] > 0 and counts[3 - wide] == 0 and counts[0] == 0
+
+
+@pytest.mark.parametrize("vocab,rows,tiles", STREAM_HEADS)
+def test_streaming_heads_with_eight_six_and_four_weight_tiles(vocab, rows, tiles):
+    """LM heads of 16, 32 and 48 rows, high enough for the weight tiles per wavefront that a whole vocabulary takes, with their argmax,
+    Gumbel-max and softmax-statistics epilogues."""
+    n_seqs = rows // 16
+    w = tiny_workload(seed=tiles, n_layers=2, draft_layers=1, vocab=vocab, block=16, qk_norm=True, kv_heads=2, dtype="bf16", n_seqs=n_seqs,
+                      taps=(0, 1), d=256, heads=4, hd=64, ffn=512)
+    prompts = [p[:9 + 4 * i] for i, p in enumerate(si.make_prompts(replace(w, ctx_min=20, ctx_max=20)))]
+    ls = Lockstep(w, prompts, max_len=20 + 4 * 16)
+    ls.prefill()
+    ls.g.e.gemm_counts()
+    ls.step(plan=[(5 * s + 3) % 16 for s in range(n_seqs)], step_idx=0)
+    ls.step(temperature=0.8, step_idx=1, key=11)
+    assert ls.g.e.gemm_counts()[0] > 0
     assert ls.stats["low_margin_flips"] <= 0.02 * ls.stats["rows"] + 2
     assert ls.stats["reseeds"] <= 1
 

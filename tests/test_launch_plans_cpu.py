@@ -4,6 +4,8 @@ import subprocess
 
 import pytest
 
+from tests.helpers import STREAM_HEADS, TILE_EDGES
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "..", "paper_2602_06036_amd", "csrc")
 
@@ -15,7 +17,8 @@ int main() {
   const Knobs kn = read_knobs();
   while (scanf("%d %d %d %d %d", &M, &N, &K, &split, &max_rows) == 5) {
     const TilePlan t = tile_plan(kn, M, N, K, split != 0, arena_rows(max_rows));
-    printf("%d %d %d %d %d\n", t.t->wn, t.t->wm, t.t->wy, t.ks, half_height_expert_tiles(N / 16) ? 128 : 256);
+    const StreamPlan s = stream_plan(kn, M, N, K, split != 0, arena_rows(max_rows));
+    printf("%d %d %d %d %d %d\n", t.t->wn, t.t->wm, t.t->wy, t.ks, half_height_expert_tiles(N / 16) ? 128 : 256, s.nt);
   }
 }
 """
@@ -28,8 +31,8 @@ def plans(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, str(d / "plans.cpp"), "-o", str(d / "plans")], check=True)
 
     def run(queries, **knobs):
-        """(weight tiles, bands, wavefronts along N, K ranges, rows of a four-band expert tile) for each (rows, height, K, may split,
-        rows of the context)."""
+        """(weight tiles, bands, wavefronts along N, K ranges, rows of a four-band expert tile, weight tiles of the streaming
+        kernel) for each (rows, height, K, may split, rows of the context)."""
         env = {k: v for k, v in os.environ.items() if not k.startswith("DFLASH_")}
         env.update({"DFLASH_" + k: str(v) for k, v in knobs.items()})
         out = subprocess.run([str(d / "plans")], input="\n".join(" ".join(str(int(x)) for x in q) for q in queries), env=env,
@@ -59,3 +62,43 @@ def test_tiles_of_four_band_expert_items_waste_less_than_a_twelfth(plans):
         tile = p[4]
         assert (-h % tile) * 12 < -(-h // tile) * tile, (h, tile)
         assert tile == 256 or h % 256          # the larger tile where it divides
+
+
+def test_forced_tiles_cover_ragged_geometries(plans):
+    """What the GPU tests over TILE_EDGES run: every shape, each with a clamped last weight block; interleaved and contiguous
+    shares of the XCDs with several activation blocks; activation blocks of one band; K ranges of 2, 3, 5 and 6, also uneven ones."""
+    seen = set()
+    for n_seqs, ffn, vocab, wide, tile, wm, ks in TILE_EDGES:
+        M = 16 * n_seqs
+        mats = [(M, 512, 256, 1, M), (M, 256, 256, 1, M), (M, 2 * ffn, 256, 0, M), (M, 256, ffn, 1, M), (M, vocab, 256, 0, M)]
+        for (_, N, K, split, _), (wn, bm, wy, k, _, _) in zip(mats, plans(mats, GEMM_WIDE=wide, GEMM_TILE=tile, GEMM_WM=wm, GEMM_KS=ks)):
+            assert (wn, bm, wy) == (tile, wm, 2 * wide)
+            nb, mb = -(-N // 16 // (wy * wn)), -(-n_seqs // (2 * wm))
+            shape = (wn, bm, wy)
+            if (N // 16) % (wy * wn):
+                seen.add(("clamped swiglu" if N == 2 * ffn else "clamped", shape))
+            if mb > 1:
+                seen.add("interleaved" if nb % 8 == 0 else "contiguous")
+            if n_seqs % (2 * wm) == 1:
+                seen.add("one band")
+            if k > 1:
+                seen.add(("K ranges", k, K // 32 % k > 0))
+    shapes = {(c[4], c[5], 2 * c[3]) for c in TILE_EDGES}
+    assert len(shapes) == 10
+    for s in shapes:
+        assert ("clamped", s) in seen and ("clamped swiglu", s) in seen, s
+    assert {"interleaved", "contiguous", "one band"} <= seen
+    assert {c[1] for c in seen if c[0] == "K ranges"} >= {2, 3, 5, 6} and any(c[0] == "K ranges" and c[2] for c in seen)
+
+
+def test_streaming_heads_take_the_weight_tiles_that_the_gpu_test_names(plans):
+    q = [(m, v, 256, 0, m) for v, m, _ in STREAM_HEADS]
+    assert [p[5] for p in plans(q)] == [nt for _, _, nt in STREAM_HEADS]
+
+
+def test_small_matrices_of_many_rows_take_four_wavefront_tiles(plans):
+    """What the dispatcher picks at the sizes of the GPU test without forced shapes."""
+    for n_seqs, d, ffn, vocab in ((5, 256, 1056, 1056), (9, 256, 2560, 4096), (17, 512, 1536, 2080)):
+        M = 16 * n_seqs
+        q = [(M, d + 256, d, 1, M), (M, d, d, 1, M), (M, 2 * ffn, d, 0, M), (M, d, ffn, 1, M), (M, vocab, d, 0, M)]
+        assert all(p[:3] == (4, 2, 2) for p in plans(q))
