@@ -1009,9 +1009,7 @@ template <>
 Engine<float>::Slab Engine<float>::gemm(const float* W, const float* A, int M, int N, int K, int epi, EpiArgs ep, bool) {
   ProfScope prof(c, st, gemm_class(epi, N, c->t.vocab), (double)N * K * 4);
   const int cols = epi == EPI_SWIGLU ? N / 2 : N;
-  // four wavefronts per column where K has a 256-wide piece for each and one column per workgroup still leaves the launch
-  // within a few rounds of the CUs; more columns share the activation rows over the workgroup's wavefronts instead
-  const bool split = K >= 1024 && cols <= 2048;
+  const bool split = split_f32_columns(cols, K, epi == EPI_SWIGLU);
   auto launch = [&](auto ec) {
     constexpr int E = decltype(ec)::value;
     if (split) hipLaunchKernelGGL((gemm_f32_kernel<E, 4>), dim3(cols), dim3(256), 0, st, W, A, M, N, K, ep);

@@ -205,6 +205,14 @@ inline StreamPlan stream_plan(const Knobs& kn, int M, int N, int K, bool split, 
   return p;
 }
 
+// fp32 GEMM: whether four wavefronts share an output column's K (each at least a 256-wide piece) instead of taking a column each.
+// It pays while the columns alone leave CUs idle, and the fewer pieces a column has the sooner they fill the chip; a SwiGLU column
+// is two.  Columns x K at 8 and 128 rows, one and four wavefronts a column: 512 x 1024 4.6 and 4.0 us, 33.5 and 27.5; 1024 x 1024
+// 4.8 and 5.1, 34 and 44; 2048 x 1024 5.4 and 7.2, 42 and 76; 1024 x 2048 6.7 and 5.9, 50.9 and 50.5; 2048 x 2048 7.8 and 8.6, 80 and 92;
+// 1536 x 4096 11.3 and 11.5, 152 and 122; 2048 x 4096 13.2 and 15.0, 159 and 160.  SwiGLU 512 x 1024 5.8 and 5.3, 48 and 41; 768 x 1024
+// 6.1 and 6.3, 48 and 61; 1536 x 2048 9.9 and 10.5, 95 and 113.  768 x 1024 is even by itself, in a step of 32 rows four are 4 % faster.
+inline bool split_f32_columns(int cols, int K, bool swiglu) { return K >= 1024 && cols <= std::min(swiglu ? K / 2 : K / 4 * 3, 1536); }
+
 // Weight rows per tile of a four-band routed-expert item: 256 (eight wavefronts), or 128 (four) for the short matrices of an odd
 // number of 128-row blocks, where the half-empty last 256-row block is a twelfth of the launch or more.  `nt`: 16-row bands of
 // the matrix.  Two-layer verifications of 512 rows, 8 of 128 experts, 2048 wide, with 256 and with 128 rows per tile: d_expert 64

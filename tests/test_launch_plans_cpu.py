@@ -18,7 +18,7 @@ int main() {
   while (scanf("%d %d %d %d %d", &M, &N, &K, &split, &max_rows) == 5) {
     const TilePlan t = tile_plan(kn, M, N, K, split != 0, arena_rows(max_rows));
     const StreamPlan s = stream_plan(kn, M, N, K, split != 0, arena_rows(max_rows));
-    printf("%d %d %d %d %d %d\n", t.t->wn, t.t->wm, t.t->wy, t.ks, half_height_expert_tiles(N / 16) ? 128 : 256, s.nt);
+    printf("%d %d %d %d %d %d %d\n", t.t->wn, t.t->wm, t.t->wy, t.ks, half_height_expert_tiles(N / 16) ? 128 : 256, s.nt, split_f32_columns(N, K, !split) ? 4 : 1);
   }
 }
 """
@@ -32,7 +32,7 @@ def plans(tmp_path_factory):
 
     def run(queries, **knobs):
         """(weight tiles, bands, wavefronts along N, K ranges, rows of a four-band expert tile, weight tiles of the streaming
-        kernel) for each (rows, height, K, may split, rows of the context)."""
+        kernel, wavefronts of an fp32 column) for each (rows, height, K, may split, rows of the context)."""
         env = {k: v for k, v in os.environ.items() if not k.startswith("DFLASH_")}
         env.update({"DFLASH_" + k: str(v) for k, v in knobs.items()})
         out = subprocess.run([str(d / "plans")], input="\n".join(" ".join(str(int(x)) for x in q) for q in queries), env=env,
@@ -71,7 +71,7 @@ def test_forced_tiles_cover_ragged_geometries(plans):
     for n_seqs, ffn, vocab, wide, tile, wm, ks in TILE_EDGES:
         M = 16 * n_seqs
         mats = [(M, 512, 256, 1, M), (M, 256, 256, 1, M), (M, 2 * ffn, 256, 0, M), (M, 256, ffn, 1, M), (M, vocab, 256, 0, M)]
-        for (_, N, K, split, _), (wn, bm, wy, k, _, _) in zip(mats, plans(mats, GEMM_WIDE=wide, GEMM_TILE=tile, GEMM_WM=wm, GEMM_KS=ks)):
+        for (_, N, K, split, _), (wn, bm, wy, k, *_) in zip(mats, plans(mats, GEMM_WIDE=wide, GEMM_TILE=tile, GEMM_WM=wm, GEMM_KS=ks)):
             assert (wn, bm, wy) == (tile, wm, 2 * wide)
             nb, mb = -(-N // 16 // (wy * wn)), -(-n_seqs // (2 * wm))
             shape = (wn, bm, wy)
@@ -102,3 +102,13 @@ def test_small_matrices_of_many_rows_take_four_wavefront_tiles(plans):
         M = 16 * n_seqs
         q = [(M, d + 256, d, 1, M), (M, d, d, 1, M), (M, 2 * ffn, d, 0, M), (M, d, ffn, 1, M), (M, vocab, d, 0, M)]
         assert all(p[:3] == (4, 2, 2) for p in plans(q))
+
+
+def test_fp32_columns_are_shared_only_where_that_is_faster(plans):
+    """(columns, K, plain or SwiGLU) as measured with one and with four wavefronts a column."""
+    four = [(256, 1024, 1), (512, 1024, 1), (768, 1024, 1), (512, 1024, 0), (768, 1536, 0), (512, 2048, 1), (1024, 2048, 0), (1024, 4096, 1),
+            (1536, 4096, 0)]
+    one = [(1024, 1024, 1), (2048, 1024, 1), (768, 1024, 0), (1536, 1536, 1), (2048, 1536, 1), (2048, 2048, 1), (1536, 2048, 0),
+           (4096, 2048, 1), (256, 512, 1), (16384, 1024, 1)]
+    got = [p[6] for p in plans([(8, n, k, plain, 8) for n, k, plain in four + one])]
+    assert got == [4] * len(four) + [1] * len(one)
