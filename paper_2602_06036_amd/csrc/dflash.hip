@@ -440,7 +440,7 @@ struct Engine {
                          eps, taps, tap, tap_K, RowMix{});
     check();
   }
-  // row-wise argmax (or Gumbel-perturbed argmax) in two launches: per-chunk winners, then one wavefront per row
+  // row-wise argmax (or Gumbel-perturbed argmax) in two launches: per-chunk winners, then one workgroup per row
   void argmax(const float* logits, int V, int M, int B, int32_t* out, int skip_slot0, int mode, float inv_T, const uint64_t* key) {
     float2* part = ws<float2>(c->ws.amax);
     int parts = amax_parts;
@@ -849,8 +849,8 @@ Engine<bf16_t>::Slab Engine<bf16_t>::gemm(const bf16_t* W, const bf16_t* A, int 
 #define DF_STREAM(NT, MT, U) case NT * 100 + MT * 10 + U: launch_bf16<NT, MT, U>(st, W, A, M, N, K, kepi, ep, ks); break
       DF_STREAM(8, 1, 2); DF_STREAM(8, 1, 1); DF_STREAM(6, 1, 2); DF_STREAM(4, 1, 4); DF_STREAM(4, 1, 2); DF_STREAM(4, 1, 1);
       DF_STREAM(2, 1, 4); DF_STREAM(1, 1, 4); DF_STREAM(8, 2, 2); DF_STREAM(8, 2, 1); DF_STREAM(6, 2, 1); DF_STREAM(4, 2, 1);
-      // (the single-buffered two-workgroups-per-CU form of this kernel that the routed experts use was measured here
-      // too: 58.7 us against 48.2 for gate/up at 64 rows -- a dense launch has fewer workgroups than CUs)
+      // (with one buffer and two workgroups per CU gate/up at 64 rows took 58.7 us against 48.2: a dense launch has fewer
+      // workgroups than CUs)
       DF_STREAM(8, 4, 2); DF_STREAM(8, 4, 1); DF_STREAM(6, 4, 1); DF_STREAM(4, 4, 1);
 #undef DF_STREAM
     }
@@ -891,7 +891,6 @@ Engine<bf16_t>::Slab Engine<bf16_t>::gemm(const bf16_t* W, const bf16_t* A, int 
   return Slab{ep.out, ks, ep.slab};
 }
 
-// (four weight tiles per wavefront instead of eight were measured at 512 rows: 192 us against 174 for gate/up)
 template <int MT, int U, int EPI>
 void launch_grouped(hipStream_t st, const bf16_t* W, const bf16_t* A, int rows, int N, int K, EpiArgs ep, int n_items) {
   const dim3 grid(((n_items + 7) / 8) * 8 * ((N / 16) / 8), 1, 1), block(256);
@@ -918,11 +917,11 @@ Engine<bf16_t>::Slab Engine<bf16_t>::moe_ffn(const dflash_dims& m, const char* l
   // so that nearly every expert's matrix is streamed by one row of workgroups only
   const double avg = (double)M * k / E, want = avg + 2.0 * sqrt(avg);
   const int mt_force = c->k.moe_mt;   // 1, 2, 4 or 8 forces the bands per work item
-  // from 64 rows per expert on (a many-row prefill pass) the items are 128-row blocks of the LDS-staged kernel: the
-  // streaming kernel would need two or more 64-row items for many experts, each streaming the expert's matrices.
-  // Measured on one-pass prefills of the 30B-A3B shape, whose rows crowd on about a quarter of the experts: 1024 rows
-  // 23.9 ms against 28.6, 2048 rows 40.5 against 51.9, 512 rows 14.9 against 16.9; the decode step of 32 sequences (32
-  // rows on every expert) loses, 26.8 against 24.5 ms, so batches below 64 rows per expert keep the 64-row items
+  // from 64 rows per expert on the items are 128-row blocks, so that an expert's matrices are still streamed by one row of
+  // workgroups.  Four layers of the 30B-A3B shape with 64- and with 128-row items: verification of rows that sit evenly, 32 on
+  // every expert 1708 and 1830 us, 48 1987 and 2019, 64 2254 and 2236; prefill of random rows, which crowd on 74 to 83 of the
+  // 128 experts, 512 rows 1442 and 1570, 1024 2099 and 2212, 2048 3492 and 3525 (the rule goes by the rows, not by the crowding,
+  // which the host does not know)
   const int MT = (mt_force == 1 || mt_force == 2 || mt_force == 4 || mt_force == 8) ? mt_force
                  : (want <= 16.0 ? 1 : (want <= 32.0 ? 2 : (avg < 64.0 ? 4 : 8)));
   const int n_items = moe_items(m, M, MT), n_pos = moe_positions(m, M);

@@ -1,7 +1,7 @@
 // Weight-streaming GEMMs: y[M,N] = a[M,K] * W[N,K]^T with fused epilogues.
 //   bf16: MFMA 16x16x32, weights in the tiled layout of common.h, activations as hi+lo bf16 pairs
 //         (two MFMAs per weight tile), fp32 accumulation.
-//   fp32: one wavefront per output column (tiny models only).
+//   fp32: one or four wavefronts per output column (small models only).
 #pragma once
 #include <type_traits>
 
@@ -94,9 +94,10 @@ struct GemmBuf {
   u32x4 w[U][NT], ah[U][MT], al[U][MT];
 };
 
-template <int NT, int MT, int U, int EPI, bool GRP = false, int NW = 4>
-__global__ __launch_bounds__(64 * NW, 1) void gemm_bf16_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ A,
+template <int NT, int MT, int U, int EPI, bool GRP = false>
+__global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ A,
                                                         int M, int N, int K, EpiArgs ep) {
+  constexpr int NW = 4;   // wavefronts of a workgroup, each with its share of the K range
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int kz = blockIdx.z;
   const int KT = K >> 5, n_tiles = N >> 4;

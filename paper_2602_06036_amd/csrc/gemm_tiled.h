@@ -6,7 +6,8 @@
 // 16x32 fragment), so a k tile is staged in LDS by copying whole fragments; every wavefront reads the WN weight and 2*WM
 // activation fragments of its part of the tile (each lane its own 16 bytes: conflict-free ds_read_b128) and issues
 // WN*WM*2 MFMAs per k tile.  The eight-wavefront form (WY = 4) is two four-wavefront workgroups fused along N: one
-// activation stage for twice the weight rows, i.e. a third less operand traffic from L2 per flop, at one workgroup per CU.
+// activation stage for twice the weight rows, i.e. a third less operand traffic from L2 per flop, at one workgroup per CU (two
+// of the 256 x 64 tile with a ring of three slots, which the routed items use: 72 KB and 100 registers).
 //
 // What bounds it: over random operands every tiling ends at 1.2-1.45 PFLOP/s of issued MFMA work (a torch matrix product of
 // the same issued size reaches 1.1-1.47), where the clock gives way to the power limit; below that the waits at the k tiles' seams count.
@@ -32,12 +33,12 @@
 #pragma once
 #include "gemm.h"
 
-// whether two workgroups of this shape share a CU (their staging fits twice)
+// wavefronts per SIMD to leave registers for: two workgroups share a CU where their staging fits twice
 template <int WN, int WM, int NS, int WY>
-constexpr bool tiled_twice() { return WY == 2 && NS * (WY * WN + 4 * WM) <= 80; }
+constexpr int tiled_waves() { return NS * (WY * WN + 4 * WM) <= 80 ? WY : 1; }
 
 template <int WN, int WM, int EPI, int NS, bool GRP = false, int WY = 2, bool REG = false>
-__global__ __launch_bounds__(128 * WY, (tiled_twice<WN, WM, NS, WY>() ? 2 : 1)) void gemm_bf16_tiled_kernel(
+__global__ __launch_bounds__(128 * WY, (tiled_waves<WN, WM, NS, WY>())) void gemm_bf16_tiled_kernel(
     const bf16_t* __restrict__ W, const bf16_t* __restrict__ A, int M, int N, int K, int n_blocks, int m_blocks, EpiArgs ep) {
   constexpr int NWV = 2 * WY;                       // wavefronts: WY along N x 2 along M
   constexpr int BNT = WY * WN, BMT = 2 * WM;        // fragments of a stage: BNT weight + 2*BMT activation (hi, lo)

@@ -1,6 +1,7 @@
 // Routed-expert FFN of a mixture-of-experts target (the Qwen3-Coder-30B-A3B target of Section 5): routing.  The expert
-// GEMMs themselves are grouped launches of the weight-streaming kernel (gemm.h); the weighted sum of a row's experts'
-// outputs is taken by the RMSNorm kernel that follows (misc.h).
+// GEMMs themselves are grouped launches of the weight-streaming kernel (gemm.h; work items of one and two bands) or of the
+// LDS-staged one (gemm_tiled.h; four and eight); the weighted sum of a row's experts' outputs is taken by the RMSNorm kernel
+// that follows (misc.h).
 //
 // Routing rule (that model family's; the paper does not restate it): a token goes to the top_k experts by router
 // logit (ties -> lowest index) with weights softmax(chosen logits); y_t = sum_j w_tj FFN_{e_tj}(a_t).

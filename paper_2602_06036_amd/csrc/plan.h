@@ -22,7 +22,7 @@ struct Knobs {
   int gemm_target_wgs;      // DFLASH_GEMM_TARGET_WGS: workgroups a K-split streaming GEMM aims at
   int gemm_u;               // DFLASH_GEMM_U: k tiles per prefetch stage (one band of rows)
   int gemm_nt8;             // DFLASH_GEMM_NT8: matrices with at least 8 * this row bands use 8 weight tiles per activation fragment
-  int gemm_fill;            // DFLASH_GEMM_FILL: 1 = weight tiles per wavefront (8 or 6) and K split chosen to fill whole rounds of the CUs
+  int gemm_fill;            // DFLASH_GEMM_FILL: 1 = weight tiles per wavefront (8, 6 or 4) and K split chosen to fill whole rounds of the CUs
   int gemm_fill4;           // DFLASH_GEMM_FILL4: the same for 17-64 rows
   int gemm_u4;              // DFLASH_GEMM_U4: k tiles per prefetch stage for 17-64 rows
   int gemm_tile, gemm_wm, gemm_ks;   // DFLASH_GEMM_TILE / _WM / _KS: force the tiled GEMM's shape / rows per tile / K split (0 = by estimated time)
@@ -124,12 +124,15 @@ inline TilePlan tile_plan(const Knobs& kn, int M, int N, int K, bool split, int 
     for (int i = 0; i < (force_ks ? 1 : 6); ++i) {
       const int k = force_ks ? kn.gemm_ks : tried[i];
       if (!fits(k)) continue;
-      // a workgroup of eight wavefronts has its CU to itself: not for launches that leave many CUs without one
+      // a workgroup of eight wavefronts has its CU to itself: not for launches that leave many CUs without one.  Over the sweep that the
+      // costs are fitted to any line up to 160 picks the same (0.74 % above the fastest shape on average), 192 loses 0.1 %, 224 0.7 %
       if (t.wy == 4 && kn.gemm_wide == 1 && nb * mb * k < 160) continue;
       const int on_cu = ((nb * mb + 7) / 8 * k + 31) / 32, per = (KT + k - 1) / k;
       const int pairs = t.wy == 2 ? on_cu / 2 : 0, single = on_cu - 2 * pairs;
       double us = (pairs * t.two + single * t.one) * per + (pairs + single) * t.fixed;
-      if (split) us += 2.25 * k * M * (double)N * 4 / 4.7e6;   // slabs, at the rate of a large copy
+      // slabs, at the rate of a large copy; the factor over the sweep: 0 picks 7.3 % above the fastest shape on average, 1 3.1, 2 0.86,
+      // 2.25 0.74, 3 0.69, 4 1.2
+      if (split) us += 2.25 * k * M * (double)N * 4 / 4.7e6;
       if (t.wy == 4 && kn.gemm_wide == 2) us *= 1e-3;           // before any four-wavefront shape
       if (us < best_t) { best_t = us; best.t = &t; best.ks = k; }
     }
