@@ -68,7 +68,8 @@ inline SplitPlan plan_splits(int S, int n_kv_heads, int max_tokens, int target_w
   // round of workgroups on the 256 CUs (target_wgs: Knobs::attn_target_wgs).  Rounded down: a second round of a few
   // workgroups costs as much as the first.  Two-layer verify steps of the 8B target, rounded up and down: 24 sequences x
   // 4000 keys 1040 and 951 us, 7 x 8000 532 and 490, 20 x 100..400 738 and 724; slower in one of 19 sizes (13 x 300..5000,
-  // lengths that differ so much that more workgroups even the load out: 469 and 476).
+  // lengths that differ so much that more workgroups even the load out: 469 and 476).  It does not fill the chip where S x heads does
+  // not divide 256: 11 and 12 sequences of eight heads run 176 and 192 workgroups, 17 to 31 run 136 to 248.
   const int max_splits = 64;
   int splits = target_wgs / (S * n_kv_heads);
   const int by_len = (max_tokens + 63) / 64;

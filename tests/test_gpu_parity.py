@@ -359,7 +359,7 @@ def test_small_bf16_many_rows_tiled_gemm(tile, rows, monkeypatch):
     ls.check_cache([3], [1])
     counts = ls.g.e.gemm_counts()
     print("small bf16 (160 rows) stats", ls.stats, "launches per kernel family", counts)
-    assert counts[1] > 0 and counts[2] == 0     # four-wavefront tiles for the 160-row steps (eight-wavefront ones need a full round of CUs)
+    assert counts[1] > 0 and counts[2] == 0     # four-wavefront tiles for the 160-row steps (eight-wavefront ones are not picked below 160 workgroups)
     assert ls.stats["low_margin_flips"] <= 0.02 * ls.stats["rows"] + 2
     assert ls.stats["reseeds"] <= 1
 
@@ -367,8 +367,8 @@ def test_small_bf16_many_rows_tiled_gemm(tile, rows, monkeypatch):
 @pytest.mark.parametrize("tile,rows,ks", [("0", "0", "0"), ("6", "4", "0"), ("4", "4", "2"), ("6", "2", "0"), ("4", "2", "2")])
 def test_small_bf16_many_rows_eight_wavefront_tiles(tile, rows, ks, monkeypatch):
     """The 160-row case through the eight-wavefront tiles of the LDS-staged GEMM (384 or 256 weight rows x 128 or 64
-    activation rows, four wavefronts along N), which the dispatcher takes at the 8B shape where they fill one round of
-    the CUs; here forced on every matrix, with and without a K split, including the LM head with its fused argmax."""
+    activation rows, four wavefronts along N), which the dispatcher takes by estimated time from 160 workgroups on;
+    here forced on every matrix, with and without a K split, including the LM head with its fused argmax."""
     monkeypatch.setenv("DFLASH_GEMM_WIDE", "2")
     monkeypatch.setenv("DFLASH_GEMM_TILE", tile)
     monkeypatch.setenv("DFLASH_GEMM_WM", rows)
