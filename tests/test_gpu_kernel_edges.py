@@ -143,9 +143,9 @@ def _many_rows(n_seqs, d, ffn, vocab):
     """Prefill, a planned and a free greedy step and a sampled one; returns the launches per kernel family of the steps."""
     w = tiny_workload(seed=d + ffn, n_layers=2, draft_layers=1, vocab=vocab, block=16, qk_norm=True, kv_heads=2, dtype="bf16",
                       n_seqs=n_seqs, taps=(0, 1), d=d, heads=d // 64, hd=64, ffn=ffn)
-    lens = [3 + (7 * i) % 31 for i in range(n_seqs)]
-    prompts = [p[:n] for p, n in zip(si.make_prompts(replace(w, ctx_min=40, ctx_max=40)), lens)]
-    ls = Lockstep(w, prompts, max_len=40 + 4 * 16)
+    lens = [20 + (7 * i) % 31 for i in range(n_seqs)]
+    prompts = [p[:n] for p, n in zip(si.make_prompts(replace(w, ctx_min=60, ctx_max=60)), lens)]
+    ls = Lockstep(w, prompts, max_len=60 + 4 * 16)
     ls.prefill()
     ls.g.e.gemm_counts()
     ls.step(plan=[(5 * s) % 16 for s in range(n_seqs)], step_idx=0)
