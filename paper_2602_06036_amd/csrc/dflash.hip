@@ -178,7 +178,7 @@ inline void launch_accept_sampled(hipStream_t st, const float* p_logits, const f
 }
 
 struct Workspace {
-  size_t status, arena, h, a, q, o, act, taps, fuse, ht, logits_d, logits_t, part_o, part_ml, stats_p, stats_q, amax, lsep, rope_t, rope_d, ssq, pf_lens, pf_plens, pf_table, pf_tokens, pf_end_row, pf_end_seq, pf_first, pf_anchor, total;
+  size_t status, arena, h, a, q, o, act, taps, fuse, ht, logits_d, logits_t, part_o, part_ml, stats_p, stats_q, amax, lsep, rope_t, rope_d, ssq, arrive, pf_lens, pf_plens, pf_table, pf_tokens, pf_end_row, pf_end_seq, pf_first, pf_anchor, total;
   size_t moe_sel_e, moe_sel_w, moe_sel_pos, moe_row_of, moe_items, moe_a, moe_act, moe_y;   // routed-expert target only
 };
 Workspace workspace_layout(const dflash_dims& t, const dflash_dims& d, const dflash_runtime& rt, const Knobs& kn) {
@@ -231,6 +231,7 @@ Workspace workspace_layout(const dflash_dims& t, const dflash_dims& d, const dfl
   w.rope_t = take((size_t)M * (t.head_dim / 2) * 8);   // rotary tables of the call's rows (target, draft)
   w.rope_d = take((size_t)M * (d.head_dim / 2) * 8);
   w.ssq = take((size_t)M * (D / 16 + 1) * 4);          // pieces of the rows' sums of squares (deferred RMSNorm, few-row path)
+  w.arrive = take(n_max / 16 * kArriveStride * 4);     // arrival counters of the GEMMs' column blocks (finish.h)
   // dflash_prefill: the prompts' lengths and the pseudo-sequence batch of a pass (see prefill_plan_kernel)
   w.pf_lens = take((size_t)rt.max_seqs * 4);
   w.pf_plens = take((size_t)rt.max_seqs * 4);
@@ -297,8 +298,9 @@ struct dflash_ctx {
   float draft_temperature = 0.f;                       // of the last dflash_draft_block call
   float stats_q_T = 0.f, stats_p_T = 0.f;              // > 0: ws.stats_q / ws.stats_p hold this step's (max, log-sum-exp) rows at that temperature
   // k.fuse, few-row path (one band of rows, dense bf16 model): 1 = the O projection runs unsplit with the residual update in
-  // its epilogue and the RMSNorm that follows deferred into the gate/up GEMM; 2 = the down projection as well (then no
-  // separate normalisation launch is left in a layer); 0 = separate kernels throughout
+  // its epilogue (gemm_resid.h), the down projection split with the update done by the last workgroup of a column block
+  // (finish.h), and the RMSNorms that follow are deferred into the GEMMs that read them; 2 = the down projection unsplit as
+  // well; 0 = separate kernels throughout
   // optional per-launch timing (dflash_profile_*): event pairs around the GEMM and attention launches
   bool prof_on = false;
   std::vector<hipEvent_t> ev;
@@ -378,45 +380,62 @@ struct Engine {
   // Few-row path: ws.a holds x * gain with the division by the row's rms deferred to the GEMM that reads it; the
   // pieces of the rows' sums of squares are in ws.ssq (see gemm_resid.h)
   int cur_layer = 0;     // layer index of the layer() call in progress (routed experts: row of the choice trace)
-  int defer_parts = 0;
-  bool few_rows(const dflash_dims& m, int M, int level = 2) const {
-    return std::is_same<T, bf16_t>::value && c->k.fuse >= level && !m.n_experts && M <= 16 && m.d_model % 16 == 0;
+  int defer_parts = 0;   // > 0: ws.a is such an operand, with that many pieces per row
+  // One band of rows.  (Measured for 17 to 64 rows too, per layer of the 8B shape: at 32 rows the finish costs a projection 3.4 us,
+  // deferring 1.1 in the QKV and 0.8 in the gate/up GEMM, for 5.3 us of a normalisation launch saved: even; at 64 rows 5.5, 2.4 and
+  // 1.0 for 5.8: 2 % of a step slower.)
+  bool few_rows(const dflash_dims& m, int M) const { return std::is_same<T, bf16_t>::value && !m.n_experts && M <= 16 && c->k.fuse > 0; }
+  // the K-split GEMM [M, N] may finish its own sums: the plan is one that the finishing kernel is built for
+  bool finishes(int M, int N, int K) const {
+    return c->k.fuse == 1 && stream_plan(c->k, M, N, K, true, arena_rows(c->rt.max_seqs * c->rt.block_size)).nt >= 4;
   }
-  EpiArgs deferred(EpiArgs ep, const dflash_dims& m) {
+  // deferred operand: the GEMM that reads ws.a scales its rows (the pieces are good for one GEMM: the next finish overwrites them)
+  EpiArgs normed(EpiArgs ep, const dflash_dims& m) {
+    if (!defer_parts) return ep;
     ep.ssq = ws<float>(c->ws.ssq);
     ep.ssq_parts = defer_parts;
     ep.ssq_inv_D = 1.0f / (float)m.d_model;
     ep.ssq_eps = m.rms_eps;
+    defer_parts = 0;
     return ep;
   }
-  // h += A W^T, ws.a = h * gain_next, sums of squares -> ws.ssq, optional tap (gemm_bf16_resid_kernel)
+  // h += A W^T, ws.a = h * gain_next, sums of squares -> ws.ssq, optional tap: unsplit (gemm_bf16_resid_kernel), or K-split and
+  // finished by the last workgroup of a column block
   void resid(const T* W, const T* A, int M, int N, int K, const float* gain_next, int tap);
-  void layer_few_rows(const dflash_dims& m, const char* lbase, const LayerOff& lo, T* pool, int l, const dflash_batch* b, bool causal,
-                      const float* gain_next, int tap) {
-    const int S = b->n_seqs, B = blk(b), M = S * B, D = m.d_model;
-    const int qd = m.n_q_heads * m.head_dim, kd = m.n_kv_heads * m.head_dim, nqkv = qd + 2 * kd;
-    float* arena = ws<float>(c->ws.arena);
-    T* a = ws<T>(c->ws.a);
-    const Slab qs = gemm(reinterpret_cast<const T*>(lbase + lo.wqkv), a, M, nqkv, D, EPI_STORE, deferred(EpiArgs{arena, nqkv, 0, nullptr, 0}, m));
-    qkv_post(m, lbase, lo, pool, l, b, qs);
-    attention(m, pool, l, b, causal);
-    resid(reinterpret_cast<const T*>(lbase + lo.wo), ws<T>(c->ws.o), M, D, qd, reinterpret_cast<const float*>(lbase + lo.g2), -1);
-    gemm(reinterpret_cast<const T*>(lbase + lo.wgu), a, M, 2 * m.d_ffn, D, EPI_SWIGLU, deferred(EpiArgs{nullptr, 0, 0, ws<T>(c->ws.act), m.d_ffn}, m));
-    resid(reinterpret_cast<const T*>(lbase + lo.wd), ws<T>(c->ws.act), M, D, m.d_ffn, gain_next, tap);
+  void resid_split(const T* W, const T* A, int M, int N, int K, const float* gain_next, int tap) {
+    EpiArgs ep{ws<float>(c->ws.arena), N, 0, nullptr, 0};
+    ep.fin.arrive = ws<unsigned>(c->ws.arrive);
+    ep.fin.h = ws<float>(c->ws.h);
+    ep.fin.gain_next = gain_next;
+    ep.fin.a_out = ws<bf16_t>(c->ws.a);
+    ep.fin.ssq = ws<float>(c->ws.ssq);
+    ep.fin.taps = tap >= 0 ? ws<bf16_t>(c->ws.taps) : nullptr;
+    ep.fin.tap_idx = tap;
+    ep.fin.tap_K = c->rt.n_taps * c->t.d_model;
+    gemm(W, A, M, N, K, EPI_FIN_RESID, ep);
+    defer_parts = launched_blocks();
   }
+  static int launched_blocks();   // column blocks of the last GEMM launch
   // workgroups of embed_kernel: one per row, then one thread per entry of the rotary tables (half a head dim each)
   static dim3 embed_grid(int M, int head_dims) { return dim3(M + (M * (head_dims / 2) + 255) / 256); }
-  void qkv_post(const dflash_dims& m, const char* lbase, const LayerOff& lo, T* pool, int l, const dflash_batch* b, const Slab& qs) {
-    const int M = b->n_seqs * blk(b);
-    const int qd = m.n_q_heads * m.head_dim, kd = m.n_kv_heads * m.head_dim, nqkv = qd + 2 * kd;
+  RopeArgs rope_args(const dflash_dims& m, int l) {
+    const int qd = m.n_q_heads * m.head_dim, kd = m.n_kv_heads * m.head_dim;
     RopeArgs ra;
     ra.n_q_heads = m.n_q_heads; ra.n_kv_heads = m.n_kv_heads; ra.head_dim = m.head_dim;
     ra.q_off = 0; ra.k_off = qd; ra.v_off = qd + kd;
     ra.qk_norm = m.qk_norm; ra.eps = m.rms_eps; ra.layer = l;
     ra.rope = ws<float2>(&m == &c->t ? c->ws.rope_t : c->ws.rope_d);
+    return ra;
+  }
+  // QKV projection of the operand in ws.a, q/k norm and rotation, K/V rows into the pool
+  void qkv(const dflash_dims& m, const char* lbase, const LayerOff& lo, T* pool, int l, const dflash_batch* b) {
+    const int M = b->n_seqs * blk(b), D = m.d_model;
+    const int nqkv = (m.n_q_heads + 2 * m.n_kv_heads) * m.head_dim;
+    const Slab qs = gemm(reinterpret_cast<const T*>(lbase + lo.wqkv), ws<T>(c->ws.a), M, nqkv, D, EPI_STORE,
+                         normed(EpiArgs{ws<float>(c->ws.arena), nqkv, 0, nullptr, 0}, m));
     hipLaunchKernelGGL(qkv_post_kernel<T>, dim3(M, (m.n_q_heads + 2 * m.n_kv_heads + 3) / 4), dim3(256), 0, st, qs.p, nqkv,
-                       reinterpret_cast<const float*>(lbase + lo.qn), reinterpret_cast<const float*>(lbase + lo.kn), ws<T>(c->ws.q), pool,
-                       geom(b), ra, qs.ks, qs.stride);
+                       reinterpret_cast<const float*>(lbase + lo.qn), reinterpret_cast<const float*>(lbase + lo.kn), ws<T>(c->ws.q), pool, geom(b),
+                       rope_args(m, l), qs.ks, qs.stride);
     check();
   }
 
@@ -463,36 +482,36 @@ struct Engine {
 
   void attention(const dflash_dims& m, const T* pool, int layer, const dflash_batch* b, bool causal);
 
-  // one Transformer layer on the M block rows held in ws.h
-  void layer(const dflash_dims& m, const char* lbase, const LayerOff& lo, T* pool, int l, const dflash_batch* b, bool causal) {
+  // one Transformer layer on the M block rows held in ws.h.  gain_next (nullable): gain of the RMSNorm behind the layer, which may
+  // then be deferred; tap: index under which the layer's output is tapped, or -1
+  void layer(const dflash_dims& m, const char* lbase, const LayerOff& lo, T* pool, int l, const dflash_batch* b, bool causal,
+             const float* gain_next, int tap) {
     const int S = b->n_seqs, B = blk(b), M = S * B, D = m.d_model;
-    const int qd = m.n_q_heads * m.head_dim, kd = m.n_kv_heads * m.head_dim, nqkv = qd + 2 * kd;
+    const int qd = m.n_q_heads * m.head_dim;
     float* h = ws<float>(c->ws.h);
-    float* arena = ws<float>(c->ws.arena);
     T* a = ws<T>(c->ws.a);
     T* o = ws<T>(c->ws.o);
     T* act = ws<T>(c->ws.act);
-    norm_h(reinterpret_cast<const float*>(lbase + lo.g1), M, D, m.rms_eps);
-    const Slab qs = gemm(reinterpret_cast<const T*>(lbase + lo.wqkv), a, M, nqkv, D, EPI_STORE, EpiArgs{arena, nqkv, 0, nullptr, 0});
-    qkv_post(m, lbase, lo, pool, l, b, qs);
+    const T* wo = reinterpret_cast<const T*>(lbase + lo.wo);
+    const T* wd = reinterpret_cast<const T*>(lbase + lo.wd);
+    const float* g2 = reinterpret_cast<const float*>(lbase + lo.g2);
+    if (!defer_parts) norm_h(reinterpret_cast<const float*>(lbase + lo.g1), M, D, m.rms_eps);
+    qkv(m, lbase, lo, pool, l, b);
     attention(m, pool, l, b, causal);
-    if (few_rows(m, M, 1)) {
-      // one band of rows: unsplit O projection with the residual update in its epilogue, the second RMSNorm deferred
-      // into the gate/up GEMM (gemm_resid.h); the down projection keeps its K split and the normalisation kernel
-      resid(reinterpret_cast<const T*>(lbase + lo.wo), o, M, D, qd, reinterpret_cast<const float*>(lbase + lo.g2), -1);
-      gemm(reinterpret_cast<const T*>(lbase + lo.wgu), a, M, 2 * m.d_ffn, D, EPI_SWIGLU, deferred(EpiArgs{nullptr, 0, 0, act, m.d_ffn}, m));
-      pending = gemm(reinterpret_cast<const T*>(lbase + lo.wd), act, M, D, m.d_ffn, EPI_RESID, EpiArgs{h, D, 0, nullptr, 0});
-      return;
-    }
-    pending = gemm(reinterpret_cast<const T*>(lbase + lo.wo), o, M, D, qd, EPI_RESID, EpiArgs{h, D, 0, nullptr, 0});
-    norm_h(reinterpret_cast<const float*>(lbase + lo.g2), M, D, m.rms_eps);
+    const bool few = few_rows(m, M);
+    if (few) resid(wo, o, M, D, qd, g2, -1);
+    else pending = gemm(wo, o, M, D, qd, EPI_RESID, EpiArgs{h, D, 0, nullptr, 0});
+    if (!defer_parts) norm_h(g2, M, D, m.rms_eps);
     if (m.n_experts) {
       cur_layer = l;
       pending = moe_ffn(m, lbase, lo, M);
-      return;
+    } else {
+      gemm(reinterpret_cast<const T*>(lbase + lo.wgu), a, M, 2 * m.d_ffn, D, EPI_SWIGLU, normed(EpiArgs{nullptr, 0, 0, act, m.d_ffn}, m));
+      if (few && gain_next && c->k.fuse == 2) return resid(wd, act, M, D, m.d_ffn, gain_next, tap);
+      if (few && gain_next && finishes(M, D, m.d_ffn)) return resid_split(wd, act, M, D, m.d_ffn, gain_next, tap);
+      pending = gemm(wd, act, M, D, m.d_ffn, EPI_RESID, EpiArgs{h, D, 0, nullptr, 0});
     }
-    gemm(reinterpret_cast<const T*>(lbase + lo.wgu), a, M, 2 * m.d_ffn, D, EPI_SWIGLU, EpiArgs{nullptr, 0, 0, act, m.d_ffn});
-    pending = gemm(reinterpret_cast<const T*>(lbase + lo.wd), act, M, D, m.d_ffn, EPI_RESID, EpiArgs{h, D, 0, nullptr, 0});
+    pending_tap = tap;   // taken by the next RMSNorm
   }
 
   // Routed-expert FFN on the normalised rows in ws.a: router GEMM -> top-k routing into an expert-sorted row list ->
@@ -523,19 +542,13 @@ struct Engine {
   // amax_parts > 0 and, unless want_logits, the [M, V] logits are never written); argmax() finishes the job
   // stats_T > 0: the epilogue also leaves the softmax statistics of logits / stats_T, combined into stats_out; returns
   // whether that happened (kernels without the fused epilogue leave it to lse_partial_kernel)
-  // few: the final norm is already deferred into ws.a / ws.ssq by the last layer's down projection
   // logits_to (nullable): the caller's buffer (see stores_to), written by the same epilogue
   bool lm_head(const float* final_gain, float eps, int M, float* logits, bool want_logits, int B, int mode, float inv_T,
-               const uint64_t* key, float stats_T = 0.f, float2* stats_out = nullptr, bool few = false, float* logits_to = nullptr) {
+               const uint64_t* key, float stats_T = 0.f, float2* stats_out = nullptr, float* logits_to = nullptr) {
     const dflash_dims& t = c->t;
     EpiArgs ep{logits, t.vocab, 0, nullptr, 0};
     ep.out2 = logits_to;
-    if (few) {
-      ep = deferred(ep, t);
-      ep.ssq_eps = eps;
-    } else {
-      norm_h(final_gain, M, t.d_model, eps);
-    }
+    norm_h(final_gain, M, t.d_model, eps);
     ep.amax = ws<float2>(c->ws.amax);
     ep.amax_mode = mode;
     ep.amax_inv_T = inv_T;
@@ -577,13 +590,8 @@ struct Engine {
     check();
     for (int i = 0; i < d.n_layers; ++i) {
       const char* lb = l0 + c->dl.lo.end * i;
-      if (few) {
-        const float* gn = i + 1 < d.n_layers ? reinterpret_cast<const float*>(lb + c->dl.lo.end + c->dl.lo.g1)
-                                             : reinterpret_cast<const float*>(c->dblob + c->dl.gf);
-        layer_few_rows(d, lb, c->dl.lo, reinterpret_cast<T*>(c->rt.draft_kv_pool), i, b, false, gn, -1);
-      } else {
-        layer(d, lb, c->dl.lo, reinterpret_cast<T*>(c->rt.draft_kv_pool), i, b, false);
-      }
+      const float* gn = i + 1 < d.n_layers ? reinterpret_cast<const float*>(lb + c->dl.lo.end + c->dl.lo.g1) : nullptr;
+      layer(d, lb, c->dl.lo, reinterpret_cast<T*>(c->rt.draft_kv_pool), i, b, false, gn, -1);
     }
     float* logits = ws<float>(c->ws.logits_d);
     const int mode = temperature > 0.f ? 1 : 0;
@@ -591,7 +599,7 @@ struct Engine {
     const bool want_logits = logits_out || mode;        // sampling: dflash_accept needs the proposal distribution
     float* logits_to = stores_to(logits_out) ? logits_out : nullptr;
     const bool st_q = lm_head(reinterpret_cast<const float*>(c->dblob + c->dl.gf), d.rms_eps, M, logits, want_logits, B, mode, inv_T, rng_key,
-                              mode ? temperature : 0.f, ws<float2>(c->ws.stats_q), few, logits_to);
+                              mode ? temperature : 0.f, ws<float2>(c->ws.stats_q), logits_to);
     c->stats_q_T = st_q ? temperature : 0.f;
     c->have_logits_d = want_logits || amax_parts == 0;
     c->draft_temperature = temperature;
@@ -622,14 +630,8 @@ struct Engine {
     for (int l = 0; l < t.n_layers; ++l) {
       const char* lb = l0 + c->tl.lo.end * l;
       const bool tapped = tap < c->rt.n_taps && c->rt.tap_layers[tap] == l;
-      if (few) {
-        const float* gn = l + 1 < t.n_layers ? reinterpret_cast<const float*>(lb + c->tl.lo.end + c->tl.lo.g1)
-                                             : reinterpret_cast<const float*>(c->tblob + c->tl.gf);
-        layer_few_rows(t, lb, c->tl.lo, reinterpret_cast<T*>(c->rt.target_kv_pool), l, b, true, gn, tapped ? tap : -1);
-      } else {
-        layer(t, lb, c->tl.lo, reinterpret_cast<T*>(c->rt.target_kv_pool), l, b, true);
-        if (tapped) pending_tap = tap;   // taken by the next RMSNorm
-      }
+      const float* gn = l + 1 < t.n_layers ? reinterpret_cast<const float*>(lb + c->tl.lo.end + c->tl.lo.g1) : nullptr;
+      layer(t, lb, c->tl.lo, reinterpret_cast<T*>(c->rt.target_kv_pool), l, b, true, gn, tapped ? tap : -1);
       if (tapped) ++tap;
     }
     float* logits = ws<float>(c->ws.logits_t);
@@ -646,7 +648,7 @@ struct Engine {
     float* logits_to = stores_to(logits_out) ? logits_out : nullptr;
     const float sT = c->draft_temperature > 0.f ? c->draft_temperature : 0.f;
     const bool st_p = lm_head(reinterpret_cast<const float*>(c->tblob + c->tl.gf), t.rms_eps, M, logits, want_logits, B, 0, 1.0f, nullptr, sT,
-                              ws<float2>(c->ws.stats_p), few, logits_to);
+                              ws<float2>(c->ws.stats_p), logits_to);
     c->stats_p_T = st_p ? sT : 0.f;
     c->have_logits_t = want_logits || amax_parts == 0;
     if (tgt_argmax) argmax(logits, t.vocab, M, B, tgt_argmax, 0, 0, 1.0f, (const uint64_t*)nullptr);
@@ -763,8 +765,12 @@ struct Engine {
       check();
       int tap = 0;
       for (int l = 0; l < t.n_layers; ++l) {
-        layer(t, c->tblob + c->tl.layer0 + c->tl.lo.end * l, c->tl.lo, reinterpret_cast<T*>(c->rt.target_kv_pool), l, &pb, true);
-        if (tap < c->rt.n_taps && c->rt.tap_layers[tap] == l) pending_tap = tap++;
+        const char* lb = c->tblob + c->tl.layer0 + c->tl.lo.end * l;
+        const bool tapped = tap < c->rt.n_taps && c->rt.tap_layers[tap] == l;
+        // the last layer's output is normalised in full: the LM head reads a selection of its rows
+        layer(t, lb, c->tl.lo, reinterpret_cast<T*>(c->rt.target_kv_pool), l, &pb, true,
+              l + 1 < t.n_layers ? reinterpret_cast<const float*>(lb + c->tl.lo.end + c->tl.lo.g1) : nullptr, tapped ? tap : -1);
+        if (tapped) ++tap;
       }
       if (n_end > 0 || pending_tap >= 0) norm_h(reinterpret_cast<const float*>(c->tblob + c->tl.gf), M, t.d_model, t.rms_eps);
       pending = Slab{};
@@ -798,6 +804,8 @@ struct Engine {
 // ---- GEMM dispatch ----------------------------------------------------------------------------------
 
 thread_local int g_launch_parts = 0;   // column blocks of the last bf16 GEMM launch (= fused-argmax partials per row)
+template <typename T>
+int Engine<T>::launched_blocks() { return g_launch_parts; }
 thread_local int g_launch_kind = 0;    // kernel family of that launch (DFLASH_GEMM_* of dflash_gemm_counts)
 
 template <int NT, int MT, int U>
@@ -807,6 +815,8 @@ void launch_bf16(hipStream_t st, const bf16_t* W, const bf16_t* A, int M, int N,
   g_launch_kind = DFLASH_GEMM_STREAMING;
   if (epi == EPI_SWIGLU) {
     if constexpr (NT >= 2) hipLaunchKernelGGL((gemm_bf16_kernel<NT, MT, U, EPI_SWIGLU>), grid, block, 0, st, W, A, M, N, K, ep);
+  } else if (epi == EPI_FIN_RESID) {
+    if constexpr (NT >= 4 && MT == 1) hipLaunchKernelGGL((gemm_bf16_kernel<NT, MT, U, EPI_FIN_RESID>), grid, block, 0, st, W, A, M, N, K, ep);
   } else {
     hipLaunchKernelGGL((gemm_bf16_kernel<NT, MT, U, EPI_STORE>), grid, block, 0, st, W, A, M, N, K, ep);
   }
@@ -828,7 +838,7 @@ inline int gemm_class(int epi, int N, int vocab) { return (epi == EPI_STORE && N
 
 template <>
 Engine<bf16_t>::Slab Engine<bf16_t>::gemm(const bf16_t* W, const bf16_t* A, int M, int N, int K, int epi, EpiArgs ep, bool allow_split) {
-  ProfScope prof(c, st, gemm_class(epi, N, c->t.vocab), (double)N * K * 2);
+  ProfScope prof(c, st, epi == EPI_FIN_RESID ? EPI_RESID : gemm_class(epi, N, c->t.vocab), (double)N * K * 2);
   const int nt = N / 16, KT = K / 32;
   int kepi = epi;
   if (epi == EPI_RESID) {   // partial slabs into the arena; the next RMSNorm adds them to the residual stream
@@ -887,7 +897,7 @@ Engine<bf16_t>::Slab Engine<bf16_t>::gemm(const bf16_t* W, const bf16_t* A, int 
   ++c->gemm_counts[g_launch_kind];
   if (ep.amax) amax_parts = g_launch_parts;
   if (ep.lse) lse_parts = g_launch_parts;
-  if (epi == EPI_SWIGLU) return Slab{};
+  if (epi == EPI_SWIGLU || epi == EPI_FIN_RESID) return Slab{};
   return Slab{ep.out, ks, ep.slab};
 }
 
@@ -1294,9 +1304,9 @@ int dflash_create(const dflash_dims* target, const void* target_blob, const dfla
   c->tblob = (const char*)target_blob; c->dblob = (const char*)draft_blob; c->wsp = (char*)rt->workspace;
   c->err[0] = 0;
   c->k = knobs;
-  if (hipMemset(c->wsp + ws.status, 0, 256) != hipSuccess) {
+  if (hipMemset(c->wsp + ws.status, 0, 256) != hipSuccess || hipMemset(c->wsp + ws.arrive, 0, align256(ws.pf_lens - ws.arrive)) != hipSuccess) {
     delete c;
-    return fail(nullptr, DFLASH_EHIP, "create: cannot clear the device status word");
+    return fail(nullptr, DFLASH_EHIP, "create: cannot clear the device status word and the arrival counters");
   }
   *out = c;
   return DFLASH_OK;

@@ -6,8 +6,10 @@
 #include <type_traits>
 
 #include "common.h"
+#include "finish.h"
 
-enum { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2 };
+// FIN_RESID: the last workgroup of a column block finishes the sum (finish.h)
+enum { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_FIN_RESID = 3 };
 
 struct EpiArgs {
   float* out;   // STORE: out[z*slab + m*ld + n] = partial y of K range z ; RESID (fp32 kernel): out[m*ld + n] += y
@@ -46,6 +48,7 @@ struct EpiArgs {
   // STORE with a single K range, LM head only: the result goes here as well (the caller's logits beside the workspace's; a
   // copy afterwards read them all again: 4 to 10 us a call)
   float* out2 = nullptr;
+  FinishArgs fin = {};   // FIN_RESID (streaming kernel; out: the slabs)
 };
 
 // score of logit y at (row m, column col) for the fused argmax
@@ -180,35 +183,37 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16_t* __restr
     }
   };
 
-  // Deferred RMSNorm: 1 / rms of this workgroup's rows, 16 threads per row, each adding every 16th piece in
-  // ascending order, then the 16 partial sums by a fixed shuffle tree.  Written to LDS here, read after the
-  // barrier of the cross-wavefront sum.
-  __shared__ float s_rstd[MT * 16];
-  if (ep.ssq && threadIdx.x < 256) {
+  // Deferred RMSNorm: 1 / rms of this workgroup's rows, 16 threads per row.  The pieces of the sums of squares are requested
+  // here and added behind the sweep (16 threads a row, each every 16th group of four in ascending order, then a fixed shuffle
+  // tree); s_rstd is read after the barrier of the cross-wavefront sum.
+  __shared__ float s_rstd[16];
+  constexpr int SQ = 4;                       // groups of four that a thread keeps in registers over the sweep
+  const bool deferred = MT == 1 && ep.ssq;    // one band of rows only
+  const bool sq_few = (ep.ssq_parts & 3) == 0 && ep.ssq_parts <= 64 * SQ;
+  float4 sq[SQ];
+  if (deferred && sq_few) {
     const int r = threadIdx.x >> 4, c = threadIdx.x & 15;
 #pragma unroll
-    for (int j = 0; j < MT; ++j) {
-      const int m = min((mt0 + j) * 16 + r, M - 1);
-      const float* pp = ep.ssq + (size_t)m * ep.ssq_parts;
-      float t = 0.f;
-      if ((ep.ssq_parts & 3) == 0 && ep.ssq_parts <= 512) {
-        // all requests of the thread go out together (up to 8 pieces of 4 values, 64 values apart)
-        float4 v[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const int p = (c + 16 * i) * 4;
-          v[i] = p < ep.ssq_parts ? *reinterpret_cast<const float4*>(pp + p) : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) t += (v[i].x + v[i].y) + (v[i].z + v[i].w);
-      } else {
-        for (int p = c; p < ep.ssq_parts; p += 16) t += pp[p];
-      }
-#pragma unroll
-      for (int o = 1; o < 16; o <<= 1) t += __shfl_xor(t, o, 64);
-      if (c == 0) s_rstd[j * 16 + r] = 1.0f / sqrtf(t * ep.ssq_inv_D + ep.ssq_eps);
+    for (int i = 0; i < SQ; ++i) {
+      const int p = (c + 16 * i) * 4;
+      sq[i] = *reinterpret_cast<const float4*>(ep.ssq + (size_t)min(mt0 * 16 + r, M - 1) * ep.ssq_parts + min(p, ep.ssq_parts - 4));
+      if (p >= ep.ssq_parts) sq[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
   }
+  auto rstd_of_rows = [&]() {
+    const int r = threadIdx.x >> 4, c = threadIdx.x & 15;
+    float t = 0.f;
+    if (sq_few) {
+#pragma unroll
+      for (int i = 0; i < SQ; ++i) t += (sq[i].x + sq[i].y) + (sq[i].z + sq[i].w);
+    } else {
+      const float* pp = ep.ssq + (size_t)min(mt0 * 16 + r, M - 1) * ep.ssq_parts;
+      for (int p = c; p < ep.ssq_parts; p += 16) t += pp[p];
+    }
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) t += __shfl_xor(t, o, 64);
+    if (c == 0) s_rstd[r] = 1.0f / sqrtf(t * ep.ssq_inv_D + ep.ssq_eps);
+  };
 
   // Two register buffers, one being multiplied while the other is on its way.  No load inside the loop is
   // conditional: a load that is skipped on some path would make the number of loads in flight unknown at compile
@@ -230,6 +235,8 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16_t* __restr
     compute(b1);
   }
 
+  if (deferred) rstd_of_rows();
+
   // The wavefronts' partial sums meet in LDS.
   __shared__ float4 red[NW][NT * MT][64];
   const int mrow = lane & 15, g = lane >> 4;
@@ -242,8 +249,8 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16_t* __restr
       const float4 a = red[w][t][lane];
       s.x += a.x; s.y += a.y; s.z += a.z; s.w += a.w;
     }
-    if (ep.ssq) {
-      const float rs = s_rstd[(t % MT) * 16 + mrow];
+    if (deferred) {
+      const float rs = s_rstd[mrow];
       s.x *= rs; s.y *= rs; s.z *= rs; s.w *= rs;
     }
     return s;
@@ -253,7 +260,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16_t* __restr
 #pragma unroll
     for (int j = 0; j < MT; ++j) red[wave][i * MT + j][lane] = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
   __syncthreads();
-  if (EPI == EPI_SWIGLU) {
+  if constexpr (EPI == EPI_SWIGLU) {
     bf16_t* act = reinterpret_cast<bf16_t*>(ep.act);
     for (int t = wave; t < (NT / 2) * MT; t += NW) {
       const int p = t / MT, j = t % MT;
@@ -265,6 +272,14 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16_t* __restr
                             make_float4(silu_f(gs.x) * us.x, silu_f(gs.y) * us.y, silu_f(gs.z) * us.z, silu_f(gs.w) * us.w));
       }
     }
+  } else if constexpr (EPI == EPI_FIN_RESID) {
+    const __amdgpu_buffer_rsrc_t out = coherent_base(ep.out);
+    for (int t = wave; t < NT; t += NW) {
+      const float4 s = tile_sum(t);
+      if (mrow < M) store_coherent(out, (unsigned)((size_t)kz * ep.slab + (size_t)mrow * ep.ld + (nt0 + t) * 16 + 4 * g) * 4u, s);
+    }
+    if (!last_to_arrive(ep.fin.arrive + blockIdx.x * kArriveStride, gridDim.z)) return;
+    finish_resid<NT>(ep.fin, ep.out, ep.ld, ep.slab, (int)gridDim.z, M, (int)blockIdx.x, (int)gridDim.x, reinterpret_cast<float*>(&red[0][0][0]));
   } else if (ep.out) {
     for (int t = wave; t < NT * MT; t += NW) {
       const int i = t / MT, j = t % MT;
@@ -278,7 +293,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16_t* __restr
     }
   }
 
-  if constexpr (EPI != EPI_SWIGLU) {
+  if constexpr (EPI == EPI_STORE) {
     if (ep.amax) {   // fused argmax over this workgroup's NT*16 columns (host guarantees a single K range)
       __shared__ float2 wbest[NW][MT * 16];
       const uint64_t key = ep.amax_mode ? ep.amax_key[0] : 0ull;

@@ -180,6 +180,33 @@ def test_forced_tiles_over_ragged_sizes(n_seqs, ffn, vocab, wide, tile, wm, ks, 
     assert counts[wide] > 0 and counts[3 - wide] == 0 and counts[0] == 0
 
 
+@pytest.mark.parametrize("d,heads,kv_heads,ffn,n_seqs,block,fill", [
+    (256, 4, 2, 64, 1, 16, 1),       # one K range: every workgroup is the last one
+    (192, 3, 1, 576, 3, 5, 1),       # three column blocks of two ranges: a block's workgroups on different XCDs
+    (320, 5, 1, 1056, 2, 7, 1),      # five blocks, an uneven last range
+    (576, 9, 3, 4096, 1, 10, 1),     # sixteen ranges
+    (1152, 18, 2, 1024, 8, 2, 1),    # eighteen blocks
+    (256, 4, 2, 1024, 1, 2, 2),      # eight weight tiles a wavefront
+    (1536, 24, 4, 4160, 1, 16, 1),   # six
+    (160, 5, 5, 512, 2, 8, 1),       # ten row bands: two weight tiles, which the finishing kernel is not built for
+])
+def test_residual_update_by_the_last_workgroup(d, heads, kv_heads, ffn, n_seqs, block, fill, monkeypatch):
+    """The down projection of up to 16 rows, whose K ranges are summed by the last workgroup of a column block, over the numbers of
+    ranges, column blocks and weight tiles that its plan can have; an inner and the last layer are tapped.  Several steps on one
+    context, so that every launch has to leave its arrival counters at zero."""
+    monkeypatch.setenv("DFLASH_GEMM_FILL", str(fill))
+    w = tiny_workload(seed=d + ffn, n_layers=3, draft_layers=2, vocab=512, block=block, qk_norm=True, kv_heads=kv_heads, dtype="bf16",
+                      n_seqs=n_seqs, taps=(1, 2), d=d, heads=heads, hd=d // heads, ffn=ffn)
+    prompts = [p[:11 + 5 * i] for i, p in enumerate(si.make_prompts(replace(w, ctx_min=64, ctx_max=64)))]
+    ls = Lockstep(w, prompts, max_len=64 + 5 * 16)
+    ls.prefill()
+    for i, plan in enumerate((None, [(3 * s + 1) % block for s in range(n_seqs)], None)):
+        ls.step(plan=plan, step_idx=i)
+    ls.check_cache([0, 2], [0, 1])
+    assert ls.stats["low_margin_flips"] <= 0.02 * ls.stats["rows"] + 2
+    assert ls.stats["reseeds"] <= 1
+
+
 @pytest.mark.parametrize("vocab,rows,tiles", STREAM_HEADS)
 def test_streaming_heads_with_eight_six_and_four_weight_tiles(vocab, rows, tiles):
     """LM heads of 16, 32 and 48 rows, high enough for the weight tiles per wavefront that a whole vocabulary takes, with their argmax,
