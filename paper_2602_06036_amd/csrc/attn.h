@@ -16,6 +16,7 @@ struct AttnArgs {
   float scale;   // 1/sqrt(head_dim)
   int q_shift = 0;   // MFMA kernels: the query heads of one kv head are shared out over 2^q_shift workgroups (a workgroup
                      // holds at most 64 query rows = block_size * heads; 8 heads per kv head at block size 16 need two)
+  void* out = nullptr;   // MFMA kernels, n_splits == 1: the finished rows go here (GEMM operand, row length Hq*hd), no merge follows
 };
 
 // partial results: for pr = (m*Hq + hq)*n_splits + split : ml[pr] = (running max, sum exp), o[pr*hd + d]

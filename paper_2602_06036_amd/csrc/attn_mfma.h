@@ -210,12 +210,19 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(const bf16_t* __restr
   float l = l_run;
   l += __shfl_xor(l, 16, 64);
   l += __shfl_xor(l, 32, 64);
-  if (valid) {
-    if (g == 0) part_ml[pr] = make_float2(m_run, l);
+  if (!valid) return;
+  if (aa.out) {   // the only split: nothing to merge
+    const float L1 = l > 0.f ? l : INFINITY;   // no visible key: a row of zeros
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
-      *reinterpret_cast<float4*>(part_o + pr * HD + dt * 16 + 4 * g) = make_float4(acc[dt][0], acc[dt][1], acc[dt][2], acc[dt][3]);
+      Act<bf16_t>::store4(reinterpret_cast<bf16_t*>(aa.out), s * B + slot, hq * HD + dt * 16 + 4 * g, aa.n_q_heads * HD,
+                          make_float4(acc[dt][0] / L1, acc[dt][1] / L1, acc[dt][2] / L1, acc[dt][3] / L1));
+    return;
   }
+  if (g == 0) part_ml[pr] = make_float2(m_run, l);
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+    *reinterpret_cast<float4*>(part_o + pr * HD + dt * 16 + 4 * g) = make_float4(acc[dt][0], acc[dt][1], acc[dt][2], acc[dt][3]);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -526,7 +533,53 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_wide_kernel(const bf16_t* __
         *p = make_float4(acc[rb][dt][0] * mine[rb] + u.x, acc[rb][dt][1] * mine[rb] + u.y, acc[rb][dt][2] * mine[rb] + u.z, acc[rb][dt][3] * mine[rb] + u.w);
       }
   }
+  __shared__ float s_L[RB * 16];
+  if (aa.out && (int)threadIdx.x < RB * 16) {
+    float m_all = -INFINITY, l = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) m_all = fmaxf(m_all, s_ml[w][threadIdx.x].x);
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float2 ml = s_ml[w][threadIdx.x];
+      l += (ml.x == -INFINITY) ? 0.f : ml.y * exp2f(ml.x - m_all);
+    }
+    s_L[threadIdx.x] = l > 0.f ? l : INFINITY;   // no visible key: a row of zeros
+  }
   __syncthreads();
+  if (aa.out) {
+    // The only split: the rows leave as GEMM operand, eight dims (16 bytes of either plane) a thread, the block's rows after each
+    // other, so that a block of 16 rows writes whole operand tiles.  The launch takes as long as with partial rows for a merge
+    // (2048 prefill rows 121 us against 123, 32 sequences of 8192 tokens 179), and the merge is gone: 22 and 7.7 us.
+    for (int idx = threadIdx.x; idx < B * group * (HD / 8); idx += 64 * NW) {
+      const int slot = idx % B, c8 = (idx / B) % (HD / 8), h = idx / (B * (HD / 8));
+      const int r = slot * group + h;
+      float4 o[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        o[i] = *reinterpret_cast<const float4*>(&s_o[0][r][c8 * 8 + 4 * i]);
+#pragma unroll
+        for (int w = 1; w < 4; ++w) {
+          const float4 a = *reinterpret_cast<const float4*>(&s_o[w][r][c8 * 8 + 4 * i]);
+          o[i].x += a.x; o[i].y += a.y; o[i].z += a.z; o[i].w += a.w;
+        }
+      }
+      const float L1 = s_L[r];
+      const float x[8] = {o[0].x / L1, o[0].y / L1, o[0].z / L1, o[0].w / L1, o[1].x / L1, o[1].y / L1, o[1].z / L1, o[1].w / L1};
+      u32x4 hi, lo;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        bf16_t h0, l0, h1, l1;
+        Act<bf16_t>::split(x[2 * i], h0, l0);
+        Act<bf16_t>::split(x[2 * i + 1], h1, l1);
+        hi[i] = (uint32_t)h0 | ((uint32_t)h1 << 16);
+        lo[i] = (uint32_t)l0 | ((uint32_t)l1 << 16);
+      }
+      bf16_t* to = reinterpret_cast<bf16_t*>(aa.out) + Act<bf16_t>::index(s * B + slot, (kvh * group + h) * HD + c8 * 8, aa.n_q_heads * HD);
+      *reinterpret_cast<u32x4*>(to) = hi;
+      *reinterpret_cast<u32x4*>(to + 512) = lo;
+    }
+    return;
+  }
   for (int idx = threadIdx.x; idx < RB * 16 * (HD / 4); idx += 64 * NW) {
     const int r = idx / (HD / 4), d4 = idx % (HD / 4);
     if (r >= rows) continue;
@@ -554,6 +607,13 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_wide_kernel(const bf16_t* __
   }
 }
 
+// whether the kernels above take this configuration
+template <typename T>
+inline bool attn_takes_mfma(const AttnArgs& aa, int block_size) {
+  const int group = aa.n_q_heads / aa.n_kv_heads;
+  return sizeof(T) == 2 && ((block_size * group) >> aa.q_shift) <= 64 && group % (1 << aa.q_shift) == 0 && (aa.head_dim == 128 || aa.head_dim == 64);
+}
+
 // Returns true when it launched a kernel for this configuration; false -> caller uses the generic kernel.
 template <typename T>
 inline bool attn_mfma_launch(hipStream_t, const T*, const T*, SeqGeom, AttnArgs, int, float*, float2*, int) {
@@ -563,8 +623,7 @@ inline bool attn_mfma_launch(hipStream_t, const T*, const T*, SeqGeom, AttnArgs,
 template <>
 inline bool attn_mfma_launch<bf16_t>(hipStream_t st, const bf16_t* q, const bf16_t* pool, SeqGeom geo, AttnArgs aa, int S,
                                      float* part_o, float2* part_ml, int wide_min_chunk) {
-  const int rows = (geo.block_size * (aa.n_q_heads / aa.n_kv_heads)) >> aa.q_shift;
-  if (rows > 64 || (aa.n_q_heads / aa.n_kv_heads) % (1 << aa.q_shift) || (aa.head_dim != 128 && aa.head_dim != 64)) return false;
+  if (!attn_takes_mfma<bf16_t>(aa, geo.block_size)) return false;
   const dim3 grid(aa.n_splits, aa.n_kv_heads, S << aa.q_shift), block(256);
   // long chunks: wavefronts split the keys
   if (aa.head_dim == 128 && aa.chunk >= wide_min_chunk)

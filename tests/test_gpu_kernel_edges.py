@@ -180,6 +180,32 @@ def test_forced_tiles_over_ragged_sizes(n_seqs, ffn, vocab, wide, tile, wm, ks, 
     assert counts[wide] > 0 and counts[3 - wide] == 0 and counts[0] == 0
 
 
+@pytest.mark.parametrize("hd,heads,kv_heads,n_seqs,block,wide_from", [
+    (128, 4, 2, 3, 16, 64),        # key-split kernel
+    (128, 8, 2, 2, 7, 64),         # ... with a block that is no whole band: two sequences' rows in one operand tile
+    (128, 8, 1, 2, 16, 64),        # ... with two workgroups a kv head
+    (128, 4, 4, 17, 2, 100000),    # row-split kernel, 34 rows
+    (64, 8, 2, 3, 16, 100000),
+    (64, 8, 1, 2, 11, 100000),     # ... two workgroups a kv head
+])
+def test_attention_of_one_split_writes_the_operand(hd, heads, kv_heads, n_seqs, block, wide_from, monkeypatch):
+    """One context split a sequence (many sequences, or short ones): the attention kernels divide by the row sums and write the O
+    projection's operand themselves, causal and not.  Ragged contexts around a page and a pair of pages."""
+    monkeypatch.setenv("DFLASH_ATTN_TARGET_WGS", "1")
+    monkeypatch.setenv("DFLASH_ATTN_WIDE_MIN_CHUNK", str(wide_from))
+    w = tiny_workload(seed=hd + heads, n_layers=2, draft_layers=2, vocab=512, block=block, qk_norm=True, kv_heads=kv_heads, dtype="bf16",
+                      n_seqs=n_seqs, taps=(0, 1), d=256, heads=heads, hd=hd, ffn=512)
+    lens = [(13, 64, 33, 150, 16, 31, 96)[i % 7] for i in range(n_seqs)]
+    prompts = [p[:n] for p, n in zip(si.make_prompts(replace(w, ctx_min=150, ctx_max=150)), lens)]
+    ls = Lockstep(w, prompts, max_len=150 + 5 * 16)
+    ls.prefill()
+    for i, plan in enumerate((None, [(3 * s + 1) % block for s in range(n_seqs)], None)):
+        ls.step(plan=plan, step_idx=i)
+    ls.check_cache([0, 1], [0, 1])
+    assert ls.stats["low_margin_flips"] <= 0.02 * ls.stats["rows"] + 2
+    assert ls.stats["reseeds"] <= 1
+
+
 @pytest.mark.parametrize("d,heads,kv_heads,ffn,n_seqs,block,fill", [
     (256, 4, 2, 64, 1, 16, 1),       # one K range: every workgroup is the last one
     (192, 3, 1, 576, 3, 5, 1),       # three column blocks of two ranges: a block's workgroups on different XCDs
