@@ -427,12 +427,13 @@ struct Engine {
     ra.rope = ws<float2>(&m == &c->t ? c->ws.rope_t : c->ws.rope_d);
     return ra;
   }
-  // QKV projection of the operand in ws.a, q/k norm and rotation, K/V rows into the pool
+  // first norm, QKV projection, q/k norm and rotation, K/V rows into the pool
   void qkv(const dflash_dims& m, const char* lbase, const LayerOff& lo, T* pool, int l, const dflash_batch* b) {
     const int M = b->n_seqs * blk(b), D = m.d_model;
     const int nqkv = (m.n_q_heads + 2 * m.n_kv_heads) * m.head_dim;
-    const Slab qs = gemm(reinterpret_cast<const T*>(lbase + lo.wqkv), ws<T>(c->ws.a), M, nqkv, D, EPI_STORE,
-                         normed(EpiArgs{ws<float>(c->ws.arena), nqkv, 0, nullptr, 0}, m));
+    EpiArgs ep{ws<float>(c->ws.arena), nqkv, 0, nullptr, 0};
+    const T* a = operand(reinterpret_cast<const float*>(lbase + lo.g1), m.rms_eps, M, D, ep, m);
+    const Slab qs = gemm(reinterpret_cast<const T*>(lbase + lo.wqkv), a, M, nqkv, D, EPI_STORE, ep);
     hipLaunchKernelGGL(qkv_post_kernel<T>, dim3(M, (m.n_q_heads + 2 * m.n_kv_heads + 3) / 4), dim3(256), 0, st, qs.p, nqkv,
                        reinterpret_cast<const float*>(lbase + lo.qn), reinterpret_cast<const float*>(lbase + lo.kn), ws<T>(c->ws.q), pool, geom(b),
                        rope_args(m, l), qs.ks, qs.stride);
@@ -459,18 +460,33 @@ struct Engine {
                          eps, taps, tap, tap_K, RowMix{});
     check();
   }
-  // row-wise argmax (or Gumbel-perturbed argmax) in two launches: per-chunk winners, then one workgroup per row
+  // row-wise argmax (or Gumbel-perturbed argmax): per-chunk winners, then one workgroup per row
   void argmax(const float* logits, int V, int M, int B, int32_t* out, int skip_slot0, int mode, float inv_T, const uint64_t* key) {
     float2* part = ws<float2>(c->ws.amax);
     int parts = amax_parts;
-    if (parts == 0) {   // not fused into the LM head (fp32 models): partials from the stored logits
-      parts = ARGMAX_CHUNKS;
-      hipLaunchKernelGGL(argmax_rows_kernel, dim3(ARGMAX_CHUNKS, M), dim3(256), 0, st, logits, V, B, part, mode, inv_T, key);
+    if (parts == 0) {   // not fused into the LM head (fp32 models): from the stored logits
+      // a short row by one workgroup: the second launch costs 3.5 us, a column more per thread some ten nanoseconds
+      parts = V <= 8192 ? 1 : ARGMAX_CHUNKS;
+      hipLaunchKernelGGL(argmax_rows_kernel, dim3(parts, M), dim3(256), 0, st, logits, V, B, part, mode, inv_T, key,
+                         parts == 1 ? out : (int32_t*)nullptr, skip_slot0);
       check();
+      if (parts == 1) return;
     }
     hipLaunchKernelGGL(argmax_finish_kernel, dim3(M), dim3(256), 0, st, part, parts, B, out, skip_slot0);
     check();
     amax_parts = 0;
+  }
+  // operand of the GEMM behind an RMSNorm of the residual stream: ws.a, normalised here unless the norm is deferred into that GEMM
+  // already; fp32 models of few rows hand over the residual stream itself and the gain (nothing is pending there)
+  const T* operand(const float* gain, float eps, int M, int D, EpiArgs& ep, const dflash_dims& m) {
+    if (std::is_same<T, float>::value && fold_norm(M)) {
+      ep.norm_gain = gain;
+      ep.norm_eps = eps;
+      return ws<T>(c->ws.h);
+    }
+    if (!defer_parts) norm_h(gain, M, D, eps);
+    ep = normed(ep, m);
+    return ws<T>(c->ws.a);
   }
   // RMSNorm of the residual stream, folding in whatever the previous GEMM left pending
   void norm_h(const float* gain, int M, int D, float eps) {
@@ -489,27 +505,32 @@ struct Engine {
     const int S = b->n_seqs, B = blk(b), M = S * B, D = m.d_model;
     const int qd = m.n_q_heads * m.head_dim;
     float* h = ws<float>(c->ws.h);
-    T* a = ws<T>(c->ws.a);
     T* o = ws<T>(c->ws.o);
     T* act = ws<T>(c->ws.act);
     const T* wo = reinterpret_cast<const T*>(lbase + lo.wo);
     const T* wd = reinterpret_cast<const T*>(lbase + lo.wd);
     const float* g2 = reinterpret_cast<const float*>(lbase + lo.g2);
-    if (!defer_parts) norm_h(reinterpret_cast<const float*>(lbase + lo.g1), M, D, m.rms_eps);
     qkv(m, lbase, lo, pool, l, b);
     attention(m, pool, l, b, causal);
     const bool few = few_rows(m, M);
     if (few) resid(wo, o, M, D, qd, g2, -1);
     else pending = gemm(wo, o, M, D, qd, EPI_RESID, EpiArgs{h, D, 0, nullptr, 0});
-    if (!defer_parts) norm_h(g2, M, D, m.rms_eps);
     if (m.n_experts) {
+      norm_h(g2, M, D, m.rms_eps);
       cur_layer = l;
       pending = moe_ffn(m, lbase, lo, M);
     } else {
-      gemm(reinterpret_cast<const T*>(lbase + lo.wgu), a, M, 2 * m.d_ffn, D, EPI_SWIGLU, normed(EpiArgs{nullptr, 0, 0, act, m.d_ffn}, m));
+      EpiArgs gu{nullptr, 0, 0, act, m.d_ffn}, down{h, D, 0, nullptr, 0};
+      const T* a = operand(g2, m.rms_eps, M, D, gu, m);
+      gemm(reinterpret_cast<const T*>(lbase + lo.wgu), a, M, 2 * m.d_ffn, D, EPI_SWIGLU, gu);
       if (few && gain_next && c->k.fuse == 2) return resid(wd, act, M, D, m.d_ffn, gain_next, tap);
       if (few && gain_next && finishes(M, D, m.d_ffn)) return resid_split(wd, act, M, D, m.d_ffn, gain_next, tap);
-      pending = gemm(wd, act, M, D, m.d_ffn, EPI_RESID, EpiArgs{h, D, 0, nullptr, 0});
+      if (std::is_same<T, float>::value && fold_norm(M) && tap >= 0) {   // no norm launch behind the layer that could take it
+        down.tap = ws<float>(c->ws.taps) + (size_t)tap * D;
+        down.tap_K = c->rt.n_taps * D;
+        tap = -1;
+      }
+      pending = gemm(wd, act, M, D, m.d_ffn, EPI_RESID, down);
     }
     pending_tap = tap;   // taken by the next RMSNorm
   }
@@ -548,7 +569,7 @@ struct Engine {
     const dflash_dims& t = c->t;
     EpiArgs ep{logits, t.vocab, 0, nullptr, 0};
     ep.out2 = logits_to;
-    norm_h(final_gain, M, t.d_model, eps);
+    const T* a = operand(final_gain, eps, M, t.d_model, ep, t);
     ep.amax = ws<float2>(c->ws.amax);
     ep.amax_mode = mode;
     ep.amax_inv_T = inv_T;
@@ -561,7 +582,7 @@ struct Engine {
     lm_skip_store = !want_logits;
     amax_parts = 0;
     lse_parts = 0;
-    gemm(reinterpret_cast<const T*>(c->tblob + c->tl.lm), ws<T>(c->ws.a), M, t.vocab, t.d_model, EPI_STORE, ep, false);
+    gemm(reinterpret_cast<const T*>(c->tblob + c->tl.lm), a, M, t.vocab, t.d_model, EPI_STORE, ep, false);
     lm_skip_store = false;
     if (lse_parts == 0) return false;
     hipLaunchKernelGGL(lse_finish_kernel, dim3(M), dim3(64), 0, st, ws<float2>(c->ws.lsep), lse_parts, stats_out);
@@ -573,8 +594,6 @@ struct Engine {
   int draft_block(const dflash_batch* b, float temperature, const uint64_t* rng_key, int32_t* draft_tokens, float* logits_out) {
     const int S = b->n_seqs, B = blk(b), M = S * B;
     const dflash_dims& d = c->d;
-    hipLaunchKernelGGL(build_block_kernel, dim3((M + 255) / 256), dim3(256), 0, st, b->anchor, draft_tokens, S, B, c->rt.mask_token_id);
-    check();
     const bool few = few_rows(d, M);
     const char* l0 = c->dblob + c->dl.layer0;
     EmbedFuse ef;
@@ -586,7 +605,8 @@ struct Engine {
     }
     hipLaunchKernelGGL(embed_kernel<T>, embed_grid(M, d.head_dim), dim3(256), 0, st, reinterpret_cast<const T*>(c->tblob + c->tl.embed), draft_tokens,
                        ws<float>(c->ws.h), d.d_model, d.vocab, status(), b->seq_lens, B, b->max_seq_len, M,
-                       RopeTab{ws<float2>(c->ws.rope_d), log((double)d.rope_theta), d.head_dim}, RopeTab{nullptr, 0.0, 0}, ef);
+                       RopeTab{ws<float2>(c->ws.rope_d), log((double)d.rope_theta), d.head_dim}, RopeTab{nullptr, 0.0, 0}, ef,
+                       EmbedBlock{b->anchor, draft_tokens, c->rt.mask_token_id});
     check();
     for (int i = 0; i < d.n_layers; ++i) {
       const char* lb = l0 + c->dl.lo.end * i;
@@ -703,10 +723,20 @@ struct Engine {
     const int D = d.d_model, kd = d.n_kv_heads * d.head_dim, nkv = d.n_layers * 2 * kd;
     float* arena = ws<float>(c->ws.arena);
     T* ht = ws<T>(c->ws.ht);
+    // (fp32 models have one K range: the complete rows, which must not lie where the second GEMM writes)
     const Slab fs = gemm(reinterpret_cast<const T*>(c->dblob + c->dl.wc), ws<T>(c->ws.taps), M, D, c->rt.n_taps * c->t.d_model, EPI_STORE,
-                         EpiArgs{arena, D, 0, nullptr, 0});
-    norm(nullptr, fs, ws<float>(c->ws.fuse), reinterpret_cast<const float*>(c->dblob + c->dl.gc), ht, M, D, d.rms_eps);
-    const Slab kvs = gemm(reinterpret_cast<const T*>(c->dblob + c->dl.wkv_all), ht, M, nkv, D, EPI_STORE, EpiArgs{arena, nkv, 0, nullptr, 0});
+                         EpiArgs{std::is_same<T, float>::value ? ws<float>(c->ws.fuse) : arena, D, 0, nullptr, 0});
+    EpiArgs ep{arena, nkv, 0, nullptr, 0};
+    const float* gc = reinterpret_cast<const float*>(c->dblob + c->dl.gc);
+    const T* a = ht;
+    if (std::is_same<T, float>::value && fold_norm(M)) {
+      ep.norm_gain = gc;
+      ep.norm_eps = d.rms_eps;
+      a = ws<T>(c->ws.fuse);
+    } else {
+      norm(nullptr, fs, ws<float>(c->ws.fuse), gc, ht, M, D, d.rms_eps);
+    }
+    const Slab kvs = gemm(reinterpret_cast<const T*>(c->dblob + c->dl.wkv_all), a, M, nkv, D, EPI_STORE, ep);
     {   // k-norm, RoPE and page write of all draft layers' context K/V in one launch (grid.z = layer)
       RopeArgs ra;
       ra.n_q_heads = 0; ra.n_kv_heads = d.n_kv_heads; ra.head_dim = d.head_dim;
@@ -1021,8 +1051,14 @@ Engine<float>::Slab Engine<float>::gemm(const float* W, const float* A, int M, i
   const bool split = split_f32_columns(cols, K, epi == EPI_SWIGLU);
   auto launch = [&](auto ec) {
     constexpr int E = decltype(ec)::value;
-    if (split) hipLaunchKernelGGL((gemm_f32_kernel<E, 4>), dim3(cols), dim3(256), 0, st, W, A, M, N, K, ep);
-    else hipLaunchKernelGGL((gemm_f32_kernel<E, 1>), dim3((cols + 3) / 4), dim3(256), 0, st, W, A, M, N, K, ep);
+    auto go = [&](auto nc) {
+      constexpr bool NORM = decltype(nc)::value;
+      if (split) hipLaunchKernelGGL((gemm_f32_kernel<E, 4, NORM>), dim3(cols), dim3(256), 0, st, W, A, M, N, K, ep);
+      else hipLaunchKernelGGL((gemm_f32_kernel<E, 1, NORM>), dim3((cols + 3) / 4), dim3(256), 0, st, W, A, M, N, K, ep);
+    };
+    if constexpr (E != EPI_RESID)
+      if (ep.norm_gain) return go(std::true_type{});
+    go(std::false_type{});
   };
   if (epi == EPI_STORE) launch(std::integral_constant<int, EPI_STORE>{});
   else if (epi == EPI_RESID) launch(std::integral_constant<int, EPI_RESID>{});
@@ -1071,16 +1107,22 @@ void Engine<T>::attention(const dflash_dims& m, const T* pool, int layer, const 
   aa.n_q_heads = m.n_q_heads; aa.n_kv_heads = m.n_kv_heads; aa.head_dim = m.head_dim; aa.layer = layer;
   aa.causal = causal ? 1 : 0; aa.chunk = p.chunk; aa.n_splits = p.n_splits; aa.scale = 1.0f / sqrtf((float)m.head_dim);
   aa.q_shift = q_shift;
-  // one split per sequence: the MFMA kernels write the O projection's operand themselves
-  const bool direct = p.n_splits == 1 && attn_takes_mfma<T>(aa, B);
+  // one split per sequence: the MFMA kernels write the O projection's operand themselves; so does the plain one for short contexts
+  const bool mfma = attn_takes_mfma<T>(aa, B);
+  const bool direct = mfma ? p.n_splits == 1 : short_context(max_tokens);
   if (direct) aa.out = ws<T>(c->ws.o);
   float* part_o = ws<float>(c->ws.part_o);
   float2* part_ml = ws<float2>(c->ws.part_ml);
   {
     // algorithmic bytes: every cached K and V row of this layer once (upper bound from the host hint)
     ProfScope prof(c, st, DFLASH_PROF_ATTN, (double)S * max_tokens * 2 * m.n_kv_heads * m.head_dim * sizeof(T));
-    if (!attn_mfma_launch<T>(st, ws<T>(c->ws.q), pool, geom(b), aa, S, part_o, part_ml, c->k.attn_wide_min_chunk))
-    {
+    if (mfma) {
+      attn_mfma_launch<T>(st, ws<T>(c->ws.q), pool, geom(b), aa, S, part_o, part_ml, c->k.attn_wide_min_chunk);
+    } else if (direct) {
+      aa.chunk *= aa.n_splits;
+      hipLaunchKernelGGL(attn_short_simple_kernel<T>, dim3(B * (m.n_q_heads / m.n_kv_heads), m.n_kv_heads, S), dim3(256), 0, st, ws<T>(c->ws.q), pool,
+                         geom(b), aa, ws<T>(c->ws.o));
+    } else {
       // query rows of a kv head over several workgroups while that leaves at most two of them a CU (each reads the
       // chunk's keys for itself, so a launch that fills the chip keeps them together)
       const int wgs = p.n_splits * m.n_kv_heads * S, rows = B * (m.n_q_heads / m.n_kv_heads);

@@ -49,6 +49,12 @@ struct EpiArgs {
   // copy afterwards read them all again: 4 to 10 us a call)
   float* out2 = nullptr;
   FinishArgs fin = {};   // FIN_RESID (streaming kernel; out: the slabs)
+  // fp32 kernel.  norm_gain: A holds rows that are to be normalised, y = (A * gain / rms(A)) W'.  tap (RESID): the new value goes
+  // there as well, row length tap_K.
+  const float* norm_gain = nullptr;
+  float norm_eps = 0.f;
+  float* tap = nullptr;
+  int tap_K = 0;
 };
 
 // score of logit y at (row m, column col) for the fused argmax
@@ -359,7 +365,10 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16_t* __restr
 // a condition would be waited for by itself), lane r of a column's first wavefront finishes row r (eight read-modify-writes
 // by one lane were eight round trips).  N = 256, K = 1024, 8 rows, RESID: 10.5 us, now 4.3 (the launch floor).
 // ------------------------------------------------------------------------------------------------
-template <int EPI, int KW>
+// NORM: the RMSNorm in front of the product is taken along, y = (1 / rms(a)) ((a * gain) W'): a wavefront multiplies the gain in and
+// the sums of squares come out of the same sweep, two of the eight rows a wavefront where all four see the whole K.  Costs 0.6 to 0.8
+// us at 8 rows of width 256 and saves a launch of 3.6 (fold_norm in plan.h).
+template <int EPI, int KW, bool NORM>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ W, const float* __restrict__ A, int M,
                                                        int N, int K, EpiArgs ep) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -369,21 +378,38 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
   const int row0 = (EPI == EPI_SWIGLU) ? (col >> 4) * 32 + (col & 15) : col;
   const float* w0 = W + (size_t)row0 * K;
   const float* w1 = w0 + (size_t)16 * K;  // SWIGLU only
+  constexpr int SQ = KW == 1 ? 2 : 8;     // rows whose squares a wavefront adds, from row SQ * wave of the eight (KW == 1) or all
   __shared__ float sum[2][4][8];
+  __shared__ float sq[KW == 1 ? 1 : 4][8];
   for (int m0 = 0; m0 < M; m0 += 8) {
-    float acc0[8], acc1[8];
+    float acc0[8], acc1[8], ss[SQ];
 #pragma unroll
     for (int r = 0; r < 8; ++r) acc0[r] = acc1[r] = 0.f;
+#pragma unroll
+    for (int r = 0; r < SQ; ++r) ss[r] = 0.f;
     for (int k = kw * 256 + lane * 4; k < K; k += 256 * KW) {
-      float4 a[8];
+      float4 a[8], own[SQ];
       const float4 wa = *reinterpret_cast<const float4*>(w0 + k);
-      float4 wb = make_float4(0.f, 0.f, 0.f, 0.f);
+      float4 wb = make_float4(0.f, 0.f, 0.f, 0.f), g = make_float4(1.f, 1.f, 1.f, 1.f);
       if (EPI == EPI_SWIGLU) wb = *reinterpret_cast<const float4*>(w1 + k);
+      if constexpr (NORM) g = *reinterpret_cast<const float4*>(ep.norm_gain + k);
 #pragma unroll
       for (int r = 0; r < 8; ++r) a[r] = *reinterpret_cast<const float4*>(A + (size_t)min(m0 + r, M - 1) * K + k);
+      if constexpr (NORM && KW == 1) {   // again, from the L1: which rows they are depends on the wavefront
+#pragma unroll
+        for (int r = 0; r < SQ; ++r) own[r] = *reinterpret_cast<const float4*>(A + (size_t)min(m0 + SQ * wave + r, M - 1) * K + k);
+      }
       __builtin_amdgcn_sched_barrier(0);
+      if constexpr (NORM) {
+#pragma unroll
+        for (int r = 0; r < SQ; ++r) {
+          const float4 x = KW == 1 ? own[r] : a[r];
+          ss[r] += x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w;
+        }
+      }
 #pragma unroll
       for (int r = 0; r < 8; ++r) {
+        if constexpr (NORM) a[r] = make_float4(a[r].x * g.x, a[r].y * g.y, a[r].z * g.z, a[r].w * g.w);
         acc0[r] += a[r].x * wa.x + a[r].y * wa.y + a[r].z * wa.z + a[r].w * wa.w;
         if (EPI == EPI_SWIGLU) acc1[r] += a[r].x * wb.x + a[r].y * wb.y + a[r].z * wb.z + a[r].w * wb.w;
       }
@@ -395,12 +421,21 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
       const float t1 = (EPI == EPI_SWIGLU) ? wave_reduce_sum(acc1[r]) : 0.f;
       if (lane == r) { s0 = t0; s1 = t1; }
     }
+    if constexpr (NORM) {
+#pragma unroll
+      for (int r = 0; r < SQ; ++r) {
+        const float t = wave_reduce_sum(ss[r]);
+        if (lane == 0) sq[KW == 1 ? 0 : wave][(KW == 1 ? SQ * wave : 0) + r] = t;
+      }
+    }
     if constexpr (KW > 1) {
       if (lane < 8) {
         sum[0][wave][lane] = s0;
         if (EPI == EPI_SWIGLU) sum[1][wave][lane] = s1;
       }
-      __syncthreads();
+    }
+    if constexpr (KW > 1 || NORM) __syncthreads();
+    if constexpr (KW > 1) {
       if (kw == 0 && lane < 8) {
 #pragma unroll
         for (int i = 1; i < KW; ++i) {
@@ -408,6 +443,18 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
           if (EPI == EPI_SWIGLU) s1 += sum[1][wave + i][lane];
         }
       }
+    }
+    if constexpr (NORM) {
+      if (lane < 8) {
+        float t = sq[0][lane];
+#pragma unroll
+        for (int i = 1; i < KW; ++i) t += sq[i][lane];
+        const float rstd = 1.0f / sqrtf(t / (float)K + ep.norm_eps);
+        s0 *= rstd;
+        s1 *= rstd;
+      }
+    }
+    if constexpr (KW > 1 || NORM) {
       if (m0 + 8 < M) __syncthreads();   // the sums are read before the next rows overwrite them
     }
     const int m = m0 + lane;
@@ -415,7 +462,9 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
       if (EPI == EPI_SWIGLU) {
         reinterpret_cast<float*>(ep.act)[(size_t)m * ep.act_K + col] = silu_f(s0) * s1;
       } else if (EPI == EPI_RESID) {
-        ep.out[(size_t)m * ep.ld + col] += s0;
+        const float h = ep.out[(size_t)m * ep.ld + col] + s0;
+        ep.out[(size_t)m * ep.ld + col] = h;
+        if (ep.tap) ep.tap[(size_t)m * ep.tap_K + col] = h;
       } else {
         ep.out[(size_t)m * ep.ld + col] = s0;
         if (ep.out2) ep.out2[(size_t)m * ep.ld + col] = s0;

@@ -7,13 +7,6 @@
 #include "common.h"
 
 // ---- block assembly + embedding gather -------------------------------------------------------
-// tokens_out[s, 0] = anchor[s], tokens_out[s, j>0] = mask_id   (Section 4.2: clean anchor + masks)
-__global__ void build_block_kernel(const int32_t* __restrict__ anchor, int32_t* __restrict__ tokens_out, int S, int B,
-                                   int mask_id) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < S * B) tokens_out[i] = (i % B == 0) ? anchor[i / B] : mask_id;
-}
-
 // Rotary table of one model for the rows of a call: out[m * hd/2 + i] = (cos, sin) of pos(m) * theta^(-2i/hd),
 // pos(m) = seq_lens[m / B] + m % B.  Angles are formed in double precision (reduced by sincos) so that long
 // contexts do not lose phase accuracy; every layer and head of the call then reads the same rounded pair.
@@ -33,12 +26,19 @@ struct EmbedFuse {
   void* a_out = nullptr;
   float* ssq = nullptr;
 };
+// Drafting: tokens are assembled here, block[s, 0] = anchor[s], block[s, j > 0] = mask_id (Section 4.2: clean anchor + masks),
+// and left in `block`; otherwise (block null) they are read.
+struct EmbedBlock {
+  const int32_t* anchor = nullptr;
+  int32_t* block = nullptr;
+  int mask_id = 0;
+};
 
 template <typename T>
 __global__ __launch_bounds__(256) void embed_kernel(const T* __restrict__ E, const int32_t* __restrict__ tokens,
                                                     float* __restrict__ h, int D, int vocab, int32_t* status,
                                                     const int32_t* __restrict__ seq_lens, int B, int len_hint, int n_rows, RopeTab t0, RopeTab t1,
-                                                    EmbedFuse fuse = EmbedFuse{}) {
+                                                    EmbedFuse fuse = EmbedFuse{}, EmbedBlock blk = EmbedBlock{}) {
   // workgroups M .. of the grid write the rotary tables (angles in double precision take longer than a row's copy): one
   // entry of a table per thread
   if ((int)blockIdx.x >= n_rows) {
@@ -57,7 +57,13 @@ __global__ __launch_bounds__(256) void embed_kernel(const T* __restrict__ E, con
   // the host sized the attention launches of this call for sequences of at most len_hint committed tokens: a longer
   // one would have its last keys left out, so it is reported
   if (threadIdx.x == 0 && seq_lens[m / B] > len_hint) atomicOr(status, DF_STATUS_CAPACITY);
-  int tok = tokens[m];
+  int tok;
+  if (blk.block) {
+    tok = m % B == 0 ? blk.anchor[m / B] : blk.mask_id;
+    if (threadIdx.x == 0) blk.block[m] = tok;
+  } else {
+    tok = tokens[m];
+  }
   if (tok < 0 || tok >= vocab) {
     if (threadIdx.x == 0) atomicOr(status, DF_STATUS_CAPACITY);
     tok = 0;
@@ -340,11 +346,14 @@ __device__ __forceinline__ void block_argmax(float& bv, int& bi) {
 
 // mode 0: greedy.  mode 1: draft sampling, score = logit * inv_T + Gumbel(key, seq, slot, purpose 0).
 // Stage 1: grid (n_chunks, M): best (score, index) of one chunk of row m -> part[m * n_chunks + chunk].
+// With a single chunk a row (n_chunks == 1, `out` given) the winner is written here, as stage 2 would.
 // Stage 2 (argmax_finish_kernel): combines the chunks in ascending order (ties -> lowest index) and writes out[m]
 // unless (skip_slot0 && slot == 0).
 __global__ __launch_bounds__(256) void argmax_rows_kernel(const float* __restrict__ logits, int V, int B, float2* __restrict__ part,
-                                                          int mode, float inv_T, const uint64_t* __restrict__ rng_key) {
+                                                          int mode, float inv_T, const uint64_t* __restrict__ rng_key,
+                                                          int32_t* __restrict__ out, int skip_slot0) {
   const int chunk = blockIdx.x, n_chunks = gridDim.x, m = blockIdx.y, slot = m % B, seq = m / B;
+  if (out && skip_slot0 && slot == 0) return;
   const int per = (V + n_chunks - 1) / n_chunks, i0 = chunk * per, i1 = min(V, i0 + per);
   const float* row = logits + (size_t)m * V;
   float bv = -INFINITY;
@@ -356,7 +365,9 @@ __global__ __launch_bounds__(256) void argmax_rows_kernel(const float* __restric
     argmax_combine(bv, bi, v, i);
   }
   block_argmax(bv, bi);
-  if (threadIdx.x == 0) part[(size_t)m * n_chunks + chunk] = make_float2(bv, __int_as_float(bi));
+  if (threadIdx.x != 0) return;
+  if (out) out[m] = bi;
+  else part[(size_t)m * n_chunks + chunk] = make_float2(bv, __int_as_float(bi));
 }
 
 __global__ __launch_bounds__(256) void argmax_finish_kernel(const float2* __restrict__ part, int n_chunks, int B, int32_t* __restrict__ out,

@@ -217,6 +217,16 @@ inline StreamPlan stream_plan(const Knobs& kn, int M, int N, int K, bool split, 
 // 6.1 and 6.3, 48 and 61; 1536 x 2048 9.9 and 10.5, 95 and 113.  768 x 1024 is even by itself, in a step of 32 rows four are 4 % faster.
 inline bool split_f32_columns(int cols, int K, bool swiglu) { return K >= 1024 && cols <= std::min(swiglu ? K / 2 : K / 4 * 3, 1536); }
 
+// fp32: whether the GEMM behind an RMSNorm takes the norm along (gemm_f32_kernel, NORM) instead of a launch for it.  The kernel goes
+// over the rows eight at a time and pays for the norm each time.  A step of the 2 + 1 layer model of width 256, with a launch and
+// taken along: 8 rows 154 and 122 us, 16 167 and 156, 21 189 and 185, 32 216 and 220, 64 320 and 355.
+inline bool fold_norm(int M) { return M <= 24; }
+
+// fp32: whether a query row's keys are few enough for one workgroup without splits (attn_short_simple_kernel): a 64-key tile for
+// each of its wavefronts.  The same step with splits and a merge launch, and without: 136 keys 131 and 122 us, 116 keys and 32 rows 230 and
+// 220, 216 keys and 64 rows 326 and 320; two tiles a wavefront lose, 316 keys 164 and 170, 508 keys and 32 rows 231 and 238.
+inline bool short_context(int max_tokens) { return max_tokens <= 256; }
+
 // Weight rows per tile of a four-band routed-expert item: 256 (eight wavefronts), or 128 (four) for the short matrices of an odd
 // number of 128-row blocks, where the half-empty last 256-row block is a twelfth of the launch or more.  `nt`: 16-row bands of
 // the matrix.  Two-layer verifications of 512 rows, 8 of 128 experts, 2048 wide, with 256 and with 128 rows per tile: d_expert 64

@@ -180,6 +180,27 @@ def test_forced_tiles_over_ragged_sizes(n_seqs, ffn, vocab, wide, tile, wm, ks, 
     assert counts[wide] > 0 and counts[3 - wide] == 0 and counts[0] == 0
 
 
+@pytest.mark.parametrize("d,heads,kv_heads,hd,ffn,vocab,n_seqs,block,lens", [
+    (256, 4, 4, 64, 1024, 1024, 1, 2, (5,)),              # two rows
+    (256, 4, 2, 64, 1024, 8192, 3, 7, (63, 64, 130)),     # 21 rows: a last piece of five; the longest row that one workgroup searches
+    (256, 4, 4, 64, 512, 8208, 3, 8, (9, 233, 240)),      # 24 rows and 256 keys at first, more behind: one workgroup, then splits
+    (256, 4, 1, 64, 512, 512, 5, 5, (20, 31, 8, 90, 64)), # 25 rows: norm launches
+    (1024, 4, 1, 128, 512, 640, 2, 8, (17, 120)),         # four wavefronts a column, in plain and in SwiGLU products; head dim 128
+])
+def test_fp32_folded_norms_and_short_contexts(d, heads, kv_heads, hd, ffn, vocab, n_seqs, block, lens):
+    """The RMSNorms that GEMMs take along, taps of an inner and the last layer, attention by one workgroup a row and the argmax of one
+    launch, on both sides of the lines where they end."""
+    w = tiny_workload(seed=ffn + vocab, n_layers=3, draft_layers=2, vocab=vocab, block=block, qk_norm=True, kv_heads=kv_heads, n_seqs=n_seqs,
+                      taps=(1, 2), d=d, heads=heads, hd=hd, ffn=ffn)
+    prompts = [p[:n] for p, n in zip(si.make_prompts(replace(w, ctx_min=max(lens), ctx_max=max(lens))), lens)]
+    ls = Lockstep(w, prompts, max_len=max(lens) + 5 * block)
+    ls.prefill()
+    for i, plan in enumerate((None, [block - 1] * n_seqs, [(3 * s + 1) % block for s in range(n_seqs)], None)):
+        ls.step(plan=plan, step_idx=i)
+    ls.check_cache([0, 2], [0, 1])
+    assert ls.stats["reseeds"] == 0
+
+
 @pytest.mark.parametrize("hd,heads,kv_heads,n_seqs,block,wide_from", [
     (128, 4, 2, 3, 16, 64),        # key-split kernel
     (128, 8, 2, 2, 7, 64),         # ... with a block that is no whole band: two sequences' rows in one operand tile
