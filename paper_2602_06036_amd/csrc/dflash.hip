@@ -479,7 +479,7 @@ struct Engine {
   // operand of the GEMM behind an RMSNorm of the residual stream: ws.a, normalised here unless the norm is deferred into that GEMM
   // already; fp32 models of few rows hand over the residual stream itself and the gain (nothing is pending there)
   const T* operand(const float* gain, float eps, int M, int D, EpiArgs& ep, const dflash_dims& m) {
-    if (std::is_same<T, float>::value && fold_norm(M)) {
+    if (std::is_same<T, float>::value && fold_norm(M, D)) {
       ep.norm_gain = gain;
       ep.norm_eps = eps;
       return ws<T>(c->ws.h);
@@ -525,7 +525,7 @@ struct Engine {
       gemm(reinterpret_cast<const T*>(lbase + lo.wgu), a, M, 2 * m.d_ffn, D, EPI_SWIGLU, gu);
       if (few && gain_next && c->k.fuse == 2) return resid(wd, act, M, D, m.d_ffn, gain_next, tap);
       if (few && gain_next && finishes(M, D, m.d_ffn)) return resid_split(wd, act, M, D, m.d_ffn, gain_next, tap);
-      if (std::is_same<T, float>::value && fold_norm(M) && tap >= 0) {   // no norm launch behind the layer that could take it
+      if (std::is_same<T, float>::value && fold_norm(M, D) && tap >= 0) {   // no norm launch behind the layer that could take it
         down.tap = ws<float>(c->ws.taps) + (size_t)tap * D;
         down.tap_K = c->rt.n_taps * D;
         tap = -1;
@@ -729,7 +729,7 @@ struct Engine {
     EpiArgs ep{arena, nkv, 0, nullptr, 0};
     const float* gc = reinterpret_cast<const float*>(c->dblob + c->dl.gc);
     const T* a = ht;
-    if (std::is_same<T, float>::value && fold_norm(M)) {
+    if (std::is_same<T, float>::value && fold_norm(M, D)) {
       ep.norm_gain = gc;
       ep.norm_eps = d.rms_eps;
       a = ws<T>(c->ws.fuse);
@@ -1048,13 +1048,13 @@ template <>
 Engine<float>::Slab Engine<float>::gemm(const float* W, const float* A, int M, int N, int K, int epi, EpiArgs ep, bool) {
   ProfScope prof(c, st, gemm_class(epi, N, c->t.vocab), (double)N * K * 4);
   const int cols = epi == EPI_SWIGLU ? N / 2 : N;
-  const bool split = split_f32_columns(cols, K, epi == EPI_SWIGLU);
+  const bool split = split_f32_columns(cols * ((M + 7) / 8), K, epi == EPI_SWIGLU);
   auto launch = [&](auto ec) {
     constexpr int E = decltype(ec)::value;
     auto go = [&](auto nc) {
       constexpr bool NORM = decltype(nc)::value;
-      if (split) hipLaunchKernelGGL((gemm_f32_kernel<E, 4, NORM>), dim3(cols), dim3(256), 0, st, W, A, M, N, K, ep);
-      else hipLaunchKernelGGL((gemm_f32_kernel<E, 1, NORM>), dim3((cols + 3) / 4), dim3(256), 0, st, W, A, M, N, K, ep);
+      if (split) hipLaunchKernelGGL((gemm_f32_kernel<E, 4, NORM>), dim3(cols, (M + 7) / 8), dim3(256), 0, st, W, A, M, N, K, ep);
+      else hipLaunchKernelGGL((gemm_f32_kernel<E, 1, NORM>), dim3((cols + 3) / 4, (M + 7) / 8), dim3(256), 0, st, W, A, M, N, K, ep);
     };
     if constexpr (E != EPI_RESID)
       if (ep.norm_gain) return go(std::true_type{});

@@ -360,8 +360,9 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16_t* __restr
 
 // ------------------------------------------------------------------------------------------------
 // fp32 kernel (small models): block = 4 wavefronts, 4 / KW output columns (SWIGLU: one activation column = a gate row
-// and the up row 16 below it), KW wavefronts per column that take every KW-th 256-wide piece of K; lanes stride over K; rows
-// in chunks of 8.  Bound by latency: all loads of a piece go out together (rows past the last one repeat it, a load under
+// and the up row 16 below it), KW wavefronts per column that take every KW-th 256-wide piece of K; lanes stride over K; eight
+// rows a workgroup (grid.y groups of them: one after the other in a workgroup, a step of the 2 + 1 layer model of width 256 took 320 us
+// at 64 rows, side by side 182; width 2048, 128 rows 3208 and 2923).  Bound by latency: all loads of a piece go out together (rows past the last one repeat it, a load under
 // a condition would be waited for by itself), lane r of a column's first wavefront finishes row r (eight read-modify-writes
 // by one lane were eight round trips).  N = 256, K = 1024, 8 rows, RESID: 10.5 us, now 4.3 (the launch floor).
 // ------------------------------------------------------------------------------------------------
@@ -381,94 +382,90 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
   constexpr int SQ = KW == 1 ? 2 : 8;     // rows whose squares a wavefront adds, from row SQ * wave of the eight (KW == 1) or all
   __shared__ float sum[2][4][8];
   __shared__ float sq[KW == 1 ? 1 : 4][8];
-  for (int m0 = 0; m0 < M; m0 += 8) {
-    float acc0[8], acc1[8], ss[SQ];
+  const int m0 = blockIdx.y * 8;
+  float acc0[8], acc1[8], ss[SQ];
 #pragma unroll
-    for (int r = 0; r < 8; ++r) acc0[r] = acc1[r] = 0.f;
+  for (int r = 0; r < 8; ++r) acc0[r] = acc1[r] = 0.f;
 #pragma unroll
-    for (int r = 0; r < SQ; ++r) ss[r] = 0.f;
-    for (int k = kw * 256 + lane * 4; k < K; k += 256 * KW) {
-      float4 a[8], own[SQ];
-      const float4 wa = *reinterpret_cast<const float4*>(w0 + k);
-      float4 wb = make_float4(0.f, 0.f, 0.f, 0.f), g = make_float4(1.f, 1.f, 1.f, 1.f);
-      if (EPI == EPI_SWIGLU) wb = *reinterpret_cast<const float4*>(w1 + k);
-      if constexpr (NORM) g = *reinterpret_cast<const float4*>(ep.norm_gain + k);
+  for (int r = 0; r < SQ; ++r) ss[r] = 0.f;
+  for (int k = kw * 256 + lane * 4; k < K; k += 256 * KW) {
+    float4 a[8], own[SQ];
+    const float4 wa = *reinterpret_cast<const float4*>(w0 + k);
+    float4 wb = make_float4(0.f, 0.f, 0.f, 0.f), g = make_float4(1.f, 1.f, 1.f, 1.f);
+    if (EPI == EPI_SWIGLU) wb = *reinterpret_cast<const float4*>(w1 + k);
+    if constexpr (NORM) g = *reinterpret_cast<const float4*>(ep.norm_gain + k);
 #pragma unroll
-      for (int r = 0; r < 8; ++r) a[r] = *reinterpret_cast<const float4*>(A + (size_t)min(m0 + r, M - 1) * K + k);
-      if constexpr (NORM && KW == 1) {   // again, from the L1: which rows they are depends on the wavefront
+    for (int r = 0; r < 8; ++r) a[r] = *reinterpret_cast<const float4*>(A + (size_t)min(m0 + r, M - 1) * K + k);
+    if constexpr (NORM && KW == 1) {   // again, from the L1: which rows they are depends on the wavefront
 #pragma unroll
-        for (int r = 0; r < SQ; ++r) own[r] = *reinterpret_cast<const float4*>(A + (size_t)min(m0 + SQ * wave + r, M - 1) * K + k);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      if constexpr (NORM) {
-#pragma unroll
-        for (int r = 0; r < SQ; ++r) {
-          const float4 x = KW == 1 ? own[r] : a[r];
-          ss[r] += x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w;
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        if constexpr (NORM) a[r] = make_float4(a[r].x * g.x, a[r].y * g.y, a[r].z * g.z, a[r].w * g.w);
-        acc0[r] += a[r].x * wa.x + a[r].y * wa.y + a[r].z * wa.z + a[r].w * wa.w;
-        if (EPI == EPI_SWIGLU) acc1[r] += a[r].x * wb.x + a[r].y * wb.y + a[r].z * wb.z + a[r].w * wb.w;
-      }
+      for (int r = 0; r < SQ; ++r) own[r] = *reinterpret_cast<const float4*>(A + (size_t)min(m0 + SQ * wave + r, M - 1) * K + k);
     }
-    float s0 = 0.f, s1 = 0.f;   // lane r: the sum of row m0 + r over this wavefront's pieces
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const float t0 = wave_reduce_sum(acc0[r]);
-      const float t1 = (EPI == EPI_SWIGLU) ? wave_reduce_sum(acc1[r]) : 0.f;
-      if (lane == r) { s0 = t0; s1 = t1; }
-    }
+    __builtin_amdgcn_sched_barrier(0);
     if constexpr (NORM) {
 #pragma unroll
       for (int r = 0; r < SQ; ++r) {
-        const float t = wave_reduce_sum(ss[r]);
-        if (lane == 0) sq[KW == 1 ? 0 : wave][(KW == 1 ? SQ * wave : 0) + r] = t;
+        const float4 x = KW == 1 ? own[r] : a[r];
+        ss[r] += x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w;
       }
     }
-    if constexpr (KW > 1) {
-      if (lane < 8) {
-        sum[0][wave][lane] = s0;
-        if (EPI == EPI_SWIGLU) sum[1][wave][lane] = s1;
-      }
-    }
-    if constexpr (KW > 1 || NORM) __syncthreads();
-    if constexpr (KW > 1) {
-      if (kw == 0 && lane < 8) {
 #pragma unroll
-        for (int i = 1; i < KW; ++i) {
-          s0 += sum[0][wave + i][lane];
-          if (EPI == EPI_SWIGLU) s1 += sum[1][wave + i][lane];
-        }
-      }
+    for (int r = 0; r < 8; ++r) {
+      if constexpr (NORM) a[r] = make_float4(a[r].x * g.x, a[r].y * g.y, a[r].z * g.z, a[r].w * g.w);
+      acc0[r] += a[r].x * wa.x + a[r].y * wa.y + a[r].z * wa.z + a[r].w * wa.w;
+      if (EPI == EPI_SWIGLU) acc1[r] += a[r].x * wb.x + a[r].y * wb.y + a[r].z * wb.z + a[r].w * wb.w;
     }
-    if constexpr (NORM) {
-      if (lane < 8) {
-        float t = sq[0][lane];
+  }
+  float s0 = 0.f, s1 = 0.f;   // lane r: the sum of row m0 + r over this wavefront's pieces
 #pragma unroll
-        for (int i = 1; i < KW; ++i) t += sq[i][lane];
-        const float rstd = 1.0f / sqrtf(t / (float)K + ep.norm_eps);
-        s0 *= rstd;
-        s1 *= rstd;
+  for (int r = 0; r < 8; ++r) {
+    const float t0 = wave_reduce_sum(acc0[r]);
+    const float t1 = (EPI == EPI_SWIGLU) ? wave_reduce_sum(acc1[r]) : 0.f;
+    if (lane == r) { s0 = t0; s1 = t1; }
+  }
+  if constexpr (NORM) {
+#pragma unroll
+    for (int r = 0; r < SQ; ++r) {
+      const float t = wave_reduce_sum(ss[r]);
+      if (lane == 0) sq[KW == 1 ? 0 : wave][(KW == 1 ? SQ * wave : 0) + r] = t;
+    }
+  }
+  if constexpr (KW > 1) {
+    if (lane < 8) {
+      sum[0][wave][lane] = s0;
+      if (EPI == EPI_SWIGLU) sum[1][wave][lane] = s1;
+    }
+  }
+  if constexpr (KW > 1 || NORM) __syncthreads();
+  if constexpr (KW > 1) {
+    if (kw == 0 && lane < 8) {
+#pragma unroll
+      for (int i = 1; i < KW; ++i) {
+        s0 += sum[0][wave + i][lane];
+        if (EPI == EPI_SWIGLU) s1 += sum[1][wave + i][lane];
       }
     }
-    if constexpr (KW > 1 || NORM) {
-      if (m0 + 8 < M) __syncthreads();   // the sums are read before the next rows overwrite them
+  }
+  if constexpr (NORM) {
+    if (lane < 8) {
+      float t = sq[0][lane];
+#pragma unroll
+      for (int i = 1; i < KW; ++i) t += sq[i][lane];
+      const float rstd = 1.0f / sqrtf(t / (float)K + ep.norm_eps);
+      s0 *= rstd;
+      s1 *= rstd;
     }
-    const int m = m0 + lane;
-    if (kw == 0 && lane < 8 && m < M && col_raw < n_cols) {
-      if (EPI == EPI_SWIGLU) {
-        reinterpret_cast<float*>(ep.act)[(size_t)m * ep.act_K + col] = silu_f(s0) * s1;
-      } else if (EPI == EPI_RESID) {
-        const float h = ep.out[(size_t)m * ep.ld + col] + s0;
-        ep.out[(size_t)m * ep.ld + col] = h;
-        if (ep.tap) ep.tap[(size_t)m * ep.tap_K + col] = h;
-      } else {
-        ep.out[(size_t)m * ep.ld + col] = s0;
-        if (ep.out2) ep.out2[(size_t)m * ep.ld + col] = s0;
-      }
+  }
+  const int m = m0 + lane;
+  if (kw == 0 && lane < 8 && m < M && col_raw < n_cols) {
+    if (EPI == EPI_SWIGLU) {
+      reinterpret_cast<float*>(ep.act)[(size_t)m * ep.act_K + col] = silu_f(s0) * s1;
+    } else if (EPI == EPI_RESID) {
+      const float h = ep.out[(size_t)m * ep.ld + col] + s0;
+      ep.out[(size_t)m * ep.ld + col] = h;
+      if (ep.tap) ep.tap[(size_t)m * ep.tap_K + col] = h;
+    } else {
+      ep.out[(size_t)m * ep.ld + col] = s0;
+      if (ep.out2) ep.out2[(size_t)m * ep.ld + col] = s0;
     }
   }
 }

@@ -210,17 +210,19 @@ inline StreamPlan stream_plan(const Knobs& kn, int M, int N, int K, bool split, 
 }
 
 // fp32 GEMM: whether four wavefronts share an output column's K (each at least a 256-wide piece) instead of taking a column each.
-// It pays while the columns alone leave CUs idle, and the fewer pieces a column has the sooner they fill the chip; a SwiGLU column
-// is two.  Columns x K at 8 and 128 rows, one and four wavefronts a column: 512 x 1024 4.6 and 4.0 us, 33.5 and 27.5; 1024 x 1024
-// 4.8 and 5.1, 34 and 44; 2048 x 1024 5.4 and 7.2, 42 and 76; 1024 x 2048 6.7 and 5.9, 50.9 and 50.5; 2048 x 2048 7.8 and 8.6, 80 and 92;
-// 1536 x 4096 11.3 and 11.5, 152 and 122; 2048 x 4096 13.2 and 15.0, 159 and 160.  SwiGLU 512 x 1024 5.8 and 5.3, 48 and 41; 768 x 1024
-// 6.1 and 6.3, 48 and 61; 1536 x 2048 9.9 and 10.5, 95 and 113.  768 x 1024 is even by itself, in a step of 32 rows four are 4 % faster.
+// `cols`: columns of all groups of eight rows (a workgroup does one group; with the columns of a single group here steps of 64 rows and more
+// were 1 to 3 % slower).  It pays while the columns alone leave CUs idle, and the fewer pieces a column has the sooner they fill
+// the chip; a SwiGLU column is two.  Columns x K at 8 rows, one and four wavefronts a column: 512 x 1024 4.6 and 4.0 us; 1024 x 1024 4.8
+// and 5.1; 2048 x 1024 5.4 and 7.2; 1024 x 2048 6.7 and 5.9; 2048 x 2048 7.8 and 8.6; 1536 x 4096 11.3 and 11.5; 2048 x 4096 13.2
+// and 15.0.  SwiGLU 512 x 1024 5.8 and 5.3; 768 x 1024 6.1 and 6.3; 1536 x 2048 9.9 and 10.5.  768 x 1024 is even by itself, in a step
+// four are faster.
 inline bool split_f32_columns(int cols, int K, bool swiglu) { return K >= 1024 && cols <= std::min(swiglu ? K / 2 : K / 4 * 3, 1536); }
 
-// fp32: whether the GEMM behind an RMSNorm takes the norm along (gemm_f32_kernel, NORM) instead of a launch for it.  The kernel goes
-// over the rows eight at a time and pays for the norm each time.  A step of the 2 + 1 layer model of width 256, with a launch and
-// taken along: 8 rows 154 and 122 us, 16 167 and 156, 21 189 and 185, 32 216 and 220, 64 320 and 355.
-inline bool fold_norm(int M) { return M <= 24; }
+// fp32: whether the GEMM behind an RMSNorm of `D` columns takes the norm along (gemm_f32_kernel, NORM) instead of a launch for it: while
+// the products are so small that they are launches more than work.  Steps of 2 + 1 layer models, with launches and taken along: width 256,
+// 8 rows 154 and 121 us, 32 159 and 147, 64 191 and 185; width 512, 8 rows 154 and 140, 32 204 and 197; width 1024, 8 rows 197 and 187, 16
+// 235 and 229, 32 311 and 320; width 2048, 8 rows 402 and 415, 16 557 and 600.
+inline bool fold_norm(int M, int D) { return M * D <= 16384 && D <= 1024; }
 
 // fp32: whether a query row's keys are few enough for one workgroup without splits (attn_short_simple_kernel): a 64-key tile for
 // each of its wavefronts.  The same step with splits and a merge launch, and without: 136 keys 131 and 122 us, 116 keys and 32 rows 230 and

@@ -184,8 +184,10 @@ def test_forced_tiles_over_ragged_sizes(n_seqs, ffn, vocab, wide, tile, wm, ks, 
     (256, 4, 4, 64, 1024, 1024, 1, 2, (5,)),              # two rows
     (256, 4, 2, 64, 1024, 8192, 3, 7, (63, 64, 130)),     # 21 rows: a last piece of five; the longest row that one workgroup searches
     (256, 4, 4, 64, 512, 8208, 3, 8, (9, 233, 240)),      # 24 rows and 256 keys at first, more behind: one workgroup, then splits
-    (256, 4, 1, 64, 512, 512, 5, 5, (20, 31, 8, 90, 64)), # 25 rows: norm launches
-    (1024, 4, 1, 128, 512, 640, 2, 8, (17, 120)),         # four wavefronts a column, in plain and in SwiGLU products; head dim 128
+    (256, 4, 4, 64, 512, 512, 9, 7, (20, 31, 8, 90, 64, 1, 3, 5, 7)),   # 63 rows
+    (256, 4, 1, 64, 512, 512, 5, 13, (20, 31, 8, 90, 64)),              # 65 rows: norm launches
+    (1024, 4, 1, 128, 256, 640, 2, 8, (17, 120)),         # 16 rows; four wavefronts a column in SwiGLU products; head dim 128
+    (1024, 4, 1, 128, 256, 640, 1, 7, (33,)),             # ... and in plain ones
 ])
 def test_fp32_folded_norms_and_short_contexts(d, heads, kv_heads, hd, ffn, vocab, n_seqs, block, lens):
     """The RMSNorms that GEMMs take along, taps of an inner and the last layer, attention by one workgroup a row and the argmax of one
