@@ -409,12 +409,20 @@ __global__ void accept_greedy_kernel(const int32_t* __restrict__ draft, const in
 // (-inf, 0).  Bound by HBM: every logit is read once (running maximum per thread), and a row is shared out over gridDim.x
 // workgroups, because a block's few rows alone leave most CUs without work.  VEC: V and both pointers allow 16-byte loads.
 // Eight sequences of 16 rows, 151936 columns, both tensors (156 MB): 2 x 99 us as one 1024-thread workgroup per row and
-// two sweeps over it, 31 us in this form, the logits being in the memory-side cache from the pass before (the whole call: 325 and
-// 46 us so, 381 and 49 over logits that have left it, 338 and 61 waited for by itself over logits just written).
+// two sweeps over it, 31 us in this form, the logits being in the memory-side cache from the pass before (the whole call: 325 us, 47
+// with the library's expf and plain loads, 42 with exp_nonpositive and non-temporal ones; the rows' log-sum-exp is off by 5.6e-8 rms
+// and 2.6e-7 at worst with either exponential).
 __device__ __forceinline__ void lse_merge(float& m, float& s, float m2, float s2) {   // union of two sets
   const float M = fmaxf(m, m2);
   s = (m == -INFINITY ? s : s * expf(m - M)) + (m2 == -INFINITY ? s2 : s2 * expf(m2 - M));   // an empty set's sum is 0 or NaN
   m = M;
+}
+// e^d, d <= 0 (-inf: 0, NaN: NaN): 2^(d log2 e) by the exponential instruction, with what the product's rounding left out put back as a
+// factor, so that it is as good for large -d as for small ones
+__device__ __forceinline__ float exp_nonpositive(float d) {
+  constexpr float kLog2e = 1.44269502162933349609f, kLog2eLow = 1.92596299e-8f, kLn2 = 0.693147180559945f;
+  const float p = d * kLog2e, left = fmaf(d, kLog2eLow, fmaf(d, kLog2e, -p)), x = __builtin_amdgcn_exp2f(p);
+  return d < -87.f ? 0.f : fmaf(x, left * kLn2, x);
 }
 template <bool VEC>
 __global__ __launch_bounds__(256) void lse_partial_kernel(const float* __restrict__ a, const float* __restrict__ b, int R, int V, float inv_T,
@@ -431,8 +439,8 @@ __global__ __launch_bounds__(256) void lse_partial_kernel(const float* __restric
     for (int u = 0; u < U; ++u) {
       const int at = i + u * 256 * E;
       if constexpr (VEC) {
-        const float4 x = at < i1 ? *reinterpret_cast<const float4*>(row + at) : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-        v[4 * u] = x.x; v[4 * u + 1] = x.y; v[4 * u + 2] = x.z; v[4 * u + 3] = x.w;
+        const f32x4 x = at < i1 ? __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(row + at)) : (f32x4){-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+        v[4 * u] = x[0]; v[4 * u + 1] = x[1]; v[4 * u + 2] = x[2]; v[4 * u + 3] = x[3];
       } else {
         v[u] = at < i1 ? row[at] : -INFINITY;
       }
@@ -449,7 +457,7 @@ __global__ __launch_bounds__(256) void lse_partial_kernel(const float* __restric
       m = mx;
     }
 #pragma unroll
-    for (int e = 0; e < U * E; ++e) s += v[e] == -INFINITY ? 0.f : expf(v[e] - m);   // a masked logit weighs nothing, a NaN stays one
+    for (int e = 0; e < U * E; ++e) s += v[e] == -INFINITY ? 0.f : exp_nonpositive(v[e] - m);   // a masked logit weighs nothing, a NaN stays one
   }
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
@@ -515,7 +523,8 @@ __device__ __forceinline__ float row_lse(const RowStats& st, size_t row, int lan
 //   none rejected:         log p_{B-1}                 (purpose 2, slot B)
 // into best[s * chunks + chunk]; the workgroup of chunk 0 writes accept_len.  Every workgroup of a sequence repeats the (small)
 // test, so that the sweep over the vocabulary (two logarithms and a 64-bit hash per column) runs on as many CUs as there are:
-// one workgroup per sequence took 124 us for eight sequences of 151936 columns, both stages together now 15 us.
+// one workgroup per sequence took 124 us for eight sequences of 151936 columns, now 11 us and stage 2 3.9; half of it is the
+// arithmetic (a column costs some 600 cycles of a SIMD).
 // A drafted id outside the vocabulary is never accepted.
 __global__ __launch_bounds__(256) void accept_sampling_kernel(const float* __restrict__ p_logits, const float* __restrict__ q_logits,
                                                               RowStats p_stats, RowStats q_stats,
@@ -553,19 +562,32 @@ __global__ __launch_bounds__(256) void accept_sampling_kernel(const float* __res
   const int per = (V + n_chunks - 1) / n_chunks, i0 = min(V, chunk * per), i1 = min(V, i0 + per);
   float bv = -INFINITY;
   int bi = 0x7FFFFFFF;
-  if (a == B - 1) {
-    const float* pr = p_logits + ((size_t)s * B + (B - 1)) * V;
-    const float lp = lse[0][B - 1];
-    for (int i = i0 + threadIdx.x; i < i1; i += 256)
-      argmax_combine(bv, bi, pr[i] * inv_T - lp + gumbel(counter_uniform(key, s, B, 2, (uint32_t)i)), i);
-  } else {
-    const int j = a + 1;
-    const float* pr = p_logits + ((size_t)s * B + j - 1) * V;
-    const float* qr = q_logits + ((size_t)s * B + j) * V;
-    const float lp = lse[0][j - 1], lq = lse[1][j];
-    for (int i = i0 + threadIdx.x; i < i1; i += 256) {
-      const float r = expf(pr[i] * inv_T - lp) - expf(qr[i] * inv_T - lq);
-      if (r > 0.f) argmax_combine(bv, bi, logf(r) + gumbel(counter_uniform(key, s, j, 1, (uint32_t)i)), i);
+  // the columns of U rounds are requested together: one at a time a workgroup's nine rounds were nine trips to memory
+  constexpr int U = 10;
+  const bool all = a == B - 1;
+  const int j = all ? B - 1 : a + 1;   // the draft row (all: not used)
+  const float* pr = p_logits + ((size_t)s * B + (all ? B - 1 : j - 1)) * V;
+  const float* qr = q_logits + ((size_t)s * B + j) * V;
+  const float lp = lse[0][all ? B - 1 : j - 1], lq = lse[1][j];
+  for (int c0 = i0 + threadIdx.x; c0 < i1; c0 += 256 * U) {
+    float p[U], q[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = min(c0 + u * 256, i1 - 1);   // past the end: the last column again, left out below
+      p[u] = pr[i];
+      q[u] = all ? 0.f : qr[i];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = c0 + u * 256;
+      if (i >= i1) break;
+      if (all) {
+        argmax_combine(bv, bi, p[u] * inv_T - lp + gumbel(counter_uniform(key, s, B, 2, (uint32_t)i)), i);
+      } else {
+        const float r = expf(p[u] * inv_T - lp) - expf(q[u] * inv_T - lq);
+        if (r > 0.f) argmax_combine(bv, bi, logf(r) + gumbel(counter_uniform(key, s, j, 1, (uint32_t)i)), i);
+      }
     }
   }
   block_argmax(bv, bi);
