@@ -68,14 +68,35 @@ __global__ __launch_bounds__(256) void embed_kernel(const T* __restrict__ E, con
     if (threadIdx.x == 0) atomicOr(status, DF_STATUS_CAPACITY);
     tok = 0;
   }
+  // eight columns a thread and round, whole rounds' loads together (one column at a time a row of 4096 was sixteen trips to memory)
   const T* src = E + (size_t)tok * D;
   float ss = 0.f;
-  for (int d = threadIdx.x; d < D; d += blockDim.x) {
-    const float v = Store<T>::to(src[d]);
-    h[(size_t)m * D + d] = v;
-    if (fuse.a_out) {
-      Act<T>::store(reinterpret_cast<T*>(fuse.a_out), m, d, D, v * fuse.gain[d]);
-      ss += v * v;
+  constexpr int U = 2;
+  for (int d0 = threadIdx.x * 8; d0 < D; d0 += 256 * 8 * U) {
+    float v[U][8], g[U][8];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int d = min(d0 + u * 2048, D - 8);   // past the end: the last eight again, not stored
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[u][e] = Store<T>::to(src[d + e]);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) g[u][e] = fuse.a_out ? fuse.gain[d + e] : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int d = d0 + u * 2048;
+      if (d >= D) break;
+      float* to = h + (size_t)m * D + d;
+      *reinterpret_cast<float4*>(to) = make_float4(v[u][0], v[u][1], v[u][2], v[u][3]);
+      *reinterpret_cast<float4*>(to + 4) = make_float4(v[u][4], v[u][5], v[u][6], v[u][7]);
+      if (fuse.a_out) {
+#pragma unroll
+        for (int e = 0; e < 8; e += 4)
+          Act<T>::store4(reinterpret_cast<T*>(fuse.a_out), m, d + e, D,
+                         make_float4(v[u][e] * g[u][e], v[u][e + 1] * g[u][e + 1], v[u][e + 2] * g[u][e + 2], v[u][e + 3] * g[u][e + 3]));
+#pragma unroll
+        for (int e = 0; e < 8; ++e) ss += v[u][e] * v[u][e];
+      }
     }
   }
   if (fuse.a_out) {   // uniform over the workgroup
