@@ -450,10 +450,14 @@ struct Engine {
     T* taps = tap >= 0 ? ws<T>(c->ws.taps) : (T*)nullptr;
     const int tap_K = c->rt.n_taps * c->t.d_model;
     if (delta.mix.pos)
-      hipLaunchKernelGGL((rmsnorm_kernel<T, 256, true>), dim3(M), dim3(256), 0, st, base, delta.p, delta.ks, delta.stride, h_out, gain, out, D,
+      hipLaunchKernelGGL((rmsnorm_kernel<T, 512, true>), dim3(M), dim3(512), 0, st, base, delta.p, delta.ks, delta.stride, h_out, gain, out, D,
                          eps, taps, tap, tap_K, delta.mix);
-    else if (D >= 4096)   // one 16-byte chunk per thread: the row's loads are all in flight at once
+    else if (D >= 4096)   // one 16-byte chunk per thread: the row's loads are all in flight at once (2048 columns with 256 and with 512
+                          // threads: a four-layer verification of the routed-expert target at 16 rows 691 and 679.5 us)
       hipLaunchKernelGGL((rmsnorm_kernel<T, 1024>), dim3(M), dim3(1024), 0, st, base, delta.p, delta.ks, delta.stride, h_out, gain, out, D,
+                         eps, taps, tap, tap_K, RowMix{});
+    else if (D >= 2048)
+      hipLaunchKernelGGL((rmsnorm_kernel<T, 512>), dim3(M), dim3(512), 0, st, base, delta.p, delta.ks, delta.stride, h_out, gain, out, D,
                          eps, taps, tap, tap_K, RowMix{});
     else
       hipLaunchKernelGGL((rmsnorm_kernel<T, 256>), dim3(M), dim3(256), 0, st, base, delta.p, delta.ks, delta.stride, h_out, gain, out, D,
