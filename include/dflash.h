@@ -83,7 +83,9 @@ typedef struct {
   int32_t mask_token_id;     /* id whose embedding fills the masked slots */
   void *target_kv_pool;      /* (device) dflash_kv_pool_bytes(target, n_pages) bytes */
   void *draft_kv_pool;       /* (device) dflash_kv_pool_bytes(draft, n_pages) bytes */
-  void *workspace;           /* (device) dflash_workspace_bytes() bytes, 256-byte aligned */
+  void *workspace;           /* (device) dflash_workspace_bytes() bytes, 256-byte aligned.  Between the calls of one step it holds that
+                                step's state; from one step (or prefill) to the next nothing in it has to survive but its first
+                                256 bytes (status and statistics), so contexts may take turns on one buffer */
   size_t workspace_bytes;
 } dflash_runtime;
 

@@ -177,6 +177,9 @@ inline void launch_accept_sampled(hipStream_t st, const float* p_logits, const f
   hipLaunchKernelGGL(accept_sampling_finish_kernel, dim3(S), dim3(64), 0, st, best, chunks, draft, B, accept_len, out_tokens);
 }
 
+// column blocks of the widest launch that finishes its own sums: D columns, four weight tiles a block at least
+inline size_t arrive_counters(size_t D) { return std::max<size_t>(1, D / 64); }
+
 struct Workspace {
   size_t status, arena, h, a, q, o, act, taps, fuse, ht, logits_d, logits_t, part_o, part_ml, stats_p, stats_q, amax, lsep, rope_t, rope_d, ssq, arrive, pf_lens, pf_plens, pf_table, pf_tokens, pf_end_row, pf_end_seq, pf_first, pf_anchor, total;
   size_t moe_sel_e, moe_sel_w, moe_sel_pos, moe_row_of, moe_items, moe_a, moe_act, moe_y;   // routed-expert target only
@@ -231,7 +234,7 @@ Workspace workspace_layout(const dflash_dims& t, const dflash_dims& d, const dfl
   w.rope_t = take((size_t)M * (t.head_dim / 2) * 8);   // rotary tables of the call's rows (target, draft)
   w.rope_d = take((size_t)M * (d.head_dim / 2) * 8);
   w.ssq = take((size_t)M * (D / 16 + 1) * 4);          // pieces of the rows' sums of squares (deferred RMSNorm, few-row path)
-  w.arrive = take(n_max / 16 * kArriveStride * 4);     // arrival counters of the GEMMs' column blocks (finish.h)
+  w.arrive = take(arrive_counters(D) * kArriveStride * 4);   // one per column block of a GEMM that finishes its own sums (finish.h)
   // dflash_prefill: the prompts' lengths and the pseudo-sequence batch of a pass (see prefill_plan_kernel)
   w.pf_lens = take((size_t)rt.max_seqs * 4);
   w.pf_plens = take((size_t)rt.max_seqs * 4);
@@ -385,6 +388,9 @@ struct Engine {
   // deferring 1.1 in the QKV and 0.8 in the gate/up GEMM, for 5.3 us of a normalisation launch saved: even; at 64 rows 5.5, 2.4 and
   // 1.0 for 5.8: 2 % of a step slower.)
   bool few_rows(const dflash_dims& m, int M) const { return std::is_same<T, bf16_t>::value && !m.n_experts && M <= 16 && c->k.fuse > 0; }
+  EmbedArrive arrivals(const dflash_dims& m, int M) {
+    return few_rows(m, M) && c->k.fuse == 1 ? EmbedArrive{ws<unsigned>(c->ws.arrive), (int)arrive_counters(m.d_model)} : EmbedArrive{};
+  }
   // the K-split GEMM [M, N] may finish its own sums: the plan is one that the finishing kernel is built for
   bool finishes(int M, int N, int K) const {
     return c->k.fuse == 1 && stream_plan(c->k, M, N, K, true, arena_rows(c->rt.max_seqs * c->rt.block_size)).nt >= 4;
@@ -610,7 +616,7 @@ struct Engine {
     hipLaunchKernelGGL(embed_kernel<T>, embed_grid(M, d.head_dim), dim3(256), 0, st, reinterpret_cast<const T*>(c->tblob + c->tl.embed), draft_tokens,
                        ws<float>(c->ws.h), d.d_model, d.vocab, status(), b->seq_lens, B, b->max_seq_len, M,
                        RopeTab{ws<float2>(c->ws.rope_d), log((double)d.rope_theta), d.head_dim}, RopeTab{nullptr, 0.0, 0}, ef,
-                       EmbedBlock{b->anchor, draft_tokens, c->rt.mask_token_id});
+                       EmbedBlock{b->anchor, draft_tokens, c->rt.mask_token_id}, arrivals(d, M));
     check();
     for (int i = 0; i < d.n_layers; ++i) {
       const char* lb = l0 + c->dl.lo.end * i;
@@ -648,7 +654,7 @@ struct Engine {
     hipLaunchKernelGGL(embed_kernel<T>, embed_grid(M, t.head_dim + c->d.head_dim), dim3(256), 0, st, reinterpret_cast<const T*>(c->tblob + c->tl.embed), tokens,
                        ws<float>(c->ws.h), t.d_model, t.vocab, status(), b->seq_lens, B, b->max_seq_len, M,
                        RopeTab{ws<float2>(c->ws.rope_t), log((double)t.rope_theta), t.head_dim},
-                       RopeTab{ws<float2>(c->ws.rope_d), log((double)c->d.rope_theta), c->d.head_dim}, ef);
+                       RopeTab{ws<float2>(c->ws.rope_d), log((double)c->d.rope_theta), c->d.head_dim}, ef, EmbedBlock{}, arrivals(t, M));
     check();
     int tap = 0;
     for (int l = 0; l < t.n_layers; ++l) {
@@ -795,7 +801,7 @@ struct Engine {
       hipLaunchKernelGGL(embed_kernel<T>, embed_grid(M, t.head_dim + c->d.head_dim), dim3(256), 0, st, reinterpret_cast<const T*>(c->tblob + c->tl.embed), pp.p_tokens,
                          ws<float>(c->ws.h), t.d_model, t.vocab, status(), pb.seq_lens, B, pb.max_seq_len, M,
                          RopeTab{ws<float2>(c->ws.rope_t), log((double)t.rope_theta), t.head_dim},
-                         RopeTab{ws<float2>(c->ws.rope_d), log((double)c->d.rope_theta), c->d.head_dim}, EmbedFuse{});
+                         RopeTab{ws<float2>(c->ws.rope_d), log((double)c->d.rope_theta), c->d.head_dim}, EmbedFuse{}, EmbedBlock{}, arrivals(t, M));
       check();
       int tap = 0;
       for (int l = 0; l < t.n_layers; ++l) {
@@ -1353,9 +1359,10 @@ int dflash_create(const dflash_dims* target, const void* target_blob, const dfla
   c->tblob = (const char*)target_blob; c->dblob = (const char*)draft_blob; c->wsp = (char*)rt->workspace;
   c->err[0] = 0;
   c->k = knobs;
-  if (hipMemset(c->wsp + ws.status, 0, 256) != hipSuccess || hipMemset(c->wsp + ws.arrive, 0, align256(ws.pf_lens - ws.arrive)) != hipSuccess) {
+  static const char zeros[256] = {};   // copied, not set: a copy from pageable memory is over when the call returns, whatever stream comes next
+  if (hipMemcpy(c->wsp + ws.status, zeros, sizeof zeros, hipMemcpyHostToDevice) != hipSuccess) {
     delete c;
-    return fail(nullptr, DFLASH_EHIP, "create: cannot clear the device status word and the arrival counters");
+    return fail(nullptr, DFLASH_EHIP, "create: cannot clear the device status word");
   }
   *out = c;
   return DFLASH_OK;

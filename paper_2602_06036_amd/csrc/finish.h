@@ -10,7 +10,8 @@
 #pragma once
 #include "common.h"
 
-// Arrival counters are 128 bytes apart (neighbouring ones are hit at the same time); zero before and after every launch.
+// Arrival counters are 128 bytes apart (neighbouring ones are hit at the same time); zero before and after every launch: the call's
+// embed_kernel clears them, each launch leaves them as it found them.
 constexpr int kArriveStride = 32;
 
 struct FinishArgs {

@@ -5,6 +5,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "finish.h"
 
 // ---- block assembly + embedding gather -------------------------------------------------------
 // Rotary table of one model for the rows of a call: out[m * hd/2 + i] = (cos, sin) of pos(m) * theta^(-2i/hd),
@@ -26,6 +27,12 @@ struct EmbedFuse {
   void* a_out = nullptr;
   float* ssq = nullptr;
 };
+// Arrival counters of the GEMMs behind it that finish their own sums (finish.h).  They are zeroed here, at the head of every call that
+// has such GEMMs, so that nothing has to survive in the workspace between calls; for a store per counter, hidden behind the rows.
+struct EmbedArrive {
+  unsigned* counters = nullptr;
+  int n = 0;
+};
 // Drafting: tokens are assembled here, block[s, 0] = anchor[s], block[s, j > 0] = mask_id (Section 4.2: clean anchor + masks),
 // and left in `block`; otherwise (block null) they are read.
 struct EmbedBlock {
@@ -38,7 +45,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void embed_kernel(const T* __restrict__ E, const int32_t* __restrict__ tokens,
                                                     float* __restrict__ h, int D, int vocab, int32_t* status,
                                                     const int32_t* __restrict__ seq_lens, int B, int len_hint, int n_rows, RopeTab t0, RopeTab t1,
-                                                    EmbedFuse fuse = EmbedFuse{}, EmbedBlock blk = EmbedBlock{}) {
+                                                    EmbedFuse fuse, EmbedBlock blk, EmbedArrive arrive) {
   // workgroups M .. of the grid write the rotary tables (angles in double precision take longer than a row's copy): one
   // entry of a table per thread
   if ((int)blockIdx.x >= n_rows) {
@@ -57,6 +64,8 @@ __global__ __launch_bounds__(256) void embed_kernel(const T* __restrict__ E, con
   // the host sized the attention launches of this call for sequences of at most len_hint committed tokens: a longer
   // one would have its last keys left out, so it is reported
   if (threadIdx.x == 0 && seq_lens[m / B] > len_hint) atomicOr(status, DF_STATUS_CAPACITY);
+  if (m == 0)
+    for (int i = threadIdx.x; i < arrive.n; i += 256) arrive.counters[i * kArriveStride] = 0u;
   int tok;
   if (blk.block) {
     tok = m % B == 0 ? blk.anchor[m / B] : blk.mask_id;

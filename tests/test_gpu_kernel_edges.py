@@ -256,6 +256,65 @@ def test_residual_update_by_the_last_workgroup(d, heads, kv_heads, ffn, n_seqs, 
     assert ls.stats["reseeds"] <= 1
 
 
+def _open_on(e, workspace):
+    """The engine's context anew, over another workspace."""
+    import ctypes as C
+    e.close()
+    e.rt.workspace, e.rt.workspace_bytes = workspace.data_ptr(), workspace.numel()
+    h = C.c_void_p()
+    assert e.l.dflash_create(C.byref(e.td), e.target_blob.data_ptr(), C.byref(e.dd), e.draft_blob.data_ptr(), C.byref(e.rt), C.byref(h)) == 0
+    e.ctx = h
+
+
+@pytest.mark.parametrize("block", [16, 5])
+def test_no_call_relies_on_what_the_workspace_held_before(block):
+    """Contexts of one, two and eight sequences of the same models, each by itself and then step by step in turn over one workspace that is
+    filled with ones (NaN, counters far from zero) behind the status block before every prefill, draft and verification: the same bits.  One and two
+    sequences (of the five-row block) take the launches whose last workgroup finishes the sums."""
+    import torch
+    _gpu()
+    import paper_2602_06036_amd as dfl
+    w = tiny_workload(seed=3, n_layers=3, draft_layers=2, vocab=512, block=block, qk_norm=True, kv_heads=2, dtype="bf16", n_seqs=8, taps=(0, 2), ffn=1024)
+    from tests.gpu_harness import GpuModel, _with_seqs
+    wt, wd = si.make_weights(w)
+    prompts = [p[:n] for p, n in zip(si.make_prompts(replace(w, ctx_min=40, ctx_max=40)), (9, 40, 17, 33, 5, 16, 21, 38))]
+    models, blobs = [], None
+    for n in (1, 2, 8):
+        models.append(GpuModel(_with_seqs(w, n), wt, wd, 40 + 6 * block, n_seqs=n, blobs=blobs))
+        blobs = blobs or models[0].blobs()
+
+    def turns(models, before):
+        out = [[] for _ in models]
+        for g, o, n in zip(models, out, (1, 2, 8)):
+            g.host_lens[:] = 0
+            g.seq_lens.zero_()
+            before()
+            o.append(g.prefill_entry(prompts[:n]))
+        for step in range(3):
+            for g, o in zip(models, out):
+                b = g.batch()
+                before()
+                dfl.dflash_draft_block(g.e, b, g.draft_tokens, 0.0, None, g.logits_d)
+                before()
+                dfl.dflash_verify(g.e, b, g.draft_tokens, g.tgt_argmax, g.logits_t)
+                dfl.dflash_accept(g.e, b, g.draft_tokens, g.tgt_argmax, g.accept_len, g.out_tokens)
+                dfl.dflash_kv_commit(g.e, b, g.accept_len, g.out_tokens)
+                o.append((g.logits_d.cpu().numpy().copy(), g.logits_t.cpu().numpy().copy(), g.out_tokens.cpu().numpy().copy()))
+                g.e.device_status()
+                g.host_lens = g.seq_lens.cpu().numpy().astype(np.int64)
+        return out
+
+    alone = turns(models, lambda: None)
+    assert all(np.isfinite(x).all() for o in alone for st in o[1:] for x in st)
+    shared = torch.zeros(max(g.e.rt.workspace_bytes for g in models), dtype=torch.uint8, device="cuda:0")
+    for g in models:
+        _open_on(g.e, shared)
+    for got, want in zip(turns(models, lambda: shared[256:].fill_(255)), alone):
+        assert np.array_equal(got[0], want[0])
+        for a, b in zip(got[1:], want[1:]):
+            assert all(np.array_equal(x, y) for x, y in zip(a, b))
+
+
 @pytest.mark.parametrize("vocab,rows,tiles", STREAM_HEADS)
 def test_streaming_heads_with_eight_six_and_four_weight_tiles(vocab, rows, tiles):
     """LM heads of 16, 32 and 48 rows, high enough for the weight tiles per wavefront that a whole vocabulary takes, with their argmax,
