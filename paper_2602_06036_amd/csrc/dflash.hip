@@ -233,7 +233,7 @@ Workspace workspace_layout(const dflash_dims& t, const dflash_dims& d, const dfl
   w.lsep = take((size_t)M * std::max(2, t.vocab / 16 + 1) * 8);
   w.rope_t = take((size_t)M * (t.head_dim / 2) * 8);   // rotary tables of the call's rows (target, draft)
   w.rope_d = take((size_t)M * (d.head_dim / 2) * 8);
-  w.ssq = take((size_t)M * (D / 16 + 1) * 4);          // pieces of the rows' sums of squares (deferred RMSNorm, few-row path)
+  w.ssq = take((size_t)M * ssq_row(D / 16) * 4);          // pieces of the rows' sums of squares (deferred RMSNorm, few-row path)
   w.arrive = take(arrive_counters(D) * kArriveStride * 4);   // one per column block of a GEMM that finishes its own sums (finish.h)
   // dflash_prefill: the prompts' lengths and the pseudo-sequence batch of a pass (see prefill_plan_kernel)
   w.pf_lens = take((size_t)rt.max_seqs * 4);

@@ -14,12 +14,16 @@
 // embed_kernel clears them, each launch leaves them as it found them.
 constexpr int kArriveStride = 32;
 
+// Pieces of the rows' sums of squares: floats from one row to the next, whole groups of four that are read together (what a row does not
+// use of its last group is never looked at)
+__host__ __device__ constexpr int ssq_row(int parts) { return (parts + 3) & ~3; }
+
 struct FinishArgs {
   unsigned* arrive;         // [column blocks * kArriveStride]
   float* h;                 // [M, N] residual stream, updated in place
   const float* gain_next;   // gain of the RMSNorm that reads the new h
   bf16_t* a_out;            // GEMM operand h * gain_next, row length N
-  float* ssq;               // [M, column blocks] pieces of the rows' sums of squares
+  float* ssq;               // [M, ssq_row(column blocks)] pieces of the rows' sums of squares
   bf16_t* taps;             // nullable: the new h as tapped hidden state `tap_idx` (operand, row length tap_K)
   int tap_idx, tap_K;
 };
@@ -113,6 +117,6 @@ __device__ __forceinline__ void finish_resid(const FinishArgs& f, const float* s
     float q = 0.f;
 #pragma unroll
     for (int c = 0; c < C4; ++c) q += s_q[threadIdx.x * C4 + c];
-    f.ssq[(size_t)threadIdx.x * n_blk + blk] = q;
+    f.ssq[(size_t)threadIdx.x * ssq_row(n_blk) + blk] = q;
   }
 }

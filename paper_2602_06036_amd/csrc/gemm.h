@@ -7,6 +7,7 @@
 
 #include "common.h"
 #include "finish.h"
+#include "plan.h"
 
 // FIN_RESID: the last workgroup of a column block finishes the sum (finish.h)
 enum { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_FIN_RESID = 3 };
@@ -193,32 +194,32 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16_t* __restr
   // here and added behind the sweep (16 threads a row, each every 16th group of four in ascending order, then a fixed shuffle
   // tree); s_rstd is read after the barrier of the cross-wavefront sum.
   __shared__ float s_rstd[16];
-  constexpr int SQ = 4;                       // groups of four that a thread keeps in registers over the sweep
-  const bool deferred = MT == 1 && ep.ssq;    // one band of rows only
-  const bool sq_few = (ep.ssq_parts & 3) == 0 && ep.ssq_parts <= 64 * SQ;
+  constexpr int SQ = kSsqAhead / 64;          // groups of four that a thread keeps in registers over the sweep
+  const bool deferred = MT == 1 && !GRP && ep.ssq;   // dense, one band of rows only
+  const int sq_c = (threadIdx.x & 15) * 4, sq_row = ssq_row(ep.ssq_parts);
+  const float* sq_p = ep.ssq + (size_t)min(mt0 * 16 + ((int)threadIdx.x >> 4), M - 1) * sq_row;
   float4 sq[SQ];
-  if (deferred && sq_few) {
-    const int r = threadIdx.x >> 4, c = threadIdx.x & 15;
+  if (deferred) {
 #pragma unroll
-    for (int i = 0; i < SQ; ++i) {
-      const int p = (c + 16 * i) * 4;
-      sq[i] = *reinterpret_cast<const float4*>(ep.ssq + (size_t)min(mt0 * 16 + r, M - 1) * ep.ssq_parts + min(p, ep.ssq_parts - 4));
-      if (p >= ep.ssq_parts) sq[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    }
+    for (int i = 0; i < SQ; ++i)
+      if (i * 64 < ep.ssq_parts) sq[i] = *reinterpret_cast<const float4*>(sq_p + min(sq_c + i * 64, sq_row - 4));   // uniform condition
   }
   auto rstd_of_rows = [&]() {
-    const int r = threadIdx.x >> 4, c = threadIdx.x & 15;
     float t = 0.f;
-    if (sq_few) {
+    auto add = [&](float4 v, int p) {   // pieces p .. p + 3 of the row
+      v.x = p < ep.ssq_parts ? v.x : 0.f;
+      v.y = p + 1 < ep.ssq_parts ? v.y : 0.f;
+      v.z = p + 2 < ep.ssq_parts ? v.z : 0.f;
+      v.w = p + 3 < ep.ssq_parts ? v.w : 0.f;
+      t += (v.x + v.y) + (v.z + v.w);
+    };
 #pragma unroll
-      for (int i = 0; i < SQ; ++i) t += (sq[i].x + sq[i].y) + (sq[i].z + sq[i].w);
-    } else {
-      const float* pp = ep.ssq + (size_t)min(mt0 * 16 + r, M - 1) * ep.ssq_parts;
-      for (int p = c; p < ep.ssq_parts; p += 16) t += pp[p];
-    }
+    for (int i = 0; i < SQ; ++i)
+      if (i * 64 < ep.ssq_parts) add(sq[i], sq_c + i * 64);
+    for (int p = sq_c + kSsqAhead; p < ep.ssq_parts; p += 64) add(*reinterpret_cast<const float4*>(sq_p + p), p);
 #pragma unroll
     for (int o = 1; o < 16; o <<= 1) t += __shfl_xor(t, o, 64);
-    if (c == 0) s_rstd[r] = 1.0f / sqrtf(t * ep.ssq_inv_D + ep.ssq_eps);
+    if ((threadIdx.x & 15) == 0) s_rstd[threadIdx.x >> 4] = 1.0f / sqrtf(t * ep.ssq_inv_D + ep.ssq_eps);
   };
 
   // Two register buffers, one being multiplied while the other is on its way.  No load inside the loop is

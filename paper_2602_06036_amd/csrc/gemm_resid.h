@@ -16,7 +16,7 @@ struct ResidArgs {
   float* h;                 // [M, N] residual stream, updated in place
   const float* gain_next;   // [N] gain of the RMSNorm that reads the new h (next layer's first norm, or the final norm)
   bf16_t* a_out;            // operand tiles, row length N
-  float* ssq;               // [M, N / 16]
+  float* ssq;               // [M, ssq_row(N / 16)]
   bf16_t* taps;             // nullable: the new h is also stored as tapped hidden state `tap_idx` (operand, row length tap_K)
   int tap_idx, tap_K;
 };
@@ -101,5 +101,5 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_resid_kernel(const bf16_t* 
   *reinterpret_cast<float4*>(ra.h + (size_t)mrow * N + col) = hn;
   Act<bf16_t>::store4(ra.a_out, mrow, col, N, make_float4(hn.x * g4.x, hn.y * g4.y, hn.z * g4.z, hn.w * g4.w));
   if (ra.taps) Act<bf16_t>::store4(ra.taps, mrow, ra.tap_idx * N + col, ra.tap_K, hn);
-  if (g == 0) ra.ssq[(size_t)mrow * gridDim.x + n] = q;
+  if (g == 0) ra.ssq[(size_t)mrow * ssq_row(gridDim.x) + n] = q;
 }

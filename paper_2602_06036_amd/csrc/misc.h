@@ -113,7 +113,7 @@ __global__ __launch_bounds__(256) void embed_kernel(const T* __restrict__ E, con
     ss = wave_reduce_sum(ss);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
     __syncthreads();
-    if (threadIdx.x == 0) fuse.ssq[m] = (part[0] + part[1]) + (part[2] + part[3]);
+    if (threadIdx.x == 0) fuse.ssq[(size_t)m * ssq_row(1)] = (part[0] + part[1]) + (part[2] + part[3]);
   }
 }
 

@@ -89,6 +89,12 @@ inline int arena_rows(int max_rows) { return std::max(1024, 4 * max_rows); }
 
 constexpr int kMaxKSplit = 16;
 
+// Deferred RMSNorm of one band of rows: pieces of a row's sum of squares that the GEMM behind it requests ahead of its sweep.  The unsplit
+// projection leaves one for 16 columns, so this covers rows of 8192; the rest of a longer row is read behind the sweep, in groups of four as well.
+// (With 256 here, and anything else one piece at a time behind the sweep, three-layer verifications of 16 rows took 363 us at width 5120, 359
+// so; 867 and 859 at 8192, 307 and 300 at 4128 (258 pieces), 611 and 601 at 9216; at 4096, whose 256 pieces either takes, 265 and 264.)
+constexpr int kSsqAhead = 512;
+
 // The LDS-staged tiles and what a k tile costs on a CU, in microseconds: `two` with two workgroups of the shape side by
 // side (four-wavefront tiles), `one` with a workgroup by itself; `fixed` per round of workgroups (ramp, prologue, epilogue).
 // Fitted to launches back to back over random operands (16 row counts from 80 to 2048, ten matrices of 2048 to 28672 rows

@@ -15,6 +15,7 @@ DRIVER = r"""
 int main() {
   int M, N, K, split, max_rows;
   const Knobs kn = read_knobs();
+  if (getenv("CONSTANTS")) return printf("%d\n", kSsqAhead), 0;
   while (scanf("%d %d %d %d %d", &M, &N, &K, &split, &max_rows) == 5) {
     const TilePlan t = tile_plan(kn, M, N, K, split != 0, arena_rows(max_rows));
     const StreamPlan s = stream_plan(kn, M, N, K, split != 0, arena_rows(max_rows));
@@ -30,14 +31,17 @@ def plans(tmp_path_factory):
     (d / "plans.cpp").write_text(DRIVER)
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, str(d / "plans.cpp"), "-o", str(d / "plans")], check=True)
 
-    def run(queries, **knobs):
+    def run(queries, constants=False, **knobs):
         """(weight tiles, bands, wavefronts along N, K ranges, rows of a four-band expert tile, weight tiles of the streaming
         kernel, wavefronts of an fp32 column) for each (rows, height, K, may split, rows of the context)."""
         env = {k: v for k, v in os.environ.items() if not k.startswith("DFLASH_")}
         env.update({"DFLASH_" + k: str(v) for k, v in knobs.items()})
+        if constants:
+            env["CONSTANTS"] = "1"
         out = subprocess.run([str(d / "plans")], input="\n".join(" ".join(str(int(x)) for x in q) for q in queries), env=env,
                              capture_output=True, text=True, check=True).stdout
-        return [tuple(int(x) for x in line.split()) for line in out.splitlines()]
+        rows = [tuple(int(x) for x in line.split()) for line in out.splitlines()]
+        return rows[0] if constants else rows
 
     return run
 
@@ -112,3 +116,10 @@ def test_fp32_columns_are_shared_only_where_that_is_faster(plans):
            (4096, 2048, 1), (256, 512, 1), (16384, 1024, 1)]
     got = [p[6] for p in plans([(8, n, k, plain, 8) for n, k, plain in four + one])]
     assert got == [4] * len(four) + [1] * len(one)
+
+
+def test_deferred_norm_requests_the_pieces_of_8192_wide_rows_ahead(plans):
+    """The unsplit projection leaves a piece for 16 columns; rows of up to 8192 are requested ahead of the sweep in whole rounds of 16
+    threads and four pieces."""
+    (ahead,) = plans([], constants=True)
+    assert ahead >= 8192 // 16 and ahead % 64 == 0
