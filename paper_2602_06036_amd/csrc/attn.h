@@ -19,6 +19,8 @@ struct AttnArgs {
   void* out = nullptr;   // MFMA kernels, n_splits == 1: the finished rows go here (GEMM operand, row length Hq*hd), no merge follows
 };
 
+// A row that sees no key is zeros.  A NaN among a row's scores is a NaN in its sum of exponentials whatever else it sees (maxima pass
+// NaN over, sums do not), and the row is NaN, in every kernel and however its context is split.
 // partial results: for pr = (m*Hq + hq)*n_splits + split : ml[pr] = (running max, sum exp), o[pr*hd + d]
 // (o unnormalised, relative to the running max)
 
@@ -79,8 +81,14 @@ __device__ __forceinline__ SimpleRow attn_simple_sweep(const float* qs, const T*
       }
       if (ok) sc = acc * aa.scale;
     }
-    const float tmax = wave_reduce_max(sc);
-    if (tmax == -INFINITY) continue;   // uniform across the wavefront
+    // A tile with nothing to see is left out, one with a NaN is not.  Asked ahead of the maximum, the fp32 kernels come out with 218 registers
+    // and two wavefronts a SIMD (asked of the maximum with 256 and one; two-layer passes of width 256 with 32 to 256 keys: 8 rows 57 us so
+    // and 52 ahead of it, 2048 rows 933 and 664), but the bf16 ones request their V rows late (64 rows, head dim 96: 86 and 91).  There the maximum is
+    // asked, in which a NaN then has to show.
+    constexpr bool ask_first = sizeof(T) == 4;
+    if (ask_first && __builtin_amdgcn_ballot_w64(!(sc == -INFINITY)) == 0ull) continue;
+    const float tmax = wave_reduce_max(!ask_first && sc != sc ? INFINITY : sc);
+    if (!ask_first && tmax == -INFINITY) continue;   // uniform across the wavefront
     const float m_new = fmaxf(row.m_run, tmax);
     const float corr = (row.m_run == -INFINITY) ? 0.f : expf(row.m_run - m_new);
     const float p = ok ? expf(sc - m_new) : 0.f;
@@ -170,7 +178,7 @@ __global__ __launch_bounds__(256) void attn_short_simple_kernel(const T* __restr
     L += ml.y * e;
     x += e * so[w][d];
   }
-  Act<T>::store(out, m, hq * hd + d, aa.n_q_heads * hd, L > 0.f ? x / L : 0.f);
+  Act<T>::store(out, m, hq * hd + d, aa.n_q_heads * hd, L == 0.f ? 0.f : x / L);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -223,7 +231,7 @@ __global__ __launch_bounds__(128) void attn_merge_rows_kernel(const float* __res
     }
     for (; c < n_splits; ++c) o += wgt[c] * po[(size_t)c * hd];
     const float L = s_L;
-    Act<T>::store(out, m, hq * hd + d, n_q_heads * hd, L > 0.f ? o / L : 0.f);
+    Act<T>::store(out, m, hq * hd + d, n_q_heads * hd, L == 0.f ? 0.f : o / L);
   }
 }
 
@@ -292,6 +300,6 @@ __global__ __launch_bounds__(512) void attn_merge_kernel(const float* __restrict
   if (live) {
     const float L = s_L[r];
     Act<T>::store4(out, m, hq * hd + c * 4, n_q_heads * hd,
-                   L > 0.f ? make_float4(o.x / L, o.y / L, o.z / L, o.w / L) : make_float4(0.f, 0.f, 0.f, 0.f));
+                   L == 0.f ? make_float4(0.f, 0.f, 0.f, 0.f) : make_float4(o.x / L, o.y / L, o.z / L, o.w / L));
   }
 }

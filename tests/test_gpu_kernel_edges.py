@@ -285,6 +285,55 @@ def test_deferred_norm_of_wide_rows(d, ffn):
     assert ls.stats["reseeds"] <= 1
 
 
+@pytest.mark.parametrize("dtype,hd,heads,kv_heads,n_seqs,block,ctx,wgs,wide_from", [
+    ("bf16", 128, 4, 2, 3, 16, 150, 1, 64),         # key-split kernel, whole contexts
+    ("bf16", 128, 4, 2, 3, 16, 150, 256, 64),       # ... and split, merged row by row
+    ("bf16", 128, 4, 2, 9, 16, 150, 256, 64),       # ... merged in bands of rows
+    ("bf16", 64, 8, 2, 3, 16, 150, 1, 100000),      # row-split kernel, whole and split
+    ("bf16", 64, 8, 2, 3, 16, 150, 256, 100000),
+    ("bf16", 96, 4, 4, 3, 8, 150, 256, 512),        # the plain kernels: one workgroup a row ...
+    ("f32", 64, 4, 4, 3, 8, 150, 256, 512),
+    ("f32", 64, 4, 4, 3, 8, 300, 256, 512),         # ... splits
+    ("f32", 64, 4, 4, 3, 8, 300, 1, 512),
+])
+@pytest.mark.parametrize("poisoned", ["one key", "all keys"])
+def test_nan_scores_make_a_row_nan_however_its_context_is_split(dtype, hd, heads, kv_heads, n_seqs, block, ctx, wgs, wide_from, poisoned, monkeypatch):
+    """A cached key (or every one) of sequence 0 is NaN in the first layer: all its logits are NaN, as a softmax over them is; the other sequences keep
+    their bits."""
+    monkeypatch.setenv("DFLASH_ATTN_TARGET_WGS", str(wgs))
+    monkeypatch.setenv("DFLASH_ATTN_WIDE_MIN_CHUNK", str(wide_from))
+    import torch
+    _gpu()
+    import paper_2602_06036_amd as dfl
+    from paper_2602_06036_amd import binding as Bd
+    from tests.gpu_harness import GpuModel
+    w = tiny_workload(seed=ctx + hd, n_layers=2, draft_layers=1, vocab=256, block=block, qk_norm=True, kv_heads=kv_heads, dtype=dtype, n_seqs=n_seqs,
+                      taps=(0,), d=256, heads=heads, hd=hd, ffn=256)
+    g = GpuModel(w, *si.make_weights(w), ctx + 2 * block)
+    lens = [ctx] + [(13, 64, 33, ctx - 1)[i % 4] for i in range(n_seqs - 1)]
+    rng = np.random.default_rng(1)
+    g.host_lens = np.array(lens, dtype=np.int64)
+    g.seq_lens.copy_(torch.tensor(lens, dtype=torch.int32))
+    for s, n in enumerate(lens):
+        for l in range(2):
+            g.write_kv(Bd.DFLASH_POOL_TARGET, l, s, 0, *(rng.standard_normal((n, kv_heads, hd)).astype(np.float32) for _ in range(2)))
+    tokens = torch.from_numpy(rng.integers(0, 255, (n_seqs, block)).astype(np.int32)).cuda()
+
+    def logits():
+        dfl.dflash_verify(g.e, g.batch(), tokens, None, g.logits_t)
+        g.e.device_status()
+        return g.logits_t.cpu().numpy().copy()
+
+    sound = logits()
+    assert np.isfinite(sound).all()
+    at, n = (77, 1) if poisoned == "one key" else (0, ctx)
+    bad = np.full((n, kv_heads, hd), np.nan, dtype=np.float32)
+    g.write_kv(Bd.DFLASH_POOL_TARGET, 0, 0, at, bad, rng.standard_normal(bad.shape).astype(np.float32))
+    got = logits()
+    assert np.isnan(got[0]).all()
+    assert np.array_equal(got[1:], sound[1:])
+
+
 def _open_on(e, workspace):
     """The engine's context anew, over another workspace."""
     import ctypes as C
