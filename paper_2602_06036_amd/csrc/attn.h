@@ -31,11 +31,17 @@ struct AttnArgs {
 // key for the scores and one or two head dims for P.V; the 64 V rows of a tile are requested together, four keys a load,
 // before their weights are known (8 rows, 136 keys, 4 heads of 64, fp32: 35.9 us with one dependent load per key, 8.9 us like this).
 // ------------------------------------------------------------------------------------------------
+// 4 consecutive keys of one head dim of a page, as they are stored.  (As floats a tile's V rows took 128 registers of bf16 kernels too and
+// were waited for one by one to be converted; with the sweep in a function of its own those kernels then came out with 257 registers and one
+// wavefront a SIMD: 512 rows, 4 heads of 96, 2000 keys 680 us a two-layer pass before, 1220 with one wavefront, 443 like this; 64 rows
+// 148, 197 and 131.)
+template <typename T> struct Keys4 { using Raw = float4; };
+template <> struct Keys4<bf16_t> { using Raw = ushort4; };
 template <typename T>
-__device__ __forceinline__ float4 load_keys4(const T* p) {   // 4 consecutive keys of one head dim of a page
-  if constexpr (sizeof(T) == 4) return *reinterpret_cast<const float4*>(p);
-  const ushort4 u = *reinterpret_cast<const ushort4*>(p);
-  return make_float4(Store<T>::to(u.x), Store<T>::to(u.y), Store<T>::to(u.z), Store<T>::to(u.w));
+__device__ __forceinline__ typename Keys4<T>::Raw load_keys4(const T* p) { return *reinterpret_cast<const typename Keys4<T>::Raw*>(p); }
+__device__ __forceinline__ float4 keys4_to_float(float4 v) { return v; }
+__device__ __forceinline__ float4 keys4_to_float(ushort4 u) {
+  return make_float4(Store<bf16_t>::to(u.x), Store<bf16_t>::to(u.y), Store<bf16_t>::to(u.z), Store<bf16_t>::to(u.w));
 }
 
 // One wavefront's sweep of a query row (in LDS, qs) over the 64-key tiles first, first + step, ... below c1: running max, sum of
@@ -58,7 +64,7 @@ __device__ __forceinline__ SimpleRow attn_simple_sweep(const float* qs, const T*
     const bool ok = vis && page_ok;
     const int any_page = page_ok ? page : 0;     // a page that may be read; keys behind it then weigh nothing
     // the tile's V rows (t0 is a multiple of 64: four whole pages), on their way while the scores are computed
-    float4 v0[16], v1[16];
+    typename Keys4<T>::Raw v0[16], v1[16];
 #pragma unroll
     for (int pg = 0; pg < 4; ++pg) {
       const T* vb = pool + kv_head_base(aa.layer, geo.n_pages, __builtin_amdgcn_readlane(any_page, pg * 16), aa.n_kv_heads, kvh, hd) + DF_PAGE * hd;
@@ -82,8 +88,8 @@ __device__ __forceinline__ SimpleRow attn_simple_sweep(const float* qs, const T*
       if (ok) sc = acc * aa.scale;
     }
     // A tile with nothing to see is left out, one with a NaN is not.  Asked ahead of the maximum, the fp32 kernels come out with 218 registers
-    // and two wavefronts a SIMD (asked of the maximum with 256 and one; two-layer passes of width 256 with 32 to 256 keys: 8 rows 57 us so
-    // and 52 ahead of it, 2048 rows 933 and 664), but the bf16 ones request their V rows late (64 rows, head dim 96: 86 and 91).  There the maximum is
+    // (asked of the maximum with 256 and one wavefront a SIMD; two-layer passes of width 256 with 32 to 256 keys: 8 rows 57 us so and 52 ahead of
+    // it, 2048 rows 933 and 664), but the bf16 ones load their K rows one by one (64 rows, head dim 96: 82 and 88).  There the maximum is
     // asked, in which a NaN then has to show.
     constexpr bool ask_first = sizeof(T) == 4;
     if (ask_first && __builtin_amdgcn_ballot_w64(!(sc == -INFINITY)) == 0ull) continue;
@@ -101,9 +107,11 @@ __device__ __forceinline__ SimpleRow attn_simple_sweep(const float* qs, const T*
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const float p0 = __shfl(p, 4 * i, 64), p1 = __shfl(p, 4 * i + 1, 64), p2 = __shfl(p, 4 * i + 2, 64), p3 = __shfl(p, 4 * i + 3, 64);
-      add(row.o0, p0, v0[i].x); add(row.o0, p1, v0[i].y); add(row.o0, p2, v0[i].z); add(row.o0, p3, v0[i].w);
+      const float4 a = keys4_to_float(v0[i]);
+      add(row.o0, p0, a.x); add(row.o0, p1, a.y); add(row.o0, p2, a.z); add(row.o0, p3, a.w);
       if (hd > 64) {
-        add(row.o1, p0, v1[i].x); add(row.o1, p1, v1[i].y); add(row.o1, p2, v1[i].z); add(row.o1, p3, v1[i].w);
+        const float4 b = keys4_to_float(v1[i]);
+        add(row.o1, p0, b.x); add(row.o1, p1, b.y); add(row.o1, p2, b.z); add(row.o1, p3, b.w);
       }
     }
   }
@@ -111,7 +119,7 @@ __device__ __forceinline__ SimpleRow attn_simple_sweep(const float* qs, const T*
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void attn_partial_simple_kernel(const T* __restrict__ q, const T* __restrict__ pool,
+__global__ __launch_bounds__(256, 2) void attn_partial_simple_kernel(const T* __restrict__ q, const T* __restrict__ pool,
                                                                   SeqGeom geo, AttnArgs aa, float* __restrict__ part_o,
                                                                   float2* __restrict__ part_ml) {
   const int split = blockIdx.x, kvh = (int)blockIdx.y % aa.n_kv_heads, s = blockIdx.z;
@@ -147,7 +155,7 @@ __global__ __launch_bounds__(256) void attn_partial_simple_kernel(const T* __res
 // Short contexts (short_context in plan.h): a workgroup per query row, its four wavefronts share the keys and merge in LDS, and the row
 // is finished: 8.7 us at 136 keys, 8 rows, 4 heads of 64, against 9.6 and a merge launch of 3.6.  grid (B * group, Hkv, S).
 template <typename T>
-__global__ __launch_bounds__(256) void attn_short_simple_kernel(const T* __restrict__ q, const T* __restrict__ pool, SeqGeom geo, AttnArgs aa,
+__global__ __launch_bounds__(256, 2) void attn_short_simple_kernel(const T* __restrict__ q, const T* __restrict__ pool, SeqGeom geo, AttnArgs aa,
                                                                 T* __restrict__ out) {
   const int kvh = blockIdx.y, s = blockIdx.z;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
