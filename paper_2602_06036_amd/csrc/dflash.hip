@@ -1117,9 +1117,9 @@ void Engine<T>::attention(const dflash_dims& m, const T* pool, int layer, const 
   aa.n_q_heads = m.n_q_heads; aa.n_kv_heads = m.n_kv_heads; aa.head_dim = m.head_dim; aa.layer = layer;
   aa.causal = causal ? 1 : 0; aa.chunk = p.chunk; aa.n_splits = p.n_splits; aa.scale = 1.0f / sqrtf((float)m.head_dim);
   aa.q_shift = q_shift;
-  // one split per sequence: the MFMA kernels write the O projection's operand themselves; so does the plain one for short contexts
+  // one split per sequence: the MFMA kernels write the O projection's operand themselves; so does the plain one for few rows with short contexts
   const bool mfma = attn_takes_mfma<T>(aa, B);
-  const bool direct = mfma ? p.n_splits == 1 : short_context(max_tokens);
+  const bool direct = mfma ? p.n_splits == 1 : short_context(M * m.n_q_heads, m.head_dim, max_tokens, sizeof(T) == 2);
   if (direct) aa.out = ws<T>(c->ws.o);
   float* part_o = ws<float>(c->ws.part_o);
   float2* part_ml = ws<float2>(c->ws.part_ml);

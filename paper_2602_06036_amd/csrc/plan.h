@@ -235,10 +235,20 @@ inline bool split_f32_columns(int cols, int K, bool swiglu) { return K >= 1024 &
 // 235 and 229, 32 311 and 320; width 2048, 8 rows 402 and 415, 16 557 and 600.
 inline bool fold_norm(int M, int D) { return M * D <= 16384 && D <= 1024; }
 
-// fp32: whether a query row's keys are few enough for one workgroup without splits (attn_short_simple_kernel): a 64-key tile for
-// each of its wavefronts.  The same step with splits and a merge launch, and without: 136 keys 131 and 122 us, 116 keys and 32 rows 230 and
-// 220, 216 keys and 64 rows 326 and 320; two tiles a wavefront lose, 316 keys 164 and 170, 508 keys and 32 rows 231 and 238.
-inline bool short_context(int max_tokens) { return max_tokens <= 256; }
+// Plain attention kernels: whether a query row's keys are few enough for one workgroup without splits (attn_short_simple_kernel): at most
+// a 64-key tile for each of its wavefronts.  `rows`: query rows of all heads, a workgroup each.  They read every key once a row, and with up to 64 keys
+// three of four wavefronts have none, so they are for launches that leave the chip room; larger heads fill it sooner.  Two-layer passes with
+// splits and a merge launch, and without, at 32, 128 and 256 keys.  fp32: 256 rows of 64 dims 73 and 65, 72 and 66, 74 and 69 us; 512 96 and 86,
+// 98 and 89, 101 and 93; 1024 127 and 125, 128 and 129, 139 and 135; 2048 187 and 202, 197 and 207, 210 and 217; 8192 561 and 660, 597 and 677,
+// 658 and 705; of 128 dims 512 158 and 152, 159 and 156, 163 and 167; 1024 242 and 248, 247 and 257, 260 and 272.
+// bf16: 512 rows of 96 dims 102 and 92, 103 and 96, 107 and 97; 1024 104 and 106, 108 and 109, 122 and 115; 2048 115 and 136, 128 and 137, 146
+// and 146; of 32 dims 1024 95 and 88, 99 and 90, 107 and 92; 2048 98 and 107, 109 and 110, 126 and 113; 4096 112 and 144, 130 and 150, 165 and 154;
+// of 48 dims 2048 108 and 123, 119 and 128, 135 and 130; 4096 125 and 171, 139 and 175, 170 and 180.  (From three tiles of keys on the splits take more
+// than one each.)  Two tiles a wavefront lose (fp32, 316 keys 164 and 170, 508 keys and 32 rows 231 and 238).
+inline bool short_context(int rows, int head_dim, int max_tokens, bool bf16) {
+  const int limit = !bf16 ? 1 << 16 : max_tokens <= 128 ? 512 * 112 : 1 << 17;
+  return max_tokens <= 256 && (long long)rows * head_dim <= limit;
+}
 
 // Weight rows per tile of a four-band routed-expert item: 256 (eight wavefronts), or 128 (four) for the short matrices of an odd
 // number of 128-row blocks, where the half-empty last 256-row block is a twelfth of the launch or more.  `nt`: 16-row bands of

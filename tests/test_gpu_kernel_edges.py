@@ -334,6 +334,25 @@ def test_nan_scores_make_a_row_nan_however_its_context_is_split(dtype, hd, heads
     assert np.array_equal(got[1:], sound[1:])
 
 
+@pytest.mark.parametrize("dtype,hd,n_seqs,lens", [
+    ("f32", 64, 32, (9, 40, 64, 1)),        # 1024 query rows: a workgroup each
+    ("f32", 64, 33, (9, 40, 64, 1)),        # 1056: splits, merged in bands of rows
+    ("bf16", 96, 19, (9, 90, 64, 1)),       # 608 of 96 dims: splits
+    ("bf16", 96, 19, (9, 150, 64, 1)),      # ... a workgroup each from three tiles of keys on
+])
+def test_plain_attention_on_both_sides_of_its_row_limit(dtype, hd, n_seqs, lens):
+    w = tiny_workload(seed=hd + n_seqs, n_layers=2, draft_layers=1, vocab=256, block=8, qk_norm=True, kv_heads=2, dtype=dtype, n_seqs=n_seqs, taps=(0,), d=256,
+                      heads=4, hd=hd, ffn=256)
+    prompts = [p[:lens[i % 4]] for i, p in enumerate(si.make_prompts(replace(w, ctx_min=max(lens), ctx_max=max(lens))))]
+    ls = Lockstep(w, prompts, max_len=max(lens) + 24)
+    ls.prefill()
+    for i, plan in enumerate((None, [(3 * s + 1) % 8 for s in range(n_seqs)])):
+        ls.step(plan=plan, step_idx=i)
+    ls.check_cache([0, 1], [0])
+    assert ls.stats["low_margin_flips"] <= 0.02 * ls.stats["rows"] + 2
+    assert ls.stats["reseeds"] <= 1
+
+
 def _open_on(e, workspace):
     """The engine's context anew, over another workspace."""
     import ctypes as C

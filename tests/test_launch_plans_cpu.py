@@ -19,7 +19,8 @@ int main() {
   while (scanf("%d %d %d %d %d", &M, &N, &K, &split, &max_rows) == 5) {
     const TilePlan t = tile_plan(kn, M, N, K, split != 0, arena_rows(max_rows));
     const StreamPlan s = stream_plan(kn, M, N, K, split != 0, arena_rows(max_rows));
-    printf("%d %d %d %d %d %d %d\n", t.t->wn, t.t->wm, t.t->wy, t.ks, half_height_expert_tiles(N / 16) ? 128 : 256, s.nt, split_f32_columns(N, K, !split) ? 4 : 1);
+    printf("%d %d %d %d %d %d %d %d\n", t.t->wn, t.t->wm, t.t->wy, t.ks, half_height_expert_tiles(N / 16) ? 128 : 256, s.nt, split_f32_columns(N, K, !split) ? 4 : 1,
+           short_context(M, K, N, split != 0));
   }
 }
 """
@@ -33,7 +34,8 @@ def plans(tmp_path_factory):
 
     def run(queries, constants=False, **knobs):
         """(weight tiles, bands, wavefronts along N, K ranges, rows of a four-band expert tile, weight tiles of the streaming
-        kernel, wavefronts of an fp32 column) for each (rows, height, K, may split, rows of the context)."""
+        kernel, wavefronts of an fp32 column, whether M query rows of K dims (of bf16, with 'may split') with N
+        keys go without splits) for each (rows, height, K, may split, rows of the context)."""
         env = {k: v for k, v in os.environ.items() if not k.startswith("DFLASH_")}
         env.update({"DFLASH_" + k: str(v) for k, v in knobs.items()})
         if constants:
@@ -123,3 +125,12 @@ def test_deferred_norm_requests_the_pieces_of_8192_wide_rows_ahead(plans):
     threads and four pieces."""
     (ahead,) = plans([], constants=True)
     assert ahead >= 8192 // 16 and ahead % 64 == 0
+
+
+def test_plain_attention_goes_without_splits_where_that_is_faster(plans):
+    """(query rows of all heads, head dim, keys, bf16) as measured both ways."""
+    whole = [(32, 64, 24, 0), (32, 64, 256, 0), (256, 64, 32, 0), (512, 64, 128, 0), (1024, 64, 32, 0), (512, 128, 128, 0), (512, 96, 32, 1), (512, 96, 256, 1),
+             (1024, 32, 32, 1), (1024, 96, 144, 1), (2048, 32, 208, 1), (4096, 32, 256, 1), (2048, 48, 256, 1)]
+    split = [(32, 64, 257, 0), (512, 96, 272, 1), (2048, 64, 32, 0), (2048, 64, 256, 0), (8192, 64, 64, 0), (1024, 128, 128, 0), (1024, 96, 32, 1), (2048, 32, 32, 1),
+             (2048, 96, 128, 1), (2048, 48, 128, 1), (4096, 48, 176, 1), (8192, 96, 256, 1), (16384, 128, 64, 0), (1 << 26, 128, 64, 1)]
+    assert [p[7] for p in plans([(r, k, d, bf, 8) for r, d, k, bf in whole + split])] == [1] * len(whole) + [0] * len(split)
