@@ -438,7 +438,7 @@ struct Engine {
     const int M = b->n_seqs * blk(b), D = m.d_model;
     const int nqkv = (m.n_q_heads + 2 * m.n_kv_heads) * m.head_dim;
     EpiArgs ep{ws<float>(c->ws.arena), nqkv, 0, nullptr, 0};
-    const T* a = operand(reinterpret_cast<const float*>(lbase + lo.g1), m.rms_eps, M, D, ep, m);
+    const T* a = operand(reinterpret_cast<const float*>(lbase + lo.g1), m.rms_eps, M, D, nqkv, ep, m);
     const Slab qs = gemm(reinterpret_cast<const T*>(lbase + lo.wqkv), a, M, nqkv, D, EPI_STORE, ep);
     hipLaunchKernelGGL(qkv_post_kernel<T>, dim3(M, (m.n_q_heads + 2 * m.n_kv_heads + 3) / 4), dim3(256), 0, st, qs.p, nqkv,
                        reinterpret_cast<const float*>(lbase + lo.qn), reinterpret_cast<const float*>(lbase + lo.kn), ws<T>(c->ws.q), pool, geom(b),
@@ -486,10 +486,10 @@ struct Engine {
     check();
     amax_parts = 0;
   }
-  // operand of the GEMM behind an RMSNorm of the residual stream: ws.a, normalised here unless the norm is deferred into that GEMM
-  // already; fp32 models of few rows hand over the residual stream itself and the gain (nothing is pending there)
-  const T* operand(const float* gain, float eps, int M, int D, EpiArgs& ep, const dflash_dims& m) {
-    if (std::is_same<T, float>::value && fold_norm(M, D)) {
+  // operand of the GEMM (of `cols` activation columns) behind an RMSNorm of the residual stream: ws.a, normalised here unless the norm is
+  // deferred into that GEMM already; small fp32 products get the residual stream itself and the gain (nothing is pending there)
+  const T* operand(const float* gain, float eps, int M, int D, int cols, EpiArgs& ep, const dflash_dims& m) {
+    if (std::is_same<T, float>::value && fold_norm(M, D, cols)) {
       ep.norm_gain = gain;
       ep.norm_eps = eps;
       return ws<T>(c->ws.h);
@@ -531,11 +531,11 @@ struct Engine {
       pending = moe_ffn(m, lbase, lo, M);
     } else {
       EpiArgs gu{nullptr, 0, 0, act, m.d_ffn}, down{h, D, 0, nullptr, 0};
-      const T* a = operand(g2, m.rms_eps, M, D, gu, m);
+      const T* a = operand(g2, m.rms_eps, M, D, m.d_ffn, gu, m);
       gemm(reinterpret_cast<const T*>(lbase + lo.wgu), a, M, 2 * m.d_ffn, D, EPI_SWIGLU, gu);
       if (few && gain_next && c->k.fuse == 2) return resid(wd, act, M, D, m.d_ffn, gain_next, tap);
       if (few && gain_next && finishes(M, D, m.d_ffn)) return resid_split(wd, act, M, D, m.d_ffn, gain_next, tap);
-      if (std::is_same<T, float>::value && fold_norm(M, D) && tap >= 0) {   // no norm launch behind the layer that could take it
+      if (std::is_same<T, float>::value && small_f32(M, D) && tap >= 0) {   // there may be no norm launch behind the layer that could take it
         down.tap = ws<float>(c->ws.taps) + (size_t)tap * D;
         down.tap_K = c->rt.n_taps * D;
         tap = -1;
@@ -579,7 +579,7 @@ struct Engine {
     const dflash_dims& t = c->t;
     EpiArgs ep{logits, t.vocab, 0, nullptr, 0};
     ep.out2 = logits_to;
-    const T* a = operand(final_gain, eps, M, t.d_model, ep, t);
+    const T* a = operand(final_gain, eps, M, t.d_model, t.vocab, ep, t);
     ep.amax = ws<float2>(c->ws.amax);
     ep.amax_mode = mode;
     ep.amax_inv_T = inv_T;
@@ -739,7 +739,7 @@ struct Engine {
     EpiArgs ep{arena, nkv, 0, nullptr, 0};
     const float* gc = reinterpret_cast<const float*>(c->dblob + c->dl.gc);
     const T* a = ht;
-    if (std::is_same<T, float>::value && fold_norm(M, D)) {
+    if (std::is_same<T, float>::value && fold_norm(M, D, nkv)) {
       ep.norm_gain = gc;
       ep.norm_eps = d.rms_eps;
       a = ws<T>(c->ws.fuse);

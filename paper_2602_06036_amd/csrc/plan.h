@@ -229,11 +229,17 @@ inline StreamPlan stream_plan(const Knobs& kn, int M, int N, int K, bool split, 
 // four are faster.
 inline bool split_f32_columns(int cols, int K, bool swiglu) { return K >= 1024 && cols <= std::min(swiglu ? K / 2 : K / 4 * 3, 1536); }
 
-// fp32: whether the GEMM behind an RMSNorm of `D` columns takes the norm along (gemm_f32_kernel, NORM) instead of a launch for it: while
-// the products are so small that they are launches more than work.  Steps of 2 + 1 layer models, with launches and taken along: width 256,
-// 8 rows 154 and 121 us, 32 159 and 147, 64 191 and 185; width 512, 8 rows 154 and 140, 32 204 and 197; width 1024, 8 rows 197 and 187, 16
-// 235 and 229, 32 311 and 320; width 2048, 8 rows 402 and 415, 16 557 and 600.
-inline bool fold_norm(int M, int D) { return M * D <= 16384 && D <= 1024; }
+// fp32: passes whose products are so small that they are launches more than work
+inline bool small_f32(int M, int D) { return M * D <= 16384 && D <= 1024; }
+
+// fp32: whether the GEMM of `cols` (activation) columns behind an RMSNorm of `D` takes the norm along (gemm_f32_kernel, NORM) instead of a launch for it.
+// Every workgroup then forms the rows' sums of squares for itself, which costs 17, 22 and 55 us a million rows x columns at width 256, 512 and
+// 1024, and a launch is worth 2 to 3.5.  Steps of 2 + 1 layer models with a vocabulary of 1024, with launches and taken along: width 256, 8
+// rows 154 and 121 us, 32 159 and 147, 64 191 and 185; width 512, 8 rows 154 and 140, 32 204 and 197; width 1024, 8 rows 197 and 187, 16
+// 235 and 229, 32 311 and 320; width 2048, 8 rows 402 and 415, 16 557 and 600.  Verifications of two layers, all with launches and all taken along: width
+// 256, vocabulary 8192, 8 rows 87 and 80, 64 rows 142 and 143; 32768, 8 rows 96 and 91, 32 rows 154 and 163; 151936, 8 rows 159 and 169, 64 rows 694 and
+// 856; width 1024, 8 rows, 8192 131 and 130, 32768 165 and 172, 151936 372 and 441.
+inline bool fold_norm(int M, int D, int cols) { return small_f32(M, D) && (long long)M * D * cols <= 1 << 25; }
 
 // Plain attention kernels: whether a query row's keys are few enough for one workgroup without splits (attn_short_simple_kernel): at most
 // a 64-key tile for each of its wavefronts.  `rows`: query rows of all heads, a workgroup each.  They read every key once a row, and with up to 64 keys

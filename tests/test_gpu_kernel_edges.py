@@ -182,10 +182,11 @@ def test_forced_tiles_over_ragged_sizes(n_seqs, ffn, vocab, wide, tile, wm, ks, 
 
 @pytest.mark.parametrize("d,heads,kv_heads,hd,ffn,vocab,n_seqs,block,lens", [
     (256, 4, 4, 64, 1024, 1024, 1, 2, (5,)),              # two rows
-    (256, 4, 2, 64, 1024, 8192, 3, 7, (63, 64, 130)),     # 21 rows: a last piece of five; the longest row that one workgroup searches
+    (256, 4, 2, 64, 1024, 8192, 3, 7, (63, 64, 130)),     # 21 rows: a last piece of five; the longest row that one workgroup searches; a launch before the head
     (256, 4, 4, 64, 512, 8208, 3, 8, (9, 233, 240)),      # 24 rows and 256 keys at first, more behind: one workgroup, then splits
     (256, 4, 4, 64, 512, 512, 9, 7, (20, 31, 8, 90, 64, 1, 3, 5, 7)),   # 63 rows
     (256, 4, 1, 64, 512, 512, 5, 13, (20, 31, 8, 90, 64)),              # 65 rows: norm launches
+    (256, 4, 4, 64, 2064, 512, 8, 8, (20, 31, 8, 90, 64, 1, 3, 5)),     # 64 rows: launches in front of the gate/up products only
     (1024, 4, 1, 128, 256, 640, 2, 8, (17, 120)),         # 16 rows; four wavefronts a column in SwiGLU products; head dim 128
     (1024, 4, 1, 128, 256, 640, 1, 7, (33,)),             # ... and in plain ones
 ])

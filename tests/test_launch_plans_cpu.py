@@ -19,8 +19,8 @@ int main() {
   while (scanf("%d %d %d %d %d", &M, &N, &K, &split, &max_rows) == 5) {
     const TilePlan t = tile_plan(kn, M, N, K, split != 0, arena_rows(max_rows));
     const StreamPlan s = stream_plan(kn, M, N, K, split != 0, arena_rows(max_rows));
-    printf("%d %d %d %d %d %d %d %d\n", t.t->wn, t.t->wm, t.t->wy, t.ks, half_height_expert_tiles(N / 16) ? 128 : 256, s.nt, split_f32_columns(N, K, !split) ? 4 : 1,
-           short_context(M, K, N, split != 0));
+    printf("%d %d %d %d %d %d %d %d %d\n", t.t->wn, t.t->wm, t.t->wy, t.ks, half_height_expert_tiles(N / 16) ? 128 : 256, s.nt, split_f32_columns(N, K, !split) ? 4 : 1,
+           short_context(M, K, N, split != 0), fold_norm(M, K, N));
   }
 }
 """
@@ -35,7 +35,7 @@ def plans(tmp_path_factory):
     def run(queries, constants=False, **knobs):
         """(weight tiles, bands, wavefronts along N, K ranges, rows of a four-band expert tile, weight tiles of the streaming
         kernel, wavefronts of an fp32 column, whether M query rows of K dims (of bf16, with 'may split') with N
-        keys go without splits) for each (rows, height, K, may split, rows of the context)."""
+        keys go without splits, whether the norm of K columns goes with the N columns behind it) for each (rows, height, K, may split, rows of the context)."""
         env = {k: v for k, v in os.environ.items() if not k.startswith("DFLASH_")}
         env.update({"DFLASH_" + k: str(v) for k, v in knobs.items()})
         if constants:
@@ -134,3 +134,11 @@ def test_plain_attention_goes_without_splits_where_that_is_faster(plans):
     split = [(32, 64, 257, 0), (512, 96, 272, 1), (2048, 64, 32, 0), (2048, 64, 256, 0), (8192, 64, 64, 0), (1024, 128, 128, 0), (1024, 96, 32, 1), (2048, 32, 32, 1),
              (2048, 96, 128, 1), (2048, 48, 128, 1), (4096, 48, 176, 1), (8192, 96, 256, 1), (16384, 128, 64, 0), (1 << 26, 128, 64, 1)]
     assert [p[7] for p in plans([(r, k, d, bf, 8) for r, d, k, bf in whole + split])] == [1] * len(whole) + [0] * len(split)
+
+
+def test_fp32_norms_go_with_the_products_that_are_cheaper_for_it(plans):
+    """(rows, activation columns, width) as measured both ways: a head of a large vocabulary pays for the norm in every workgroup."""
+    along = [(8, 768, 256), (8, 8192, 256), (64, 1024, 256), (32, 2048, 512), (8, 3072, 1024), (16, 1024, 1024)]
+    launch = [(64, 8192, 256), (32, 32768, 256), (8, 151936, 256), (64, 4096, 256), (8, 32768, 1024), (8, 8192, 1024), (32, 1024, 1024), (8, 1024, 2048),
+              (64, 1 << 28, 256)]
+    assert [p[8] for p in plans([(m, n, d, 0, 64) for m, n, d in along + launch])] == [1] * len(along) + [0] * len(launch)
