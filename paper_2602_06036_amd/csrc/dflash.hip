@@ -1059,12 +1059,15 @@ Engine<float>::Slab Engine<float>::gemm(const float* W, const float* A, int M, i
   ProfScope prof(c, st, gemm_class(epi, N, c->t.vocab), (double)N * K * 4);
   const int cols = epi == EPI_SWIGLU ? N / 2 : N;
   const bool split = split_f32_columns(cols * ((M + 7) / 8), K, epi == EPI_SWIGLU);
+  const int blocks = split ? cols : (cols + 3) / 4, groups = (M + 7) / 8;
+  ep.groups_side_by_side = f32_groups_side_by_side(groups, blocks, (long long)N * K * 4);
+  const dim3 grid = ep.groups_side_by_side ? dim3(8 * groups, (blocks + 7) / 8) : dim3(blocks, groups);
   auto launch = [&](auto ec) {
     constexpr int E = decltype(ec)::value;
     auto go = [&](auto nc) {
       constexpr bool NORM = decltype(nc)::value;
-      if (split) hipLaunchKernelGGL((gemm_f32_kernel<E, 4, NORM>), dim3(cols, (M + 7) / 8), dim3(256), 0, st, W, A, M, N, K, ep);
-      else hipLaunchKernelGGL((gemm_f32_kernel<E, 1, NORM>), dim3((cols + 3) / 4, (M + 7) / 8), dim3(256), 0, st, W, A, M, N, K, ep);
+      if (split) hipLaunchKernelGGL((gemm_f32_kernel<E, 4, NORM>), grid, dim3(256), 0, st, W, A, M, N, K, ep);
+      else hipLaunchKernelGGL((gemm_f32_kernel<E, 1, NORM>), grid, dim3(256), 0, st, W, A, M, N, K, ep);
     };
     if constexpr (E != EPI_RESID)
       if (ep.norm_gain) return go(std::true_type{});

@@ -56,6 +56,7 @@ struct EpiArgs {
   float norm_eps = 0.f;
   float* tap = nullptr;
   int tap_K = 0;
+  bool groups_side_by_side = false;   // see f32_groups_side_by_side in plan.h
 };
 
 // score of logit y at (row m, column col) for the fused argmax
@@ -362,7 +363,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16_t* __restr
 // ------------------------------------------------------------------------------------------------
 // fp32 kernel (small models): block = 4 wavefronts, 4 / KW output columns (SWIGLU: one activation column = a gate row
 // and the up row 16 below it), KW wavefronts per column that take every KW-th 256-wide piece of K; lanes stride over K; eight
-// rows a workgroup (grid.y groups of them: one after the other in a workgroup, a step of the 2 + 1 layer model of width 256 took 320 us
+// rows a workgroup (groups of them: one after the other in a workgroup, a step of the 2 + 1 layer model of width 256 took 320 us
 // at 64 rows, side by side 182; width 2048, 128 rows 3208 and 2923).  Bound by latency: all loads of a piece go out together (rows past the last one repeat it, a load under
 // a condition would be waited for by itself), lane r of a column's first wavefront finishes row r (eight read-modify-writes
 // by one lane were eight round trips).  N = 256, K = 1024, 8 rows, RESID: 10.5 us, now 4.3 (the launch floor).
@@ -376,14 +377,19 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int kw = wave % KW;
   const int n_cols = (EPI == EPI_SWIGLU) ? N / 2 : N;
-  const int col_raw = blockIdx.x * (4 / KW) + wave / KW, col = min(col_raw, n_cols - 1);   // a column past the end is not stored
+  // grid (column blocks, groups of eight rows), or the groups of a column block one after the other on one XCD: workgroup ids are dealt to
+  // the eight XCDs round-robin, x first, so grid (8 * groups, column blocks / 8) and XCD x % 8 takes the block y * 8 + x % 8
+  const int col_block = ep.groups_side_by_side ? (int)blockIdx.y * 8 + ((int)blockIdx.x & 7) : (int)blockIdx.x;
+  const int row_group = ep.groups_side_by_side ? (int)blockIdx.x >> 3 : (int)blockIdx.y;
+  if (col_block * (4 / KW) >= n_cols) return;
+  const int col_raw = col_block * (4 / KW) + wave / KW, col = min(col_raw, n_cols - 1);   // a column past the end is not stored
   const int row0 = (EPI == EPI_SWIGLU) ? (col >> 4) * 32 + (col & 15) : col;
   const float* w0 = W + (size_t)row0 * K;
   const float* w1 = w0 + (size_t)16 * K;  // SWIGLU only
   constexpr int SQ = KW == 1 ? 2 : 8;     // rows whose squares a wavefront adds, from row SQ * wave of the eight (KW == 1) or all
   __shared__ float sum[2][4][8];
   __shared__ float sq[KW == 1 ? 1 : 4][8];
-  const int m0 = blockIdx.y * 8;
+  const int m0 = row_group * 8;
   float acc0[8], acc1[8], ss[SQ];
 #pragma unroll
   for (int r = 0; r < 8; ++r) acc0[r] = acc1[r] = 0.f;

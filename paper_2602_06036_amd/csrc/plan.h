@@ -229,6 +229,14 @@ inline StreamPlan stream_plan(const Knobs& kn, int M, int N, int K, bool split, 
 // four are faster.
 inline bool split_f32_columns(int cols, int K, bool swiglu) { return K >= 1024 && cols <= std::min(swiglu ? K / 2 : K / 4 * 3, 1536); }
 
+// fp32 GEMM: whether the groups of eight rows that share a block of weights run one after the other on one XCD (its L2 serves them), instead of all column
+// blocks of one group after those of the other: for matrices that the memory-side cache of 256 MB does not hold from group to group.  `blocks`:
+// workgroups of a group (the limit: grid.y).  Verifications, the largest matrix in MB, group by group and side by side: width 1024, 213 MB, 16 rows 194
+// and 199 us, 256 rows 2216 and 2337; 268 MB 249 and 251, 3025 and 2854; 328 MB 330 and 291, 4571 and 3346; 622 MB 560 and 481, 8358 and 5935; width
+// 2048, 201 MB 241 and 248, 2501 and 2602; 268 MB 303 and 300, 3232 and 3301; 336 MB 383 and 355, 4851 and 4096; width 4096, 470 MB 535 and 494, 7023 and
+// 5791.  (As a loop inside a workgroup, before the groups ran as workgroups: 328 MB 342 and 3563, 622 MB 562 and 6146.)
+inline bool f32_groups_side_by_side(int groups, int blocks, long long bytes) { return groups > 1 && bytes > (256ll << 20) && blocks <= 8 * 65535; }
+
 // fp32: passes whose products are so small that they are launches more than work
 inline bool small_f32(int M, int D) { return M * D <= 16384 && D <= 1024; }
 

@@ -204,6 +204,32 @@ def test_fp32_folded_norms_and_short_contexts(d, heads, kv_heads, hd, ffn, vocab
     assert ls.stats["reseeds"] == 0
 
 
+def test_fp32_row_groups_side_by_side_on_a_matrix_that_leaves_the_cache():
+    """An LM head of 65605 rows of 1024 (269 MB; 16402 column blocks, no multiple of eight) over 21 rows, three groups of which the last has five: every column
+    with the bits that it has in a head of the first and one of the last 16384 rows, whose groups run one after the other."""
+    import torch
+    _gpu()
+    import paper_2602_06036_amd as dfl
+    from tests.gpu_harness import GpuModel
+    V, n, kw = 65605, 16384, dict(seed=5, n_layers=1, draft_layers=1, block=7, kv_heads=1, n_seqs=3, taps=(0,), d=1024, heads=4, hd=64, ffn=64)
+    wt, wd = si.make_weights(tiny_workload(vocab=V, **kw))
+    embed, head = wt.t["E"], wt.t["lm"]
+    tokens = torch.from_numpy(np.random.default_rng(2).integers(0, n, (3, 7)).astype(np.int32)).cuda()
+
+    def logits(rows):
+        wt.t["E"], wt.t["lm"] = wd.t["E"], wd.t["lm"] = embed[:len(rows)], rows
+        g = GpuModel(tiny_workload(vocab=len(rows), **kw), wt, wd, 32)
+        dfl.dflash_verify(g.e, g.batch(), tokens, g.tgt_argmax, g.logits_t)
+        g.e.device_status()
+        assert np.array_equal(g.tgt_argmax.cpu().numpy(), g.logits_t.argmax(-1).to(torch.int32).cpu().numpy())
+        return g.logits_t.cpu().numpy().copy()
+
+    whole = logits(head)
+    assert np.array_equal(whole[..., :n], logits(head[:n]))
+    assert np.array_equal(whole[..., -n:], logits(head[-n:]))
+    assert np.isfinite(whole).all() and (np.abs(whole).max(axis=(0, 1)) > 0).all()
+
+
 @pytest.mark.parametrize("hd,heads,kv_heads,n_seqs,block,wide_from", [
     (128, 4, 2, 3, 16, 64),        # key-split kernel
     (128, 8, 2, 2, 7, 64),         # ... with a block that is no whole band: two sequences' rows in one operand tile

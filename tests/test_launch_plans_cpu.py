@@ -19,8 +19,9 @@ int main() {
   while (scanf("%d %d %d %d %d", &M, &N, &K, &split, &max_rows) == 5) {
     const TilePlan t = tile_plan(kn, M, N, K, split != 0, arena_rows(max_rows));
     const StreamPlan s = stream_plan(kn, M, N, K, split != 0, arena_rows(max_rows));
-    printf("%d %d %d %d %d %d %d %d %d\n", t.t->wn, t.t->wm, t.t->wy, t.ks, half_height_expert_tiles(N / 16) ? 128 : 256, s.nt, split_f32_columns(N, K, !split) ? 4 : 1,
-           short_context(M, K, N, split != 0), fold_norm(M, K, N));
+    printf("%d %d %d %d %d %d %d %d %d %d\n", t.t->wn, t.t->wm, t.t->wy, t.ks, half_height_expert_tiles(N / 16) ? 128 : 256, s.nt, split_f32_columns(N, K, !split) ? 4 : 1,
+           short_context(M, K, N, split != 0), fold_norm(M, K, N),
+           f32_groups_side_by_side((M + 7) / 8, (N + 3) / 4, (long long)N * K * 4));
   }
 }
 """
@@ -35,7 +36,8 @@ def plans(tmp_path_factory):
     def run(queries, constants=False, **knobs):
         """(weight tiles, bands, wavefronts along N, K ranges, rows of a four-band expert tile, weight tiles of the streaming
         kernel, wavefronts of an fp32 column, whether M query rows of K dims (of bf16, with 'may split') with N
-        keys go without splits, whether the norm of K columns goes with the N columns behind it) for each (rows, height, K, may split, rows of the context)."""
+        keys go without splits, whether the norm of K columns goes with the N columns behind it,
+        whether groups of eight rows run side by side) for each (rows, height, K, may split, rows of the context)."""
         env = {k: v for k, v in os.environ.items() if not k.startswith("DFLASH_")}
         env.update({"DFLASH_" + k: str(v) for k, v in knobs.items()})
         if constants:
@@ -142,3 +144,10 @@ def test_fp32_norms_go_with_the_products_that_are_cheaper_for_it(plans):
     launch = [(64, 8192, 256), (32, 32768, 256), (8, 151936, 256), (64, 4096, 256), (8, 32768, 1024), (8, 8192, 1024), (32, 1024, 1024), (8, 1024, 2048),
               (64, 1 << 28, 256)]
     assert [p[8] for p in plans([(m, n, d, 0, 64) for m, n, d in along + launch])] == [1] * len(along) + [0] * len(launch)
+
+
+def test_fp32_row_groups_run_side_by_side_where_the_matrix_leaves_the_cache(plans):
+    """(rows, columns, K) as measured both ways; a single group has nothing to share, and grid.y holds 65535 blocks of eight."""
+    apart = [(8, 151936, 1024), (16, 52000, 1024), (256, 52000, 1024), (64, 65536, 1024), (64, 24576, 2048), (16, 2097153, 1024)]
+    beside = [(9, 80000, 1024), (16, 151936, 1024), (256, 151936, 1024), (32, 40960, 2048), (64, 28672, 4096), (16, 2097120, 1024)]
+    assert [p[9] for p in plans([(m, n, k, 0, 256) for m, n, k in apart + beside])] == [0] * len(apart) + [1] * len(beside)
