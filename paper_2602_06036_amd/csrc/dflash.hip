@@ -303,7 +303,7 @@ struct dflash_ctx {
   // k.fuse, few-row path (one band of rows, dense bf16 model): 1 = the O projection runs unsplit with the residual update in
   // its epilogue (gemm_resid.h), the down projection split with the update done by the last workgroup of a column block
   // (finish.h), and the RMSNorms that follow are deferred into the GEMMs that read them; 2 = the down projection unsplit as
-  // well; 0 = separate kernels throughout
+  // well; 0 = separate kernels throughout.  The last layer's down projection leaves its sums to the final RMSNorm's launch in all of them
   // optional per-launch timing (dflash_profile_*): event pairs around the GEMM and attention launches
   bool prof_on = false;
   std::vector<hipEvent_t> ev;
@@ -396,14 +396,13 @@ struct Engine {
     return c->k.fuse == 1 && stream_plan(c->k, M, N, K, true, arena_rows(c->rt.max_seqs * c->rt.block_size)).nt >= 4;
   }
   // deferred operand: the GEMM that reads ws.a scales its rows (the pieces are good for one GEMM: the next finish overwrites them)
-  EpiArgs normed(EpiArgs ep, const dflash_dims& m) {
-    if (!defer_parts) return ep;
+  void normed(EpiArgs& ep, float eps, int D) {
+    if (!defer_parts) return;
     ep.ssq = ws<float>(c->ws.ssq);
     ep.ssq_parts = defer_parts;
-    ep.ssq_inv_D = 1.0f / (float)m.d_model;
-    ep.ssq_eps = m.rms_eps;
+    ep.ssq_inv_D = 1.0f / (float)D;
+    ep.ssq_eps = eps;
     defer_parts = 0;
-    return ep;
   }
   // h += A W^T, ws.a = h * gain_next, sums of squares -> ws.ssq, optional tap: unsplit (gemm_bf16_resid_kernel), or K-split and
   // finished by the last workgroup of a column block
@@ -438,7 +437,7 @@ struct Engine {
     const int M = b->n_seqs * blk(b), D = m.d_model;
     const int nqkv = (m.n_q_heads + 2 * m.n_kv_heads) * m.head_dim;
     EpiArgs ep{ws<float>(c->ws.arena), nqkv, 0, nullptr, 0};
-    const T* a = operand(reinterpret_cast<const float*>(lbase + lo.g1), m.rms_eps, M, D, nqkv, ep, m);
+    const T* a = operand(reinterpret_cast<const float*>(lbase + lo.g1), m.rms_eps, M, D, nqkv, ep);
     const Slab qs = gemm(reinterpret_cast<const T*>(lbase + lo.wqkv), a, M, nqkv, D, EPI_STORE, ep);
     hipLaunchKernelGGL(qkv_post_kernel<T>, dim3(M, (m.n_q_heads + 2 * m.n_kv_heads + 3) / 4), dim3(256), 0, st, qs.p, nqkv,
                        reinterpret_cast<const float*>(lbase + lo.qn), reinterpret_cast<const float*>(lbase + lo.kn), ws<T>(c->ws.q), pool, geom(b),
@@ -488,14 +487,14 @@ struct Engine {
   }
   // operand of the GEMM (of `cols` activation columns) behind an RMSNorm of the residual stream: ws.a, normalised here unless the norm is
   // deferred into that GEMM already; small fp32 products get the residual stream itself and the gain (nothing is pending there)
-  const T* operand(const float* gain, float eps, int M, int D, int cols, EpiArgs& ep, const dflash_dims& m) {
+  const T* operand(const float* gain, float eps, int M, int D, int cols, EpiArgs& ep) {
     if (std::is_same<T, float>::value && fold_norm(M, D, cols)) {
       ep.norm_gain = gain;
       ep.norm_eps = eps;
       return ws<T>(c->ws.h);
     }
     if (!defer_parts) norm_h(gain, M, D, eps);
-    ep = normed(ep, m);
+    normed(ep, eps, D);
     return ws<T>(c->ws.a);
   }
   // RMSNorm of the residual stream, folding in whatever the previous GEMM left pending
@@ -531,7 +530,7 @@ struct Engine {
       pending = moe_ffn(m, lbase, lo, M);
     } else {
       EpiArgs gu{nullptr, 0, 0, act, m.d_ffn}, down{h, D, 0, nullptr, 0};
-      const T* a = operand(g2, m.rms_eps, M, D, m.d_ffn, gu, m);
+      const T* a = operand(g2, m.rms_eps, M, D, m.d_ffn, gu);
       gemm(reinterpret_cast<const T*>(lbase + lo.wgu), a, M, 2 * m.d_ffn, D, EPI_SWIGLU, gu);
       if (few && gain_next && c->k.fuse == 2) return resid(wd, act, M, D, m.d_ffn, gain_next, tap);
       if (few && gain_next && finishes(M, D, m.d_ffn)) return resid_split(wd, act, M, D, m.d_ffn, gain_next, tap);
@@ -579,7 +578,7 @@ struct Engine {
     const dflash_dims& t = c->t;
     EpiArgs ep{logits, t.vocab, 0, nullptr, 0};
     ep.out2 = logits_to;
-    const T* a = operand(final_gain, eps, M, t.d_model, t.vocab, ep, t);
+    const T* a = operand(final_gain, eps, M, t.d_model, t.vocab, ep);
     ep.amax = ws<float2>(c->ws.amax);
     ep.amax_mode = mode;
     ep.amax_inv_T = inv_T;

@@ -380,6 +380,22 @@ def test_plain_attention_on_both_sides_of_its_row_limit(dtype, hd, n_seqs, lens)
     assert ls.stats["reseeds"] <= 1
 
 
+@pytest.mark.parametrize("fuse", [1, 2])
+def test_deferred_norms_use_the_eps_of_their_own_model(fuse, monkeypatch):
+    """A target with an eps of 1e-6 and a draft with one of 5e-3, more than ten times the mean square of an embedding row (4e-4), over one band of rows: any norm
+    with the other model's would show in the logits."""
+    monkeypatch.setenv("DFLASH_FUSE", str(fuse))
+    w = tiny_workload(seed=8, n_layers=3, draft_layers=2, vocab=512, block=5, qk_norm=True, kv_heads=2, dtype="bf16", n_seqs=2, taps=(0, 2), ffn=1024)
+    w = replace(w, draft=replace(w.draft, rms_eps=5e-3))
+    prompts = [p[:n] for p, n in zip(si.make_prompts(replace(w, ctx_min=33, ctx_max=33)), (7, 33))]
+    ls = Lockstep(w, prompts, max_len=64)
+    ls.prefill()
+    for i, plan in enumerate((None, [2, 0])):
+        ls.step(plan=plan, step_idx=i)
+    ls.check_cache([0, 2], [0, 1])
+    assert ls.stats["reseeds"] == 0
+
+
 def _open_on(e, workspace):
     """The engine's context anew, over another workspace."""
     import ctypes as C
