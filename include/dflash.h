@@ -256,7 +256,7 @@ enum {
   DFLASH_GEMM_STREAMING = 0, /* weight-streaming kernel, up to 64 rows (K split across workgroups and wavefronts) */
   DFLASH_GEMM_TILED4 = 1,    /* LDS-staged tiles, four wavefronts */
   DFLASH_GEMM_TILED8 = 2,    /* LDS-staged tiles, eight wavefronts (384 or 256 weight rows) */
-  DFLASH_GEMM_FEW_ROWS = 3,  /* unsplit projection with the residual update in its epilogue (one band of rows) */
+  DFLASH_GEMM_FEW_ROWS = 3,  /* one band of rows: projections that update the residual stream themselves (O, and down but for the last layer) */
   DFLASH_GEMM_GROUPED = 4,   /* routed experts: grouped launches */
   DFLASH_GEMM_F32 = 5        /* fp32 models */
 };

@@ -393,7 +393,7 @@ struct Engine {
   }
   // the K-split GEMM [M, N] may finish its own sums: the plan is one that the finishing kernel is built for
   bool finishes(int M, int N, int K) const {
-    return c->k.fuse == 1 && stream_plan(c->k, M, N, K, true, arena_rows(c->rt.max_seqs * c->rt.block_size)).nt >= 4;
+    return c->k.fuse == 1 && stream_finishes(stream_plan(c->k, M, N, K, true, arena_rows(c->rt.max_seqs * c->rt.block_size)));
   }
   // deferred operand: the GEMM that reads ws.a scales its rows (the pieces are good for one GEMM: the next finish overwrites them)
   void normed(EpiArgs& ep, float eps, int D) {
@@ -851,7 +851,7 @@ template <int NT, int MT, int U>
 void launch_bf16(hipStream_t st, const bf16_t* W, const bf16_t* A, int M, int N, int K, int epi, EpiArgs ep, int ks) {
   const dim3 grid((N / 16) / NT, ((M + 15) / 16 + MT - 1) / MT, ks), block(256);
   g_launch_parts = (int)grid.x;
-  g_launch_kind = DFLASH_GEMM_STREAMING;
+  g_launch_kind = epi == EPI_FIN_RESID ? DFLASH_GEMM_FEW_ROWS : DFLASH_GEMM_STREAMING;
   if (epi == EPI_SWIGLU) {
     if constexpr (NT >= 2) hipLaunchKernelGGL((gemm_bf16_kernel<NT, MT, U, EPI_SWIGLU>), grid, block, 0, st, W, A, M, N, K, ep);
   } else if (epi == EPI_FIN_RESID) {
@@ -890,7 +890,13 @@ Engine<bf16_t>::Slab Engine<bf16_t>::gemm(const bf16_t* W, const bf16_t* A, int 
   if (ep.amax && (split || epi != EPI_STORE)) ep.amax = nullptr;   // the fused argmax needs complete sums
   if (ep.lse && (split || epi != EPI_STORE)) ep.lse = nullptr;      // so do the fused softmax statistics
   if (ep.amax && lm_skip_store) ep.out = nullptr;
-  if (const StreamPlan sp = stream_plan(c->k, M, N, K, split, arena); sp.nt) {
+  const StreamPlan sp = stream_plan(c->k, M, N, K, split, arena);
+  if (epi == EPI_FIN_RESID && !stream_finishes(sp)) {   // no such kernel (finishes() is asked first)
+    if (!hip_err) fail(c->err, DFLASH_EHIP, "no launch finishes the sums of %d columns by itself", N);
+    hip_err = 1;
+    return Slab{};
+  }
+  if (sp.nt) {
     ks = sp.ks;
     ep.slab = (size_t)M * ep.ld;
     const int shape = sp.nt * 100 + sp.mt * 10 + sp.u;

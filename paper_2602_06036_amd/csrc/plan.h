@@ -164,6 +164,8 @@ inline int pick_ksplit(int n_blocks, int KT, int M, int arena, int target) {
 struct StreamPlan {
   int nt = 0, mt = 0, u = 0, ks = 1;   // nt = 0: another kernel's shape
 };
+// whether the launch may finish its own sums (finish.h): plans that the finishing kernel is built for
+inline bool stream_finishes(const StreamPlan& p) { return p.nt >= 4 && p.mt == 1; }
 inline StreamPlan stream_plan(const Knobs& kn, int M, int N, int K, bool split, int arena) {
   const int nt = N / 16, KT = K / 32;
   StreamPlan p;

@@ -47,3 +47,16 @@ TILE_EDGES = [
 ]
 # (vocabulary, rows, weight tiles per wavefront) of LM heads that the streaming GEMM takes with eight, six and four weight tiles
 STREAM_HEADS = [(v, m, nt) for v, nt in ((32768, 8), (24576, 6), (4096, 4)) for m in (16, 32, 48)]
+
+# Down projections of one band of rows: (d_model, heads, kv heads, FFN width, sequences, block, DFLASH_GEMM_FILL, weight tiles, K ranges, column blocks).
+# Four weight tiles and more: the last workgroup of a column block finishes the sums.
+LAST_WORKGROUP = [
+    (256, 4, 2, 64, 1, 16, 1, 4, 1, 4),       # every workgroup is the last one
+    (192, 3, 1, 576, 3, 5, 1, 4, 2, 3),       # a block's workgroups on different XCDs
+    (320, 5, 1, 1056, 2, 7, 1, 4, 4, 5),      # an uneven last range
+    (576, 9, 3, 4096, 1, 10, 1, 4, 16, 9),
+    (1152, 18, 2, 1024, 8, 2, 1, 4, 4, 18),
+    (256, 4, 2, 1024, 1, 2, 2, 8, 4, 2),
+    (1536, 24, 4, 4160, 1, 16, 1, 6, 16, 16),
+    (160, 5, 5, 512, 2, 8, 1, 2, 2, 5),       # two weight tiles, which the finishing kernel is not built for
+]

@@ -7,7 +7,7 @@ import pytest
 
 from oracle import dflash_oracle as O
 from synth import inputs as si
-from tests.helpers import STREAM_HEADS, TILE_EDGES, W64, tiny_workload
+from tests.helpers import LAST_WORKGROUP, STREAM_HEADS, TILE_EDGES, W64, tiny_workload
 from tests.test_gpu_parity import ROUTE_CLEAR, Lockstep, _gpu
 
 pytestmark = pytest.mark.gpu
@@ -256,20 +256,11 @@ def test_attention_of_one_split_writes_the_operand(hd, heads, kv_heads, n_seqs, 
     assert ls.stats["reseeds"] <= 1
 
 
-@pytest.mark.parametrize("d,heads,kv_heads,ffn,n_seqs,block,fill", [
-    (256, 4, 2, 64, 1, 16, 1),       # one K range: every workgroup is the last one
-    (192, 3, 1, 576, 3, 5, 1),       # three column blocks of two ranges: a block's workgroups on different XCDs
-    (320, 5, 1, 1056, 2, 7, 1),      # five blocks, an uneven last range
-    (576, 9, 3, 4096, 1, 10, 1),     # sixteen ranges
-    (1152, 18, 2, 1024, 8, 2, 1),    # eighteen blocks
-    (256, 4, 2, 1024, 1, 2, 2),      # eight weight tiles a wavefront
-    (1536, 24, 4, 4160, 1, 16, 1),   # six
-    (160, 5, 5, 512, 2, 8, 1),       # ten row bands: two weight tiles, which the finishing kernel is not built for
-])
-def test_residual_update_by_the_last_workgroup(d, heads, kv_heads, ffn, n_seqs, block, fill, monkeypatch):
+@pytest.mark.parametrize("d,heads,kv_heads,ffn,n_seqs,block,fill,tiles,ranges,blocks", LAST_WORKGROUP)
+def test_residual_update_by_the_last_workgroup(d, heads, kv_heads, ffn, n_seqs, block, fill, tiles, ranges, blocks, monkeypatch):
     """The down projection of up to 16 rows, whose K ranges are summed by the last workgroup of a column block, over the numbers of
     ranges, column blocks and weight tiles that its plan can have; an inner and the last layer are tapped.  Several steps on one
-    context, so that every launch has to leave its arrival counters at zero."""
+    context; the launches that update the residual stream themselves are counted."""
     monkeypatch.setenv("DFLASH_GEMM_FILL", str(fill))
     w = tiny_workload(seed=d + ffn, n_layers=3, draft_layers=2, vocab=512, block=block, qk_norm=True, kv_heads=kv_heads, dtype="bf16",
                       n_seqs=n_seqs, taps=(1, 2), d=d, heads=heads, hd=d // heads, ffn=ffn)
@@ -277,15 +268,18 @@ def test_residual_update_by_the_last_workgroup(d, heads, kv_heads, ffn, n_seqs, 
     ls = Lockstep(w, prompts, max_len=64 + 5 * 16)
     ls.prefill()
     for i, plan in enumerate((None, [(3 * s + 1) % block for s in range(n_seqs)], None)):
+        ls.g.e.gemm_counts()
         ls.step(plan=plan, step_idx=i)
+        # O projections of three and two layers, and the down projections but for the models' last layers
+        assert ls.g.e.gemm_counts()[3] == 5 + (3 if tiles >= 4 else 0)
     ls.check_cache([0, 2], [0, 1])
     assert ls.stats["low_margin_flips"] <= 0.02 * ls.stats["rows"] + 2
     assert ls.stats["reseeds"] <= 1
 
 
 @pytest.mark.parametrize("d,ffn", [
-    (4128, 576),      # 258 and 129 pieces: a last group of two and of one (down projection: no plan that finishes its sums)
-    (4160, 64),       # 260 from the O projection, 65 from the down projection
+    (4128, 576),      # 258 pieces from the O projection, 43 from the down projection: last groups of two and three
+    (4160, 64),       # 260 and 65
     (8192, 64),       # 512: all of them requested ahead
     (8288, 64),       # 518: the last six behind the sweep
 ])

@@ -4,7 +4,7 @@ import subprocess
 
 import pytest
 
-from tests.helpers import STREAM_HEADS, TILE_EDGES
+from tests.helpers import LAST_WORKGROUP, STREAM_HEADS, TILE_EDGES
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "..", "paper_2602_06036_amd", "csrc")
@@ -19,9 +19,9 @@ int main() {
   while (scanf("%d %d %d %d %d", &M, &N, &K, &split, &max_rows) == 5) {
     const TilePlan t = tile_plan(kn, M, N, K, split != 0, arena_rows(max_rows));
     const StreamPlan s = stream_plan(kn, M, N, K, split != 0, arena_rows(max_rows));
-    printf("%d %d %d %d %d %d %d %d %d %d\n", t.t->wn, t.t->wm, t.t->wy, t.ks, half_height_expert_tiles(N / 16) ? 128 : 256, s.nt, split_f32_columns(N, K, !split) ? 4 : 1,
+    printf("%d %d %d %d %d %d %d %d %d %d %d %d\n", t.t->wn, t.t->wm, t.t->wy, t.ks, half_height_expert_tiles(N / 16) ? 128 : 256, s.nt, split_f32_columns(N, K, !split) ? 4 : 1,
            short_context(M, K, N, split != 0), fold_norm(M, K, N),
-           f32_groups_side_by_side((M + 7) / 8, (N + 3) / 4, (long long)N * K * 4));
+           f32_groups_side_by_side((M + 7) / 8, (N + 3) / 4, (long long)N * K * 4), s.ks, stream_finishes(s));
   }
 }
 """
@@ -37,7 +37,7 @@ def plans(tmp_path_factory):
         """(weight tiles, bands, wavefronts along N, K ranges, rows of a four-band expert tile, weight tiles of the streaming
         kernel, wavefronts of an fp32 column, whether M query rows of K dims (of bf16, with 'may split') with N
         keys go without splits, whether the norm of K columns goes with the N columns behind it,
-        whether groups of eight rows run side by side) for each (rows, height, K, may split, rows of the context)."""
+        whether groups of eight rows run side by side, K ranges of the streaming kernel, whether its launch may finish its sums) for each (rows, height, K, may split, rows of the context)."""
         env = {k: v for k, v in os.environ.items() if not k.startswith("DFLASH_")}
         env.update({"DFLASH_" + k: str(v) for k, v in knobs.items()})
         if constants:
@@ -151,3 +151,19 @@ def test_fp32_row_groups_run_side_by_side_where_the_matrix_leaves_the_cache(plan
     apart = [(8, 151936, 1024), (16, 52000, 1024), (256, 52000, 1024), (64, 65536, 1024), (64, 24576, 2048), (16, 2097153, 1024)]
     beside = [(9, 80000, 1024), (16, 151936, 1024), (256, 151936, 1024), (32, 40960, 2048), (64, 28672, 4096), (16, 2097120, 1024)]
     assert [p[9] for p in plans([(m, n, k, 0, 256) for m, n, k in apart + beside])] == [0] * len(apart) + [1] * len(beside)
+
+
+def test_down_projections_of_one_band_have_the_plans_that_the_gpu_test_names(plans):
+    """Number of K ranges, weight tiles and column blocks of the launches whose last workgroup finishes the sums."""
+    for d, _, _, ffn, n_seqs, block, fill, tiles, ranges, blocks in LAST_WORKGROUP:
+        M = n_seqs * block
+        (p,) = plans([(M, d, ffn, 1, M)], GEMM_FILL=fill)
+        assert (p[5], p[10], d // 16 // p[5], p[11]) == (tiles, ranges, blocks, int(tiles >= 4)), (d, ffn)
+
+
+def test_one_band_of_rows_takes_four_weight_tiles_where_plans_tie(plans):
+    """Half the K ranges, so half the slabs; from two bands on a tie goes to eight tiles."""
+    cases = [(4096, 12288, 4, 4), (4096, 14336, 4, 4), (2048, 4096, 4, 8), (6144, 4096, 6, 4), (5120, 2048, 4, 3)]
+    for n, k, tiles, ranges in cases:
+        assert [(p[5], p[10]) for p in plans([(16, n, k, 1, 16)])] == [(tiles, ranges)]
+    assert [(p[5], p[10]) for p in plans([(32, 4096, 12288, 1, 32), (64, 4096, 12288, 1, 64)])] == [(8, 8), (8, 8)]
