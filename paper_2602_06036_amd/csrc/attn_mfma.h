@@ -614,16 +614,8 @@ inline bool attn_takes_mfma(const AttnArgs& aa, int block_size) {
   return sizeof(T) == 2 && ((block_size * group) >> aa.q_shift) <= 64 && group % (1 << aa.q_shift) == 0 && (aa.head_dim == 128 || aa.head_dim == 64);
 }
 
-// Returns true when it launched a kernel for this configuration; false -> caller uses the generic kernel.
-template <typename T>
-inline bool attn_mfma_launch(hipStream_t, const T*, const T*, SeqGeom, AttnArgs, int, float*, float2*, int) {
-  return false;
-}
-
-template <>
-inline bool attn_mfma_launch<bf16_t>(hipStream_t st, const bf16_t* q, const bf16_t* pool, SeqGeom geo, AttnArgs aa, int S,
-                                     float* part_o, float2* part_ml, int wide_min_chunk) {
-  if (!attn_takes_mfma<bf16_t>(aa, geo.block_size)) return false;
+inline void attn_mfma_launch(hipStream_t st, const bf16_t* q, const bf16_t* pool, SeqGeom geo, AttnArgs aa, int S, float* part_o, float2* part_ml,
+                             int wide_min_chunk) {
   const dim3 grid(aa.n_splits, aa.n_kv_heads, S << aa.q_shift), block(256);
   // long chunks: wavefronts split the keys
   if (aa.head_dim == 128 && aa.chunk >= wide_min_chunk)
@@ -632,5 +624,4 @@ inline bool attn_mfma_launch<bf16_t>(hipStream_t st, const bf16_t* q, const bf16
     hipLaunchKernelGGL(attn_mfma_kernel<128>, grid, block, 0, st, q, pool, geo, aa, part_o, part_ml);
   else
     hipLaunchKernelGGL(attn_mfma_kernel<64>, grid, block, 0, st, q, pool, geo, aa, part_o, part_ml);
-  return true;
 }

@@ -1135,7 +1135,7 @@ void Engine<T>::attention(const dflash_dims& m, const T* pool, int layer, const 
     // algorithmic bytes: every cached K and V row of this layer once (upper bound from the host hint)
     ProfScope prof(c, st, DFLASH_PROF_ATTN, (double)S * max_tokens * 2 * m.n_kv_heads * m.head_dim * sizeof(T));
     if (mfma) {
-      attn_mfma_launch<T>(st, ws<T>(c->ws.q), pool, geom(b), aa, S, part_o, part_ml, c->k.attn_wide_min_chunk);
+      if constexpr (std::is_same<T, bf16_t>::value) attn_mfma_launch(st, ws<bf16_t>(c->ws.q), pool, geom(b), aa, S, part_o, part_ml, c->k.attn_wide_min_chunk);
     } else if (direct) {
       aa.chunk *= aa.n_splits;
       hipLaunchKernelGGL(attn_short_simple_kernel<T>, dim3(B * (m.n_q_heads / m.n_kv_heads), m.n_kv_heads, S), dim3(256), 0, st, ws<T>(c->ws.q), pool,
