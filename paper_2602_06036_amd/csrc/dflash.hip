@@ -743,7 +743,9 @@ struct Engine {
       ep.norm_eps = d.rms_eps;
       a = ws<T>(c->ws.fuse);
     } else {
-      norm(nullptr, fs, ws<float>(c->ws.fuse), gc, ht, M, D, d.rms_eps);
+      float* fused = ws<float>(c->ws.fuse);
+      if (std::is_same<T, float>::value) norm(fused, Slab{}, fused, gc, ht, M, D, d.rms_eps);   // complete already
+      else norm(nullptr, fs, fused, gc, ht, M, D, d.rms_eps);
     }
     const Slab kvs = gemm(reinterpret_cast<const T*>(c->dblob + c->dl.wkv_all), a, M, nkv, D, EPI_STORE, ep);
     {   // k-norm, RoPE and page write of all draft layers' context K/V in one launch (grid.z = layer)
