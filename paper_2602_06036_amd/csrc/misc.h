@@ -5,6 +5,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "exp_nonpositive.h"
 #include "finish.h"
 
 // ---- block assembly + embedding gather -------------------------------------------------------
@@ -447,13 +448,6 @@ __device__ __forceinline__ void lse_merge(float& m, float& s, float m2, float s2
   s = (m == -INFINITY ? s : s * expf(m - M)) + (m2 == -INFINITY ? s2 : s2 * expf(m2 - M));   // an empty set's sum is 0 or NaN
   m = M;
 }
-// e^d, d <= 0 (-inf: 0, NaN: NaN): 2^(d log2 e) by the exponential instruction, with what the product's rounding left out put back as a
-// factor, so that it is as good for large -d as for small ones
-__device__ __forceinline__ float exp_nonpositive(float d) {
-  constexpr float kLog2e = 1.44269502162933349609f, kLog2eLow = 1.92596299e-8f, kLn2 = 0.693147180559945f;
-  const float p = d * kLog2e, left = fmaf(d, kLog2eLow, fmaf(d, kLog2e, -p)), x = __builtin_amdgcn_exp2f(p);
-  return d < -87.f ? 0.f : fmaf(x, left * kLn2, x);
-}
 template <bool VEC>
 __global__ __launch_bounds__(256) void lse_partial_kernel(const float* __restrict__ a, const float* __restrict__ b, int R, int V, float inv_T,
                                                           float2* __restrict__ part) {
@@ -487,7 +481,7 @@ __global__ __launch_bounds__(256) void lse_partial_kernel(const float* __restric
       m = mx;
     }
 #pragma unroll
-    for (int e = 0; e < U * E; ++e) s += v[e] == -INFINITY ? 0.f : exp_nonpositive(v[e] - m);   // a masked logit weighs nothing, a NaN stays one
+    for (int e = 0; e < U * E; ++e) s += v[e] == -INFINITY ? 0.f : exp_nonpositive(v[e] - m, [](float p) { return __builtin_amdgcn_exp2f(p); });   // a masked logit weighs nothing, a NaN stays one
   }
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
