@@ -454,14 +454,19 @@ struct Engine {
   void norm(const float* base, Slab delta, float* h_out, const float* gain, T* out, int M, int D, float eps, int tap = -1) {
     T* taps = tap >= 0 ? ws<T>(c->ws.taps) : (T*)nullptr;
     const int tap_K = c->rt.n_taps * c->t.d_model;
-    if (delta.mix.pos)
+    // One 16-byte chunk per thread: the row's loads are all in flight at once.  (2048 columns with 256 and with 512 threads: a four-layer verification of
+    // the routed-expert target at 16 rows 691 and 679.5 us.  The kernel keeps the order of 256 threads' sums up to 8192 columns.)
+    const bool mid = D >= 2048 && D <= 8192;
+    if (delta.mix.pos && mid)
       hipLaunchKernelGGL((rmsnorm_kernel<T, 512, true>), dim3(M), dim3(512), 0, st, base, delta.p, delta.ks, delta.stride, h_out, gain, out, D,
                          eps, taps, tap, tap_K, delta.mix);
-    else if (D >= 4096)   // one 16-byte chunk per thread: the row's loads are all in flight at once (2048 columns with 256 and with 512
-                          // threads: a four-layer verification of the routed-expert target at 16 rows 691 and 679.5 us)
+    else if (delta.mix.pos)
+      hipLaunchKernelGGL((rmsnorm_kernel<T, 256, true>), dim3(M), dim3(256), 0, st, base, delta.p, delta.ks, delta.stride, h_out, gain, out, D,
+                         eps, taps, tap, tap_K, delta.mix);
+    else if (D >= 4096)
       hipLaunchKernelGGL((rmsnorm_kernel<T, 1024>), dim3(M), dim3(1024), 0, st, base, delta.p, delta.ks, delta.stride, h_out, gain, out, D,
                          eps, taps, tap, tap_K, RowMix{});
-    else if (D >= 2048)
+    else if (mid)
       hipLaunchKernelGGL((rmsnorm_kernel<T, 512>), dim3(M), dim3(512), 0, st, base, delta.p, delta.ks, delta.stride, h_out, gain, out, D,
                          eps, taps, tap, tap_K, RowMix{});
     else
