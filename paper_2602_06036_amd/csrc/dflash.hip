@@ -383,6 +383,7 @@ struct Engine {
   // Few-row path: ws.a holds x * gain with the division by the row's rms deferred to the GEMM that reads it; the
   // pieces of the rows' sums of squares are in ws.ssq (see gemm_resid.h)
   int cur_layer = 0;     // layer index of the layer() call in progress (routed experts: row of the choice trace)
+  bool routed = false;   // the layer() call in progress is a routed-expert target's
   int defer_parts = 0;   // > 0: ws.a is such an operand, with that many pieces per row
   // One band of rows.  (Measured for 17 to 64 rows too, per layer of the 8B shape: at 32 rows the finish costs a projection 3.4 us,
   // deferring 1.1 in the QKV and 0.8 in the gate/up GEMM, for 5.3 us of a normalisation launch saved: even; at 64 rows 5.5, 2.4 and
@@ -524,6 +525,7 @@ struct Engine {
     const T* wo = reinterpret_cast<const T*>(lbase + lo.wo);
     const T* wd = reinterpret_cast<const T*>(lbase + lo.wd);
     const float* g2 = reinterpret_cast<const float*>(lbase + lo.g2);
+    routed = m.n_experts != 0;
     qkv(m, lbase, lo, pool, l, b);
     attention(m, pool, l, b, causal);
     const bool few = few_rows(m, M);
@@ -533,6 +535,7 @@ struct Engine {
       norm_h(g2, M, D, m.rms_eps);
       cur_layer = l;
       pending = moe_ffn(m, lbase, lo, M);
+      routed = false;
     } else {
       EpiArgs gu{nullptr, 0, 0, act, m.d_ffn}, down{h, D, 0, nullptr, 0};
       const T* a = operand(g2, m.rms_eps, M, D, m.d_ffn, gu);
@@ -897,7 +900,7 @@ Engine<bf16_t>::Slab Engine<bf16_t>::gemm(const bf16_t* W, const bf16_t* A, int 
   if (ep.amax && (split || epi != EPI_STORE)) ep.amax = nullptr;   // the fused argmax needs complete sums
   if (ep.lse && (split || epi != EPI_STORE)) ep.lse = nullptr;      // so do the fused softmax statistics
   if (ep.amax && lm_skip_store) ep.out = nullptr;
-  const StreamPlan sp = stream_plan(c->k, M, N, K, split, arena);
+  const StreamPlan sp = stream_plan(c->k, M, N, K, split, arena, !routed);
   if (epi == EPI_FIN_RESID && !stream_finishes(sp)) {   // no such kernel (finishes() is asked first)
     if (!hip_err) fail(c->err, DFLASH_EHIP, "no launch finishes the sums of %d columns by itself", N);
     hip_err = 1;

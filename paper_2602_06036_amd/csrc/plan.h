@@ -166,21 +166,22 @@ struct StreamPlan {
 };
 // whether the launch may finish its own sums (finish.h): plans that the finishing kernel is built for
 inline bool stream_finishes(const StreamPlan& p) { return p.nt >= 4 && p.mt == 1; }
-inline StreamPlan stream_plan(const Knobs& kn, int M, int N, int K, bool split, int arena) {
+inline StreamPlan stream_plan(const Knobs& kn, int M, int N, int K, bool split, int arena, bool four_first = true) {
   const int nt = N / 16, KT = K / 32;
   StreamPlan p;
   // a launch of 192 workgroups leaves a quarter of the CUs idle: among 8, 6 or 4 weight tiles per wavefront and any K split
   // (not only powers of two) take the fullest last round.  Ties go to more tiles (a band of activations is read for more of the
-  // matrix), for one band of rows to four tiles first: half the K ranges, so half the slabs for whoever adds them.  (4096 rows of
-  // matrix as 32 blocks x 8 ranges and as 64 x 4: verification of blocks of ten of the 14336-wide model 409 and 401.5 us; routed
-  // experts at 16 rows, O projection 16 x 16 and 32 x 8, QKV 40 x 6 and 80 x 3: 709 and 691.)  (Four tiles pay
+  // matrix), for one band of rows of a dense model to four tiles first: half the K ranges, so half the slabs for whoever adds them.  (4096 rows of
+  // matrix as 32 blocks x 8 ranges and as 64 x 4: verification of blocks of ten of the 14336-wide model 409 and 401.5 us.)  The layers of a
+  // routed-expert target (`four_first` false) gain as much, O projection 16 x 16 and 32 x 8, QKV 40 x 6 and 80 x 3: 709 and 691, but the
+  // router's near-ties turn another order of sums into another expert: one row of sixteen that goes the other way is 1 % of the logits.  (Four tiles pay
   // where nothing else fills the chip: an unsplit 16384-column LM head, 128 workgroups with 8, took 31 us at 16 rows and 49 at
   // 64, now 23 and 39.)
   auto fullest = [&]() {
     double best = -1.0;
-    const int one_band[] = {4, 8, 6}, more[] = {8, 6, 4};
+    const int four[] = {4, 8, 6}, more[] = {8, 6, 4};
     for (int i = 0; i < 3; ++i) {
-      const int cand = M <= 16 ? one_band[i] : more[i];
+      const int cand = M <= 16 && four_first ? four[i] : more[i];
       if (nt % cand) continue;
       const int nb = nt / cand;
       for (int k = 1; k <= (split ? kMaxKSplit : 1); ++k) {

@@ -18,10 +18,10 @@ int main() {
   if (getenv("CONSTANTS")) return printf("%d\n", kSsqAhead), 0;
   while (scanf("%d %d %d %d %d", &M, &N, &K, &split, &max_rows) == 5) {
     const TilePlan t = tile_plan(kn, M, N, K, split != 0, arena_rows(max_rows));
-    const StreamPlan s = stream_plan(kn, M, N, K, split != 0, arena_rows(max_rows));
-    printf("%d %d %d %d %d %d %d %d %d %d %d %d\n", t.t->wn, t.t->wm, t.t->wy, t.ks, half_height_expert_tiles(N / 16) ? 128 : 256, s.nt, split_f32_columns(N, K, !split) ? 4 : 1,
+    const StreamPlan s = stream_plan(kn, M, N, K, split != 0, arena_rows(max_rows)), r = stream_plan(kn, M, N, K, split != 0, arena_rows(max_rows), false);
+    printf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d\n", t.t->wn, t.t->wm, t.t->wy, t.ks, half_height_expert_tiles(N / 16) ? 128 : 256, s.nt, split_f32_columns(N, K, !split) ? 4 : 1,
            short_context(M, K, N, split != 0), fold_norm(M, K, N),
-           f32_groups_side_by_side((M + 7) / 8, (N + 3) / 4, (long long)N * K * 4), s.ks, stream_finishes(s));
+           f32_groups_side_by_side((M + 7) / 8, (N + 3) / 4, (long long)N * K * 4), s.ks, stream_finishes(s), r.nt, r.ks);
   }
 }
 """
@@ -37,7 +37,8 @@ def plans(tmp_path_factory):
         """(weight tiles, bands, wavefronts along N, K ranges, rows of a four-band expert tile, weight tiles of the streaming
         kernel, wavefronts of an fp32 column, whether M query rows of K dims (of bf16, with 'may split') with N
         keys go without splits, whether the norm of K columns goes with the N columns behind it,
-        whether groups of eight rows run side by side, K ranges of the streaming kernel, whether its launch may finish its sums) for each (rows, height, K, may split, rows of the context)."""
+        whether groups of eight rows run side by side, K ranges of the streaming kernel, whether its launch may finish its sums,
+        weight tiles and K ranges in a routed-expert target's layers) for each (rows, height, K, may split, rows of the context)."""
         env = {k: v for k, v in os.environ.items() if not k.startswith("DFLASH_")}
         env.update({"DFLASH_" + k: str(v) for k, v in knobs.items()})
         if constants:
@@ -162,8 +163,10 @@ def test_down_projections_of_one_band_have_the_plans_that_the_gpu_test_names(pla
 
 
 def test_one_band_of_rows_takes_four_weight_tiles_where_plans_tie(plans):
-    """Half the K ranges, so half the slabs; from two bands on a tie goes to eight tiles."""
-    cases = [(4096, 12288, 4, 4), (4096, 14336, 4, 4), (2048, 4096, 4, 8), (6144, 4096, 6, 4), (5120, 2048, 4, 3)]
-    for n, k, tiles, ranges in cases:
-        assert [(p[5], p[10]) for p in plans([(16, n, k, 1, 16)])] == [(tiles, ranges)]
+    """Half the K ranges, so half the slabs; from two bands on, and in the layers of a routed-expert target, whose router's near-ties turn another order of sums
+    into another expert, a tie goes to eight tiles."""
+    cases = [(4096, 12288, (4, 4), (8, 8)), (4096, 14336, (4, 4), (8, 8)), (2048, 4096, (4, 8), (8, 16)), (5120, 2048, (4, 3), (8, 6)), (6144, 4096, (6, 4), (6, 4))]
+    for n, k, dense, routed in cases:
+        for m in (1, 16):
+            assert [(p[5], p[10], p[12], p[13]) for p in plans([(m, n, k, 1, 16)])] == [dense + routed], (n, k)
     assert [(p[5], p[10]) for p in plans([(32, 4096, 12288, 1, 32), (64, 4096, 12288, 1, 64)])] == [(8, 8), (8, 8)]
