@@ -153,7 +153,7 @@ __global__ __launch_bounds__(256, 2) void attn_partial_simple_kernel(const T* __
 }
 
 // Short contexts (short_context in plan.h): a workgroup per query row, its four wavefronts share the keys and merge in LDS, and the row
-// is finished: 8.7 us at 136 keys, 8 rows, 4 heads of 64, against 9.6 and a merge launch of 3.6.  grid (B * group, Hkv, S).
+// is finished: 8.7 us at 136 keys, 8 rows, 4 heads of 64, against 9.6 and a merge launch of 3.6 (with 256 registers; 6.6 with 218).  grid (B * group, Hkv, S).
 template <typename T>
 __global__ __launch_bounds__(256, 2) void attn_short_simple_kernel(const T* __restrict__ q, const T* __restrict__ pool, SeqGeom geo, AttnArgs aa,
                                                                 T* __restrict__ out) {

@@ -1,8 +1,8 @@
 // What the workgroup that arrives last at a column block of a K-split GEMM does with the block's complete sums, so that no
 // launch of its own has to add the slabs (streaming kernel, one band of rows):
 // h += sum of the slabs, and the operand of the RMSNorm that follows with its division deferred (gemm_resid.h).
-// A dependent launch costs 4.4 to 5.2 us however little it does; this costs 2.6: down projection of the 8B shape at 16 rows (eight
-// K ranges) 18.6 us + 5.3 for the normalisation launch behind it before, 21.2 now.  The slabs are written through the L2 (sc1:
+// A dependent launch costs 4.4 to 5.2 us however little it does; this costs 2.6: down projection of the 8B shape at 16 rows, eight K ranges, 18.6 us + 5.3
+// for the normalisation launch behind it before, 21.2 finished, 20.7 with the four ranges of 64 blocks that the plan takes now.  The slabs are written through the L2 (sc1:
 // an XCD's L2 is not the others'), waited for, a counter says who is last, and that workgroup reads the slabs back past its
 // L2.  Nobody waits for anybody, and the sums are added in ascending order whoever is last.  No fence: a device-scope one
 // writes back and invalidates the whole L2.  (The q/k norm and rotation finished the same way behind the QKV GEMM, sixteen

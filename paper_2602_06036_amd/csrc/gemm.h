@@ -41,7 +41,7 @@ struct EpiArgs {
   size_t grp_w_stride = 0;
   const int32_t* grp_rows = nullptr;
   // Deferred RMSNorm (streaming kernel only): the operand holds x * gain without the division by the row's rms; row m
-  // of the result is multiplied by 1 / sqrt(sum_p ssq[m * ssq_parts + p] * ssq_inv_D + ssq_eps) before any epilogue
+  // of the result is multiplied by 1 / sqrt(sum_p ssq[m * ssq_row(ssq_parts) + p] * ssq_inv_D + ssq_eps) before any epilogue
   // sees it (the sums of squares come in ssq_parts pieces, added in ascending order; see gemm_resid.h).
   const float* ssq = nullptr;
   int ssq_parts = 0;

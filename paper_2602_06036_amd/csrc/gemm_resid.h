@@ -1,4 +1,4 @@
-// O and down projections for a single band of rows (M <= 16), unsplit, with the residual update and the input of
+// O projection (with DFLASH_FUSE=2 the down projection too) for a single band of rows (M <= 16), unsplit, with the residual update and the input of
 // the following RMSNorm folded into the epilogue:
 //     h[m, n] += sum_k a[m, k] W[n, k]                       (residual stream, fp32, in place)
 //     a_out[m, n] = h[m, n] * gain_next[n]                   (GEMM operand, hi + lo bf16 pair; NOT divided by the rms)
