@@ -480,8 +480,7 @@ struct Engine {
     float2* part = ws<float2>(c->ws.amax);
     int parts = amax_parts;
     if (parts == 0) {   // not fused into the LM head (fp32 models): from the stored logits
-      // a short row by one workgroup: the second launch costs 3.5 us, a column more per thread some ten nanoseconds
-      parts = V <= 8192 ? 1 : ARGMAX_CHUNKS;
+      parts = argmax_in_one_launch(M, V) ? 1 : ARGMAX_CHUNKS;
       hipLaunchKernelGGL(argmax_rows_kernel, dim3(parts, M), dim3(256), 0, st, logits, V, B, part, mode, inv_T, key,
                          parts == 1 ? out : (int32_t*)nullptr, skip_slot0);
       check();

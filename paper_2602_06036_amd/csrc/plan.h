@@ -274,6 +274,12 @@ inline bool short_context(int rows, int head_dim, int max_tokens, bool bf16) {
 // 1181 and 1192; 192 is 480 and 486 there, 659 and 625 at 896 rows.
 inline bool half_height_expert_tiles(int nt) { return nt % 16 != 0 && nt < 96; }
 
+// Argmax of stored logits (fp32 models): whether a row is searched by one workgroup, in one launch, or by 32 and a second launch that combines them.
+// A workgroup takes a column a thread and round, a trip to memory each, unless other rows hide it.  Verifications of one layer of width 256, two launches and one: 2048
+// columns, 8 rows 38.2 and 37.5 us, 128 75 and 70; 4096, 8 rows 39.2 and 40.8, 128 91 and 89, 512 251 and 235; 8192, 8 rows 42 and 49, 128 123.5 and 126, 512 377
+// and 363, 2048 1379 and 1308.
+inline bool argmax_in_one_launch(int rows, int V) { return V <= 2048 || (V <= 8192 && V * V <= (long long)rows << 17); }
+
 // ---- sampled acceptance ------------------------------------------------------------------------------------
 // Workgroups per row of the statistics launch: enough for 4096 of them (16 a CU), not below 1024 columns each, and no
 // more pieces than `room` entries hold.  Workgroups per sequence of the sweep over the vocabulary: 1024 in all, 1024 columns

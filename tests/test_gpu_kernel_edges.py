@@ -182,7 +182,10 @@ def test_forced_tiles_over_ragged_sizes(n_seqs, ffn, vocab, wide, tile, wm, ks, 
 
 @pytest.mark.parametrize("d,heads,kv_heads,hd,ffn,vocab,n_seqs,block,lens", [
     (256, 4, 4, 64, 1024, 1024, 1, 2, (5,)),              # two rows
-    (256, 4, 2, 64, 1024, 8192, 3, 7, (63, 64, 130)),     # 21 rows: a last piece of five; the longest row that one workgroup searches; a launch before the head
+    (256, 4, 2, 64, 1024, 8192, 3, 7, (63, 64, 130)),     # 21 rows: a last piece of five; a launch before the head
+    (256, 4, 2, 64, 512, 2048, 2, 4, (9, 30)),            # the longest row that one workgroup searches whatever the number of rows
+    (256, 4, 2, 64, 512, 2056, 2, 4, (9, 30)),            # ... 32 workgroups
+    (256, 4, 2, 64, 256, 4096, 16, 16, (9, 30, 5, 17) * 4),   # ... and one again where there are rows enough
     (256, 4, 4, 64, 512, 8208, 3, 8, (9, 233, 240)),      # 24 rows and 256 keys at first, more behind: one workgroup, then splits
     (256, 4, 4, 64, 512, 512, 9, 7, (20, 31, 8, 90, 64, 1, 3, 5, 7)),   # 63 rows
     (256, 4, 1, 64, 512, 512, 5, 13, (20, 31, 8, 90, 64)),              # 65 rows: norm launches

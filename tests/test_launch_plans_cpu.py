@@ -19,9 +19,9 @@ int main() {
   while (scanf("%d %d %d %d %d", &M, &N, &K, &split, &max_rows) == 5) {
     const TilePlan t = tile_plan(kn, M, N, K, split != 0, arena_rows(max_rows));
     const StreamPlan s = stream_plan(kn, M, N, K, split != 0, arena_rows(max_rows)), r = stream_plan(kn, M, N, K, split != 0, arena_rows(max_rows), false);
-    printf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d\n", t.t->wn, t.t->wm, t.t->wy, t.ks, half_height_expert_tiles(N / 16) ? 128 : 256, s.nt, split_f32_columns(N, K, !split) ? 4 : 1,
+    printf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d %d\n", t.t->wn, t.t->wm, t.t->wy, t.ks, half_height_expert_tiles(N / 16) ? 128 : 256, s.nt, split_f32_columns(N, K, !split) ? 4 : 1,
            short_context(M, K, N, split != 0), fold_norm(M, K, N),
-           f32_groups_side_by_side((M + 7) / 8, (N + 3) / 4, (long long)N * K * 4), s.ks, stream_finishes(s), r.nt, r.ks);
+           f32_groups_side_by_side((M + 7) / 8, (N + 3) / 4, (long long)N * K * 4), s.ks, stream_finishes(s), r.nt, r.ks, argmax_in_one_launch(M, N));
   }
 }
 """
@@ -38,7 +38,7 @@ def plans(tmp_path_factory):
         kernel, wavefronts of an fp32 column, whether M query rows of K dims (of bf16, with 'may split') with N
         keys go without splits, whether the norm of K columns goes with the N columns behind it,
         whether groups of eight rows run side by side, K ranges of the streaming kernel, whether its launch may finish its sums,
-        weight tiles and K ranges in a routed-expert target's layers) for each (rows, height, K, may split, rows of the context)."""
+        weight tiles and K ranges in a routed-expert target's layers, whether the argmax of M rows of N is one launch) for each (rows, height, K, may split, rows of the context)."""
         env = {k: v for k, v in os.environ.items() if not k.startswith("DFLASH_")}
         env.update({"DFLASH_" + k: str(v) for k, v in knobs.items()})
         if constants:
@@ -170,3 +170,10 @@ def test_one_band_of_rows_takes_four_weight_tiles_where_plans_tie(plans):
         for m in (1, 16):
             assert [(p[5], p[10], p[12], p[13]) for p in plans([(m, n, k, 1, 16)])] == [dense + routed], (n, k)
     assert [(p[5], p[10]) for p in plans([(32, 4096, 12288, 1, 32), (64, 4096, 12288, 1, 64)])] == [(8, 8), (8, 8)]
+
+
+def test_argmax_of_stored_logits_is_one_launch_where_that_is_faster(plans):
+    """(rows, columns) as measured both ways."""
+    one = [(8, 512), (8, 2048), (2048, 2048), (128, 4096), (512, 4096), (512, 8192), (2048, 8192)]
+    two = [(8, 2049), (8, 4096), (32, 4096), (8, 8192), (128, 8192), (2048, 8193)]
+    assert [p[14] for p in plans([(m, n, 256, 0, m) for m, n in one + two])] == [1] * len(one) + [0] * len(two)
