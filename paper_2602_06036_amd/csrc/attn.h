@@ -19,8 +19,9 @@ struct AttnArgs {
   void* out = nullptr;   // MFMA kernels, n_splits == 1: the finished rows go here (GEMM operand, row length Hq*hd), no merge follows
 };
 
-// A row that sees no key is zeros.  A NaN among a row's scores is a NaN in its sum of exponentials whatever else it sees (maxima pass
-// NaN over, sums do not), and the row is NaN, in every kernel and however its context is split.
+// A row that sees no key is zeros: its sums are, and they are divided by infinity where there is no positive sum of exponentials.  A NaN among a
+// row's scores is a NaN in the products with V whatever else it sees (maxima pass NaN over, sums do not, and a weight of zero keeps it), so the
+// row is NaN, in every kernel and however its context is split.
 // partial results: for pr = (m*Hq + hq)*n_splits + split : ml[pr] = (running max, sum exp), o[pr*hd + d]
 // (o unnormalised, relative to the running max)
 
@@ -186,7 +187,7 @@ __global__ __launch_bounds__(256, 2) void attn_short_simple_kernel(const T* __re
     L += ml.y * e;
     x += e * so[w][d];
   }
-  Act<T>::store(out, m, hq * hd + d, aa.n_q_heads * hd, L == 0.f ? 0.f : x / L);
+  Act<T>::store(out, m, hq * hd + d, aa.n_q_heads * hd, x / (L > 0.f ? L : INFINITY));
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -239,7 +240,7 @@ __global__ __launch_bounds__(128) void attn_merge_rows_kernel(const float* __res
     }
     for (; c < n_splits; ++c) o += wgt[c] * po[(size_t)c * hd];
     const float L = s_L;
-    Act<T>::store(out, m, hq * hd + d, n_q_heads * hd, L == 0.f ? 0.f : o / L);
+    Act<T>::store(out, m, hq * hd + d, n_q_heads * hd, o / (L > 0.f ? L : INFINITY));
   }
 }
 
@@ -306,8 +307,7 @@ __global__ __launch_bounds__(512) void attn_merge_kernel(const float* __restrict
     o.x += w * a.x; o.y += w * a.y; o.z += w * a.z; o.w += w * a.w;
   }
   if (live) {
-    const float L = s_L[r];
-    Act<T>::store4(out, m, hq * hd + c * 4, n_q_heads * hd,
-                   L == 0.f ? make_float4(0.f, 0.f, 0.f, 0.f) : make_float4(o.x / L, o.y / L, o.z / L, o.w / L));
+    const float L = s_L[r] > 0.f ? s_L[r] : INFINITY;
+    Act<T>::store4(out, m, hq * hd + c * 4, n_q_heads * hd, make_float4(o.x / L, o.y / L, o.z / L, o.w / L));
   }
 }

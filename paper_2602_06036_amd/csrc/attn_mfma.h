@@ -212,7 +212,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(const bf16_t* __restr
   l += __shfl_xor(l, 32, 64);
   if (!valid) return;
   if (aa.out) {   // the only split: nothing to merge
-    const float L1 = l == 0.f ? INFINITY : l;   // no visible key: a row of zeros
+    const float L1 = l > 0.f ? l : INFINITY;   // no visible key: a row of zeros
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
       Act<bf16_t>::store4(reinterpret_cast<bf16_t*>(aa.out), s * B + slot, hq * HD + dt * 16 + 4 * g, aa.n_q_heads * HD,
@@ -541,9 +541,9 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_wide_kernel(const bf16_t* __
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
       const float2 ml = s_ml[w][threadIdx.x];
-      l += (ml.x == -INFINITY) ? ml.y : ml.y * exp2f(ml.x - m_all);   // without a maximum: 0 or NaN
+      l += (ml.x == -INFINITY) ? 0.f : ml.y * exp2f(ml.x - m_all);
     }
-    s_L[threadIdx.x] = l == 0.f ? INFINITY : l;   // no visible key: a row of zeros
+    s_L[threadIdx.x] = l > 0.f ? l : INFINITY;   // no visible key: a row of zeros
   }
   __syncthreads();
   if (aa.out) {
@@ -600,7 +600,7 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_wide_kernel(const bf16_t* __
 #pragma unroll
       for (int w = 0; w < NW; ++w) {
         const float2 ml = s_ml[w][r];
-        l += (ml.x == -INFINITY) ? ml.y : ml.y * exp2f(ml.x - m_all);   // without a maximum: 0 or NaN
+        l += (ml.x == -INFINITY) ? 0.f : ml.y * exp2f(ml.x - m_all);
       }
       part_ml[pr] = make_float2(m_all * 0.69314718055994531f, l);   // the cross-split merge works with natural exponents
     }
