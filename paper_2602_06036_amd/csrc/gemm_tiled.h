@@ -15,8 +15,11 @@
 // Pipelined variant (REG = false): a ring of NS LDS slots filled by direct-to-LDS loads (global_load_lds_dwordx4: every
 // lane's 16 bytes go straight to consecutive LDS addresses, which is exactly a fragment in operand order), and the
 // fragments double-buffered in registers: while the MFMAs of k tile t run out of one register set, the LDS reads of k tile
-// t+1 fill the other, so no MFMA waits for LDS behind the barrier.  One barrier per k tile.  Against the same ring with the
-// reads behind the barrier: gate/up of the 8B shape 155-160 -> 150 us at 512 rows, 92 -> 85-89 at 256, 2-4 % elsewhere.
+// t+1 fill the other, so no MFMA waits for LDS behind the barrier.  One barrier per k tile.  The reads and the refill's copies are
+// issued one behind each MFMA: in bursts ahead of the MFMAs (all wavefronts of a SIMD come out of the barrier together) their 14 to 19
+// instructions kept the matrix cores idle.  Launch after launch over random operands, bursts and one by one: gate/up of the 8B shape at 512 rows
+// 150 -> 143 us (1.44 PFLOP/s issued), 256 rows 90 -> 86, 2048 rows on the same 384 x 128 tiles 574 -> 547; 256 x 128 tiles at 512
+// rows 187 -> 177; a step of 512 rows 3 %, of 256 rows 2.5 %.
 // Register-staged variant (REG = true, 256 x 128 tiles): global -> registers -> one of two LDS slots.  Its 128
 // accumulators leave no registers for a second fragment set with two workgroups on a CU, and the two cover each other's
 // seams; the largest wavefront tile moves the fewest bytes per flop and is the fastest one over many rounds (2048 rows:
@@ -31,11 +34,18 @@
 // more than one tile more than another (20 blocks are 3 on four XCDs and 2 on four: a fifth of the launch; the even case is
 // 1 % faster the first way).
 #pragma once
+#include <utility>
+
 #include "gemm.h"
 
 // wavefronts per SIMD to leave registers for: two workgroups share a CU where their staging fits twice
 template <int WN, int WM, int NS, int WY>
 constexpr int tiled_waves() { return NS * (WY * WN + 4 * WM) <= 80 ? WY : 1; }
+
+template <typename F, int... I>
+__device__ __forceinline__ void unroll_each(F& f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, typename F>
+__device__ __forceinline__ void unroll(F f) { unroll_each(f, std::make_integer_sequence<int, N>{}); }
 
 template <int WN, int WM, int EPI, int NS, bool GRP = false, int WY = 2, bool REG = false>
 __global__ __launch_bounds__(128 * WY, (tiled_waves<WN, WM, NS, WY>())) void gemm_bf16_tiled_kernel(
@@ -192,34 +202,49 @@ __global__ __launch_bounds__(128 * WY, (tiled_waves<WN, WM, NS, WY>())) void gem
       for (int i = 0; i < PER; ++i) dma(i, d);
       advance();
     }
+    auto w_at = [&](int sl, int i) { return stage[sl][wy * WN + i][lane]; };
+    auto a_at = [&](int sl, int jj, int p) { return stage[sl][BNT + 2 * (wx * WM + jj) + p][lane]; };
+    // the next k tile's copies of this wavefront have landed, its reads of the one before are done
+    auto seam = [&]() {
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER * (NS - 2)) : "memory");
+      __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+    };
     u32x4 wf[2][WN], ap[2][WM][2];
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER * (NS - 1)) : "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    read(0, wf[0], ap[0]);
+#pragma unroll
+    for (int i = 0; i < WN; ++i) wf[0][i] = w_at(0, i);
+#pragma unroll
+    for (int jj = 0; jj < WM; ++jj)
+#pragma unroll
+      for (int p = 0; p < 2; ++p) ap[0][jj][p] = a_at(0, jj, p);
     int slot = 0;
-    // the refill's loads go out in front of the MFMAs or between the activation bands: 384 x 128 tiles like the former (150
-    // against 155 us for gate/up at 512 rows), the others the latter
-    constexpr bool SPREAD = !(WN == 6 && WM == 4);
+    // K tile t.  Behind each MFMA (band, then plane, then weight tile) goes one of the loads that are due meanwhile, pinned there.
     auto k_tile = [&](auto cur_c) {
       constexpr int C = decltype(cur_c)::value;
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER * (NS - 2)) : "memory");
-      __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): this wavefront's reads of k tile t are done
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_sched_barrier(0);
       const int next = slot == NS - 1 ? 0 : slot + 1;
-      read(next, wf[C ^ 1], ap[C ^ 1]);     // past the end: a landed copy of the last k tile, not used
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int jj = 0; jj < WM; ++jj) {
-#pragma unroll
-        for (int i = 0; i < PER; ++i)
-          if ((SPREAD ? i * WM / PER : 0) == jj) dma(i, slot);
+      constexpr int RD = WN + 2 * WM, ITEMS = RD + PER;   // the next k tile's fragments, then the refill of this one's slot
+      auto item = [&](auto qc) {
+        constexpr int q = decltype(qc)::value;
+        // past the end of the K range: a landed copy of the last k tile, not used
+        if constexpr (q < 1) ap[C ^ 1][0][0] = a_at(next, 0, 0);
+        else if constexpr (q < 1 + WN) wf[C ^ 1][q - 1] = w_at(next, q - 1);
+        else if constexpr (q < RD) ap[C ^ 1][(q - WN) / 2][(q - WN) & 1] = a_at(next, (q - WN) / 2, (q - WN) & 1);
+        else if constexpr (q < ITEMS) dma(q - RD, slot);
+      };
+      seam();
+      unroll<2 * WN * WM>([&](auto mc) {
+        constexpr int m = decltype(mc)::value, jj = m / (2 * WN), p = (m / WN) & 1, i = m % WN;
+        acc[i][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf[C][i]), __builtin_bit_cast(bf16x8, ap[C][jj][p]), acc[i][jj], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
-        mma_band(jj, wf[C], ap[C][jj]);
+        item(mc);
+        static_assert(ITEMS <= 2 * WN * WM, "an item behind each MFMA");
         __builtin_amdgcn_sched_barrier(0);
-      }
+      });
       advance();
       slot = next;
     };
