@@ -870,16 +870,16 @@ void launch_bf16(hipStream_t st, const bf16_t* W, const bf16_t* A, int M, int N,
   }
 }
 
-template <int WN, int WM, int NS, int WY = 2, bool REG = false>
+template <int WN, int WM, int NS, int WY = 2>
 void launch_tiled(hipStream_t st, const bf16_t* W, const bf16_t* A, int M, int N, int K, int epi, EpiArgs ep, int ks) {
   const int n_blocks = (N / 16 + WY * WN - 1) / (WY * WN), m_blocks = ((M + 15) / 16 + 2 * WM - 1) / (2 * WM);
   const dim3 grid((n_blocks * m_blocks + 7) / 8 * 8, ks), block(128 * WY);
   g_launch_parts = n_blocks;
   g_launch_kind = WY == 4 ? DFLASH_GEMM_TILED8 : DFLASH_GEMM_TILED4;
   if (epi == EPI_SWIGLU)
-    hipLaunchKernelGGL((gemm_bf16_tiled_kernel<WN, WM, EPI_SWIGLU, NS, false, WY, REG>), grid, block, 0, st, W, A, M, N, K, n_blocks, m_blocks, ep);
+    hipLaunchKernelGGL((gemm_bf16_tiled_kernel<WN, WM, EPI_SWIGLU, NS, false, WY>), grid, block, 0, st, W, A, M, N, K, n_blocks, m_blocks, ep);
   else
-    hipLaunchKernelGGL((gemm_bf16_tiled_kernel<WN, WM, EPI_STORE, NS, false, WY, REG>), grid, block, 0, st, W, A, M, N, K, n_blocks, m_blocks, ep);
+    hipLaunchKernelGGL((gemm_bf16_tiled_kernel<WN, WM, EPI_STORE, NS, false, WY>), grid, block, 0, st, W, A, M, N, K, n_blocks, m_blocks, ep);
 }
 
 inline int gemm_class(int epi, int N, int vocab) { return (epi == EPI_STORE && N == vocab) ? DFLASH_PROF_GEMM_LMHEAD : epi; }
@@ -924,12 +924,13 @@ Engine<bf16_t>::Slab Engine<bf16_t>::gemm(const bf16_t* W, const bf16_t* A, int 
     ks = tp.ks;
     ep.slab = (size_t)M * ep.ld;
     switch (tp.t->wy * 100 + tp.t->wn * 10 + tp.t->wm) {
-      case 284: launch_tiled<8, 4, 2, 2, true>(st, W, A, M, N, K, kepi, ep, ks); break;
+      case 284: launch_tiled<8, 4, 3>(st, W, A, M, N, K, kepi, ep, ks); break;
       case 264: launch_tiled<6, 4, 2>(st, W, A, M, N, K, kepi, ep, ks); break;
       case 244: launch_tiled<4, 4, 3>(st, W, A, M, N, K, kepi, ep, ks); break;
       case 282: launch_tiled<8, 2, 3>(st, W, A, M, N, K, kepi, ep, ks); break;
       case 262: launch_tiled<6, 2, 3>(st, W, A, M, N, K, kepi, ep, ks); break;
       case 242: launch_tiled<4, 2, 4>(st, W, A, M, N, K, kepi, ep, ks); break;
+      case 484: launch_tiled<8, 4, 3, 4>(st, W, A, M, N, K, kepi, ep, ks); break;
       case 464: launch_tiled<6, 4, 3, 4>(st, W, A, M, N, K, kepi, ep, ks); break;
       case 444: launch_tiled<4, 4, 4, 4>(st, W, A, M, N, K, kepi, ep, ks); break;
       case 462: launch_tiled<6, 2, 4, 4>(st, W, A, M, N, K, kepi, ep, ks); break;

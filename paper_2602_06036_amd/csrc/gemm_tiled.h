@@ -12,20 +12,18 @@
 // What bounds it: over random operands every tiling ends at 1.2-1.45 PFLOP/s of issued MFMA work (a torch matrix product of
 // the same issued size reaches 1.1-1.47), where the clock gives way to the power limit; below that the waits at the k tiles' seams count.
 //
-// Pipelined variant (REG = false): a ring of NS LDS slots filled by direct-to-LDS loads (global_load_lds_dwordx4: every
-// lane's 16 bytes go straight to consecutive LDS addresses, which is exactly a fragment in operand order), and the
-// fragments double-buffered in registers: while the MFMAs of k tile t run out of one register set, the LDS reads of k tile
-// t+1 fill the other, so no MFMA waits for LDS behind the barrier.  One barrier per k tile.  The reads and the refill's copies are
-// issued one behind each MFMA: in bursts ahead of the MFMAs (all wavefronts of a SIMD come out of the barrier together) their 14 to 19
-// instructions kept the matrix cores idle.  Launch after launch over random operands, bursts and one by one: gate/up of the 8B shape at 512 rows
-// 150 -> 143 us (1.44 PFLOP/s issued), 256 rows 90 -> 86, 2048 rows on the same 384 x 128 tiles 574 -> 547; 256 x 128 tiles at 512
-// rows 187 -> 177; a step of 512 rows 3 %, of 256 rows 2.5 %.
-// Register-staged variant (REG = true, 256 x 128 tiles): global -> registers -> one of two LDS slots.  Its 128
-// accumulators leave no registers for a second fragment set with two workgroups on a CU, and the two cover each other's
-// seams; the largest wavefront tile moves the fewest bytes per flop and is the fastest one over many rounds (2048 rows:
-// gate/up 570 us, 1.45 PFLOP/s).  Order inside a k tile: barrier -> all fragment reads -> the LDS writes of the next k
-// tile and the global loads after it -> the MFMAs; LDS operations of a wavefront complete in order, so the MFMAs wait for
-// the reads only and the (slow) writes drain behind the MFMA stream.
+// A ring of NS LDS slots is filled by direct-to-LDS loads (global_load_lds_dwordx4: every lane's 16 bytes go straight to
+// consecutive LDS addresses, which is exactly a fragment in operand order), and the fragments are double-buffered in registers:
+// while the MFMAs of k tile t run out of one register set, the LDS reads of k tile t+1 fill the other, so no MFMA waits for LDS
+// behind the barrier.  One barrier per k tile.  The reads and the refill's copies are issued one behind each MFMA: in bursts ahead
+// of the MFMAs (all wavefronts of a SIMD come out of the barrier together) their 14 to 19 instructions kept the matrix cores idle.
+// Launch after launch over random operands, bursts and one by one: gate/up of the 8B shape at 512 rows 150 -> 143 us (1.44
+// PFLOP/s issued), 256 rows 90 -> 86, 2048 rows on the same 384 x 128 tiles 574 -> 547; 256 x 128 tiles at 512 rows 187 -> 177; a
+// step of 512 rows 3 %, of 256 rows 2.5 %.
+// Rolling form (512 x 128 tiles): 128 accumulators leave no room for a second set of all activation fragments, so they roll, one
+// band ahead, and the seam between two k tiles lies in front of the last band instead of the first.  The fewest bytes a flop from
+// L2 and from LDS of all tiles, and the fastest over many rows: gate/up at 2048 rows 541 us (1.52 PFLOP/s issued) against 547 on 384 x 128
+// tiles and 563 on 256 x 128 tiles staged through registers, two workgroups a CU (the form before); down projection 276 against 290.
 //
 // Workgroup order: consecutive workgroup ids go to different XCDs (round-robin dispatch, id = 8*j + x), and the
 // workgroups that re-read one weight block run back to back on one XCD and share its L2.  Where the weight blocks divide
@@ -42,18 +40,21 @@
 template <int WN, int WM, int NS, int WY>
 constexpr int tiled_waves() { return NS * (WY * WN + 4 * WM) <= 80 ? WY : 1; }
 
+template <int WN, int WM>
+constexpr bool tiled_rolls() { return WN * WM >= 32; }   // see above
+
 template <typename F, int... I>
 __device__ __forceinline__ void unroll_each(F& f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
 template <int N, typename F>
 __device__ __forceinline__ void unroll(F f) { unroll_each(f, std::make_integer_sequence<int, N>{}); }
 
-template <int WN, int WM, int EPI, int NS, bool GRP = false, int WY = 2, bool REG = false>
+template <int WN, int WM, int EPI, int NS, bool GRP = false, int WY = 2>
 __global__ __launch_bounds__(128 * WY, (tiled_waves<WN, WM, NS, WY>())) void gemm_bf16_tiled_kernel(
     const bf16_t* __restrict__ W, const bf16_t* __restrict__ A, int M, int N, int K, int n_blocks, int m_blocks, EpiArgs ep) {
   constexpr int NWV = 2 * WY;                       // wavefronts: WY along N x 2 along M
   constexpr int BNT = WY * WN, BMT = 2 * WM;        // fragments of a stage: BNT weight + 2*BMT activation (hi, lo)
   constexpr int FR = BNT + 2 * BMT, PER = FR / NWV; // fragments copied by each wavefront
-  static_assert(WN % 2 == 0 && WM % 2 == 0 && FR % NWV == 0 && NS >= 2 && (!REG || NS == 2) && NS * FR <= 160 && (WY == 2 || WY == 4),
+  static_assert(WN % 2 == 0 && WM % 2 == 0 && FR % NWV == 0 && NS >= 2 && NS * FR <= 160 && (WY == 2 || WY == 4),
                 "tile shape");
   __shared__ u32x4 stage[NS][FR][64];
 
@@ -82,7 +83,7 @@ __global__ __launch_bounds__(128 * WY, (tiled_waves<WN, WM, NS, WY>())) void gem
   const int kb = min(KT, kz * per), ke = min(KT, kb + per);
   const int nt0 = nb * BNT;
 
-  // the PER fragments this wavefront copies per stage: address at k tile kb (the same for all lanes) and bytes per k tile (ring)
+  // the PER fragments this wavefront copies per stage: address at k tile kb (the same for all lanes) and bytes per k tile
   const char* src[PER];
   unsigned step[PER];
 #pragma unroll
@@ -109,82 +110,8 @@ __global__ __launch_bounds__(128 * WY, (tiled_waves<WN, WM, NS, WY>())) void gem
   for (int i = 0; i < WN; ++i)
 #pragma unroll
     for (int jj = 0; jj < WM; ++jj) acc[i][jj] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  auto mma_band = [&](int jj, const u32x4 (&wf)[WN], const u32x4 (&ap)[2]) {
-#pragma unroll
-    for (int i = 0; i < WN; ++i)
-      acc[i][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf[i]), __builtin_bit_cast(bf16x8, ap[0]), acc[i][jj], 0, 0, 0);
-#pragma unroll
-    for (int i = 0; i < WN; ++i)
-      acc[i][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf[i]), __builtin_bit_cast(bf16x8, ap[1]), acc[i][jj], 0, 0, 0);
-  };
-  auto read = [&](int slot, u32x4 (&wf)[WN], u32x4 (&ap)[WM][2]) {
-    const u32x4* sp = &stage[0][0][0] + (size_t)slot * (FR * 64) + lane;
-#pragma unroll
-    for (int i = 0; i < WN; ++i) wf[i] = sp[(wy * WN + i) * 64];
-#pragma unroll
-    for (int jj = 0; jj < WM; ++jj) {
-      ap[jj][0] = sp[(BNT + 2 * (wx * WM + jj)) * 64];
-      ap[jj][1] = sp[(BNT + 2 * (wx * WM + jj) + 1) * 64];
-    }
-  };
 
   if (kb < ke) {
-   if constexpr (REG) {
-    // Addresses in lane registers, from the number of the k tile: 2-3 % faster than the ring's (uniform pointers moved on under
-    // a branch), which every MFMA burst then starts behind: gate/up of 28672 rows at 512 activation rows 185 against 190 us, of
-    // 24576 rows at 2048 574 against 587.
-    const u32x4* g_base[PER];
-    size_t g_off[PER];   // u32x4 units, at k tile 0
-    int g_step[PER];
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {   // the same fragments as in the ring
-      const int f = wave * PER + i;
-      if (f < BNT) {
-        g_base[i] = reinterpret_cast<const u32x4*>(W);
-        g_off[i] = (size_t)min(nt0 + f, n_tiles - 1) * 64 + lane;
-        g_step[i] = n_tiles * 64;
-      } else {
-        const int a = f - BNT;
-        g_base[i] = reinterpret_cast<const u32x4*>(A);
-        g_off[i] = (size_t)min(mt0 + (a >> 1), m_tiles - 1) * KT * 128 + (a & 1) * 64 + lane;
-        g_step[i] = 128;
-      }
-    }
-    u32x4 g[PER];   // k tile t+1 on its way from global memory while k tile t is multiplied
-    auto load_global = [&](int kt) {
-#pragma unroll
-      for (int i = 0; i < PER; ++i) g[i] = g_base[i][g_off[i] + (size_t)kt * g_step[i]];
-    };
-    auto write_lds = [&](int slot) {
-#pragma unroll
-      for (int i = 0; i < PER; ++i) stage[slot][wave * PER + i][lane] = g[i];
-    };
-    load_global(kb);
-    write_lds(0);
-    load_global(min(kb + 1, ke - 1));
-    // Straight-line body: past the end of the K range the global loads repeat the last k tile and the write fills a
-    // slot nobody reads any more.
-    auto k_tile = [&](auto s0_c, int kt) {
-      constexpr int s0 = decltype(s0_c)::value;
-      u32x4 wf[WN], ap[WM][2];
-      __syncthreads();                       // k tile t is complete in s0, everybody is done with the other slot
-      __builtin_amdgcn_sched_barrier(0);
-      read(s0, wf, ap);
-      __builtin_amdgcn_sched_barrier(0);
-      write_lds(s0 ^ 1);
-      load_global(min(kt + 2, ke - 1));
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int jj = 0; jj < WM; ++jj) mma_band(jj, wf, ap[jj]);
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    int kt = kb;
-    for (; kt + 1 < ke; kt += 2) {
-      k_tile(std::integral_constant<int, 0>{}, kt);
-      k_tile(std::integral_constant<int, 1>{}, kt + 1);
-    }
-    if (kt < ke) k_tile(std::integral_constant<int, 0>{}, kt);
-   } else {
     // The direct-to-LDS loads are inline assembly so that the compiler does not count them: it would otherwise wait for ALL of
     // them before every LDS read.  Completion is tracked by hand: each wavefront issues PER loads per k tile, in order, so
     // "at most PER*(NS-2) outstanding" says that its share of k tile t+1 has landed.  The barrier extends that to the whole
@@ -212,37 +139,48 @@ __global__ __launch_bounds__(128 * WY, (tiled_waves<WN, WM, NS, WY>())) void gem
       asm volatile("" ::: "memory");
       __builtin_amdgcn_sched_barrier(0);
     };
-    u32x4 wf[2][WN], ap[2][WM][2];
+    constexpr bool ROLL = tiled_rolls<WN, WM>();
+    u32x4 wf[2][WN], ap[2][ROLL ? 1 : WM][2];
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER * (NS - 1)) : "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 #pragma unroll
     for (int i = 0; i < WN; ++i) wf[0][i] = w_at(0, i);
 #pragma unroll
-    for (int jj = 0; jj < WM; ++jj)
+    for (int jj = 0; jj < (ROLL ? 1 : WM); ++jj)
 #pragma unroll
       for (int p = 0; p < 2; ++p) ap[0][jj][p] = a_at(0, jj, p);
     int slot = 0;
-    // K tile t.  Behind each MFMA (band, then plane, then weight tile) goes one of the loads that are due meanwhile, pinned there.
+    // K tile t.  MFMA number q (band, then plane, then weight tile) is followed by at most a few of the loads that are due meanwhile,
+    // pinned there: in a burst ahead of the MFMAs they kept the matrix cores idle for a sixth of the k tile.
     auto k_tile = [&](auto cur_c) {
       constexpr int C = decltype(cur_c)::value;
       const int next = slot == NS - 1 ? 0 : slot + 1;
-      constexpr int RD = WN + 2 * WM, ITEMS = RD + PER;   // the next k tile's fragments, then the refill of this one's slot
+      constexpr int RD = WN + (ROLL ? 2 : 2 * WM), ITEMS = RD + PER;   // the next k tile's fragments, then the refill of this one's slot
       auto item = [&](auto qc) {
         constexpr int q = decltype(qc)::value;
         // past the end of the K range: a landed copy of the last k tile, not used
-        if constexpr (q < 1) ap[C ^ 1][0][0] = a_at(next, 0, 0);
+        if constexpr (q < 1) ap[ROLL ? 0 : C ^ 1][0][0] = a_at(next, 0, 0);
         else if constexpr (q < 1 + WN) wf[C ^ 1][q - 1] = w_at(next, q - 1);
-        else if constexpr (q < RD) ap[C ^ 1][(q - WN) / 2][(q - WN) & 1] = a_at(next, (q - WN) / 2, (q - WN) & 1);
+        else if constexpr (q < RD) ap[ROLL ? 0 : C ^ 1][ROLL ? 0 : (q - WN) / 2][(q - WN) & 1] = a_at(next, (q - WN) / 2, (q - WN) & 1);
         else if constexpr (q < ITEMS) dma(q - RD, slot);
       };
-      seam();
+      if constexpr (!ROLL) seam();
       unroll<2 * WN * WM>([&](auto mc) {
-        constexpr int m = decltype(mc)::value, jj = m / (2 * WN), p = (m / WN) & 1, i = m % WN;
-        acc[i][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf[C][i]), __builtin_bit_cast(bf16x8, ap[C][jj][p]), acc[i][jj], 0, 0, 0);
+        constexpr int m = decltype(mc)::value, jj = m / (2 * WN), p = (m / WN) & 1, i = m % WN, at = m % (2 * WN);
+        if constexpr (ROLL && jj == WM - 1 && at == 0) seam();   // this k tile is in registers from here on
+        const u32x4 a = ROLL ? ap[jj & 1][0][p] : ap[C][ROLL ? 0 : jj][p];
+        acc[i][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf[C][i]), __builtin_bit_cast(bf16x8, a), acc[i][jj], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
-        item(mc);
-        static_assert(ITEMS <= 2 * WN * WM, "an item behind each MFMA");
+        if constexpr (!ROLL) {
+          item(mc);
+          static_assert(ITEMS <= 2 * WN * WM, "an item behind each MFMA");
+        } else if constexpr (jj < WM - 1) {
+          if constexpr (at < 2) ap[(jj + 1) & 1][0][at] = a_at(slot, jj + 1, at);   // the next band
+        } else {
+          constexpr int EACH = (ITEMS + 2 * WN - 1) / (2 * WN);
+          unroll<EACH>([&](auto ec) { item(std::integral_constant<int, at * EACH + decltype(ec)::value>{}); });
+        }
         __builtin_amdgcn_sched_barrier(0);
       });
       advance();
@@ -255,7 +193,6 @@ __global__ __launch_bounds__(128 * WY, (tiled_waves<WN, WM, NS, WY>())) void gem
     }
     if (kt < ke) k_tile(std::integral_constant<int, 0>{});
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // nothing may still be on its way into LDS when the slots are reused or released
-   }
   }
 
   // lane l holds y[m = band*16 + l%16][n = tile*16 + 4*(l/16) .. +3]

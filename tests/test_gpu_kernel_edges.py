@@ -7,7 +7,7 @@ import pytest
 
 from oracle import dflash_oracle as O
 from synth import inputs as si
-from tests.helpers import LAST_WORKGROUP, STREAM_HEADS, TILE_EDGES, W64, tiny_workload
+from tests.helpers import LAST_WORKGROUP, ROLLED_TILES, STREAM_HEADS, TILE_EDGES, W64, tiny_workload
 from tests.test_gpu_parity import ROUTE_CLEAR, Lockstep, _gpu
 
 pytestmark = pytest.mark.gpu
@@ -178,6 +178,12 @@ def test_forced_tiles_over_ragged_sizes(n_seqs, ffn, vocab, wide, tile, wm, ks, 
         monkeypatch.setenv("DFLASH_GEMM_" + k, str(v))
     counts = _many_rows(n_seqs, 256, ffn, vocab)
     assert counts[wide] > 0 and counts[3 - wide] == 0 and counts[0] == 0
+
+
+@pytest.mark.parametrize("n_seqs,ffn,vocab,wide,tile,wm,ks", ROLLED_TILES)
+def test_rolled_tiles_over_ragged_sizes(n_seqs, ffn, vocab, wide, tile, wm, ks, monkeypatch):
+    """512 x 128 tiles: clamped last weight blocks, activation blocks of one band, K ranges of a k tile or two (shorter than the ring), odd numbers of k tiles."""
+    test_forced_tiles_over_ragged_sizes(n_seqs, ffn, vocab, wide, tile, wm, ks, monkeypatch)
 
 
 @pytest.mark.parametrize("d,heads,kv_heads,hd,ffn,vocab,n_seqs,block,lens", [

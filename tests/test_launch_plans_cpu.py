@@ -4,7 +4,7 @@ import subprocess
 
 import pytest
 
-from tests.helpers import LAST_WORKGROUP, STREAM_HEADS, TILE_EDGES
+from tests.helpers import LAST_WORKGROUP, ROLLED_TILES, STREAM_HEADS, TILE_EDGES
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "..", "paper_2602_06036_amd", "csrc")
@@ -98,6 +98,22 @@ def test_forced_tiles_cover_ragged_geometries(plans):
         assert ("clamped", s) in seen and ("clamped swiglu", s) in seen, s
     assert {"interleaved", "contiguous", "one band"} <= seen
     assert {c[1] for c in seen if c[0] == "K ranges"} >= {2, 3, 5, 6} and any(c[0] == "K ranges" and c[2] for c in seen)
+
+
+def test_rolled_tiles_where_the_gpu_test_forces_them_and_over_many_rows(plans):
+    for n_seqs, ffn, vocab, wide, tile, wm, ks in ROLLED_TILES:
+        M = 16 * n_seqs
+        mats = [(M, 512, 256, 1, M), (M, 256, 256, 1, M), (M, 2 * ffn, 256, 0, M), (M, 256, ffn, 1, M), (M, vocab, 256, 0, M)]
+        assert all(p[:3] == (8, 4, 4) for p in plans(mats, GEMM_WIDE=wide, GEMM_TILE=tile, GEMM_WM=wm, GEMM_KS=ks))
+    assert [p[:4] for p in plans([(2048, 24576, 4096, 0, 2048), (1088, 24576, 4096, 0, 2048), (2048, 4096, 12288, 1, 2048)])] == [(8, 4, 4, 1), (8, 4, 4, 1), (8, 4, 4, 2)]
+
+
+def test_routed_layers_keep_their_k_ranges(plans):
+    """Another order of sums ahead of a router turns near-ties into other experts: QKV and O projection of the 2048-wide routed target."""
+    rows = (80, 128, 160, 200, 256, 288, 320, 384, 448, 512, 1024, 2048)
+    want = {(5120, 2048): [3, 3, 2, 3, 3, 2, 2, 1, 2, 2, 1, 1], (2048, 4096): [8, 8, 4, 4, 4, 3, 3, 4, 2, 2, 2, 2]}
+    for (n, k), ks in want.items():
+        assert [p[3] for p in plans([(m, n, k, 1, m) for m in rows])] == ks
 
 
 def test_streaming_heads_take_the_weight_tiles_that_the_gpu_test_names(plans):
