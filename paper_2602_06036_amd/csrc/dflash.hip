@@ -876,10 +876,17 @@ void launch_tiled(hipStream_t st, const bf16_t* W, const bf16_t* A, int M, int N
   const dim3 grid((n_blocks * m_blocks + 7) / 8 * 8, ks), block(128 * WY);
   g_launch_parts = n_blocks;
   g_launch_kind = WY == 4 ? DFLASH_GEMM_TILED8 : DFLASH_GEMM_TILED4;
-  if (epi == EPI_SWIGLU)
-    hipLaunchKernelGGL((gemm_bf16_tiled_kernel<WN, WM, EPI_SWIGLU, NS, false, WY>), grid, block, 0, st, W, A, M, N, K, n_blocks, m_blocks, ep);
-  else
-    hipLaunchKernelGGL((gemm_bf16_tiled_kernel<WN, WM, EPI_STORE, NS, false, WY>), grid, block, 0, st, W, A, M, N, K, n_blocks, m_blocks, ep);
+  auto go = [&](auto sc) {
+    constexpr bool STREAM = decltype(sc)::value;
+    if (epi == EPI_SWIGLU)
+      hipLaunchKernelGGL((gemm_bf16_tiled_kernel<WN, WM, EPI_SWIGLU, NS, false, WY, STREAM>), grid, block, 0, st, W, A, M, N, K, n_blocks, m_blocks, ep);
+    else
+      hipLaunchKernelGGL((gemm_bf16_tiled_kernel<WN, WM, EPI_STORE, NS, false, WY, STREAM>), grid, block, 0, st, W, A, M, N, K, n_blocks, m_blocks, ep);
+  };
+  if constexpr (WY == 4) {
+    if (m_blocks <= 8) return go(std::true_type{});
+  }
+  go(std::false_type{});
 }
 
 inline int gemm_class(int epi, int N, int vocab) { return (epi == EPI_STORE && N == vocab) ? DFLASH_PROF_GEMM_LMHEAD : epi; }

@@ -25,6 +25,12 @@
 // L2 and from LDS of all tiles, and the fastest over many rows: gate/up at 2048 rows 541 us (1.52 PFLOP/s issued) against 547 on 384 x 128
 // tiles and 563 on 256 x 128 tiles staged through registers, two workgroups a CU (the form before); down projection 276 against 290.
 //
+// STREAM: the weights are read past the caches' usual order of eviction (nt), so that the activations stay: for routed items, whose
+// weights are read once, and for the eight-wavefront tiles of few activation blocks, whose workgroups read a weight block at the same
+// time.  Two-layer verification of 512 routed rows 947 -> 917 us by the former, 907 by both; four-layer step of 256 rows 1585 -> 1546,
+// verification of 128 rows 768 -> 752, prefill of 1024 (eight blocks) 3008 -> 2985; but of 1088 (nine) 3572 -> 3607, of 2048 5605
+// -> 5630, and with the four-wavefront tiles' weights as well, verification of 128 routed rows 624 -> 632.
+//
 // Workgroup order: consecutive workgroup ids go to different XCDs (round-robin dispatch, id = 8*j + x), and the
 // workgroups that re-read one weight block run back to back on one XCD and share its L2.  Where the weight blocks divide
 // evenly over the XCDs, XCD x takes blocks x, x + 8, ...: the chip sweeps neighbouring blocks together.  Otherwise XCD x
@@ -48,13 +54,13 @@ __device__ __forceinline__ void unroll_each(F& f, std::integer_sequence<int, I..
 template <int N, typename F>
 __device__ __forceinline__ void unroll(F f) { unroll_each(f, std::make_integer_sequence<int, N>{}); }
 
-template <int WN, int WM, int EPI, int NS, bool GRP = false, int WY = 2>
+template <int WN, int WM, int EPI, int NS, bool GRP = false, int WY = 2, bool STREAM = GRP>
 __global__ __launch_bounds__(128 * WY, (tiled_waves<WN, WM, NS, WY>())) void gemm_bf16_tiled_kernel(
     const bf16_t* __restrict__ W, const bf16_t* __restrict__ A, int M, int N, int K, int n_blocks, int m_blocks, EpiArgs ep) {
   constexpr int NWV = 2 * WY;                       // wavefronts: WY along N x 2 along M
   constexpr int BNT = WY * WN, BMT = 2 * WM;        // fragments of a stage: BNT weight + 2*BMT activation (hi, lo)
-  constexpr int FR = BNT + 2 * BMT, PER = FR / NWV; // fragments copied by each wavefront
-  static_assert(WN % 2 == 0 && WM % 2 == 0 && FR % NWV == 0 && NS >= 2 && NS * FR <= 160 && (WY == 2 || WY == 4),
+  constexpr int FR = BNT + 2 * BMT, PER = FR / NWV, PW = BNT / NWV;   // fragments copied by each wavefront, PW of them weights
+  static_assert(WN % 2 == 0 && WM % 2 == 0 && FR % NWV == 0 && BNT % NWV == 0 && NS >= 2 && NS * FR <= 160 && (WY == 2 || WY == 4),
                 "tile shape");
   __shared__ u32x4 stage[NS][FR][64];
 
@@ -86,10 +92,11 @@ __global__ __launch_bounds__(128 * WY, (tiled_waves<WN, WM, NS, WY>())) void gem
   // the PER fragments this wavefront copies per stage: address at k tile kb (the same for all lanes) and bytes per k tile
   const char* src[PER];
   unsigned step[PER];
+  auto fragment = [&](int i) { return i < PW ? wave * PW + i : BNT + wave * (PER - PW) + i - PW; };
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
-    const int f = wave * PER + i;
-    if (f < BNT) {   // weight fragment: bands past the matrix alias the last band (never stored)
+    const int f = fragment(i);
+    if (i < PW) {    // weight fragment: bands past the matrix alias the last band (never stored)
       src[i] = reinterpret_cast<const char*>(W) + ((size_t)kb * n_tiles + min(nt0 + f, n_tiles - 1)) * 1024;
       step[i] = (unsigned)n_tiles * 1024u;
     } else {         // activation fragment: band (f - BNT) / 2, plane (f - BNT) % 2
@@ -116,14 +123,18 @@ __global__ __launch_bounds__(128 * WY, (tiled_waves<WN, WM, NS, WY>())) void gem
     // them before every LDS read.  Completion is tracked by hand: each wavefront issues PER loads per k tile, in order, so
     // "at most PER*(NS-2) outstanding" says that its share of k tile t+1 has landed.  The barrier extends that to the whole
     // workgroup; every wavefront has waited for its reads of k tile t before it, so slot t may be refilled behind it.
-    const unsigned lds_base = (unsigned)(size_t)&stage[0][0][0] + (unsigned)(wave * PER) * 1024u, voff = lane * 16;
+    const unsigned lds_base = (unsigned)(size_t)&stage[0][0][0], voff = lane * 16;
+    // m0 carries the LDS address; whatever the compiler keeps in it is put back, so the statement clobbers nothing
+#define DF_COPY(hint)                                                                                                                    \
+  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3" hint "\n\ts_nop 0\n\ts_mov_b32 m0, %0" \
+               : "=&s"(keep_m0) : "s"(dst), "v"(voff), "s"(src[i]) : "memory")
     auto dma = [&](int i, int slot) {
-      const unsigned dst = __builtin_amdgcn_readfirstlane(lds_base + (unsigned)((slot * FR + i) * 1024));
-      // m0 carries the LDS address; whatever the compiler keeps in it is put back, so the statement clobbers nothing
+      const unsigned dst = __builtin_amdgcn_readfirstlane(lds_base + (unsigned)((slot * FR + fragment(i)) * 1024));
       unsigned keep_m0;
-      asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_nop 0\n\ts_mov_b32 m0, %0"
-                   : "=&s"(keep_m0) : "s"(dst), "v"(voff), "s"(src[i]) : "memory");
+      if (STREAM && i < PW) DF_COPY(" nt");
+      else DF_COPY("");
     };
+#undef DF_COPY
     for (int d = 0; d < NS; ++d) {
 #pragma unroll
       for (int i = 0; i < PER; ++i) dma(i, d);

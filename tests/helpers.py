@@ -45,8 +45,8 @@ TILE_EDGES = [
     (17, 1056, 2080, 2, 6, 2, 2), (5, 2112, 2080, 2, 6, 2, 6),
     (9, 2112, 1056, 2, 4, 2, 3), (17, 1312, 2080, 2, 4, 2, 0),
 ]
-# The same for the 512 x 128 tiles, whose activation fragments roll
-ROLLED_TILES = [(5, 1312, 1056, 2, 8, 4, 3), (9, 1056, 2080, 2, 8, 4, 0), (17, 2112, 2080, 2, 8, 4, 2), (8, 256, 512, 2, 8, 4, 5), (1 + 8 * 4, 1312, 1056, 2, 8, 4, 0)]
+# The same for the 512 x 128 tiles, whose activation fragments roll (nine activation blocks at last: the weights without the hint of few blocks)
+ROLLED_TILES = [(5, 1312, 1056, 2, 8, 4, 3), (9, 1056, 2080, 2, 8, 4, 0), (17, 2112, 2080, 2, 8, 4, 2), (8, 256, 512, 2, 8, 4, 5), (1 + 8 * 8, 1312, 1056, 2, 8, 4, 0)]
 # (vocabulary, rows, weight tiles per wavefront) of LM heads that the streaming GEMM takes with eight, six and four weight tiles
 STREAM_HEADS = [(v, m, nt) for v, nt in ((32768, 8), (24576, 6), (4096, 4)) for m in (16, 32, 48)]
 
