@@ -26,12 +26,14 @@
 #include "plan.h"
 
 // Scratch of dflash_accept_sampled_noalloc (the entry point for callers that cannot allocate): the pieces of the rows'
-// softmax statistics (target rows, then draft rows), followed by the best scores of the vocabulary chunks.  Every GPU the
+// softmax statistics (target rows, then draft rows), followed by the best scores of the vocabulary chunks and the sequences' arrival counters.  Every GPU the
 // library runs on holds its own copy of this array until the process ends; host code reaches it through the address that
 // hipGetSymbolAddress returns for the current device, never through this name.
 #define DFLASH_NOALLOC_MAX_ROWS 4096
 #define DFLASH_NOALLOC_BESTS 4096
-static __device__ __align__(256) unsigned char scratch[(2 * DFLASH_NOALLOC_MAX_ROWS + DFLASH_NOALLOC_BESTS) * sizeof(float2)];
+#define DFLASH_NOALLOC_COUNTERS 8192
+static __device__ __align__(256) unsigned char scratch[(2 * DFLASH_NOALLOC_MAX_ROWS + DFLASH_NOALLOC_BESTS) * sizeof(float2) +
+                                                       DFLASH_NOALLOC_COUNTERS * sizeof(unsigned)];
 
 namespace {
 
@@ -162,19 +164,22 @@ constexpr int ARGMAX_CHUNKS = 32;   // workgroups that share one vocabulary row 
 
 // ---- sampled acceptance (dflash_accept, dflash_accept_sampled_noalloc) -----------------------------
 // statistics of R rows of `a` and R rows of `b` (may be null with R_b = 0) in `chunks` pieces per row
-inline void launch_lse(hipStream_t st, const float* a, const float* b, int R, int R_b, int V, float inv_T, int chunks, float2* part) {
+inline void launch_lse(hipStream_t st, const float* a, const float* b, int R, int R_b, int V, float inv_T, int chunks, float2* part, int B,
+                       AcceptArrive arrive = AcceptArrive{}) {
   const dim3 grid(chunks, R + R_b), block(256);
   if (V % 4 == 0 && (((uintptr_t)a | (uintptr_t)b) & 15) == 0)
-    hipLaunchKernelGGL(lse_partial_kernel<true>, grid, block, 0, st, a, b, R, V, inv_T, part);
+    hipLaunchKernelGGL(lse_partial_kernel<true>, grid, block, 0, st, a, b, R, V, inv_T, part, B, arrive);
   else
-    hipLaunchKernelGGL(lse_partial_kernel<false>, grid, block, 0, st, a, b, R, V, inv_T, part);
+    hipLaunchKernelGGL(lse_partial_kernel<false>, grid, block, 0, st, a, b, R, V, inv_T, part, B, arrive);
 }
+// arrive: counters that a statistics launch of the same call has zeroed; without them the sequences' tokens take a launch of their own
 inline void launch_accept_sampled(hipStream_t st, const float* p_logits, const float* q_logits, RowStats ps, RowStats qs, const int32_t* draft,
                                   const float* uniforms, const uint64_t* key, int S, int B, int V, float inv_T, int32_t* accept_len,
-                                  int32_t* out_tokens, float2* best, size_t room) {
+                                  int32_t* out_tokens, float2* best, size_t room, AcceptArrive arrive = AcceptArrive{}) {
   const int chunks = accept_chunks(S, V, room);
-  hipLaunchKernelGGL(accept_sampling_kernel, dim3(chunks, S), dim3(256), 0, st, p_logits, q_logits, ps, qs, draft, uniforms, key, V, B, inv_T, accept_len, best);
-  hipLaunchKernelGGL(accept_sampling_finish_kernel, dim3(S), dim3(64), 0, st, best, chunks, draft, B, accept_len, out_tokens);
+  hipLaunchKernelGGL(accept_sampling_kernel, dim3(chunks, S), dim3(256), 0, st, p_logits, q_logits, ps, qs, draft, uniforms, key, V, B, inv_T, accept_len, best,
+                     out_tokens, arrive);
+  if (!arrive.counters) hipLaunchKernelGGL(accept_sampling_finish_kernel, dim3(S), dim3(64), 0, st, best, chunks, draft, B, accept_len, out_tokens);
 }
 
 // column blocks of the widest launch that finishes its own sums: D columns, four weight tiles a block at least
@@ -709,8 +714,8 @@ struct Engine {
         float2* part = ws<float2>(c->ws.lsep);
         const bool both = c->stats_p_T != temperature && c->stats_q_T != temperature;
         const int chunks = lse_chunks(both ? 2 * M : M, V, room);
-        if (both) launch_lse(st, ws<float>(c->ws.logits_t), ws<float>(c->ws.logits_d), M, M, V, inv_T, chunks, part);
-        else launch_lse(st, ws<float>(c->stats_p_T != temperature ? c->ws.logits_t : c->ws.logits_d), nullptr, M, 0, V, inv_T, chunks, part);
+        if (both) launch_lse(st, ws<float>(c->ws.logits_t), ws<float>(c->ws.logits_d), M, M, V, inv_T, chunks, part, B);
+        else launch_lse(st, ws<float>(c->stats_p_T != temperature ? c->ws.logits_t : c->ws.logits_d), nullptr, M, 0, V, inv_T, chunks, part, B);
         check();
         if (c->stats_p_T != temperature) ps = RowStats{part, chunks};
         if (c->stats_q_T != temperature) qs = RowStats{both ? part + (size_t)M * chunks : part, chunks};
@@ -1588,9 +1593,11 @@ int dflash_accept_sampled_noalloc(const float* target_logits, const float* draft
   const int M = n_seqs * block_size;
   const float inv_T = 1.0f / temperature;
   const int chunks = lse_chunks(2 * M, vocab, 2 * DFLASH_NOALLOC_MAX_ROWS);
-  launch_lse(st, target_logits, draft_logits, M, M, vocab, inv_T, chunks, part);
+  // counters of different sequences on lines of their own where there is room (kArriveStride)
+  const AcceptArrive arrive{reinterpret_cast<unsigned*>(best + DFLASH_NOALLOC_BESTS), n_seqs, std::min(kArriveStride, DFLASH_NOALLOC_COUNTERS / n_seqs)};
+  launch_lse(st, target_logits, draft_logits, M, M, vocab, inv_T, chunks, part, block_size, arrive);
   launch_accept_sampled(st, target_logits, draft_logits, RowStats{part, chunks}, RowStats{part + (size_t)M * chunks, chunks}, draft_tokens, uniforms,
-                        rng_key, n_seqs, block_size, vocab, inv_T, accept_len, out_tokens, best, DFLASH_NOALLOC_BESTS);
+                        rng_key, n_seqs, block_size, vocab, inv_T, accept_len, out_tokens, best, DFLASH_NOALLOC_BESTS, arrive);
   if (hipGetLastError() != hipSuccess) return fail(nullptr, DFLASH_EHIP, "accept_sampled_noalloc: launch failed");
   return DFLASH_OK;
 }

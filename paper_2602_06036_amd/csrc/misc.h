@@ -452,14 +452,20 @@ __global__ void accept_greedy_kernel(const int32_t* __restrict__ draft, const in
 }
 
 // ---- speculative sampling ---------------------------------------------------------------------------
+// Arrival counters of the sequences, `stride` apart, where the sweep over the vocabulary finishes by itself (finish.h); the statistics launch
+// in front of it zeroes them.
+struct AcceptArrive {
+  unsigned* counters = nullptr;
+  int n = 0, stride = 0;
+};
 // Softmax statistics of stored logits: part[row * gridDim.x + chunk] = (max, sum of exp(logit * inv_T - max)) over one
 // chunk of the row; row r < R is row r of `a`, row R + r is row r of `b` (one launch for target and draft).  An empty set is
 // (-inf, 0).  Bound by HBM: every logit is read once (running maximum per thread), and a row is shared out over gridDim.x
 // workgroups, because a block's few rows alone leave most CUs without work.  VEC: V and both pointers allow 16-byte loads.
 // Eight sequences of 16 rows, 151936 columns, both tensors (156 MB): 2 x 99 us as one 1024-thread workgroup per row and
-// two sweeps over it, 31 us in this form, the logits being in the memory-side cache from the pass before (the whole call: 325 us, 47
-// with the library's expf and plain loads, 42 with exp_nonpositive and non-temporal ones; the rows' log-sum-exp is off by 5.6e-8 rms
-// and 2.6e-7 at worst with either exponential).
+// two sweeps over it, 28.4 us in this form (the anchors' draft rows left out; 29.4 with a branch per element for masked logits and bounds in
+// every round), the logits being in the memory-side cache from the pass before; 5.3 TB/s whatever the chunks, eight a row or thirty-two.  The
+// rows' log-sum-exp is off by 5.6e-8 rms and 2.6e-7 at worst, as with the library's exponential.
 __device__ __forceinline__ void lse_merge(float& m, float& s, float m2, float s2) {   // union of two sets
   const float M = fmaxf(m, m2);
   s = (m == -INFINITY ? s : s * expf(m - M)) + (m2 == -INFINITY ? s2 : s2 * expf(m2 - M));   // an empty set's sum is 0 or NaN
@@ -467,23 +473,28 @@ __device__ __forceinline__ void lse_merge(float& m, float& s, float m2, float s2
 }
 template <bool VEC>
 __global__ __launch_bounds__(256) void lse_partial_kernel(const float* __restrict__ a, const float* __restrict__ b, int R, int V, float inv_T,
-                                                          float2* __restrict__ part) {
+                                                          float2* __restrict__ part, int B, AcceptArrive arrive) {
   const int r = blockIdx.y, chunk = blockIdx.x, n_chunks = gridDim.x;
+  if (r == 0 && chunk == 0)
+    for (int i = threadIdx.x; i < arrive.n; i += 256) arrive.counters[i * arrive.stride] = 0u;
+  if (r >= R && (r - R) % B == 0) return;   // the anchor's draft row: nobody asks for its distribution
   const float* row = (r < R ? a + (size_t)r * V : b + (size_t)(r - R) * V);
   const int per = (((V + n_chunks - 1) / n_chunks) + 3) & ~3;
   const int i0 = min(V, chunk * per), i1 = min(V, i0 + per);
-  constexpr int E = VEC ? 4 : 1, U = 5;
-  float m = -INFINITY, s = 0.f;
-  for (int i = i0 + (int)threadIdx.x * E; i < i1; i += 256 * E * U) {
+  constexpr int E = VEC ? 4 : 1, U = 5, ROUND = 256 * E * U;
+  float m = -INFINITY, s = 0.f, s_left = 0.f;   // the sum, and what is left out of it (see ExpParts)
+  auto round = [&](int i, auto whole_c) {
+    constexpr bool WHOLE = decltype(whole_c)::value;
     float v[U * E];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int at = i + u * 256 * E;
+      const bool in = WHOLE || at < i1;
       if constexpr (VEC) {
-        const f32x4 x = at < i1 ? __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(row + at)) : (f32x4){-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+        const f32x4 x = in ? __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(row + at)) : (f32x4){-INFINITY, -INFINITY, -INFINITY, -INFINITY};
         v[4 * u] = x[0]; v[4 * u + 1] = x[1]; v[4 * u + 2] = x[2]; v[4 * u + 3] = x[3];
       } else {
-        v[u] = at < i1 ? row[at] : -INFINITY;
+        v[u] = in ? row[at] : -INFINITY;
       }
     }
     __builtin_amdgcn_sched_barrier(0);   // all loads of a round are out before the first is waited for
@@ -494,12 +505,23 @@ __global__ __launch_bounds__(256) void lse_partial_kernel(const float* __restric
       mx = fmaxf(mx, v[e]);
     }
     if (mx > m) {
-      s = m == -INFINITY ? s : s * expf(m - mx);
+      const float f = expf(m - mx);   // nothing so far: 0
+      s *= f;
+      s_left *= f;
       m = mx;
     }
+    const float base = m == -INFINITY ? 0.f : m;   // a masked logit weighs nothing, also where all are, a NaN stays one
 #pragma unroll
-    for (int e = 0; e < U * E; ++e) s += v[e] == -INFINITY ? 0.f : exp_nonpositive(v[e] - m, [](float p) { return __builtin_amdgcn_exp2f(p); });   // a masked logit weighs nothing, a NaN stays one
-  }
+    for (int e = 0; e < U * E; ++e) {
+      const ExpParts x = exp_nonpositive_parts(v[e] - base, [](float p) { return __builtin_amdgcn_exp2f(p); });
+      s += x.x;
+      s_left = fmaf(x.x, x.left, s_left);
+    }
+  };
+  int c0 = i0;
+  for (; c0 + ROUND <= i1; c0 += ROUND) round(c0 + (int)threadIdx.x * E, std::true_type{});
+  if (c0 < i1) round(c0 + (int)threadIdx.x * E, std::false_type{});
+  s = fmaf(s_left, kExpLn2, s);
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
     const float om = __shfl_xor(m, o, 64), os = __shfl_xor(s, o, 64);
@@ -541,11 +563,16 @@ struct RowStats {
   const float2* p;
   int parts;
 };
-// log-sum-exp of a row, found by 16 lanes that share it (the same value in each of them)
-__device__ __forceinline__ float row_lse(const RowStats& st, size_t row, int lane16) {
-  if (st.parts == 0) return st.p[row].y;
-  float m = -INFINITY, s = 0.f;
-  for (int c = lane16; c < st.parts; c += 16) {
+// what lane `lane16` of the 16 that share a row begins with: its first piece
+__device__ __forceinline__ float2 row_piece(const RowStats& st, size_t row, int lane16) {
+  if (st.parts == 0) return st.p[row];
+  return lane16 < st.parts ? st.p[row * st.parts + lane16] : make_float2(-INFINITY, 0.f);
+}
+// log-sum-exp of the row (the same value in each of the lanes)
+__device__ __forceinline__ float row_lse(const RowStats& st, size_t row, int lane16, float2 first) {
+  if (st.parts == 0) return first.y;
+  float m = first.x, s = first.y;
+  for (int c = lane16 + 16; c < st.parts; c += 16) {
     const float2 x = st.p[row * st.parts + c];
     lse_merge(m, s, x.x, x.y);
   }
@@ -557,41 +584,75 @@ __device__ __forceinline__ float row_lse(const RowStats& st, size_t row, int lan
   return m + logf(s);
 }
 
+// Stage 2, one wavefront per sequence: combines the chunks' bests (ties -> lowest index) and writes the sequence's tokens.
+template <typename Best>
+__device__ __forceinline__ void accept_finish(int lane, int n_chunks, int a, int B, const int32_t* draft, int32_t* out_tokens, Best best) {
+  float bv = -INFINITY;
+  int bi = 0x7FFFFFFF;
+  for (int c = lane; c < n_chunks; c += 64) {
+    const float2 x = best(c);
+    argmax_combine(bv, bi, x.x, __float_as_int(x.y));
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const float ov = __shfl_xor(bv, o, 64);
+    const int oi = __shfl_xor(bi, o, 64);
+    argmax_combine(bv, bi, ov, oi);
+  }
+  if (lane < B) out_tokens[lane] = lane < a ? draft[lane + 1] : (lane == a ? bi : -1);
+}
+
 // Speculative sampling, stage 1.  grid (chunks, S).  The slots are tested side by side, lane j for slot j: slot j is accepted
 // iff u_j * q_j(d_j) < p_{j-1}(d_j), the first one that is not ends the block.  Then the workgroup takes the best
 // Gumbel-perturbed score of its columns for the token that follows the accepted ones,
 //   first rejected slot j: log max(p_{j-1} - q_j, 0)   (purpose 1, slot j)
 //   none rejected:         log p_{B-1}                 (purpose 2, slot B)
 // into best[s * chunks + chunk]; the workgroup of chunk 0 writes accept_len.  Every workgroup of a sequence repeats the (small)
-// test, so that the sweep over the vocabulary (two logarithms and a 64-bit hash per column) runs on as many CUs as there are:
-// one workgroup per sequence took 124 us for eight sequences of 151936 columns, now 11 us and stage 2 3.9; half of it is the
-// arithmetic (a column costs some 600 cycles of a SIMD).
+// test, so that the sweep over the vocabulary (two logarithms and a 64-bit hash per column) runs on as many CUs as there are: one
+// workgroup per sequence took 124 us for eight sequences of 151936 columns, now 10.7, half of it arithmetic (a column costs some 600
+// cycles of a SIMD).  With arrival counters the last workgroup of a sequence writes its tokens: 11.8 us for both stages, 10.7 + 3.9 as two
+// launches; the whole call 40.2 -> 37.6 us, one sequence of ten rows of 16000 columns 15.7 -> 12.5.  (128 workgroups a sequence: 38.8.)
 // A drafted id outside the vocabulary is never accepted.
 __global__ __launch_bounds__(256) void accept_sampling_kernel(const float* __restrict__ p_logits, const float* __restrict__ q_logits,
                                                               RowStats p_stats, RowStats q_stats,
                                                               const int32_t* __restrict__ draft, const float* __restrict__ uniforms,
                                                               const uint64_t* __restrict__ rng_key, int V, int B, float inv_T,
-                                                              int32_t* __restrict__ accept_len, float2* __restrict__ best) {
+                                                              int32_t* __restrict__ accept_len, float2* __restrict__ best,
+                                                              int32_t* __restrict__ out_tokens, AcceptArrive arrive) {
   const int s = blockIdx.y, chunk = blockIdx.x, n_chunks = gridDim.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   __shared__ float lse[2][16];   // log-sum-exp of the target rows, of the draft rows (B <= 16)
   __shared__ int sh_a;
-  for (int r = threadIdx.x >> 4; r < 2 * B; r += 16) {   // 16 rows at a time
-    const int at = r < B ? r : r - B;
-    const float v = row_lse(r < B ? p_stats : q_stats, (size_t)s * B + at, threadIdx.x & 15);
-    if ((threadIdx.x & 15) == 0) lse[r >= B][at] = v;
+  // Everything the test needs is requested at once: the pieces of the rows (sixteen lanes a row, the target's and the draft's), and in the first
+  // wavefront the drafted tokens' own logits.
+  const int r16 = threadIdx.x >> 4, lane16 = threadIdx.x & 15;
+  const size_t row = (size_t)s * B + min(r16, B - 1);
+  const float2 piece_p = row_piece(p_stats, row, lane16), piece_q = row_piece(q_stats, row, lane16);
+  const uint64_t key = rng_key[0];
+  const bool slot = wave == 0 && lane >= 1 && lane < B;
+  int d = -1;
+  float at_p = 0.f, at_q = 0.f, uniform = 0.f;
+  if (slot) {
+    d = draft[(size_t)s * B + lane];
+    uniform = uniforms[(size_t)s * B + lane];
+    const int col = min(max(d, 0), V - 1);
+    at_p = p_logits[((size_t)s * B + lane - 1) * V + col];
+    at_q = q_logits[((size_t)s * B + lane) * V + col];
+  }
+  const float lse_p = row_lse(p_stats, row, lane16, piece_p), lse_q = row_lse(q_stats, row, lane16, piece_q);
+  if (lane16 == 0 && r16 < B) {
+    lse[0][r16] = lse_p;
+    lse[1][r16] = lse_q;   // of slot 0: not used
   }
   __syncthreads();
   if (wave == 0) {
     bool rejected = false;
-    if (lane >= 1 && lane < B) {
-      const int d = draft[(size_t)s * B + lane];
+    if (slot) {
       rejected = true;
       if (d >= 0 && d < V) {
-        const size_t mp = (size_t)s * B + lane - 1, mq = (size_t)s * B + lane;
-        const float p = expf(p_logits[mp * V + d] * inv_T - lse[0][lane - 1]);
-        const float q = expf(q_logits[mq * V + d] * inv_T - lse[1][lane]);
-        rejected = !(uniforms[(size_t)s * B + lane] * q < p);
+        const float p = expf(at_p * inv_T - lse[0][lane - 1]);
+        const float q = expf(at_q * inv_T - lse[1][lane]);
+        rejected = !(uniform * q < p);
       }
     }
     const unsigned long long m = __builtin_amdgcn_ballot_w64(rejected);
@@ -599,7 +660,6 @@ __global__ __launch_bounds__(256) void accept_sampling_kernel(const float* __res
   }
   __syncthreads();
   const int a = sh_a;
-  const uint64_t key = rng_key[0];
   const int per = (V + n_chunks - 1) / n_chunks, i0 = min(V, chunk * per), i1 = min(V, i0 + per);
   float bv = -INFINITY;
   int bi = 0x7FFFFFFF;
@@ -632,26 +692,26 @@ __global__ __launch_bounds__(256) void accept_sampling_kernel(const float* __res
     }
   }
   block_argmax(bv, bi);
-  if (threadIdx.x == 0) {
-    best[(size_t)s * n_chunks + chunk] = make_float2(bv, __int_as_float(bi));
-    if (chunk == 0) accept_len[s] = a;
+  if (threadIdx.x == 0 && chunk == 0) accept_len[s] = a;
+  if (!arrive.counters) {   // stage 2 is a launch of its own
+    if (threadIdx.x == 0) best[(size_t)s * n_chunks + chunk] = make_float2(bv, __int_as_float(bi));
+    return;
   }
+  uint64_t* mine = reinterpret_cast<uint64_t*>(best + (size_t)s * n_chunks);
+  if (threadIdx.x == 0)
+    __hip_atomic_store(mine + chunk, (uint64_t)__float_as_uint(bv) | (uint64_t)(unsigned)bi << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (!last_to_arrive(arrive.counters + s * arrive.stride, (unsigned)n_chunks) || wave != 0) return;
+  accept_finish(lane, n_chunks, a, B, draft + (size_t)s * B, out_tokens + (size_t)s * B, [&](int c) {
+    const uint64_t x = __hip_atomic_load(mine + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return make_float2(__uint_as_float((unsigned)x), __uint_as_float((unsigned)(x >> 32)));
+  });
 }
 
-// Stage 2: combines the chunks (ties -> lowest index) and writes the sequence's tokens.  One wavefront per sequence.
 __global__ __launch_bounds__(64) void accept_sampling_finish_kernel(const float2* __restrict__ best, int n_chunks, const int32_t* __restrict__ draft,
                                                                     int B, const int32_t* __restrict__ accept_len, int32_t* __restrict__ out_tokens) {
-  const int s = blockIdx.x, lane = threadIdx.x, a = accept_len[s];
-  float bv = -INFINITY;
-  int bi = 0x7FFFFFFF;
-  for (int c = lane; c < n_chunks; c += 64) argmax_combine(bv, bi, best[(size_t)s * n_chunks + c].x, __float_as_int(best[(size_t)s * n_chunks + c].y));
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const float ov = __shfl_xor(bv, o, 64);
-    const int oi = __shfl_xor(bi, o, 64);
-    argmax_combine(bv, bi, ov, oi);
-  }
-  if (lane < B) out_tokens[(size_t)s * B + lane] = lane < a ? draft[(size_t)s * B + lane + 1] : (lane == a ? bi : -1);
+  const int s = blockIdx.x;
+  accept_finish(threadIdx.x, n_chunks, accept_len[s], B, draft + (size_t)s * B, out_tokens + (size_t)s * B,
+                [&](int c) { return best[(size_t)s * n_chunks + c]; });
 }
 
 // ---- commit bookkeeping ----------------------------------------------------------------------------
