@@ -484,6 +484,7 @@ __global__ __launch_bounds__(256) void lse_partial_kernel(const float* __restric
   constexpr int E = VEC ? 4 : 1, U = 5, ROUND = 256 * E * U;
   float m = -INFINITY, s = 0.f, s_left = 0.f;   // the sum, and what is left out of it (see ExpParts)
   auto round = [&](int i, auto whole_c) {
+#pragma clang fp contract(off)   // the scaled logit is rounded before the maximum is taken off, as where the maximum was found
     constexpr bool WHOLE = decltype(whole_c)::value;
     float v[U * E];
 #pragma unroll
