@@ -607,6 +607,258 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_wide_kernel(const bf16_t* __
   }
 }
 
+// ------------------------------------------------------------------------------------------------
+// Prefill: two consecutive blocks of one prompt (a tile) and one group of query heads per workgroup, against all keys up to the tile's last.
+// Four wavefronts own 32 of the query rows each, and eight of them two sets: the even and the odd pairs of pages, added at the end.  (A block by
+// itself, the kernels above, has its keys in eight parts to merge and pays 6 us a workgroup for ramp and merge whatever its length; one set of
+// wavefronts makes the longest tile of a 2048-token prompt the launch: 64 pairs of 1.4 us, each a chain of scores, softmax and products.)
+// The pages are staged in an LDS ring that all share, two pairs a stage (a 16-key page's K and V halves are a wavefront's copies each), one
+// barrier per stage.  Row r of a block's part is slot r % B of head r / B, so that at B = 16 a store of 64 lanes is 512 bytes of an operand
+// tile and the rows leave from registers.  Workgroup id = tile * head groups + head group: an XCD keeps to the K/V of one head group where there
+// are eight; long tiles first.
+// ------------------------------------------------------------------------------------------------
+template <int HD>
+__global__ __launch_bounds__(512, 2) void attn_prefill_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ pool, SeqGeom geo, AttnArgs aa,
+                                                              const int4* __restrict__ tiles, int n_tiles) {
+  constexpr int KT = HD / 32, DT = HD / 16, RB = 2, NS = 4, LD = HD + 4;
+  constexpr int PART = DF_PAGE * HD * 2, NI = PART / 1024;   // bytes and load instructions of the K or V half of a page
+  // two pairs a stage: K of page A, V of page A, K of page B, V of page B; at the end the second set's rows
+  __shared__ __attribute__((aligned(1024))) char ring[NS][2][4 * PART];
+  __shared__ float2 s_ml[4][RB * 16];
+  static_assert(4 * RB * 16 * LD * 4 <= (int)sizeof(ring), "the second set's rows overlay the ring");
+  float (*s_o)[RB * 16][LD] = reinterpret_cast<float (*)[RB * 16][LD]>(&ring[0][0][0]);
+  const int lane = threadIdx.x & 63, set = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), wave = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 3);
+  const int n = lane & 15, g = lane >> 4, B = geo.block_size;
+  const int groups = aa.n_kv_heads << aa.q_shift, hg = blockIdx.x % groups, at = blockIdx.x / groups;
+  const int t = n_tiles - 1 - at;
+  const int4 tile = tiles[t];   // first block, one or two of them, tokens before the first
+  const int group = (aa.n_q_heads / aa.n_kv_heads) >> aa.q_shift, rows = B * group, kv = hg >> aa.q_shift;
+  const bool live = (wave >> 1) < tile.y;
+  const int s = tile.x + min(wave >> 1, tile.y - 1);
+  const int cap = geo.max_pages_per_seq * DF_PAGE;
+  const int32_t* table = geo.block_table + (size_t)tile.x * geo.max_pages_per_seq;
+  auto load_ids = [&](int p0) { return table[min(2 * p0 + lane, geo.max_pages_per_seq - 1)]; };   // 32 pairs' page ids
+  int ids = load_ids(0);
+
+  const int n_s = tile.z + (s - tile.x) * B, n_tok = min(n_s + B, cap), n_end = min(tile.z + tile.y * B, cap);
+  u32x4 qf[RB][KT];
+  int last_vis[RB];   // last key that the lane's row of the block sees
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const int r = (wave & 1) * 32 + rb * 16 + n;
+    const bool valid = live && r < rows;   // a row that is not reads along and is not stored
+    const int slot = valid ? r % B : 0, hq = hg * group + (valid ? r / B : 0);
+    last_vis[rb] = valid ? min(n_s + slot, n_tok - 1) : -1;
+    const u32x4* qp = reinterpret_cast<const u32x4*>(q + ((size_t)(s * B + slot) * aa.n_q_heads + hq) * HD);
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) qf[rb][kt] = qp[kt * 4 + g];
+  }
+  const int n_pairs = (n_end + 31) >> 5;
+  const int my_pairs = live && (wave & 1) * 32 < rows ? (n_tok + 31) >> 5 : 0;
+  int ids_next = n_pairs > 32 ? load_ids(32) : 0;
+
+  const int n_stages = (n_pairs + 1) >> 1;
+  const unsigned lds = (unsigned)(size_t)&ring[0][0][0] + (unsigned)(set * 4 + wave) * PART, voff = lane * 16;
+  auto page_at = [&](int pages, int p, int b) { return __builtin_amdgcn_readlane(pages, (p & 31) * 2 + b); };
+  auto readable = [&](int page) { return page >= 0 && page < geo.n_pages; };
+  // this wavefront's quarter of its set's pair of stage st into a slot; a foreign or missing page aliases page 0 and weighs nothing
+  auto fetch = [&](int pages, int st, int slot) {
+    const int page = page_at(pages, 2 * st + set, wave >> 1);
+    const bf16_t* src = pool + kv_head_base(aa.layer, geo.n_pages, readable(page) ? page : 0, aa.n_kv_heads, kv, HD) + (size_t)(wave & 1) * DF_PAGE * HD;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const unsigned dst = __builtin_amdgcn_readfirstlane(lds + (unsigned)((slot & (NS - 1)) * 8 * PART + i * 1024));
+      const bf16_t* from = src + i * 512;
+      unsigned keep_m0;   // whatever the compiler keeps in m0 is put back
+      asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_nop 0\n\ts_mov_b32 m0, %0"
+                   : "=&s"(keep_m0) : "s"(dst), "v"(voff), "s"(from) : "memory");
+    }
+  };
+  // (past the end the last stage again, into a slot that is not read: the number of loads in flight stays the same)
+  fetch(ids, 0, 0);
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) asm volatile("" : "+v"(qf[rb][kt]));   // the queries are waited for here: inside the loop that would be a wait for every copy
+  for (int st = 1; st < NS - 1; ++st) fetch(ids, min(st, n_stages - 1), st);
+
+  float m_run[RB], l_run[RB];
+  f32x4 acc[RB][DT];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    m_run[rb] = -INFINITY;
+    l_run[rb] = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) acc[rb][dt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  }
+  const float scale2 = aa.scale * 1.44269504088896341f;   // scores and running maxima in the base-2 exponent domain
+
+  for (int st = 0; st < n_stages; ++st) {
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NI * (NS - 2)) : "memory");   // this wavefront's quarter of the stage has landed
+    __builtin_amdgcn_s_waitcnt(0xC07F);                                    // lgkmcnt(0): its reads of the stage before are done
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    const int ahead = min(st + NS - 1, n_stages - 1);
+    fetch((ahead >> 4) > (st >> 4) ? ids_next : ids, ahead, st + NS - 1);   // into the slot of the stage before
+    const int ids_p = ids, p = 2 * st + set;
+    if (((st + 1) & 15) == 0) {   // uniform: the next stage's page ids come into use
+      ids = ids_next;
+      if (2 * st + 34 < n_pairs) ids_next = load_ids(2 * st + 34);
+    }
+    if (p >= my_pairs) continue;
+    const int base = p * 32;
+    const bool ok_a = readable(page_at(ids_p, p, 0)), ok_b = base + 16 < n_end && readable(page_at(ids_p, p, 1));
+    const char* slot = ring[st & (NS - 1)][set];
+    f32x4 sc[RB][2];
+    {
+      const u32x4* kp = reinterpret_cast<const u32x4*>(slot) + lane;
+      u32x4 ka[KT], kb[KT];
+#pragma unroll
+      for (int kt = 0; kt < KT; ++kt) {
+        ka[kt] = kp[kt * 64];
+        kb[kt] = kp[2 * PART / 16 + kt * 64];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) sc[rb][0] = sc[rb][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+          sc[rb][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ka[kt]), __builtin_bit_cast(bf16x8, qf[rb][kt]), sc[rb][0], 0, 0, 0);
+          sc[rb][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kb[kt]), __builtin_bit_cast(bf16x8, qf[rb][kt]), sc[rb][1], 0, 0, 0);
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // V is read while the softmax runs
+    uint2 va[DT], vb[DT];
+    {
+      const uint2* vp = reinterpret_cast<const uint2*>(slot + PART) + lane;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) {
+        va[dt] = vp[dt * 64];
+        vb[dt] = vp[2 * PART / 8 + dt * 64];
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (!ok_a || !ok_b || base + 32 > n_s) {   // the last pairs of a block and foreign pages
+      const int p0 = base + 4 * g;
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if (!(ok_a && p0 + i <= last_vis[rb])) sc[rb][0][i] = -INFINITY;
+          if (!(ok_b && p0 + 16 + i <= last_vis[rb])) sc[rb][1][i] = -INFINITY;
+        }
+    }
+    // the reference maximum moves only when the row's has grown by more than 8, decided from each lane's own scores (see above)
+    float lmx[RB];
+    bool grew = false;
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      const f32x4 x = sc[rb][0], y = sc[rb][1];
+      lmx[rb] = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(y[0], y[1]), fmaxf(y[2], y[3]))) * scale2;
+      grew = grew || lmx[rb] > m_run[rb] + 8.f;
+    }
+    if (__builtin_amdgcn_ballot_w64(grew) != 0ull) {
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+        float mx = lmx[rb];
+        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        const bool grow = mx > m_run[rb] + 8.f;
+        const float corr = grow ? (m_run[rb] == -INFINITY ? 0.f : exp2f(m_run[rb] - mx)) : 1.f;
+        l_run[rb] *= corr;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) {
+          acc[rb][dt][0] *= corr; acc[rb][dt][1] *= corr; acc[rb][dt][2] *= corr; acc[rb][dt][3] *= corr;
+        }
+        if (grow) m_run[rb] = mx;
+      }
+    }
+    u32x4 ph[RB], pl[RB];   // probabilities as hi + lo pairs
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      const float mb = (m_run[rb] == -INFINITY) ? 0.f : m_run[rb];
+      float pe[8];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        pe[i] = __builtin_amdgcn_exp2f(fmaf(sc[rb][0][i], scale2, -mb));
+        pe[4 + i] = __builtin_amdgcn_exp2f(fmaf(sc[rb][1][i], scale2, -mb));
+      }
+      l_run[rb] += ((pe[0] + pe[1]) + (pe[2] + pe[3])) + ((pe[4] + pe[5]) + (pe[6] + pe[7]));
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t h = pack_bf16_pair(pe[2 * i], pe[2 * i + 1]);
+        ph[rb][i] = h;
+        pl[rb][i] = pack_bf16_pair(pe[2 * i] - __uint_as_float(h << 16), pe[2 * i + 1] - __uint_as_float(h & 0xFFFF0000u));
+      }
+    }
+    auto products = [&](auto masked_c) {
+      constexpr bool MASKED = decltype(masked_c)::value;
+      // rows behind the block (never written, or a later block's) and foreign pages: 0 * whatever is there must stay 0
+      u32x4 keep;
+      if constexpr (MASKED) {
+        const int pos_a = base + 4 * g, pos_b = base + 16 + 4 * g;
+        auto half = [&](bool ok, int p0) { return (ok && p0 < n_tok ? 0x0000FFFFu : 0u) | (ok && p0 + 1 < n_tok ? 0xFFFF0000u : 0u); };
+        keep = (u32x4){half(ok_a, pos_a), half(ok_a, pos_a + 2), half(ok_b, pos_b), half(ok_b, pos_b + 2)};
+      }
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) {
+        u32x4 vf = {va[dt].x, va[dt].y, vb[dt].x, vb[dt].y};
+        if constexpr (MASKED) vf &= keep;
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+          acc[rb][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vf), __builtin_bit_cast(bf16x8, ph[rb]), acc[rb][dt], 0, 0, 0);
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+          acc[rb][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vf), __builtin_bit_cast(bf16x8, pl[rb]), acc[rb][dt], 0, 0, 0);
+      }
+    };
+    if (base + 32 > n_tok || !ok_a || !ok_b) products(std::true_type{});
+    else products(std::false_type{});
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // nothing may still be on its way into the ring when it is overlaid
+  float l_row[RB];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    l_row[rb] = l_run[rb];
+    l_row[rb] += __shfl_xor(l_row[rb], 16, 64);
+    l_row[rb] += __shfl_xor(l_row[rb], 32, 64);
+  }
+  __syncthreads();
+  if (set == 1) {
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      if (g == 0) s_ml[wave][rb * 16 + n] = make_float2(m_run[rb], l_row[rb]);
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+        *reinterpret_cast<float4*>(&s_o[wave][rb * 16 + n][dt * 16 + 4 * g]) = make_float4(acc[rb][dt][0], acc[rb][dt][1], acc[rb][dt][2], acc[rb][dt][3]);
+    }
+  }
+  __syncthreads();
+  if (set == 1) return;
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const int r = (wave & 1) * 32 + rb * 16 + n;
+    if (!live || r >= rows) continue;
+    const float2 other = s_ml[wave][rb * 16 + n];
+    const float m_all = fmaxf(m_run[rb], other.x);
+    const float f0 = m_run[rb] == -INFINITY ? 0.f : exp2f(m_run[rb] - m_all), f1 = other.x == -INFINITY ? 0.f : exp2f(other.x - m_all);
+    const float l = l_row[rb] * f0 + other.y * f1;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) {
+      const float4 o = *reinterpret_cast<const float4*>(&s_o[wave][rb * 16 + n][dt * 16 + 4 * g]);
+      acc[rb][dt] = (f32x4){acc[rb][dt][0] * f0 + o.x * f1, acc[rb][dt][1] * f0 + o.y * f1, acc[rb][dt][2] * f0 + o.z * f1, acc[rb][dt][3] * f0 + o.w * f1};
+    }
+    const float L1 = l > 0.f ? l : INFINITY;   // no visible key: a row of zeros
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+      Act<bf16_t>::store4(reinterpret_cast<bf16_t*>(aa.out), s * B + r % B, (hg * group + r / B) * HD + dt * 16 + 4 * g, aa.n_q_heads * HD,
+                          make_float4(acc[rb][dt][0] / L1, acc[rb][dt][1] / L1, acc[rb][dt][2] / L1, acc[rb][dt][3] / L1));
+  }
+}
+
 // whether the kernels above take this configuration
 template <typename T>
 inline bool attn_takes_mfma(const AttnArgs& aa, int block_size) {
@@ -614,9 +866,19 @@ inline bool attn_takes_mfma(const AttnArgs& aa, int block_size) {
   return sizeof(T) == 2 && ((block_size * group) >> aa.q_shift) <= 64 && group % (1 << aa.q_shift) == 0 && (aa.head_dim == 128 || aa.head_dim == 64);
 }
 
+// pairs of a prompt's consecutive blocks: (first pseudo-sequence, one or two of them, tokens before them, -)
+struct PrefillTiles {
+  const int4* at = nullptr;
+  int n = 0;   // 0: not a prefill, or too little work for one workgroup a tile and group of heads
+};
+
 inline void attn_mfma_launch(hipStream_t st, const bf16_t* q, const bf16_t* pool, SeqGeom geo, AttnArgs aa, int S, float* part_o, float2* part_ml,
-                             int wide_min_chunk) {
+                             int wide_min_chunk, PrefillTiles tiles) {
   const dim3 grid(aa.n_splits, aa.n_kv_heads, S << aa.q_shift), block(256);
+  if (tiles.n) {
+    hipLaunchKernelGGL(attn_prefill_kernel<128>, dim3(tiles.n * (aa.n_kv_heads << aa.q_shift)), dim3(512), 0, st, q, pool, geo, aa, tiles.at, tiles.n);
+    return;
+  }
   // long chunks: wavefronts split the keys
   if (aa.head_dim == 128 && aa.chunk >= wide_min_chunk)
     hipLaunchKernelGGL((attn_mfma_wide_kernel<128, 4>), grid, dim3(512), 0, st, q, pool, geo, aa, part_o, part_ml);

@@ -186,7 +186,7 @@ inline void launch_accept_sampled(hipStream_t st, const float* p_logits, const f
 inline size_t arrive_counters(size_t D) { return std::max<size_t>(1, D / 64); }
 
 struct Workspace {
-  size_t status, arena, h, a, q, o, act, taps, fuse, ht, logits_d, logits_t, part_o, part_ml, stats_p, stats_q, amax, lsep, rope_t, rope_d, ssq, arrive, pf_lens, pf_plens, pf_table, pf_tokens, pf_end_row, pf_end_seq, pf_first, pf_anchor, total;
+  size_t status, arena, h, a, q, o, act, taps, fuse, ht, logits_d, logits_t, part_o, part_ml, stats_p, stats_q, amax, lsep, rope_t, rope_d, ssq, arrive, pf_lens, pf_plens, pf_table, pf_tokens, pf_end_row, pf_end_seq, pf_first, pf_anchor, pf_tiles, total;
   size_t moe_sel_e, moe_sel_w, moe_sel_pos, moe_row_of, moe_items, moe_a, moe_act, moe_y;   // routed-expert target only
 };
 Workspace workspace_layout(const dflash_dims& t, const dflash_dims& d, const dflash_runtime& rt, const Knobs& kn) {
@@ -249,6 +249,7 @@ Workspace workspace_layout(const dflash_dims& t, const dflash_dims& d, const dfl
   w.pf_end_seq = take((size_t)rt.max_seqs * 4);
   w.pf_first = take((size_t)rt.max_seqs * 4);
   w.pf_anchor = take((size_t)rt.max_seqs * 4);
+  w.pf_tiles = take((size_t)rt.max_seqs * 16);
   w.moe_sel_e = w.moe_sel_w = w.moe_sel_pos = w.moe_row_of = w.moe_items = w.moe_a = w.moe_act = w.moe_y = 0;
   if (t.n_experts) {
     const size_t mk = (size_t)M * t.top_k, np = moe_positions(t, M);
@@ -383,6 +384,7 @@ struct Engine {
   int amax_parts = 0;    // > 0: the last LM-head GEMM left that many per-row argmax partials in ws.amax (fused epilogue)
   int lse_parts = 0;     // > 0: ... and that many per-row softmax-statistics partials in ws.lsep
   bool lm_skip_store = false;   // the LM-head GEMM may drop its logits when its argmax is fused (nobody will read them)
+  PrefillTiles tiles;    // the layer() call in progress is a prefill's, whose attention goes by these
   int pending_tap = -1;  // tap index to be taken from the completed residual stream by the next RMSNorm
 
   // Few-row path: ws.a holds x * gain with the division by the row's rms deferred to the GEMM that reads it; the
@@ -793,9 +795,10 @@ struct Engine {
     for (int chunk0 = 0; chunk0 < total_chunks; chunk0 += c->rt.max_seqs) {
       const int n = std::min(c->rt.max_seqs, total_chunks - chunk0), M = n * B;
       // prompts whose last chunk lies in this pass (the host counts them from the same lengths as the kernel)
-      int n_end = 0, first = 0;
+      int n_end = 0, first = 0, n_tiles = 0;
       for (int s = 0; s < S; ++s) {
         const int nc = (lens_host[s] + B - 1) / B;
+        n_tiles += prefill_tiles(std::min(first + nc, chunk0 + n) - std::max(first, chunk0));
         if (nc > 0 && first + nc - 1 >= chunk0 && first + nc - 1 < chunk0 + n) ++n_end;
         first += nc;
       }
@@ -804,6 +807,7 @@ struct Engine {
       pp.S = S; pp.B = B; pp.mpps = c->rt.max_pages_per_seq; pp.chunk0 = chunk0; pp.n_chunks = n;
       pp.p_lens = ws<int32_t>(c->ws.pf_plens); pp.p_table = ws<int32_t>(c->ws.pf_table); pp.p_tokens = ws<int32_t>(c->ws.pf_tokens);
       pp.end_row = ws<int32_t>(c->ws.pf_end_row); pp.end_seq = ws<int32_t>(c->ws.pf_end_seq);
+      pp.tiles = ws<int4>(c->ws.pf_tiles);
       hipLaunchKernelGGL(prefill_plan_kernel, dim3(n), dim3(256), 0, st, pp);
       check();
       dflash_batch pb;
@@ -816,6 +820,8 @@ struct Engine {
                          RopeTab{ws<float2>(c->ws.rope_t), log((double)t.rope_theta), t.head_dim},
                          RopeTab{ws<float2>(c->ws.rope_d), log((double)c->d.rope_theta), c->d.head_dim}, EmbedFuse{}, EmbedBlock{}, arrivals(t, M));
       check();
+      const int q_shift = attn_q_shift(t, B);
+      if (q_shift >= 0 && t.head_dim == 128 && attention_by_tiles(n_tiles, t.n_kv_heads << q_shift, pb.max_seq_len + B, c->k.attn_tile_wgs)) tiles = PrefillTiles{pp.tiles, n_tiles};
       int tap = 0;
       for (int l = 0; l < t.n_layers; ++l) {
         const char* lb = c->tblob + c->tl.layer0 + c->tl.lo.end * l;
@@ -825,6 +831,7 @@ struct Engine {
               l + 1 < t.n_layers ? reinterpret_cast<const float*>(lb + c->tl.lo.end + c->tl.lo.g1) : nullptr, tapped ? tap : -1);
         if (tapped) ++tap;
       }
+      tiles = PrefillTiles{};
       if (n_end > 0 || pending_tap >= 0) norm_h(reinterpret_cast<const float*>(c->tblob + c->tl.gf), M, t.d_model, t.rms_eps);
       pending = Slab{};
       if (n_end > 0) {   // the first generated token of every prompt that ends here: LM head on those rows only
@@ -1149,7 +1156,7 @@ void Engine<T>::attention(const dflash_dims& m, const T* pool, int layer, const 
   aa.q_shift = q_shift;
   // one split per sequence: the MFMA kernels write the O projection's operand themselves; so does the plain one for few rows with short contexts
   const bool mfma = attn_takes_mfma<T>(aa, B);
-  const bool direct = mfma ? p.n_splits == 1 : short_context(M * m.n_q_heads, m.head_dim, max_tokens, sizeof(T) == 2);
+  const bool direct = mfma ? tiles.n || p.n_splits == 1 : short_context(M * m.n_q_heads, m.head_dim, max_tokens, sizeof(T) == 2);
   if (direct) aa.out = ws<T>(c->ws.o);
   float* part_o = ws<float>(c->ws.part_o);
   float2* part_ml = ws<float2>(c->ws.part_ml);
@@ -1157,7 +1164,7 @@ void Engine<T>::attention(const dflash_dims& m, const T* pool, int layer, const 
     // algorithmic bytes: every cached K and V row of this layer once (upper bound from the host hint)
     ProfScope prof(c, st, DFLASH_PROF_ATTN, (double)S * max_tokens * 2 * m.n_kv_heads * m.head_dim * sizeof(T));
     if (mfma) {
-      if constexpr (std::is_same<T, bf16_t>::value) attn_mfma_launch(st, ws<bf16_t>(c->ws.q), pool, geom(b), aa, S, part_o, part_ml, c->k.attn_wide_min_chunk);
+      if constexpr (std::is_same<T, bf16_t>::value) attn_mfma_launch(st, ws<bf16_t>(c->ws.q), pool, geom(b), aa, S, part_o, part_ml, c->k.attn_wide_min_chunk, tiles);
     } else if (direct) {
       aa.chunk *= aa.n_splits;
       hipLaunchKernelGGL(attn_short_simple_kernel<T>, dim3(B * (m.n_q_heads / m.n_kv_heads), m.n_kv_heads, S), dim3(256), 0, st, ws<T>(c->ws.q), pool,

@@ -7,6 +7,7 @@
 #include "common.h"
 #include "exp_nonpositive.h"
 #include "finish.h"
+#include "plan.h"
 
 // ---- block assembly + embedding gather -------------------------------------------------------
 // Rotary table of one model for the rows of a call: out[m * hd/2 + i] = (cos, sin) of pos(m) * theta^(-2i/hd),
@@ -868,16 +869,22 @@ struct PrefillPlan {
   int32_t* p_tokens;           // [n_chunks, B], zero-padded
   int32_t* end_row;            // [.] row (in this pass) of the last token of every prompt that ends in this pass, in prompt order
   int32_t* end_seq;            // [.] and that prompt's index
+  int4* tiles;                 // [.] pairs of consecutive pseudo-sequences of a prompt: (first, how many, tokens before, -), in order; see prefill_tiles
 };
 
 __global__ __launch_bounds__(256) void prefill_plan_kernel(PrefillPlan p) {
   const int i = blockIdx.x, c = p.chunk0 + i;
   __shared__ int sh[4];
   if (threadIdx.x == 0) {
-    int first = 0, s = 0, n_end_before = 0;
+    int first = 0, s = 0, n_end_before = 0, n_tiles = 0;
     for (; s < p.S; ++s) {
       const int nc = (p.lens[s] + p.B - 1) / p.B;
-      if (c < first + nc) break;
+      const int from = max(first, p.chunk0), to = min(first + nc, p.chunk0 + p.n_chunks);   // its chunks in this pass
+      if (c < first + nc) {
+        if (((c - from) & 1) == 0) p.tiles[n_tiles + ((c - from) >> 1)] = make_int4(i, min(2, to - c), p.seq_lens[s] + (c - first) * p.B, 0);
+        break;
+      }
+      n_tiles += prefill_tiles(to - from);
       // a prompt before ours whose last chunk lies in this pass takes an earlier place in the end list
       if (nc > 0 && first + nc - 1 >= p.chunk0) ++n_end_before;
       first += nc;

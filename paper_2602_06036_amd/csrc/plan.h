@@ -19,6 +19,7 @@ struct Knobs {
   int gemm_wide;            // DFLASH_GEMM_WIDE: 1 = eight-wavefront tiles by estimated time (default), 2 = always (tests), any other value = never
   int attn_target_wgs;      // DFLASH_ATTN_TARGET_WGS: workgroups an attention launch aims at
   int attn_wide_min_chunk;  // DFLASH_ATTN_WIDE_MIN_CHUNK: keys per workgroup from which the key-split attention kernel is used
+  int attn_tile_wgs;        // DFLASH_ATTN_TILE_WGS: workgroups from which a prefill's attention goes by tiles (256; the tests set 1)
   int gemm_target_wgs;      // DFLASH_GEMM_TARGET_WGS: workgroups a K-split streaming GEMM aims at
   int gemm_u;               // DFLASH_GEMM_U: k tiles per prefetch stage (one band of rows)
   int gemm_nt8;             // DFLASH_GEMM_NT8: matrices with at least 8 * this row bands use 8 weight tiles per activation fragment
@@ -38,6 +39,7 @@ inline Knobs read_knobs() {
   k.gemm_wide = env_int("DFLASH_GEMM_WIDE", 1);
   k.attn_target_wgs = env_int("DFLASH_ATTN_TARGET_WGS", 256);
   k.attn_wide_min_chunk = env_int("DFLASH_ATTN_WIDE_MIN_CHUNK", 512);
+  k.attn_tile_wgs = env_int("DFLASH_ATTN_TILE_WGS", 256);
   k.gemm_target_wgs = env_int("DFLASH_GEMM_TARGET_WGS", 256);
   k.gemm_u = env_int("DFLASH_GEMM_U", 2);
   k.gemm_nt8 = env_int("DFLASH_GEMM_NT8", 1);
@@ -82,6 +84,15 @@ inline SplitPlan plan_splits(int S, int n_kv_heads, int max_tokens, int target_w
   p.n_splits = (max_tokens + chunk - 1) / chunk;
   return p;
 }
+
+// Prefill: tiles of two consecutive blocks of a prompt that has `chunks` of them in a pass (constexpr: for host and device)
+constexpr int prefill_tiles(int chunks) { return chunks > 0 ? (chunks + 1) / 2 : 0; }
+// ... and whether the pass's attention goes by tiles, a workgroup for each and every group of heads: where they fill the CUs (their keys are not
+// split any further) and the contexts are short enough for the ramp and the merge of a block by itself to count.  Layers of the 8B shape, block by block
+// and by tiles: one prompt of 2048 110 and 83 us, six of 37 to 311 behind up to 600 cached tokens (296 workgroups) 55 and 37.  Passes of four layers: those two
+// 5410 and 5325, 3453 and 3387; a prompt of 1024 (256 workgroups) 2910 and 2911, of 640 (160) 1948 and 1956; 1024 behind 1000, 2000, 4000 and 8000
+// tokens 3016 and 2991, 3105 and 3090, 3320 and 3331, 3779 and 3838; 2000 behind 2000, 4000 and 16000 5928 and 5861, 6296 and 6281, 8900 and 9068.
+inline bool attention_by_tiles(int tiles, int head_groups, int max_tokens, int from) { return tiles * head_groups >= from && max_tokens <= 4608; }
 
 // ---- GEMMs ----------------------------------------------------------------------------------------------
 // rows of partial results the split-K arena holds for a context of at most max_rows activation rows

@@ -180,6 +180,29 @@ def test_forced_tiles_over_ragged_sizes(n_seqs, ffn, vocab, wide, tile, wm, ks, 
     assert counts[wide] > 0 and counts[3 - wide] == 0 and counts[0] == 0
 
 
+@pytest.mark.parametrize("heads,kv_heads,block,lens,max_seqs,pieces", [
+    (8, 2, 16, (16, 17, 150, 33), 16, 1),       # one block and two of them a tile; a last block of one row
+    (8, 2, 16, (97, 5, 160), 6, 2),             # several passes, prompts cut at odd blocks; the second call behind cached rows
+    (4, 4, 16, (70, 31), 8, 1),                 # sixteen query rows of a group of heads
+    (8, 1, 16, (90, 49), 12, 3),                # two groups of heads share a kv head
+    (8, 2, 10, (44, 71), 9, 2),                 # blocks that straddle pages
+    (6, 2, 5, (23, 37, 4), 7, 1),               # fifteen query rows
+    (4, 2, 16, (1100,), 69, 1),                 # page ids beyond the first set of 32 pairs
+])
+def test_prefill_attention_by_tiles(heads, kv_heads, block, lens, max_seqs, pieces, monkeypatch):
+    """dflash_prefill with the attention that takes two blocks of a prompt together, forced at every size."""
+    monkeypatch.setenv("DFLASH_ATTN_TILE_WGS", "1")
+    n = len(lens)
+    w = tiny_workload(seed=heads + block, n_layers=2, draft_layers=1, vocab=512, block=block, qk_norm=True, kv_heads=kv_heads, dtype="bf16", n_seqs=n,
+                      taps=(0, 1), d=256, heads=heads, hd=128, ffn=512)
+    prompts = [p[:k] for p, k in zip(si.make_prompts(replace(w, ctx_min=max(lens), ctx_max=max(lens))), lens)]
+    ls = Lockstep(w, prompts, max_len=max(lens) + 5 * block, max_seqs=max_seqs)
+    ls.prefill(entry=True, pieces=pieces)
+    ls.check_cache([0, 1], [0])
+    ls.step(plan=[(3 * s + 1) % block for s in range(n)], step_idx=0)
+    assert ls.stats["reseeds"] <= 1
+
+
 @pytest.mark.parametrize("n_seqs,ffn,vocab,wide,tile,wm,ks", ROLLED_TILES)
 def test_rolled_tiles_over_ragged_sizes(n_seqs, ffn, vocab, wide, tile, wm, ks, monkeypatch):
     """512 x 128 tiles: clamped last weight blocks, activation blocks of one band, K ranges of a k tile or two (shorter than the ring), odd numbers of k tiles."""
