@@ -882,7 +882,8 @@ void launch_bf16(hipStream_t st, const bf16_t* W, const bf16_t* A, int M, int N,
   }
 }
 
-template <int WN, int WM, int NS, int WY = 2>
+// FEW: a single activation block, which reads the weights once
+template <int WN, int WM, int NS, int WY = 2, bool FEW = false>
 void launch_tiled(hipStream_t st, const bf16_t* W, const bf16_t* A, int M, int N, int K, int epi, EpiArgs ep, int ks) {
   const int n_blocks = (N / 16 + WY * WN - 1) / (WY * WN), m_blocks = ((M + 15) / 16 + 2 * WM - 1) / (2 * WM);
   const dim3 grid((n_blocks * m_blocks + 7) / 8 * 8, ks), block(128 * WY);
@@ -898,7 +899,7 @@ void launch_tiled(hipStream_t st, const bf16_t* W, const bf16_t* A, int M, int N
   if constexpr (WY == 4) {
     if (m_blocks <= 8) return go(std::true_type{});
   }
-  go(std::false_type{});
+  go(std::integral_constant<bool, FEW>{});
 }
 
 inline int gemm_class(int epi, int N, int vocab) { return (epi == EPI_STORE && N == vocab) ? DFLASH_PROF_GEMM_LMHEAD : epi; }
@@ -924,7 +925,11 @@ Engine<bf16_t>::Slab Engine<bf16_t>::gemm(const bf16_t* W, const bf16_t* A, int 
     hip_err = 1;
     return Slab{};
   }
-  if (sp.nt) {
+  if (sp.staged) {
+    ks = sp.ks;
+    ep.slab = (size_t)M * ep.ld;
+    launch_tiled<4, 2, 4, 2, true>(st, W, A, M, N, K, kepi, ep, ks);
+  } else if (sp.nt) {
     ks = sp.ks;
     ep.slab = (size_t)M * ep.ld;
     const int shape = sp.nt * 100 + sp.mt * 10 + sp.u;

@@ -176,6 +176,7 @@ inline int pick_ksplit(int n_blocks, int KT, int M, int arena, int target) {
 // prefetch stage, K ranges.
 struct StreamPlan {
   int nt = 0, mt = 0, u = 0, ks = 1;   // nt = 0: another kernel's shape
+  bool staged = false;   // its blocks and K ranges as 128 x 64 tiles of the LDS-staged kernel
 };
 // whether the launch may finish its own sums (finish.h): plans that the finishing kernel is built for
 inline bool stream_finishes(const StreamPlan& p) { return p.nt >= 4 && p.mt == 1; }
@@ -232,6 +233,13 @@ inline StreamPlan stream_plan(const Knobs& kn, int M, int N, int K, bool split, 
     if (kn.gemm_fill4 == 1) fullest();
     else powers(8);
     if (p.nt == 8 && kn.gemm_u4 >= 2) p.u = 2;   // (measured slower)
+    // Four bands: a wavefront that has all of them reads every activation fragment for itself, and what it reads from the L2 waits behind
+    // its weights from HBM; staged in LDS a fragment is read once for four wavefronts.  Split matrices of 128-row blocks, as streaming launches and
+    // as LDS-staged ones with the same K ranges, 64 rows: 4096 x 12288 24.5 and 22.7 us, 4096 x 4096 11.7 and 10.5, 4096 x 20480 35.6 and 33.7; four-layer
+    // steps and verifications 1008 and 992, 546 and 541, 582 and 574.  But three bands (4096 x 12288 22.0 and 20.8 by itself) 517.9 and 518.7 in a
+    // verification, two 18.4 and 19.7, half the CUs (2048 x 2048, 64 rows) 5.8 and 6.6, unsplit 96-row blocks (24576 x 4096) 41.9 and 44.5.
+    // (Not in a routed target's layers: another order of sums, as above.)
+    p.staged = four_first && split && M > 48 && p.nt == 8 && p.u == 1 && nt / 8 * p.ks >= 192;
   }
   return p;
 }

@@ -180,6 +180,22 @@ def test_forced_tiles_over_ragged_sizes(n_seqs, ffn, vocab, wide, tile, wm, ks, 
     assert counts[wide] > 0 and counts[3 - wide] == 0 and counts[0] == 0
 
 
+@pytest.mark.parametrize("n_seqs,block,ffn", [(4, 16, 4096), (7, 7, 4224), (5, 11, 4096)])
+def test_four_bands_of_rows_by_staged_tiles(n_seqs, block, ffn):
+    """64, 49 and 55 rows: the down projection of a 2048-wide model as 16 blocks x 16 K ranges of the LDS-staged kernel (the last one uneven)."""
+    w = tiny_workload(seed=ffn + block, n_layers=2, draft_layers=1, vocab=512, block=block, qk_norm=True, kv_heads=4, dtype="bf16", n_seqs=n_seqs,
+                      taps=(0, 1), d=2048, heads=32, hd=64, ffn=ffn)
+    lens = [9 + 5 * i for i in range(n_seqs)]
+    prompts = [p[:n] for p, n in zip(si.make_prompts(replace(w, ctx_min=60, ctx_max=60)), lens)]
+    ls = Lockstep(w, prompts, max_len=60 + 4 * block)
+    ls.prefill()
+    ls.g.e.gemm_counts()
+    ls.step(plan=[(5 * s) % block for s in range(n_seqs)], step_idx=0)
+    assert ls.g.e.gemm_counts()[1] > 0
+    ls.check_cache([0, 1], [0])
+    assert ls.stats["reseeds"] <= 1
+
+
 @pytest.mark.parametrize("heads,kv_heads,block,lens,max_seqs,pieces", [
     (8, 2, 16, (16, 17, 150, 33), 16, 1),       # one block and two of them a tile; a last block of one row
     (8, 2, 16, (97, 5, 160), 6, 2),             # several passes, prompts cut at odd blocks; the second call behind cached rows

@@ -19,9 +19,9 @@ int main() {
   while (scanf("%d %d %d %d %d", &M, &N, &K, &split, &max_rows) == 5) {
     const TilePlan t = tile_plan(kn, M, N, K, split != 0, arena_rows(max_rows));
     const StreamPlan s = stream_plan(kn, M, N, K, split != 0, arena_rows(max_rows)), r = stream_plan(kn, M, N, K, split != 0, arena_rows(max_rows), false);
-    printf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d %d\n", t.t->wn, t.t->wm, t.t->wy, t.ks, half_height_expert_tiles(N / 16) ? 128 : 256, s.nt, split_f32_columns(N, K, !split) ? 4 : 1,
+    printf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d\n", t.t->wn, t.t->wm, t.t->wy, t.ks, half_height_expert_tiles(N / 16) ? 128 : 256, s.nt, split_f32_columns(N, K, !split) ? 4 : 1,
            short_context(M, K, N, split != 0), fold_norm(M, K, N),
-           f32_groups_side_by_side((M + 7) / 8, (N + 3) / 4, (long long)N * K * 4), s.ks, stream_finishes(s), r.nt, r.ks, argmax_in_one_launch(M, N));
+           f32_groups_side_by_side((M + 7) / 8, (N + 3) / 4, (long long)N * K * 4), s.ks, stream_finishes(s), r.nt, r.ks, argmax_in_one_launch(M, N), s.staged + 2 * r.staged);
   }
 }
 """
@@ -38,7 +38,8 @@ def plans(tmp_path_factory):
         kernel, wavefronts of an fp32 column, whether M query rows of K dims (of bf16, with 'may split') with N
         keys go without splits, whether the norm of K columns goes with the N columns behind it,
         whether groups of eight rows run side by side, K ranges of the streaming kernel, whether its launch may finish its sums,
-        weight tiles and K ranges in a routed-expert target's layers, whether the argmax of M rows of N is one launch) for each (rows, height, K, may split, rows of the context)."""
+        weight tiles and K ranges in a routed-expert target's layers, whether the argmax of M rows of N is one launch, whether the streaming plan goes by LDS-staged tiles (2: in a routed
+        target's layers)) for each (rows, height, K, may split, rows of the context)."""
         env = {k: v for k, v in os.environ.items() if not k.startswith("DFLASH_")}
         env.update({"DFLASH_" + k: str(v) for k, v in knobs.items()})
         if constants:
@@ -186,6 +187,13 @@ def test_one_band_of_rows_takes_four_weight_tiles_where_plans_tie(plans):
         for m in (1, 16):
             assert [(p[5], p[10], p[12], p[13]) for p in plans([(m, n, k, 1, 16)])] == [dense + routed], (n, k)
     assert [(p[5], p[10]) for p in plans([(32, 4096, 12288, 1, 32), (64, 4096, 12288, 1, 64)])] == [(8, 8), (8, 8)]
+
+
+def test_split_matrices_of_four_bands_go_by_staged_tiles(plans):
+    """(rows, height, K, may split): dense, 49 to 64 rows, blocks of 128 rows that fill the CUs; the model of the GPU test has such a down projection."""
+    staged = [(64, 4096, 12288, 1), (49, 4096, 4096, 1), (64, 4096, 20480, 1), (64, 2048, 4096, 1)]
+    plain = [(48, 4096, 12288, 1), (64, 24576, 4096, 0), (64, 16384, 4096, 0), (64, 2048, 2048, 1), (64, 6144, 4096, 1), (32, 4096, 12288, 1)]
+    assert [p[15] for p in plans([(m, n, k, sp, 64) for m, n, k, sp in staged + plain])] == [1] * len(staged) + [0] * len(plain)
 
 
 def test_argmax_of_stored_logits_is_one_launch_where_that_is_faster(plans):
