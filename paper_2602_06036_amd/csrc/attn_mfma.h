@@ -91,8 +91,7 @@ __device__ __forceinline__ void attn_process_pair(KvFrags<HD>& f, int p, const u
   v7 = DF_VIS(f.ok_b, pa0 + 19) ? sb[3] * scale : -INFINITY;
 #undef DF_VIS
   float mx = fmaxf(fmaxf(fmaxf(v0, v1), fmaxf(v2, v3)), fmaxf(fmaxf(v4, v5), fmaxf(v6, v7)));
-  mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-  mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+  mx = quarter_max(mx);
   const float m_new = fmaxf(m_run, mx);
   // all keys so far masked: exponent base 0 gives exp(-inf) = 0 for every (masked) key and corr 1
   const float mb = (m_new == -INFINITY) ? 0.f : m_new;
@@ -207,9 +206,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(const bf16_t* __restr
   }
 
   // ---- partial result of this split: (max, sum) and the unnormalised output row -------------------------
-  float l = l_run;
-  l += __shfl_xor(l, 16, 64);
-  l += __shfl_xor(l, 32, 64);
+  const float l = quarter_sum(l_run);
   if (!valid) return;
   if (aa.out) {   // the only split: nothing to merge
     const float L1 = l > 0.f ? l : INFINITY;   // no visible key: a row of zeros
@@ -433,8 +430,7 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_wide_kernel(const bf16_t* __
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) {
         float mx = lmx[rb];   // the maximum commutes with the positive scale
-        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        mx = quarter_max(mx);
         const bool grow = mx > m_run[rb] + 8.f;
         const float corr = grow ? (m_run[rb] == -INFINITY ? 0.f : exp2f(m_run[rb] - mx)) : 1.f;
         l_run[rb] *= corr;
@@ -500,9 +496,7 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_wide_kernel(const bf16_t* __
   // ---- merge the wavefronts' partial results (each over its own keys): the upper four hand theirs to the lower four ----
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
-    float l = l_run[rb];
-    l += __shfl_xor(l, 16, 64);
-    l += __shfl_xor(l, 32, 64);
+    const float l = quarter_sum(l_run[rb]);
     if (g == 0) s_ml[wave][rb * 16 + n] = make_float2(m_run[rb], l);
   }
   __syncthreads();   // also: every wavefront is done with the ring and the query fragments that s_o overlays
@@ -764,8 +758,7 @@ __global__ __launch_bounds__(512, 2) void attn_prefill_kernel(const bf16_t* __re
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) {
         float mx = lmx[rb];
-        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        mx = quarter_max(mx);
         const bool grow = mx > m_run[rb] + 8.f;
         const float corr = grow ? (m_run[rb] == -INFINITY ? 0.f : exp2f(m_run[rb] - mx)) : 1.f;
         l_run[rb] *= corr;
@@ -821,11 +814,7 @@ __global__ __launch_bounds__(512, 2) void attn_prefill_kernel(const bf16_t* __re
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // nothing may still be on its way into the ring when it is overlaid
   float l_row[RB];
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    l_row[rb] = l_run[rb];
-    l_row[rb] += __shfl_xor(l_row[rb], 16, 64);
-    l_row[rb] += __shfl_xor(l_row[rb], 32, 64);
-  }
+  for (int rb = 0; rb < RB; ++rb) l_row[rb] = quarter_sum(l_run[rb]);
   __syncthreads();
   if (set == 1) {
 #pragma unroll

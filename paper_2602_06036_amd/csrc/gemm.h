@@ -365,7 +365,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16_t* __restr
 // and the up row 16 below it), KW wavefronts per column that take every KW-th 256-wide piece of K; lanes stride over K; eight
 // rows a workgroup (groups of them: one after the other in a workgroup, a step of the 2 + 1 layer model of width 256 took 320 us
 // at 64 rows, side by side 182; width 2048, 128 rows 3208 and 2923).  Bound by latency: all loads of a piece go out together (rows past the last one repeat it, a load under
-// a condition would be waited for by itself), lane r of a column's first wavefront finishes row r (eight read-modify-writes
+// a condition would be waited for by itself), a lane for each row of a column's first wavefront finishes it (eight read-modify-writes
 // by one lane were eight round trips).  N = 256, K = 1024, 8 rows, RESID: 10.5 us, now 4.3 (the launch floor).
 // ------------------------------------------------------------------------------------------------
 // NORM: the RMSNorm in front of the product is taken along, y = (1 / rms(a)) ((a * gain) W'): a wavefront multiplies the gain in and
@@ -422,48 +422,50 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
       if (EPI == EPI_SWIGLU) acc1[r] += a[r].x * wb.x + a[r].y * wb.y + a[r].z * wb.z + a[r].w * wb.w;
     }
   }
-  float s0 = 0.f, s1 = 0.f;   // lane r: the sum of row m0 + r over this wavefront's pieces
-#pragma unroll
-  for (int r = 0; r < 8; ++r) {
-    const float t0 = wave_reduce_sum(acc0[r]);
-    const float t1 = (EPI == EPI_SWIGLU) ? wave_reduce_sum(acc1[r]) : 0.f;
-    if (lane == r) { s0 = t0; s1 = t1; }
-  }
+  // one lane of eight finishes row m0 + r
+  const int r = wave_sum8_index(lane);
+  const bool finish = (lane & 7) == 0;
+  float s0 = wave_sum8(acc0), s1 = EPI == EPI_SWIGLU ? wave_sum8(acc1) : 0.f;
   if constexpr (NORM) {
+    if constexpr (SQ == 8) {
+      const float t = wave_sum8(ss);
+      if (finish) sq[wave][r] = t;
+    } else {
 #pragma unroll
-    for (int r = 0; r < SQ; ++r) {
-      const float t = wave_reduce_sum(ss[r]);
-      if (lane == 0) sq[KW == 1 ? 0 : wave][(KW == 1 ? SQ * wave : 0) + r] = t;
+      for (int i = 0; i < SQ; ++i) {
+        const float t = wave_reduce_sum(ss[i]);
+        if (lane == 0) sq[0][SQ * wave + i] = t;
+      }
     }
   }
   if constexpr (KW > 1) {
-    if (lane < 8) {
-      sum[0][wave][lane] = s0;
-      if (EPI == EPI_SWIGLU) sum[1][wave][lane] = s1;
+    if (finish) {
+      sum[0][wave][r] = s0;
+      if (EPI == EPI_SWIGLU) sum[1][wave][r] = s1;
     }
   }
   if constexpr (KW > 1 || NORM) __syncthreads();
   if constexpr (KW > 1) {
-    if (kw == 0 && lane < 8) {
+    if (kw == 0 && finish) {
 #pragma unroll
       for (int i = 1; i < KW; ++i) {
-        s0 += sum[0][wave + i][lane];
-        if (EPI == EPI_SWIGLU) s1 += sum[1][wave + i][lane];
+        s0 += sum[0][wave + i][r];
+        if (EPI == EPI_SWIGLU) s1 += sum[1][wave + i][r];
       }
     }
   }
   if constexpr (NORM) {
-    if (lane < 8) {
-      float t = sq[0][lane];
+    if (finish) {
+      float t = sq[0][r];
 #pragma unroll
-      for (int i = 1; i < KW; ++i) t += sq[i][lane];
+      for (int i = 1; i < KW; ++i) t += sq[i][r];
       const float rstd = 1.0f / sqrtf(t / (float)K + ep.norm_eps);
       s0 *= rstd;
       s1 *= rstd;
     }
   }
-  const int m = m0 + lane;
-  if (kw == 0 && lane < 8 && m < M && col_raw < n_cols) {
+  const int m = m0 + r;
+  if (kw == 0 && finish && m < M && col_raw < n_cols) {
     if (EPI == EPI_SWIGLU) {
       reinterpret_cast<float*>(ep.act)[(size_t)m * ep.act_K + col] = silu_f(s0) * s1;
     } else if (EPI == EPI_RESID) {

@@ -94,9 +94,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_resid_kernel(const bf16_t* 
     s.x += a.x; s.y += a.y; s.z += a.z; s.w += a.w;
   }
   const float4 hn = make_float4(h4.x + s.x, h4.y + s.y, h4.z + s.z, h4.w + s.w);
-  float q = hn.x * hn.x + hn.y * hn.y + hn.z * hn.z + hn.w * hn.w;
-  q += __shfl_xor(q, 16, 64);
-  q += __shfl_xor(q, 32, 64);
+  const float q = quarter_sum(hn.x * hn.x + hn.y * hn.y + hn.z * hn.z + hn.w * hn.w);
   if (!live) return;
   *reinterpret_cast<float4*>(ra.h + (size_t)mrow * N + col) = hn;
   Act<bf16_t>::store4(ra.a_out, mrow, col, N, make_float4(hn.x * g4.x, hn.y * g4.y, hn.z * g4.z, hn.w * g4.w));

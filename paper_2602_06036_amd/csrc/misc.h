@@ -379,12 +379,7 @@ __global__ __launch_bounds__(256) void qkv_post_kernel(const float* __restrict__
 __device__ __forceinline__ void block_argmax(float& bv, int& bi) {
   __shared__ float sv[16];
   __shared__ int si[16];
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const float ov = __shfl_xor(bv, o, 64);
-    const int oi = __shfl_xor(bi, o, 64);
-    argmax_combine(bv, bi, ov, oi);
-  }
+  wave_argmax(bv, bi);
   const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
   if ((threadIdx.x & 63) == 0) { sv[wave] = bv; si[wave] = bi; }
   __syncthreads();
@@ -595,12 +590,7 @@ __device__ __forceinline__ void accept_finish(int lane, int n_chunks, int a, int
     const float2 x = best(c);
     argmax_combine(bv, bi, x.x, __float_as_int(x.y));
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const float ov = __shfl_xor(bv, o, 64);
-    const int oi = __shfl_xor(bi, o, 64);
-    argmax_combine(bv, bi, ov, oi);
-  }
+  wave_argmax(bv, bi);
   if (lane < B) out_tokens[lane] = lane < a ? draft[lane + 1] : (lane == a ? bi : -1);
 }
 
