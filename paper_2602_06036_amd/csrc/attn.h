@@ -221,7 +221,7 @@ __global__ __launch_bounds__(128) void attn_merge_rows_kernel(const float* __res
     wgt[c] = w;
     // sum in ascending split order (fixed order, independent of the wavefront reduction tree)
     float L = 0.f;
-    for (int i = 0; i < n_splits; ++i) L += __shfl(ml.y * w, i, 64);
+    for (int i = 0; i < n_splits; ++i) L += lane_value(ml.y * w, i);
     if (c == 0) s_L = L;
   }
   __syncthreads();
@@ -278,7 +278,7 @@ __global__ __launch_bounds__(512) void attn_merge_kernel(const float* __restrict
       wgt[rr][lane] = w;
       // sum in ascending split order (fixed order, independent of the wavefront reduction tree)
       float L = 0.f;
-      for (int i = 0; i < n_splits; ++i) L += __shfl(ml.y * w, i, 64);
+      for (int i = 0; i < n_splits; ++i) L += lane_value(ml.y * w, i);
       if (lane == 0) s_L[rr] = L;
     }
   }

@@ -218,8 +218,10 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16_t* __restr
     for (int i = 0; i < SQ; ++i)
       if (i * 64 < ep.ssq_parts) add(sq[i], sq_c + i * 64);
     for (int p = sq_c + kSsqAhead; p < ep.ssq_parts; p += 64) add(*reinterpret_cast<const float4*>(sq_p + p), p);
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) t += __shfl_xor(t, o, 64);
+    t += lane_xor<1>(t);
+    t += lane_xor<2>(t);
+    t += lane_xor<4>(t);
+    t += lane_xor<8>(t);
     if ((threadIdx.x & 15) == 0) s_rstd[threadIdx.x >> 4] = 1.0f / sqrtf(t * ep.ssq_inv_D + ep.ssq_eps);
   };
 
@@ -318,12 +320,8 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16_t* __restr
           argmax_combine(bv, bi, amax_score(ep, key, s.z, m, col + 2), col + 2);
           argmax_combine(bv, bi, amax_score(ep, key, s.w, m, col + 3), col + 3);
         }
-#pragma unroll
-        for (int o = 16; o <= 32; o <<= 1) {
-          const float ov = __shfl_xor(bv, o, 64);
-          const int oi = __shfl_xor(bi, o, 64);
-          argmax_combine(bv, bi, ov, oi);
-        }
+        argmax_swap16(bv, bi);
+        argmax_swap32(bv, bi);
         if (g == 0) wbest[wave][j * 16 + mrow] = make_float2(bv, __int_as_float(bi));
       }
       __syncthreads();

@@ -251,12 +251,8 @@ __global__ __launch_bounds__(128 * WY, (tiled_waves<WN, WM, NS, WY>())) void gem
 #pragma unroll
         for (int e = 0; e < 4; ++e) argmax_combine(bv, bi, amax_score(ep, key, acc[i][jj][e], m, col + e), col + e);
       }
-#pragma unroll
-      for (int o = 16; o <= 32; o <<= 1) {
-        const float ov = __shfl_xor(bv, o, 64);
-        const int oi = __shfl_xor(bi, o, 64);
-        argmax_combine(bv, bi, ov, oi);
-      }
+      argmax_swap16(bv, bi);
+      argmax_swap32(bv, bi);
       if (gq == 0) wbest[wy * (BMT * 16) + (wx * WM + jj) * 16 + mrow] = make_float2(bv, __int_as_float(bi));
     }
     __syncthreads();

@@ -519,8 +519,9 @@ __global__ __launch_bounds__(256) void lse_partial_kernel(const float* __restric
   for (; c0 + ROUND <= i1; c0 += ROUND) round(c0 + (int)threadIdx.x * E, std::true_type{});
   if (c0 < i1) round(c0 + (int)threadIdx.x * E, std::false_type{});
   s = fmaf(s_left, kExpLn2, s);
+  lane_xor16(m, s, [&](float om, float os) { lse_merge(m, s, om, os); });
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
+  for (int o = 16; o < 64; o <<= 1) {
     const float om = __shfl_xor(m, o, 64), os = __shfl_xor(s, o, 64);
     lse_merge(m, s, om, os);
   }
@@ -550,7 +551,8 @@ __global__ __launch_bounds__(64) void lse_finish_kernel(const float2* __restrict
     s += p.x == -INFINITY ? 0.f : p.y * expf(p.x - mx);
   }
   float tot = 0.f;
-  for (int i = 0; i < 64; ++i) tot += __shfl(s, i, 64);
+#pragma unroll
+  for (int i = 0; i < 64; ++i) tot += lane_value(s, i);
   if (lane == 0) stats[m] = make_float2(mx, mx + logf(tot));
 }
 
@@ -573,11 +575,7 @@ __device__ __forceinline__ float row_lse(const RowStats& st, size_t row, int lan
     const float2 x = st.p[row * st.parts + c];
     lse_merge(m, s, x.x, x.y);
   }
-#pragma unroll
-  for (int o = 1; o < 16; o <<= 1) {
-    const float om = __shfl_xor(m, o, 64), os = __shfl_xor(s, o, 64);
-    lse_merge(m, s, om, os);
-  }
+  lane_xor16(m, s, [&](float om, float os) { lse_merge(m, s, om, os); });
   return m + logf(s);
 }
 
