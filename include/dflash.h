@@ -182,7 +182,7 @@ int dflash_accept(dflash_ctx *ctx, const dflash_batch *batch, const int32_t *dra
 /* For callers that cannot allocate device memory or hand over a workspace (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc): the temperature > 0 branch of dflash_accept on logits the caller holds itself
  * (e.g. the logits_out of dflash_draft_block and dflash_verify), with the rows' softmax statistics kept in an array that
- * is built into the library (96 KB of device memory per GPU, held until the process ends) instead of a workspace.
+ * is built into the library (128 KB of device memory per GPU, held until the process ends) instead of a workspace.
  * target_logits, draft_logits (device) [S,B,V] fp32; draft_tokens (device) [S,B]; uniforms (device) [S,B]; rng_key
  * (device) [1]; outputs as dflash_accept.  Needs no context, allocates nothing, calls no allocating routine.
  * At most 4096 rows (n_seqs * block_size): DFLASH_ECAPACITY beyond that; DFLASH_EINVAL for temperature <= 0 (greedy
