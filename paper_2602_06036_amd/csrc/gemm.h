@@ -192,7 +192,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16_t* __restr
   };
 
   // Deferred RMSNorm: 1 / rms of this workgroup's rows, 16 threads per row.  The pieces of the sums of squares are requested
-  // here and added behind the sweep (16 threads a row, each every 16th group of four in ascending order, then a fixed shuffle
+  // here and added behind the sweep (16 threads a row, each every 16th group of four in ascending order, then a fixed butterfly
   // tree); s_rstd is read after the barrier of the cross-wavefront sum.
   __shared__ float s_rstd[16];
   constexpr int SQ = kSsqAhead / 64;          // groups of four that a thread keeps in registers over the sweep
