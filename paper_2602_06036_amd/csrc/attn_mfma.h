@@ -697,7 +697,12 @@ __global__ __launch_bounds__(512, 2) void attn_prefill_kernel(const bf16_t* __re
     const int ids_p = ids, p = 2 * st + set;
     if (((st + 1) & 15) == 0) {   // uniform: the next stage's page ids come into use
       ids = ids_next;
-      if (2 * st + 34 < n_pairs) ids_next = load_ids(2 * st + 34);
+      if (2 * st + 34 < n_pairs) {
+        ids_next = load_ids(2 * st + 34);
+        // waited for here, once in sixteen stages: left to the compiler it is a wait for every copy at the end of every stage.  (Even in time, 82 us for
+        // 2048 fresh tokens, 292 for 2000 behind 4000: a stage's scores, softmax and products are longer than its copies.)
+        asm volatile("" : "+v"(ids_next));
+      }
     }
     if (p >= my_pairs) continue;
     const int base = p * 32;
