@@ -795,10 +795,12 @@ struct Engine {
     for (int chunk0 = 0; chunk0 < total_chunks; chunk0 += c->rt.max_seqs) {
       const int n = std::min(c->rt.max_seqs, total_chunks - chunk0), M = n * B;
       // prompts whose last chunk lies in this pass (the host counts them from the same lengths as the kernel)
-      int n_end = 0, first = 0, n_tiles = 0;
+      int n_end = 0, first = 0, n_tiles = 0, ahead = 0;
       for (int s = 0; s < S; ++s) {
         const int nc = (lens_host[s] + B - 1) / B;
-        n_tiles += prefill_tiles(std::min(first + nc, chunk0 + n) - std::max(first, chunk0));
+        const int from = std::max(first, chunk0), here = std::min(first + nc, chunk0 + n) - from;   // its chunks in this pass
+        n_tiles += prefill_tiles(here);
+        if (here > 0) ahead = std::max(ahead, (from - first) * B);
         if (nc > 0 && first + nc - 1 >= chunk0 && first + nc - 1 < chunk0 + n) ++n_end;
         first += nc;
       }
@@ -821,7 +823,9 @@ struct Engine {
                          RopeTab{ws<float2>(c->ws.rope_d), log((double)c->d.rope_theta), c->d.head_dim}, EmbedFuse{}, EmbedBlock{}, arrivals(t, M));
       check();
       const int q_shift = attn_q_shift(t, B);
-      if (q_shift >= 0 && t.head_dim == 128 && attention_by_tiles(n_tiles, t.n_kv_heads << q_shift, pb.max_seq_len + B, c->k.attn_tile_wgs)) tiles = PrefillTiles{pp.tiles, n_tiles};
+      if (q_shift >= 0 && t.head_dim == 128 &&
+          attention_by_tiles(n_tiles, n, t.n_kv_heads << q_shift, b->max_seq_len + ahead, pb.max_seq_len + B, c->k.attn_tile_wgs))
+        tiles = PrefillTiles{pp.tiles, n_tiles};
       int tap = 0;
       for (int l = 0; l < t.n_layers; ++l) {
         const char* lb = c->tblob + c->tl.layer0 + c->tl.lo.end * l;

@@ -12,6 +12,8 @@ inline int env_int(const char* name, int dflt) {
   return v > 0 ? v : dflt;
 }
 
+constexpr int kTileWgs = 256;   // see attention_by_tiles
+
 // Tuning and testing knobs, read from the environment whenever a context is created (or a workspace is sized): a
 // context keeps the values it was created with, so a test that sets one before dflash_create gets exactly that path
 // whatever ran earlier in the process.  Defaults are what the measurements in the documentation use.
@@ -19,7 +21,7 @@ struct Knobs {
   int gemm_wide;            // DFLASH_GEMM_WIDE: 1 = eight-wavefront tiles by estimated time (default), 2 = always (tests), any other value = never
   int attn_target_wgs;      // DFLASH_ATTN_TARGET_WGS: workgroups an attention launch aims at
   int attn_wide_min_chunk;  // DFLASH_ATTN_WIDE_MIN_CHUNK: keys per workgroup from which the key-split attention kernel is used
-  int attn_tile_wgs;        // DFLASH_ATTN_TILE_WGS: workgroups from which a prefill's attention goes by tiles (256; the tests set 1)
+  int attn_tile_wgs;        // DFLASH_ATTN_TILE_WGS: workgroups from which a prefill's attention goes by tiles, whatever its contexts (default 256: by rule)
   int gemm_target_wgs;      // DFLASH_GEMM_TARGET_WGS: workgroups a K-split streaming GEMM aims at
   int gemm_u;               // DFLASH_GEMM_U: k tiles per prefetch stage (one band of rows)
   int gemm_nt8;             // DFLASH_GEMM_NT8: matrices with at least 8 * this row bands use 8 weight tiles per activation fragment
@@ -39,7 +41,7 @@ inline Knobs read_knobs() {
   k.gemm_wide = env_int("DFLASH_GEMM_WIDE", 1);
   k.attn_target_wgs = env_int("DFLASH_ATTN_TARGET_WGS", 256);
   k.attn_wide_min_chunk = env_int("DFLASH_ATTN_WIDE_MIN_CHUNK", 512);
-  k.attn_tile_wgs = env_int("DFLASH_ATTN_TILE_WGS", 256);
+  k.attn_tile_wgs = env_int("DFLASH_ATTN_TILE_WGS", kTileWgs);
   k.gemm_target_wgs = env_int("DFLASH_GEMM_TARGET_WGS", 256);
   k.gemm_u = env_int("DFLASH_GEMM_U", 2);
   k.gemm_nt8 = env_int("DFLASH_GEMM_NT8", 1);
@@ -87,12 +89,23 @@ inline SplitPlan plan_splits(int S, int n_kv_heads, int max_tokens, int target_w
 
 // Prefill: tiles of two consecutive blocks of a prompt that has `chunks` of them in a pass (constexpr: for host and device)
 constexpr int prefill_tiles(int chunks) { return chunks > 0 ? (chunks + 1) / 2 : 0; }
-// ... and whether the pass's attention goes by tiles, a workgroup for each and every group of heads: where they fill the CUs (their keys are not
-// split any further) and the contexts are short enough for the ramp and the merge of a block by itself to count.  Layers of the 8B shape, block by block
-// and by tiles: one prompt of 2048 110 and 83 us, six of 37 to 311 behind up to 600 cached tokens (296 workgroups) 55 and 37.  Passes of four layers: those two
-// 5410 and 5325, 3453 and 3387; a prompt of 1024 (256 workgroups) 2910 and 2911, of 640 (160) 1948 and 1956; 1024 behind 1000, 2000, 4000 and 8000
-// tokens 3016 and 2991, 3105 and 3090, 3320 and 3331, 3779 and 3838; 2000 behind 2000, 4000 and 16000 5928 and 5861, 6296 and 6281, 8900 and 9068.
-inline bool attention_by_tiles(int tiles, int head_groups, int max_tokens, int from) { return tiles * head_groups >= from && max_tokens <= 4608; }
+// ... and whether the pass's attention goes by tiles, a workgroup for each and every group of heads.  `blocks`: those of the pass; `cached`: the most tokens
+// that lie in front of a prompt's first block in it; `from`: Knobs::attn_tile_wgs, set by hand the only condition.  Attention of a layer block by block and by
+// tiles, eight head groups of 64 query rows unless said.
+// - Tiles have to fill the CUs, their keys are not split: one prompt of 320 tokens (80 workgroups) 16.5 and 20 us, of 1024 (256) 42.7 and 39.6, of 2048 106 and 82.
+// - Contexts below 256 tokens are all ramp, which a block by itself with four wavefronts has less of: 12 prompts of 21 to 170 28 and 31.
+// - Equally long tiles go in whole rounds of the CUs, and a block alone in its tile takes a tile's time, while blocks, twice as many and bound by their
+//   pages, fill in: 6 prompts of 340 behind 4000 (528 workgroups) 299 and 400, 12 of 170 behind 2652 (576, every sixth tile half empty) 202 and 313.  Where the
+//   cached part is short the tiles' lengths differ and even the load out: six of 37 to 311 behind 0 to 600 (296 workgroups, half a round empty) 53 and 37.
+// - Behind longer contexts a block's ramp and merge do not count: 1024 behind 4000 142 and 148, 2000 behind 16000 875 and 900.
+// Over 1600 passes (six head layouts, blocks of 2 to 16, 1 to 32 prompts, up to 4600 tokens) the rule takes 7 % off the attention time of the passes' mean, and 24 are
+// more than 3 % slower by tiles; 256 workgroups and 4608 tokens as the only conditions, as before, 4.5 % and 438.
+inline bool attention_by_tiles(int tiles, int blocks, int head_groups, int cached, int max_tokens, int from) {
+  const int wgs = tiles * head_groups, rounds = (wgs + 255) / 256;
+  if (from != kTileWgs) return wgs >= from;
+  if (wgs < kTileWgs || max_tokens < 256 || max_tokens > 3072) return false;
+  return cached <= 768 || blocks * head_groups * 10 >= rounds * 512 * 9;   // nine tenths of the rounds' places for blocks taken
+}
 
 // ---- GEMMs ----------------------------------------------------------------------------------------------
 // rows of partial results the split-K arena holds for a context of at most max_rows activation rows

@@ -16,6 +16,10 @@ int main() {
   int M, N, K, split, max_rows;
   const Knobs kn = read_knobs();
   if (getenv("CONSTANTS")) return printf("%d\n", kSsqAhead), 0;
+  if (getenv("PREFILL")) {
+    while (scanf("%d %d %d %d %d", &M, &N, &K, &split, &max_rows) == 5) printf("%d\n", attention_by_tiles(M, N, K, split, max_rows, kn.attn_tile_wgs));
+    return 0;
+  }
   while (scanf("%d %d %d %d %d", &M, &N, &K, &split, &max_rows) == 5) {
     const TilePlan t = tile_plan(kn, M, N, K, split != 0, arena_rows(max_rows));
     const StreamPlan s = stream_plan(kn, M, N, K, split != 0, arena_rows(max_rows)), r = stream_plan(kn, M, N, K, split != 0, arena_rows(max_rows), false);
@@ -33,7 +37,7 @@ def plans(tmp_path_factory):
     (d / "plans.cpp").write_text(DRIVER)
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, str(d / "plans.cpp"), "-o", str(d / "plans")], check=True)
 
-    def run(queries, constants=False, **knobs):
+    def run(queries, constants=False, prefill=False, **knobs):
         """(weight tiles, bands, wavefronts along N, K ranges, rows of a four-band expert tile, weight tiles of the streaming
         kernel, wavefronts of an fp32 column, whether M query rows of K dims (of bf16, with 'may split') with N
         keys go without splits, whether the norm of K columns goes with the N columns behind it,
@@ -44,6 +48,8 @@ def plans(tmp_path_factory):
         env.update({"DFLASH_" + k: str(v) for k, v in knobs.items()})
         if constants:
             env["CONSTANTS"] = "1"
+        if prefill:   # queries: (tiles, blocks, head groups, cached tokens, tokens of the longest context)
+            env["PREFILL"] = "1"
         out = subprocess.run([str(d / "plans")], input="\n".join(" ".join(str(int(x)) for x in q) for q in queries), env=env,
                              capture_output=True, text=True, check=True).stdout
         rows = [tuple(int(x) for x in line.split()) for line in out.splitlines()]
@@ -201,3 +207,20 @@ def test_argmax_of_stored_logits_is_one_launch_where_that_is_faster(plans):
     one = [(8, 512), (8, 2048), (2048, 2048), (128, 4096), (512, 4096), (512, 8192), (2048, 8192)]
     two = [(8, 2049), (8, 4096), (32, 4096), (8, 8192), (128, 8192), (2048, 8193)]
     assert [p[14] for p in plans([(m, n, 256, 0, m) for m, n in one + two])] == [1] * len(one) + [0] * len(two)
+
+
+def test_prefill_attention_goes_by_tiles_where_that_is_faster(plans):
+    """(prompts of n blocks each, head groups, block, cached tokens) as measured both ways, and the edges of the rule."""
+    def query(blocks, groups, block, cached):
+        return sum((n + 1) // 2 for n in blocks), sum(blocks), groups, cached, cached + (max(blocks) + 1) * block
+
+    tiles = [query([128], 8, 16, 0), query([64], 8, 16, 0), query([3, 6, 9, 13, 16, 20], 8, 16, 600), query([32], 32, 16, 0), query([256], 8, 8, 0),
+             query([8] * 16, 16, 16, 2000), query([150], 8, 10, 768)]
+    blocks = [query([22] * 6, 8, 16, 4000), query([11] * 12, 8, 16, 2652), query([20], 8, 16, 0), query([62], 8, 16, 0), query([125], 8, 16, 4000), query([8] * 32, 8, 8, 69),
+              query([43] * 3, 8, 16, 1618), query([150], 8, 10, 769), query([14] * 16, 8, 16, 0)]
+    assert [p[0] for p in plans(tiles + blocks, prefill=True)] == [1] * len(tiles) + [0] * len(blocks)
+    # longest contexts on both sides of the lines
+    assert [p[0] for p in plans([(128, 256, 8, 0, n) for n in (255, 256, 3072, 3073)], prefill=True)] == [0, 1, 1, 0]
+    # set by hand, the number of workgroups decides alone
+    assert [p[0] for p in plans(tiles + blocks, prefill=True, ATTN_TILE_WGS=1)] == [1] * (len(tiles) + len(blocks))
+    assert [p[0] for p in plans([(1, 2, 8, 0, 48), (2, 4, 8, 5000, 6000)], prefill=True, ATTN_TILE_WGS=16)] == [0, 1]
