@@ -252,7 +252,11 @@ inline StreamPlan stream_plan(const Knobs& kn, int M, int N, int K, bool split, 
     // steps and verifications 1008 and 992, 546 and 541, 582 and 574.  But three bands (4096 x 12288 22.0 and 20.8 by itself) 517.9 and 518.7 in a
     // verification, two 18.4 and 19.7, half the CUs (2048 x 2048, 64 rows) 5.8 and 6.6, unsplit 96-row blocks (24576 x 4096) 41.9 and 44.5.
     // (Not in a routed target's layers: another order of sums, as above.)
-    p.staged = four_first && split && M > 48 && p.nt == 8 && p.u == 1 && nt / 8 * p.ks >= 192;
+    // The staged launch deals whole blocks to the XCDs, the streaming one workgroups: where the blocks do not divide by eight, an XCD may get more
+    // workgroups than its 32 CUs a round.  20 blocks x 12 ranges (36 on most XCDs, none on one) with K = 3072 8.5 and 11.7 us at 64 rows, with 20480 26.0 and
+    // 40.3, 28 x 9 17.3 and 21.6; but 28 x 8 (32 each) 8.3 and 7.8, 40 x 6 20.8 and 18.4, 56 x 9 32.8 and 27.0.
+    const int wgs = nt / 8 * p.ks, of_xcd = (nt / 8 + 7) / 8 * p.ks;
+    p.staged = four_first && split && M > 48 && p.nt == 8 && p.u == 1 && wgs >= 192 && of_xcd <= (wgs + 255) / 256 * 32;
   }
   return p;
 }

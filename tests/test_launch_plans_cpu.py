@@ -202,6 +202,13 @@ def test_split_matrices_of_four_bands_go_by_staged_tiles(plans):
     assert [p[15] for p in plans([(m, n, k, sp, 64) for m, n, k, sp in staged + plain])] == [1] * len(staged) + [0] * len(plain)
 
 
+def test_staged_tiles_leave_no_xcd_a_round_more_than_the_others(plans):
+    """(height, K) at 64 rows as measured both ways: 20 and 28 blocks of 128 rows give most XCDs 36 workgroups, 28 x 8 and 40 x 6 at most 32, 56 x 9 two rounds."""
+    plain = [(2560, 3072), (2560, 8192), (2560, 20480), (3584, 2560), (3584, 8192), (3584, 20480)]
+    staged = [(3584, 2048), (5120, 1536), (5120, 8192), (7168, 1024), (7168, 2560), (7168, 16384), (8192, 1024), (8192, 8192)]
+    assert [p[15] for p in plans([(64, n, k, 1, 64) for n, k in plain + staged])] == [0] * len(plain) + [1] * len(staged)
+
+
 def test_argmax_of_stored_logits_is_one_launch_where_that_is_faster(plans):
     """(rows, columns) as measured both ways."""
     one = [(8, 512), (8, 2048), (2048, 2048), (128, 4096), (512, 4096), (512, 8192), (2048, 8192)]
