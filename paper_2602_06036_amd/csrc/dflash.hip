@@ -948,7 +948,7 @@ Engine<bf16_t>::Slab Engine<bf16_t>::gemm(const bf16_t* W, const bf16_t* A, int 
     }
   } else if (M > 64 && nt % 2 == 0) {
     // compute-bound: LDS-staged tiles
-    const TilePlan tp = tile_plan(c->k, M, N, K, split, arena);
+    const TilePlan tp = tile_plan(c->k, M, N, K, split, arena, routed);
     ks = tp.ks;
     ep.slab = (size_t)M * ep.ld;
     switch (tp.t->wy * 100 + tp.t->wn * 10 + tp.t->wm) {

@@ -141,21 +141,23 @@ struct TilePlan {
 };
 // Time of a launch = k tiles of a K range x cost of the workgroups on the busiest CU + the partial slabs (written by the
 // GEMM, read by its consumer).  XCDs take equal shares of the tiles, so the busiest CU has ceil(share / 32 CUs) workgroups.
-inline TilePlan tile_plan(const Knobs& kn, int M, int N, int K, bool split, int arena) {
+// `ranges`: 0 = the number of K ranges is free.
+template <size_t SHAPES>
+inline TilePlan cheapest_tiles(const TileShape (&shapes)[SHAPES], const Knobs& kn, int M, int N, int K, bool split, int arena, int ranges) {
   const int nt = N / 16, KT = K / 32;
   const bool forced = kn.gemm_tile || kn.gemm_wm || kn.gemm_ks;   // a forced four-wavefront shape stays forced
   auto fits = [&](int k) { return k == 1 || (split && KT / k >= 8 && k * M <= arena); };
-  const bool force_ks = kn.gemm_ks && split && fits(kn.gemm_ks);   // any number of ranges that fits
+  if (kn.gemm_ks && split && fits(kn.gemm_ks)) ranges = kn.gemm_ks;   // any number of ranges that fits
   TilePlan best;
   double best_t = 1e30;
-  for (const TileShape& t : kTiles) {
+  for (const TileShape& t : shapes) {
     const int nb = (nt + t.wy * t.wn - 1) / (t.wy * t.wn), mb = ((M + 15) / 16 + 2 * t.wm - 1) / (2 * t.wm);
     if (t.wy == 4 && kn.gemm_wide != 2 && (kn.gemm_wide != 1 || forced)) continue;
     if (kn.gemm_tile && kn.gemm_tile != t.wn) continue;
     if (kn.gemm_wm && kn.gemm_wm != t.wm) continue;
     const int tried[] = {1, 2, 3, 4, 6, 8};
-    for (int i = 0; i < (force_ks ? 1 : 6); ++i) {
-      const int k = force_ks ? kn.gemm_ks : tried[i];
+    for (int i = 0; i < (ranges ? 1 : 6); ++i) {
+      const int k = ranges ? ranges : tried[i];
       if (!fits(k)) continue;
       // a workgroup of eight wavefronts has its CU to itself: not for launches that leave many CUs without one.  Over the sweep that the
       // costs are fitted to any line up to 160 picks the same (0.74 % above the fastest shape on average), 192 loses 0.1 %, 224 0.7 %
@@ -171,10 +173,23 @@ inline TilePlan tile_plan(const Knobs& kn, int M, int N, int K, bool split, int 
     }
   }
   if (!best.t) {   // a knob that names no shape
-    best.t = &kTiles[2];
-    if (force_ks) best.ks = kn.gemm_ks;
+    best.t = &shapes[2];
+    if (ranges) best.ks = ranges;
   }
   return best;
+}
+
+// K ranges of a routed-expert target's layers: by costs of their own, which stay when the tiles' are fitted anew.  Another number of ranges is another order of
+// sums, which turns near-ties of the routers behind them into other experts, for targets of any width; whichever tiles then run add the products of a range in
+// the same order.  (The costs are those of the tiles of an earlier fit; by the present ones 31 of 348 shapes of a 2048-wide target get other ranges.)
+constexpr TileShape kRangeCosts[] = {
+    {8, 4, 2, 1.32f, 1.00f, 1.0f},   {6, 4, 2, 1.02f, 0.72f, 1.5f},  {4, 4, 2, 0.747f, 0.464f, 3.5f}, {8, 2, 2, 0.727f, 0.463f, 3.1f},
+    {6, 2, 2, 0.579f, 0.397f, 3.4f}, {4, 2, 2, 0.44f, 0.269f, 2.9f}, {6, 4, 4, 0.f, 1.00f, 1.5f},     {4, 4, 4, 0.f, 0.715f, 2.0f},
+    {6, 2, 4, 0.f, 0.562f, 2.5f},    {4, 2, 4, 0.f, 0.425f, 3.3f}};
+inline TilePlan tile_plan(const Knobs& kn, int M, int N, int K, bool split, int arena, bool routed = false) {
+  const bool forced = kn.gemm_tile || kn.gemm_wm || kn.gemm_ks;
+  const int ranges = routed && split && !forced ? cheapest_tiles(kRangeCosts, kn, M, N, K, split, arena, 0).ks : 0;
+  return cheapest_tiles(kTiles, kn, M, N, K, split, arena, ranges);
 }
 
 // K split across workgroups: aim at enough workgroups that every CU keeps several wavefronts streaming,

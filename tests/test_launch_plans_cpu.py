@@ -23,9 +23,10 @@ int main() {
   while (scanf("%d %d %d %d %d", &M, &N, &K, &split, &max_rows) == 5) {
     const TilePlan t = tile_plan(kn, M, N, K, split != 0, arena_rows(max_rows));
     const StreamPlan s = stream_plan(kn, M, N, K, split != 0, arena_rows(max_rows)), r = stream_plan(kn, M, N, K, split != 0, arena_rows(max_rows), false);
-    printf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d\n", t.t->wn, t.t->wm, t.t->wy, t.ks, half_height_expert_tiles(N / 16) ? 128 : 256, s.nt, split_f32_columns(N, K, !split) ? 4 : 1,
+    const TilePlan tr = tile_plan(kn, M, N, K, split != 0, arena_rows(max_rows), true);
+    printf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d\n", t.t->wn, t.t->wm, t.t->wy, t.ks, half_height_expert_tiles(N / 16) ? 128 : 256, s.nt, split_f32_columns(N, K, !split) ? 4 : 1,
            short_context(M, K, N, split != 0), fold_norm(M, K, N),
-           f32_groups_side_by_side((M + 7) / 8, (N + 3) / 4, (long long)N * K * 4), s.ks, stream_finishes(s), r.nt, r.ks, argmax_in_one_launch(M, N), s.staged + 2 * r.staged);
+           f32_groups_side_by_side((M + 7) / 8, (N + 3) / 4, (long long)N * K * 4), s.ks, stream_finishes(s), r.nt, r.ks, argmax_in_one_launch(M, N), s.staged + 2 * r.staged, tr.ks);
   }
 }
 """
@@ -43,7 +44,7 @@ def plans(tmp_path_factory):
         keys go without splits, whether the norm of K columns goes with the N columns behind it,
         whether groups of eight rows run side by side, K ranges of the streaming kernel, whether its launch may finish its sums,
         weight tiles and K ranges in a routed-expert target's layers, whether the argmax of M rows of N is one launch, whether the streaming plan goes by LDS-staged tiles (2: in a routed
-        target's layers)) for each (rows, height, K, may split, rows of the context)."""
+        target's layers), K ranges of the tiled kernel there) for each (rows, height, K, may split, rows of the context)."""
         env = {k: v for k, v in os.environ.items() if not k.startswith("DFLASH_")}
         env.update({"DFLASH_" + k: str(v) for k, v in knobs.items()})
         if constants:
@@ -116,11 +117,17 @@ def test_rolled_tiles_where_the_gpu_test_forces_them_and_over_many_rows(plans):
 
 
 def test_routed_layers_keep_their_k_ranges(plans):
-    """Another order of sums ahead of a router turns near-ties into other experts: QKV and O projection of the 2048-wide routed target."""
+    """Another order of sums ahead of a router turns near-ties into other experts: QKV and O projections and routers of targets of several widths, whatever the
+    costs of the tiles."""
     rows = (80, 128, 160, 200, 256, 288, 320, 384, 448, 512, 1024, 2048)
-    want = {(5120, 2048): [3, 3, 2, 3, 3, 2, 2, 1, 2, 2, 1, 1], (2048, 4096): [8, 8, 4, 4, 4, 3, 3, 4, 2, 2, 2, 2]}
+    want = {(5120, 2048): [3, 3, 2, 3, 3, 2, 2, 1, 2, 2, 1, 1], (2048, 4096): [8, 8, 4, 4, 4, 3, 3, 4, 2, 2, 2, 2],
+            (1280, 1024): [4, 4, 4, 4, 4, 4, 4, 3, 3, 3, 1, 1], (2560, 2560): [6, 6, 4, 3, 3, 2, 2, 2, 3, 3, 2, 1],
+            (4608, 4096): [3, 3, 4, 3, 3, 4, 4, 3, 2, 3, 1, 1], (8192, 5120): [4, 4, 3, 4, 2, 3, 3, 2, 2, 2, 1, 1],
+            (5120, 8192): [6, 6, 4, 3, 3, 4, 3, 4, 3, 3, 3, 1], (128, 4096): [8, 8, 6, 4, 4, 4, 4, 4, 4, 4, 4, 4]}
     for (n, k), ks in want.items():
-        assert [p[3] for p in plans([(m, n, k, 1, m) for m in rows])] == ks
+        assert [p[16] for p in plans([(m, n, k, 1, m) for m in rows])] == ks
+    # an unsplit launch, and a forced shape, as anywhere
+    assert plans([(512, 5120, 2048, 0, 512)])[0][16] == 1 and plans([(512, 5120, 2048, 1, 512)], GEMM_KS=3)[0][16] == 3
 
 
 def test_streaming_heads_take_the_weight_tiles_that_the_gpu_test_names(plans):
