@@ -824,7 +824,7 @@ struct Engine {
       check();
       const int q_shift = attn_q_shift(t, B);
       if (q_shift >= 0 && t.head_dim == 128 &&
-          attention_by_tiles(n_tiles, n, t.n_kv_heads << q_shift, b->max_seq_len + ahead, pb.max_seq_len + B, c->k.attn_tile_wgs))
+          attention_by_tiles(n_tiles, n, t.n_kv_heads << q_shift, b->max_seq_len + ahead, pb.max_seq_len + B, c->k.attn_tile_wgs, t.n_experts != 0))
         tiles = PrefillTiles{pp.tiles, n_tiles};
       int tap = 0;
       for (int l = 0; l < t.n_layers; ++l) {

@@ -17,7 +17,7 @@ int main() {
   const Knobs kn = read_knobs();
   if (getenv("CONSTANTS")) return printf("%d\n", kSsqAhead), 0;
   if (getenv("PREFILL")) {
-    while (scanf("%d %d %d %d %d", &M, &N, &K, &split, &max_rows) == 5) printf("%d\n", attention_by_tiles(M, N, K, split, max_rows, kn.attn_tile_wgs));
+    while (scanf("%d %d %d %d %d", &M, &N, &K, &split, &max_rows) == 5) printf("%d\n", attention_by_tiles(M, N, K, split, max_rows, kn.attn_tile_wgs) + 2 * attention_by_tiles(M, N, K, split, max_rows, kn.attn_tile_wgs, true));
     return 0;
   }
   while (scanf("%d %d %d %d %d", &M, &N, &K, &split, &max_rows) == 5) {
@@ -49,7 +49,7 @@ def plans(tmp_path_factory):
         env.update({"DFLASH_" + k: str(v) for k, v in knobs.items()})
         if constants:
             env["CONSTANTS"] = "1"
-        if prefill:   # queries: (tiles, blocks, head groups, cached tokens, tokens of the longest context)
+        if prefill:   # queries: (tiles, blocks, head groups, cached tokens, tokens of the longest context); 2: a routed target's goes by tiles
             env["PREFILL"] = "1"
         out = subprocess.run([str(d / "plans")], input="\n".join(" ".join(str(int(x)) for x in q) for q in queries), env=env,
                              capture_output=True, text=True, check=True).stdout
@@ -224,7 +224,8 @@ def test_argmax_of_stored_logits_is_one_launch_where_that_is_faster(plans):
 
 
 def test_prefill_attention_goes_by_tiles_where_that_is_faster(plans):
-    """(prompts of n blocks each, head groups, block, cached tokens) as measured both ways, and the edges of the rule."""
+    """(prompts of n blocks each, head groups, block, cached tokens) as measured both ways, and the edges of the rule.  A routed target's
+    keeps the order of its sums, whatever the knob."""
     def query(blocks, groups, block, cached):
         return sum((n + 1) // 2 for n in blocks), sum(blocks), groups, cached, cached + (max(blocks) + 1) * block
 
