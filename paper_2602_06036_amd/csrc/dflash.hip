@@ -1054,10 +1054,14 @@ Engine<bf16_t>::Slab Engine<bf16_t>::moe_ffn(const dflash_dims& m, const char* l
   // kernel's cross-wavefront sum takes a whole CU's LDS and its short sweeps (16 k tiles a wavefront) end in it.  512 rows, 8 of
   // 128 experts each (805 / 403 MB of matrices): gate/up 188 -> 175 us, down 96 -> 84 in the step; 177 -> 150 and 92 -> 87 as
   // isolated launches.
+  // The non-temporal hint on an item's weights keeps them out of the caches: not where the next item of the expert reads them again (moe_route_kernel
+  // says which, see gemm_tiled.h), nor where all layers' experts are small enough to be there still at the next call.  Two-layer verifications without and with
+  // it: 100 MB of experts, 133 rows 211 and 225 us, 128 rows 168 and 184; but 200 MB, 150 rows 274 and 264, 604 MB a layer, 512 rows 939 and 894.
+  const bool stream = ((long long)m.n_layers * E * Fe * D * 6 >> 10) > c->k.moe_kept_kb;
   {
     ProfScope prof(c, st, DFLASH_PROF_MOE_GATEUP, used * 2 * Fe * D * 2);
     EpiArgs ep{nullptr, 0, 0, act, Fe};
-    ep.grp_items = r.items; ep.grp_w_stride = (size_t)2 * Fe * D; ep.grp_rows = r.row_of;
+    ep.grp_items = r.items; ep.grp_w_stride = (size_t)2 * Fe * D; ep.grp_stream = stream; ep.grp_rows = r.row_of;
     if (gathered) ep.grp_rows = nullptr;
     const bf16_t* W = reinterpret_cast<const bf16_t*>(lbase + lo.wgu);
     if (MT == 8) {
@@ -1074,7 +1078,7 @@ Engine<bf16_t>::Slab Engine<bf16_t>::moe_ffn(const dflash_dims& m, const char* l
   {
     ProfScope prof(c, st, DFLASH_PROF_MOE_DOWN, used * Fe * D * 2);
     EpiArgs ep{y, D, 0, nullptr, 0};
-    ep.grp_items = r.items; ep.grp_w_stride = (size_t)D * Fe;
+    ep.grp_items = r.items; ep.grp_w_stride = (size_t)D * Fe; ep.grp_stream = stream;
     const bf16_t* W = reinterpret_cast<const bf16_t*>(lbase + lo.wd);
     // tuning knob: k tiles per prefetch stage of the one-band down projection.  Its K is short (6 k tiles per wavefront
     // at the 30B-A3B shape): one tile per stage leaves registers for four workgroups per CU, whose prologues and

@@ -33,12 +33,13 @@ struct EpiArgs {
   float2* lse = nullptr;
   float lse_inv_T = 1.f;
   // grouped launch (routed experts): a 1-D grid over (work item, column block); grp_items[item] = (expert, first band,
-  // end band, -) replaces the fixed band range; the workgroup multiplies those bands by the expert's matrix W + expert * grp_w_stride
+  // end band, whether it is the expert's only item) replaces the fixed band range; the workgroup multiplies those bands by the expert's matrix W + expert * grp_w_stride
   // (elements), an item with expert < 0 has nothing to do.  grp_rows (nullable) [bands * 16]: the activation row
   // behind each row of a band (the operand is then read through this list; < 0 = padding, any row will do).
   const int4* grp_items = nullptr;
   int grp_n_items = 0;
   size_t grp_w_stride = 0;
+  bool grp_stream = false;   // LDS-staged kernel: weights of an expert's only item with the non-temporal hint
   const int32_t* grp_rows = nullptr;
   // Deferred RMSNorm (streaming kernel only): the operand holds x * gain without the division by the row's rms; row m
   // of the result is multiplied by 1 / sqrt(sum_p ssq[m * ssq_row(ssq_parts) + p] * ssq_inv_D + ssq_eps) before any epilogue

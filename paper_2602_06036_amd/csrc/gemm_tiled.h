@@ -25,11 +25,14 @@
 // L2 and from LDS of all tiles, and the fastest over many rows: gate/up at 2048 rows 541 us (1.52 PFLOP/s issued) against 547 on 384 x 128
 // tiles and 563 on 256 x 128 tiles staged through registers, two workgroups a CU (the form before); down projection 276 against 290.
 //
-// STREAM: the weights are read past the caches' usual order of eviction (nt), so that the activations stay: for routed items, whose
-// weights are read once, and for the eight-wavefront tiles of few activation blocks, whose workgroups read a weight block at the same
-// time.  Two-layer verification of 512 routed rows 947 -> 917 us by the former, 907 by both; four-layer step of 256 rows 1585 -> 1546,
-// verification of 128 rows 768 -> 752, prefill of 1024 (eight blocks) 3008 -> 2985; but of 1088 (nine) 3572 -> 3607, of 2048 5605
-// -> 5630, and with the four-wavefront tiles' weights as well, verification of 128 routed rows 624 -> 632.
+// STREAM: the weights are read past the caches' usual order of eviction (nt), so that the activations stay: for the
+// eight-wavefront tiles of few activation blocks, whose workgroups read a weight block at the same time.  Four-layer step of 256 rows
+// 1585 -> 1546 us, verification of 128 rows 768 -> 752, prefill of 1024 (eight blocks) 3008 -> 2985; but of 1088 (nine) 3572 -> 3607, of 2048
+// 5605 -> 5630, and with the four-wavefront tiles' weights as well, verification of 128 routed rows 624 -> 632.
+// Grouped launches choose by the item: the weights of an expert's only item are read once, by anybody.  Two-layer verification of 512 routed
+// rows 939 -> 894.  Where an expert has several items they all read its weights, and the memory-side cache serves the later ones: two-layer prefills
+// of one prompt with the hint on every item and on the only ones, 1638 tokens of 64 experts of 1024 x 1024 860 and 818 us, four of 421 behind up to 1000 and 128
+// experts of 4096 x 1024 3691 and 3495, one of 1579 and 32 of 2048 x 512 478 and 452.
 //
 // Workgroup order: consecutive workgroup ids go to different XCDs (round-robin dispatch, id = 8*j + x), and the
 // workgroups that re-read one weight block run back to back on one XCD and share its L2.  Where the weight blocks divide
@@ -54,7 +57,7 @@ __device__ __forceinline__ void unroll_each(F& f, std::integer_sequence<int, I..
 template <int N, typename F>
 __device__ __forceinline__ void unroll(F f) { unroll_each(f, std::make_integer_sequence<int, N>{}); }
 
-template <int WN, int WM, int EPI, int NS, bool GRP = false, int WY = 2, bool STREAM = GRP>
+template <int WN, int WM, int EPI, int NS, bool GRP = false, int WY = 2, bool STREAM = false>
 __global__ __launch_bounds__(128 * WY, (tiled_waves<WN, WM, NS, WY>())) void gemm_bf16_tiled_kernel(
     const bf16_t* __restrict__ W, const bf16_t* __restrict__ A, int M, int N, int K, int n_blocks, int m_blocks, EpiArgs ep) {
   constexpr int NWV = 2 * WY;                       // wavefronts: WY along N x 2 along M
@@ -71,6 +74,7 @@ __global__ __launch_bounds__(128 * WY, (tiled_waves<WN, WM, NS, WY>())) void gem
   if ((n_blocks & 7) == 0) { nb = (j / m_blocks) * 8 + xcd; mb = j % m_blocks; }
   const int KT = K >> 5, n_tiles = N >> 4;
   int m_tiles = (M + 15) >> 4, mt0 = mb * BMT;
+  bool read_once = false;
   if constexpr (GRP) {
     // grouped launch (routed experts, see EpiArgs): m_blocks counts work items of up to BMT bands; the workgroups of
     // one item (its n_blocks weight blocks) run back to back on one XCD and share the item's activation rows there
@@ -82,6 +86,7 @@ __global__ __launch_bounds__(128 * WY, (tiled_waves<WN, WM, NS, WY>())) void gem
     W += (size_t)item.x * ep.grp_w_stride;
     mt0 = item.y;
     m_tiles = item.z;
+    read_once = item.w != 0 && ep.grp_stream;
   }
   if (nb >= n_blocks) return;                      // whole workgroup leaves before any barrier
   const int ks = gridDim.y, kz = blockIdx.y;
@@ -127,82 +132,93 @@ __global__ __launch_bounds__(128 * WY, (tiled_waves<WN, WM, NS, WY>())) void gem
     // m0 carries the LDS address; whatever the compiler keeps in it is put back, so the statement clobbers nothing
 #define DF_COPY(hint)                                                                                                                    \
   asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3" hint "\n\ts_nop 0\n\ts_mov_b32 m0, %0" \
-               : "=&s"(keep_m0) : "s"(dst), "v"(voff), "s"(src[i]) : "memory")
-    auto dma = [&](int i, int slot) {
-      const unsigned dst = __builtin_amdgcn_readfirstlane(lds_base + (unsigned)((slot * FR + fragment(i)) * 1024));
-      unsigned keep_m0;
-      if (STREAM && i < PW) DF_COPY(" nt");
-      else DF_COPY("");
-    };
-#undef DF_COPY
-    for (int d = 0; d < NS; ++d) {
+               : "=&s"(keep_m0) : "s"(dst), "v"(at_lane), "s"(from) : "memory")
+    auto sweep = [&](auto hint_c) __attribute__((always_inline)) {
+      constexpr bool HINT = decltype(hint_c)::value;
+      auto dma = [&](int i, int slot) {
+        const unsigned dst = __builtin_amdgcn_readfirstlane(lds_base + (unsigned)((slot * FR + fragment(i)) * 1024));
+        const unsigned at_lane = voff;
+        const char* from = src[i];
+        unsigned keep_m0;
+        if (HINT && i < PW) DF_COPY(" nt");
+        else DF_COPY("");
+      };
+      for (int d = 0; d < NS; ++d) {
 #pragma unroll
-      for (int i = 0; i < PER; ++i) dma(i, d);
-      advance();
-    }
-    auto w_at = [&](int sl, int i) { return stage[sl][wy * WN + i][lane]; };
-    auto a_at = [&](int sl, int jj, int p) { return stage[sl][BNT + 2 * (wx * WM + jj) + p][lane]; };
-    // the next k tile's copies of this wavefront have landed, its reads of the one before are done
-    auto seam = [&]() {
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER * (NS - 2)) : "memory");
-      __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
+        for (int i = 0; i < PER; ++i) dma(i, d);
+        advance();
+      }
+      auto w_at = [&](int sl, int i) { return stage[sl][wy * WN + i][lane]; };
+      auto a_at = [&](int sl, int jj, int p) { return stage[sl][BNT + 2 * (wx * WM + jj) + p][lane]; };
+      // the next k tile's copies of this wavefront have landed, its reads of the one before are done
+      auto seam = [&]() {
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER * (NS - 2)) : "memory");
+        __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      constexpr bool ROLL = tiled_rolls<WN, WM>();
+      u32x4 wf[2][WN], ap[2][ROLL ? 1 : WM][2];
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER * (NS - 1)) : "memory");
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    constexpr bool ROLL = tiled_rolls<WN, WM>();
-    u32x4 wf[2][WN], ap[2][ROLL ? 1 : WM][2];
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER * (NS - 1)) : "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
 #pragma unroll
-    for (int i = 0; i < WN; ++i) wf[0][i] = w_at(0, i);
+      for (int i = 0; i < WN; ++i) wf[0][i] = w_at(0, i);
 #pragma unroll
-    for (int jj = 0; jj < (ROLL ? 1 : WM); ++jj)
+      for (int jj = 0; jj < (ROLL ? 1 : WM); ++jj)
 #pragma unroll
-      for (int p = 0; p < 2; ++p) ap[0][jj][p] = a_at(0, jj, p);
-    int slot = 0;
-    // K tile t.  MFMA number q (band, then plane, then weight tile) is followed by at most a few of the loads that are due meanwhile,
-    // pinned there: in a burst ahead of the MFMAs they kept the matrix cores idle for a sixth of the k tile.
-    auto k_tile = [&](auto cur_c) {
-      constexpr int C = decltype(cur_c)::value;
-      const int next = slot == NS - 1 ? 0 : slot + 1;
-      constexpr int RD = WN + (ROLL ? 2 : 2 * WM), ITEMS = RD + PER;   // the next k tile's fragments, then the refill of this one's slot
-      auto item = [&](auto qc) {
-        constexpr int q = decltype(qc)::value;
-        // past the end of the K range: a landed copy of the last k tile, not used
-        if constexpr (q < 1) ap[ROLL ? 0 : C ^ 1][0][0] = a_at(next, 0, 0);
-        else if constexpr (q < 1 + WN) wf[C ^ 1][q - 1] = w_at(next, q - 1);
-        else if constexpr (q < RD) ap[ROLL ? 0 : C ^ 1][ROLL ? 0 : (q - WN) / 2][(q - WN) & 1] = a_at(next, (q - WN) / 2, (q - WN) & 1);
-        else if constexpr (q < ITEMS) dma(q - RD, slot);
+        for (int p = 0; p < 2; ++p) ap[0][jj][p] = a_at(0, jj, p);
+      int slot = 0;
+      // K tile t.  MFMA number q (band, then plane, then weight tile) is followed by at most a few of the loads that are due meanwhile,
+      // pinned there: in a burst ahead of the MFMAs they kept the matrix cores idle for a sixth of the k tile.
+      auto k_tile = [&](auto cur_c) {
+        constexpr int C = decltype(cur_c)::value;
+        const int next = slot == NS - 1 ? 0 : slot + 1;
+        constexpr int RD = WN + (ROLL ? 2 : 2 * WM), ITEMS = RD + PER;   // the next k tile's fragments, then the refill of this one's slot
+        auto item = [&](auto qc) {
+          constexpr int q = decltype(qc)::value;
+          // past the end of the K range: a landed copy of the last k tile, not used
+          if constexpr (q < 1) ap[ROLL ? 0 : C ^ 1][0][0] = a_at(next, 0, 0);
+          else if constexpr (q < 1 + WN) wf[C ^ 1][q - 1] = w_at(next, q - 1);
+          else if constexpr (q < RD) ap[ROLL ? 0 : C ^ 1][ROLL ? 0 : (q - WN) / 2][(q - WN) & 1] = a_at(next, (q - WN) / 2, (q - WN) & 1);
+          else if constexpr (q < ITEMS) dma(q - RD, slot);
+        };
+        if constexpr (!ROLL) seam();
+        unroll<2 * WN * WM>([&](auto mc) {
+          constexpr int m = decltype(mc)::value, jj = m / (2 * WN), p = (m / WN) & 1, i = m % WN, at = m % (2 * WN);
+          if constexpr (ROLL && jj == WM - 1 && at == 0) seam();   // this k tile is in registers from here on
+          const u32x4 a = ROLL ? ap[jj & 1][0][p] : ap[C][ROLL ? 0 : jj][p];
+          acc[i][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf[C][i]), __builtin_bit_cast(bf16x8, a), acc[i][jj], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+          if constexpr (!ROLL) {
+            item(mc);
+            static_assert(ITEMS <= 2 * WN * WM, "an item behind each MFMA");
+          } else if constexpr (jj < WM - 1) {
+            if constexpr (at < 2) ap[(jj + 1) & 1][0][at] = a_at(slot, jj + 1, at);   // the next band
+          } else {
+            constexpr int EACH = (ITEMS + 2 * WN - 1) / (2 * WN);
+            unroll<EACH>([&](auto ec) { item(std::integral_constant<int, at * EACH + decltype(ec)::value>{}); });
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        });
+        advance();
+        slot = next;
       };
-      if constexpr (!ROLL) seam();
-      unroll<2 * WN * WM>([&](auto mc) {
-        constexpr int m = decltype(mc)::value, jj = m / (2 * WN), p = (m / WN) & 1, i = m % WN, at = m % (2 * WN);
-        if constexpr (ROLL && jj == WM - 1 && at == 0) seam();   // this k tile is in registers from here on
-        const u32x4 a = ROLL ? ap[jj & 1][0][p] : ap[C][ROLL ? 0 : jj][p];
-        acc[i][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf[C][i]), __builtin_bit_cast(bf16x8, a), acc[i][jj], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (!ROLL) {
-          item(mc);
-          static_assert(ITEMS <= 2 * WN * WM, "an item behind each MFMA");
-        } else if constexpr (jj < WM - 1) {
-          if constexpr (at < 2) ap[(jj + 1) & 1][0][at] = a_at(slot, jj + 1, at);   // the next band
-        } else {
-          constexpr int EACH = (ITEMS + 2 * WN - 1) / (2 * WN);
-          unroll<EACH>([&](auto ec) { item(std::integral_constant<int, at * EACH + decltype(ec)::value>{}); });
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      });
-      advance();
-      slot = next;
+      int kt = kb;
+      for (; kt + 1 < ke; kt += 2) {
+        k_tile(std::integral_constant<int, 0>{});
+        k_tile(std::integral_constant<int, 1>{});
+      }
+      if (kt < ke) k_tile(std::integral_constant<int, 0>{});
     };
-    int kt = kb;
-    for (; kt + 1 < ke; kt += 2) {
-      k_tile(std::integral_constant<int, 0>{});
-      k_tile(std::integral_constant<int, 1>{});
+#undef DF_COPY
+    if constexpr (GRP) {
+      if (read_once) sweep(std::true_type{});
+      else sweep(std::false_type{});
+    } else {
+      sweep(std::integral_constant<bool, STREAM>{});
     }
-    if (kt < ke) k_tile(std::integral_constant<int, 0>{});
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // nothing may still be on its way into LDS when the slots are reused or released
   }
 

@@ -24,7 +24,7 @@ struct MoeRoute {
   float* sel_w;          // [M * k] their weights
   int32_t* sel_pos;      // [M * k] row of the expert-sorted list that holds (t, j)
   int32_t* row_of;       // [n_pos_max] expert-sorted list: token row behind each position, -1 = padding
-  int4* items;           // [max_items] (expert, first band, end band, 0), expert = -1: unused
+  int4* items;           // [max_items] (expert, first band, end band, 1 = the expert's only item), expert = -1: unused
   int max_items;
   unsigned long long* counters;   // [5] running totals: routing launches, experts reached, 16-row bands, work items; [4] = bands per work item of the last launch (statistics)
   int32_t* n_bands_out;           // [1] bands of the list this launch built
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(1024) void moe_route_kernel(MoeRoute a) {
   if (tid < a.E && tot[tid] > 0) {
     const int b0 = base[tid] >> 4, nb = (tot[tid] + 15) >> 4;
     for (int q = 0; q * a.MT < nb; ++q)
-      if (item0[tid] + q < a.max_items) a.items[item0[tid] + q] = make_int4(tid, b0 + q * a.MT, min(b0 + (q + 1) * a.MT, b0 + nb), 0);
+      if (item0[tid] + q < a.max_items) a.items[item0[tid] + q] = make_int4(tid, b0 + q * a.MT, min(b0 + (q + 1) * a.MT, b0 + nb), nb <= a.MT);
     for (int p = base[tid] + tot[tid]; p < base[tid] + nb * 16; ++p) a.row_of[p] = -1;
   }
   for (int i = n_items + tid; i < a.max_items; i += 1024) a.items[i] = make_int4(-1, 0, 0, 0);

@@ -32,6 +32,7 @@ struct Knobs {
   int lm_stats;             // DFLASH_LM_STATS: 1 = softmax statistics from the LM-head epilogue, other = from the stored logits
   int moe_mt;               // DFLASH_MOE_MT: 1, 2, 4 or 8 forces the bands per routed-expert work item (0 = by rows per expert)
   int moe_gather_min_rows;  // DFLASH_MOE_GATHER_MIN_ROWS: rows from which the routed-expert GEMMs get their rows copied into list order
+  int moe_kept_kb;          // DFLASH_MOE_KEPT_KB: a target's expert matrices up to this size are taken to stay in the memory-side cache
   int moe_down_u;           // DFLASH_MOE_DOWN_U: k tiles per stage of the one-band down projection
   int fuse;                 // DFLASH_FUSE: few-row path, see dflash_ctx::fuse
   int resid_nw, resid_u;    // DFLASH_RESID_NW / _U: wavefronts per workgroup and k tiles per stage of the unsplit projection kernel
@@ -54,6 +55,7 @@ inline Knobs read_knobs() {
   k.lm_stats = env_int("DFLASH_LM_STATS", 1);
   k.moe_mt = env_int("DFLASH_MOE_MT", 0);
   k.moe_gather_min_rows = env_int("DFLASH_MOE_GATHER_MIN_ROWS", 64);
+  k.moe_kept_kb = env_int("DFLASH_MOE_KEPT_KB", 128 << 10);
   k.moe_down_u = env_int("DFLASH_MOE_DOWN_U", 1);
   k.fuse = env_int("DFLASH_FUSE", 1);
   if (k.fuse != 1 && k.fuse != 2) k.fuse = 0;

@@ -422,6 +422,31 @@ def test_plain_attention_on_both_sides_of_its_row_limit(dtype, hd, n_seqs, lens)
     assert ls.stats["reseeds"] <= 1
 
 
+@pytest.mark.parametrize("mt,d_expert,n_seqs", [(4, 256, 14), (4, 320, 14), (8, 192, 30), (8, 256, 30)])
+def test_routed_items_with_and_without_the_hint_on_their_weights(mt, d_expert, n_seqs, monkeypatch):
+    """Experts with one item and with several in the same launches, 256- and 128-row tiles of four bands and both heights of eight: the same bits whether or not
+    the weights of single items are read with the non-temporal hint."""
+    import torch
+    _gpu()
+    import paper_2602_06036_amd as dfl
+    from tests.gpu_harness import GpuModel
+    monkeypatch.setenv("DFLASH_MOE_MT", str(mt))
+    w = si.small_moe_workload(n_seqs=n_seqs, ctx_min=12, ctx_max=40, seed=mt + d_expert, n_experts=16, top_k=4, d_expert=d_expert)
+    wts, blobs, got = si.make_weights(w), None, []
+    tokens = torch.from_numpy(np.random.default_rng(2).integers(0, 255, (n_seqs, w.block_size)).astype(np.int32)).cuda()
+    for kept in ("131072", "1"):
+        monkeypatch.setenv("DFLASH_MOE_KEPT_KB", kept)
+        g = GpuModel(w, *wts, 64, blobs=blobs)
+        blobs = g.blobs()
+        g.e.moe_stats()
+        dfl.dflash_verify(g.e, g.batch(), tokens, None, g.logits_t)
+        g.e.device_status()
+        got.append(g.logits_t.cpu().numpy().copy())
+        launches, reached, bands, items, per_item = g.e.moe_stats()
+        assert per_item == mt and reached < items < 2 * reached, (launches, reached, bands, items)
+    assert np.isfinite(got[0]).all() and np.array_equal(got[0], got[1])
+
+
 @pytest.mark.parametrize("fuse", [1, 2])
 def test_deferred_norms_use_the_eps_of_their_own_model(fuse, monkeypatch):
     """A target with an eps of 1e-6 and a draft with one of 5e-3, more than ten times the mean square of an embedding row (4e-4), over one band of rows: any norm
