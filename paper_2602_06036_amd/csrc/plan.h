@@ -127,9 +127,10 @@ constexpr int kSsqAhead = 512;
 // side (four-wavefront tiles), `one` with a workgroup by itself; `fixed` per round of workgroups (ramp, prologue, epilogue).
 // Fitted to launches back to back over random operands (16 row counts from 80 to 2048, ten matrices of 2048 to 28672 rows
 // with K of 2048 to 12288, one to eight K ranges); the shape picked with them is on average 1.0 % slower than the fastest one (2.1 %
-// before the loads went between the MFMAs and the 512 x 128 tiles came).  Fitted without a condition 0.5 %, but then QKV and O projection of the
-// 2048-wide routed target get other K ranges at 258 to 448 rows, and its router's near-ties other experts.  256 x 128 tiles of four wavefronts
-// (8, 4, 2) are the slowest everywhere (gate/up at 2048 rows 743 us against 541); only the tests force them.
+// before the loads went between the MFMAs and the 512 x 128 tiles came).  A fit that comes within 0.5 % of the fastest launches does not make the faster
+// passes: step of 16 sequences 1489 us with these costs and 1510 with it, verification of 11 sequences 899 and 919, of 8 728 and 722, of 20 1231 and
+// 1228, prefills even.  256 x 128 tiles of four wavefronts (8, 4, 2) are the slowest everywhere (gate/up at 2048 rows 743 us against
+// 541); only the tests force them.
 struct TileShape {
   int wn, wm, wy;      // weight tiles and activation bands per wavefront, wavefronts along N
   float two, one, fixed;
