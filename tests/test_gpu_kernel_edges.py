@@ -21,6 +21,7 @@ pytestmark = pytest.mark.gpu
     (300, 2, 1040, 1.0, 0),     # many sequences: few chunks
     (1, 16, 151936, 1.0, 0),
     (256, 16, 64, 1.0, 0),      # the most rows the entry point takes
+    (1, 2, 164096, 1.0, 0),     # eight columns a piece behind a whole round
 ])
 def test_sampled_acceptance_on_held_logits(S, B, V, T, shift):
     """dflash_accept_sampled_noalloc against the oracle's acceptance rule, with masked (-inf) columns and, for some
