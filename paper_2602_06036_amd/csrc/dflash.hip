@@ -888,7 +888,7 @@ void launch_bf16(hipStream_t st, const bf16_t* W, const bf16_t* A, int M, int N,
 
 // FEW: a single activation block, which reads the weights once
 template <int WN, int WM, int NS, int WY = 2, bool FEW = false>
-void launch_tiled(hipStream_t st, const bf16_t* W, const bf16_t* A, int M, int N, int K, int epi, EpiArgs ep, int ks) {
+void launch_tiled(hipStream_t st, const bf16_t* W, const bf16_t* A, int M, int N, int K, int epi, EpiArgs ep, int ks, bool routed = false) {
   const int n_blocks = (N / 16 + WY * WN - 1) / (WY * WN), m_blocks = ((M + 15) / 16 + 2 * WM - 1) / (2 * WM);
   const dim3 grid((n_blocks * m_blocks + 7) / 8 * 8, ks), block(128 * WY);
   g_launch_parts = n_blocks;
@@ -901,7 +901,7 @@ void launch_tiled(hipStream_t st, const bf16_t* W, const bf16_t* A, int M, int N
       hipLaunchKernelGGL((gemm_bf16_tiled_kernel<WN, WM, EPI_STORE, NS, false, WY, STREAM>), grid, block, 0, st, W, A, M, N, K, n_blocks, m_blocks, ep);
   };
   if constexpr (WY == 4) {
-    if (m_blocks <= 8) return go(std::true_type{});
+    if (stream_weights(n_blocks, m_blocks, routed)) return go(std::true_type{});
   }
   go(std::integral_constant<bool, FEW>{});
 }
@@ -958,11 +958,11 @@ Engine<bf16_t>::Slab Engine<bf16_t>::gemm(const bf16_t* W, const bf16_t* A, int 
       case 282: launch_tiled<8, 2, 3>(st, W, A, M, N, K, kepi, ep, ks); break;
       case 262: launch_tiled<6, 2, 3>(st, W, A, M, N, K, kepi, ep, ks); break;
       case 242: launch_tiled<4, 2, 4>(st, W, A, M, N, K, kepi, ep, ks); break;
-      case 484: launch_tiled<8, 4, 3, 4>(st, W, A, M, N, K, kepi, ep, ks); break;
-      case 464: launch_tiled<6, 4, 3, 4>(st, W, A, M, N, K, kepi, ep, ks); break;
-      case 444: launch_tiled<4, 4, 4, 4>(st, W, A, M, N, K, kepi, ep, ks); break;
-      case 462: launch_tiled<6, 2, 4, 4>(st, W, A, M, N, K, kepi, ep, ks); break;
-      default: launch_tiled<4, 2, 4, 4>(st, W, A, M, N, K, kepi, ep, ks); break;
+      case 484: launch_tiled<8, 4, 3, 4>(st, W, A, M, N, K, kepi, ep, ks, routed); break;
+      case 464: launch_tiled<6, 4, 3, 4>(st, W, A, M, N, K, kepi, ep, ks, routed); break;
+      case 444: launch_tiled<4, 4, 4, 4>(st, W, A, M, N, K, kepi, ep, ks, routed); break;
+      case 462: launch_tiled<6, 2, 4, 4>(st, W, A, M, N, K, kepi, ep, ks, routed); break;
+      default: launch_tiled<4, 2, 4, 4>(st, W, A, M, N, K, kepi, ep, ks, routed); break;
     }
   } else {
     const int my = ((M + 15) / 16 + 3) / 4;

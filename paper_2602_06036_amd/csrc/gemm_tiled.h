@@ -26,9 +26,9 @@
 // tiles and 563 on 256 x 128 tiles staged through registers, two workgroups a CU (the form before); down projection 276 against 290.
 //
 // STREAM: the weights are read past the caches' usual order of eviction (nt), so that the activations stay: for the
-// eight-wavefront tiles of few activation blocks, whose workgroups read a weight block at the same time.  Four-layer step of 256 rows
-// 1585 -> 1546 us, verification of 128 rows 768 -> 752, prefill of 1024 (eight blocks) 3008 -> 2985; but of 1088 (nine) 3572 -> 3607, of 2048
-// 5605 -> 5630, and with the four-wavefront tiles' weights as well, verification of 128 routed rows 624 -> 632.
+// eight-wavefront tiles of few activation blocks, whose workgroups read a weight block at the same time (stream_weights in plan.h).  Prefill of
+// 1024 (eight blocks) 3008 -> 2985 us; but of 1088 (nine) 3572 -> 3607, of 2048 5605 -> 5630, and with the four-wavefront tiles' weights
+// as well, verification of 128 routed rows 624 -> 632.
 // Grouped launches choose by the item: the weights of an expert's only item are read once, by anybody.  Two-layer verification of 512 routed
 // rows 939 -> 894.  Where an expert has several items they all read its weights, and the memory-side cache serves the later ones: two-layer prefills
 // of one prompt with the hint on every item and on the only ones, 1638 tokens of 64 experts of 1024 x 1024 860 and 818 us, four of 421 behind up to 1000 and 128

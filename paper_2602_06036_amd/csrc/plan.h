@@ -197,6 +197,13 @@ inline TilePlan tile_plan(const Knobs& kn, int M, int N, int K, bool split, int 
   return cheapest_tiles(kTiles, kn, M, N, K, split, arena, ranges);
 }
 
+// Whether the eight-wavefront tiles read the weights with the non-temporal hint (STREAM in gemm_tiled.h): few activation blocks, and weight blocks that
+// divide by the XCDs.  Where they do not, a block's workgroups may sit on two XCDs, which then both fetch it past the memory-side cache.  Six-layer verifications
+// with and without it there: 140 rows of a 5120-wide model of FFN 14080 1610 and 1500 us, 135 of 3584 and 9856 1114 and 1032, 224 of 3072 and 8448 1060 and
+// 1028.  Where they do: four-layer step of 256 rows at the 8B shape 1517 and 1530, verification of 176 901 and 924, 512 rows even.  In a routed target's layers the
+// hint pays either way: what follows reads hundreds of megabytes of experts past the caches (two layers of 512 rows 889 and 905 us, deeper ones even).
+inline bool stream_weights(int n_blocks, int m_blocks, bool routed) { return m_blocks <= 8 && (n_blocks % 8 == 0 || routed); }
+
 // K split across workgroups: aim at enough workgroups that every CU keeps several wavefronts streaming,
 // keep at least 2 k-tiles per wavefront, and stay inside the arena.
 inline int pick_ksplit(int n_blocks, int KT, int M, int arena, int target) {

@@ -24,9 +24,9 @@ int main() {
     const TilePlan t = tile_plan(kn, M, N, K, split != 0, arena_rows(max_rows));
     const StreamPlan s = stream_plan(kn, M, N, K, split != 0, arena_rows(max_rows)), r = stream_plan(kn, M, N, K, split != 0, arena_rows(max_rows), false);
     const TilePlan tr = tile_plan(kn, M, N, K, split != 0, arena_rows(max_rows), true);
-    printf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d\n", t.t->wn, t.t->wm, t.t->wy, t.ks, half_height_expert_tiles(N / 16) ? 128 : 256, s.nt, split_f32_columns(N, K, !split) ? 4 : 1,
+    printf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d\n", t.t->wn, t.t->wm, t.t->wy, t.ks, half_height_expert_tiles(N / 16) ? 128 : 256, s.nt, split_f32_columns(N, K, !split) ? 4 : 1,
            short_context(M, K, N, split != 0), fold_norm(M, K, N),
-           f32_groups_side_by_side((M + 7) / 8, (N + 3) / 4, (long long)N * K * 4), s.ks, stream_finishes(s), r.nt, r.ks, argmax_in_one_launch(M, N), s.staged + 2 * r.staged, tr.ks);
+           f32_groups_side_by_side((M + 7) / 8, (N + 3) / 4, (long long)N * K * 4), s.ks, stream_finishes(s), r.nt, r.ks, argmax_in_one_launch(M, N), s.staged + 2 * r.staged, tr.ks, stream_weights(N, M, split != 0));
   }
 }
 """
@@ -44,7 +44,8 @@ def plans(tmp_path_factory):
         keys go without splits, whether the norm of K columns goes with the N columns behind it,
         whether groups of eight rows run side by side, K ranges of the streaming kernel, whether its launch may finish its sums,
         weight tiles and K ranges in a routed-expert target's layers, whether the argmax of M rows of N is one launch, whether the streaming plan goes by LDS-staged tiles (2: in a routed
-        target's layers), K ranges of the tiled kernel there) for each (rows, height, K, may split, rows of the context)."""
+        target's layers), K ranges of the tiled kernel there, whether M activation and N weight blocks (of a
+        routed target, with 'may split') read the weights with the hint) for each (rows, height, K, may split, rows of the context)."""
         env = {k: v for k, v in os.environ.items() if not k.startswith("DFLASH_")}
         env.update({"DFLASH_" + k: str(v) for k, v in knobs.items()})
         if constants:
@@ -239,3 +240,10 @@ def test_prefill_attention_goes_by_tiles_where_that_is_faster(plans):
     # set by hand, the number of workgroups decides alone
     assert [p[0] for p in plans(tiles + blocks, prefill=True, ATTN_TILE_WGS=1)] == [1] * (len(tiles) + len(blocks))
     assert [p[0] for p in plans([(1, 2, 8, 0, 48), (2, 4, 8, 5000, 6000)], prefill=True, ATTN_TILE_WGS=16)] == [0, 1]
+
+
+def test_weights_carry_the_hint_where_their_blocks_divide_by_the_xcds(plans):
+    """(activation blocks, weight blocks, routed)."""
+    hint = [(1, 16, 0), (8, 64, 0), (2, 20, 1), (8, 12, 1)]
+    none = [(9, 64, 0), (2, 20, 0), (3, 67, 0), (8, 12, 0), (9, 20, 1)]
+    assert [p[17] for p in plans([(m, n, 256, r, 64) for m, n, r in hint + none])] == [1] * len(hint) + [0] * len(none)
