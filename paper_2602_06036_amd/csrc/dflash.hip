@@ -886,7 +886,7 @@ void launch_bf16(hipStream_t st, const bf16_t* W, const bf16_t* A, int M, int N,
   }
 }
 
-// FEW: a single activation block, which reads the weights once
+// FEW: a single activation block of a split matrix, which reads the weights once
 template <int WN, int WM, int NS, int WY = 2, bool FEW = false>
 void launch_tiled(hipStream_t st, const bf16_t* W, const bf16_t* A, int M, int N, int K, int epi, EpiArgs ep, int ks, bool routed = false) {
   const int n_blocks = (N / 16 + WY * WN - 1) / (WY * WN), m_blocks = ((M + 15) / 16 + 2 * WM - 1) / (2 * WM);
@@ -895,10 +895,12 @@ void launch_tiled(hipStream_t st, const bf16_t* W, const bf16_t* A, int M, int N
   g_launch_kind = WY == 4 ? DFLASH_GEMM_TILED8 : DFLASH_GEMM_TILED4;
   auto go = [&](auto sc) {
     constexpr bool STREAM = decltype(sc)::value;
-    if (epi == EPI_SWIGLU)
-      hipLaunchKernelGGL((gemm_bf16_tiled_kernel<WN, WM, EPI_SWIGLU, NS, false, WY, STREAM>), grid, block, 0, st, W, A, M, N, K, n_blocks, m_blocks, ep);
-    else
-      hipLaunchKernelGGL((gemm_bf16_tiled_kernel<WN, WM, EPI_STORE, NS, false, WY, STREAM>), grid, block, 0, st, W, A, M, N, K, n_blocks, m_blocks, ep);
+    if constexpr (!FEW)
+      if (epi == EPI_SWIGLU) {
+        hipLaunchKernelGGL((gemm_bf16_tiled_kernel<WN, WM, EPI_SWIGLU, NS, false, WY, STREAM>), grid, block, 0, st, W, A, M, N, K, n_blocks, m_blocks, ep);
+        return;
+      }
+    hipLaunchKernelGGL((gemm_bf16_tiled_kernel<WN, WM, EPI_STORE, NS, false, WY, STREAM>), grid, block, 0, st, W, A, M, N, K, n_blocks, m_blocks, ep);
   };
   if constexpr (WY == 4) {
     if (stream_weights(n_blocks, m_blocks, routed)) return go(std::true_type{});
@@ -952,7 +954,6 @@ Engine<bf16_t>::Slab Engine<bf16_t>::gemm(const bf16_t* W, const bf16_t* A, int 
     ks = tp.ks;
     ep.slab = (size_t)M * ep.ld;
     switch (tp.t->wy * 100 + tp.t->wn * 10 + tp.t->wm) {
-      case 284: launch_tiled<8, 4, 3>(st, W, A, M, N, K, kepi, ep, ks); break;
       case 264: launch_tiled<6, 4, 2>(st, W, A, M, N, K, kepi, ep, ks); break;
       case 244: launch_tiled<4, 4, 3>(st, W, A, M, N, K, kepi, ep, ks); break;
       case 282: launch_tiled<8, 2, 3>(st, W, A, M, N, K, kepi, ep, ks); break;

@@ -33,7 +33,8 @@ def tiny_workload(seed=0, n_layers=2, draft_layers=1, vocab=1024, block=8, qk_no
 
 
 # Forced shapes of the LDS-staged GEMM over row counts and heights that leave tiles, activation blocks and the XCDs' shares ragged:
-# (sequences of 16 rows, FFN width, vocabulary, DFLASH_GEMM_WIDE, _TILE, _WM, _KS).  Rows of the model: d_model 256, QKV 512.
+# (sequences of 16 rows, FFN width, vocabulary, DFLASH_GEMM_WIDE, _TILE, _WM, _KS).  Rows of the model: d_model 256, QKV 512.  The first two name no shape of four
+# wavefronts and get 128 x 128 tiles.
 TILE_EDGES = [
     (5, 1056, 1056, 1, 8, 4, 3), (9, 2112, 2080, 1, 8, 4, 0),
     (17, 1312, 2080, 1, 6, 4, 0), (5, 2112, 1056, 1, 6, 4, 6),

@@ -66,8 +66,9 @@ def test_forced_k_split_is_taken_whatever_its_value(plans):
     q = (80, 4096, 4096, 1, 400)          # 128 k tiles, room for 1600 rows of slabs
     for ks in range(1, 17):
         assert plans([q], GEMM_KS=ks)[0][3] == ks
-        for wn, wm in ((8, 4), (6, 4), (4, 4), (8, 2), (6, 2), (4, 2)):
+        for wn, wm in ((6, 4), (4, 4), (8, 2), (6, 2), (4, 2)):
             assert plans([q], GEMM_KS=ks, GEMM_TILE=wn, GEMM_WM=wm)[0][:4] == (wn, wm, 2, ks)
+        assert plans([q], GEMM_KS=ks, GEMM_TILE=8, GEMM_WM=4)[0][:4] == (4, 4, 2, ks)   # no shape of four wavefronts
     assert plans([q], GEMM_KS=17)[0][3] in (1, 2, 3, 4, 6, 8)           # seven k tiles a range
     assert plans([(80, 4096, 4096, 0, 400)], GEMM_KS=5)[0][3] == 1
     assert plans([(400, 4096, 4096, 1, 400)], GEMM_KS=5)[0][3] in (1, 2, 3, 4)   # 2000 rows of slabs, room for 1600
@@ -90,7 +91,7 @@ def test_forced_tiles_cover_ragged_geometries(plans):
         M = 16 * n_seqs
         mats = [(M, 512, 256, 1, M), (M, 256, 256, 1, M), (M, 2 * ffn, 256, 0, M), (M, 256, ffn, 1, M), (M, vocab, 256, 0, M)]
         for (_, N, K, split, _), (wn, bm, wy, k, *_) in zip(mats, plans(mats, GEMM_WIDE=wide, GEMM_TILE=tile, GEMM_WM=wm, GEMM_KS=ks)):
-            assert (wn, bm, wy) == (tile, wm, 2 * wide)
+            assert (wn, bm, wy) == ((tile, wm, 2 * wide) if (tile, wm, wide) != (8, 4, 1) else (4, 4, 2))
             nb, mb = -(-N // 16 // (wy * wn)), -(-n_seqs // (2 * wm))
             shape = (wn, bm, wy)
             if (N // 16) % (wy * wn):
@@ -101,8 +102,8 @@ def test_forced_tiles_cover_ragged_geometries(plans):
                 seen.add("one band")
             if k > 1:
                 seen.add(("K ranges", k, K // 32 % k > 0))
-    shapes = {(c[4], c[5], 2 * c[3]) for c in TILE_EDGES}
-    assert len(shapes) == 10
+    shapes = {(c[4], c[5], 2 * c[3]) for c in TILE_EDGES} - {(8, 4, 2)}   # no such shape: the default
+    assert len(shapes) == 9
     for s in shapes:
         assert ("clamped", s) in seen and ("clamped swiglu", s) in seen, s
     assert {"interleaved", "contiguous", "one band"} <= seen
