@@ -12,6 +12,8 @@ from tests.test_gpu_parity import ROUTE_CLEAR, Lockstep, _gpu
 
 pytestmark = pytest.mark.gpu
 
+PROF_ATTN, PROF_ATTN_MERGE = 3, 4   # classes of dflash_profile_read
+
 
 @pytest.mark.parametrize("S,B,V,T,shift", [
     (1, 2, 8, 1.0, 0),          # one chunk, fewer columns than threads
@@ -205,6 +207,8 @@ def test_four_bands_of_rows_by_staged_tiles(n_seqs, block, ffn):
     (8, 2, 10, (44, 71), 9, 2),                 # blocks that straddle pages
     (6, 2, 5, (23, 37, 4), 7, 1),               # fifteen query rows
     (4, 2, 16, (1100,), 69, 1),                 # page ids beyond the first set of 32 pairs
+    (4, 2, 16, (2100, 40), 140, 1),             # ... the third set, loaded inside the loop
+    (4, 2, 16, (3150,), 197, 1),                # ... and the fourth
 ])
 def test_prefill_attention_by_tiles(heads, kv_heads, block, lens, max_seqs, pieces, monkeypatch):
     """dflash_prefill with the attention that takes two blocks of a prompt together, forced at every size."""
@@ -214,10 +218,85 @@ def test_prefill_attention_by_tiles(heads, kv_heads, block, lens, max_seqs, piec
                       taps=(0, 1), d=256, heads=heads, hd=128, ffn=512)
     prompts = [p[:k] for p, k in zip(si.make_prompts(replace(w, ctx_min=max(lens), ctx_max=max(lens))), lens)]
     ls = Lockstep(w, prompts, max_len=max(lens) + 5 * block, max_seqs=max_seqs)
+    ls.g.e.profile_enable(True)
     ls.prefill(entry=True, pieces=pieces)
+    launches = ls.g.e.profile_read()
+    ls.g.e.profile_enable(False)
+    # by tiles a pass has one attention launch a layer; by blocks, contexts of more than 64 tokens are split over workgroups and merged
+    assert launches[PROF_ATTN][1] % 2 == 0 and PROF_ATTN_MERGE not in launches, launches
     ls.check_cache([0, 1], [0])
     ls.step(plan=[(3 * s + 1) % block for s in range(n)], step_idx=0)
     assert ls.stats["reseeds"] <= 1
+
+
+@pytest.mark.parametrize("poisoned", ["one key", "all keys"])
+@pytest.mark.parametrize("ctx", [90, 1500])
+def test_nan_scores_make_a_row_nan_in_a_prefill_by_tiles(ctx, poisoned, monkeypatch):
+    """A cached key (or every one) of sequence 0 is NaN in the first layer: its new rows are NaN in the second, those of the other sequences keep their bits."""
+    import torch
+    _gpu()
+    import paper_2602_06036_amd as dfl
+    from paper_2602_06036_amd import binding as Bd
+    from tests.gpu_harness import GpuModel
+    monkeypatch.setenv("DFLASH_ATTN_TILE_WGS", "1")
+    w = tiny_workload(seed=ctx, n_layers=2, draft_layers=1, vocab=256, block=16, qk_norm=True, kv_heads=2, dtype="bf16", n_seqs=3, taps=(0,), d=256, heads=8, hd=128,
+                      ffn=256)
+    lens, new = [ctx, 13, ctx - 1], [55, 40, 17]
+    g = GpuModel(w, *si.make_weights(w), ctx + 80, max_seqs=9)
+    rng = np.random.default_rng(1)
+    g.host_lens = np.array(lens, dtype=np.int64)
+    g.seq_lens.copy_(torch.tensor(lens, dtype=torch.int32))
+    for s, n in enumerate(lens):
+        for l in range(2):
+            g.write_kv(Bd.DFLASH_POOL_TARGET, l, s, 0, *(rng.standard_normal((n, 2, 128)).astype(np.float32) for _ in range(2)))
+    tokens = torch.from_numpy(rng.integers(0, 255, sum(new)).astype(np.int32)).cuda()
+    first = torch.zeros(3, dtype=torch.int32, device="cuda")
+
+    def rows():
+        g.seq_lens.copy_(torch.tensor(lens, dtype=torch.int32))
+        g.e.profile_enable(True)
+        dfl.dflash_prefill(g.e, g.batch(), tokens, new, first)
+        launches = g.e.profile_read()
+        g.e.profile_enable(False)
+        g.e.device_status()
+        assert launches[PROF_ATTN][1] == 2 and PROF_ATTN_MERGE not in launches, launches
+        return [np.stack(g.read_kv(Bd.DFLASH_POOL_TARGET, 1, s, lens[s], new[s])) for s in range(3)]
+
+    sound = rows()
+    assert all(np.isfinite(x).all() for x in sound)
+    at, n = (77, 1) if poisoned == "one key" else (0, ctx)
+    bad = np.full((n, 2, 128), np.nan, dtype=np.float32)
+    g.write_kv(Bd.DFLASH_POOL_TARGET, 0, 0, at, bad, rng.standard_normal(bad.shape).astype(np.float32))
+    got = rows()
+    assert np.isnan(got[0]).all()
+    assert all(np.array_equal(x, y) for x, y in zip(got[1:], sound[1:]))
+
+
+def test_prefill_attention_of_a_routed_target_stays_with_the_blocks(monkeypatch):
+    """Whatever the knob asks for: the same bits of the new rows, from launches with a merge behind them."""
+    import torch
+    _gpu()
+    import paper_2602_06036_amd as dfl
+    from paper_2602_06036_amd import binding as Bd
+    from tests.gpu_harness import GpuModel
+    w = si.small_moe_workload(n_seqs=2, ctx_min=100, ctx_max=100, seed=5, n_experts=16, top_k=2)
+    wts, blobs, got = si.make_weights(w), None, []
+    new = [130, 70]
+    tokens = torch.from_numpy(np.random.default_rng(2).integers(0, 255, sum(new)).astype(np.int32)).cuda()
+    first = torch.zeros(2, dtype=torch.int32, device="cuda")
+    for wgs in ("256", "1"):
+        monkeypatch.setenv("DFLASH_ATTN_TILE_WGS", wgs)
+        g = GpuModel(w, *wts, 160, blobs=blobs, max_seqs=14)
+        blobs = g.blobs()
+        g.e.profile_enable(True)
+        dfl.dflash_prefill(g.e, g.batch(), tokens, new, first)
+        launches = g.e.profile_read()
+        g.e.profile_enable(False)
+        g.e.device_status()
+        assert launches[PROF_ATTN][1] == launches[PROF_ATTN_MERGE][1] == w.target.n_layers
+        g.host_lens = np.array(new, dtype=np.int64)
+        got.append([np.stack(g.read_kv(Bd.DFLASH_POOL_TARGET, w.target.n_layers - 1, s, 0, n)) for s, n in enumerate(new)])
+    assert all(np.isfinite(x).all() and np.array_equal(x, y) for x, y in zip(*got))
 
 
 @pytest.mark.parametrize("n_seqs,ffn,vocab,wide,tile,wm,ks", ROLLED_TILES)
