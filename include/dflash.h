@@ -188,7 +188,7 @@ int dflash_accept(dflash_ctx *ctx, const dflash_batch *batch, const int32_t *dra
  * At most 4096 rows (n_seqs * block_size): DFLASH_ECAPACITY beyond that; DFLASH_EINVAL for temperature <= 0 (greedy
  * acceptance needs no scratch at all: use dflash_accept).  All calls on one GPU share the one array: calls that overlap
  * on the same GPU (different streams, different threads) race on it and must be serialised by the caller.  Nothing in
- * the array has to start at zero: every call overwrites the entries it reads. */
+ * the array has to start at zero: no result depends on an entry that the call has not written. */
 int dflash_accept_sampled_noalloc(const float *target_logits, const float *draft_logits, const int32_t *draft_tokens,
                                   const float *uniforms, const uint64_t *rng_key, float temperature, int32_t n_seqs,
                                   int32_t block_size, int32_t vocab, int32_t *accept_len, int32_t *out_tokens, void *stream);

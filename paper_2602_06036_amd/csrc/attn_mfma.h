@@ -609,7 +609,7 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_wide_kernel(const bf16_t* __
 // The pages are staged in an LDS ring that all share, two pairs a stage (a 16-key page's K and V halves are a wavefront's copies each), one
 // barrier per stage.  Row r of a block's part is slot r % B of head r / B, so that at B = 16 a store of 64 lanes is 512 bytes of an operand
 // tile and the rows leave from registers.  Workgroup id = tile * head groups + head group: an XCD keeps to the K/V of one head group where there
-// are eight; long tiles first.
+// are eight.  The list is taken from its end: the longest tiles of a prompt first, the prompts in reverse order.
 // ------------------------------------------------------------------------------------------------
 template <int HD>
 __global__ __launch_bounds__(512, 2) void attn_prefill_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ pool, SeqGeom geo, AttnArgs aa,

@@ -149,7 +149,7 @@ __device__ __forceinline__ void lane_xor16(float& a, float& b, Op op) {   // op(
   op(lane_xor<4>(a), lane_xor<4>(b));
   op(lane_xor<8>(a), lane_xor<8>(b));
 }
-// lane: the same in all lanes.  Sums in lane order of up to 64 values in a loop of shuffles waited for LDS in every turn; the merges of split
+// Sums in lane order of up to 64 values in a loop of shuffles waited for LDS in every turn; the merges of split
 // attention end in one: a step of 4 sequences of 16384 tokens 992 -> 984 us, of one of 1000 4228 -> 4208.
 __device__ __forceinline__ float lane_value(float x, int lane) {   // lane: the same in all lanes
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), lane));

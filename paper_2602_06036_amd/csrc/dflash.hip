@@ -172,7 +172,8 @@ inline void launch_lse(hipStream_t st, const float* a, const float* b, int R, in
   else
     hipLaunchKernelGGL(lse_partial_kernel<false>, grid, block, 0, st, a, b, R, V, inv_T, part, B, arrive);
 }
-// arrive: counters that a statistics launch of the same call has zeroed; without them the sequences' tokens take a launch of their own
+// arrive: counters that a statistics launch of the same call has zeroed; without them the sequences' tokens take a launch of their own.  (dflash_accept: its
+// statistics come with the LM heads' launches, so that nothing of the call stands in front of the sweep to zero counters; a launch for that costs what it saves.)
 inline void launch_accept_sampled(hipStream_t st, const float* p_logits, const float* q_logits, RowStats ps, RowStats qs, const int32_t* draft,
                                   const float* uniforms, const uint64_t* key, int S, int B, int V, float inv_T, int32_t* accept_len,
                                   int32_t* out_tokens, float2* best, size_t room, AcceptArrive arrive = AcceptArrive{}) {

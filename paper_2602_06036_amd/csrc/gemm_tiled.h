@@ -9,8 +9,9 @@
 // activation stage for twice the weight rows, i.e. a third less operand traffic from L2 per flop, at one workgroup per CU (two
 // of the 256 x 64 tile with a ring of three slots, which the routed items use: 72 KB and 100 registers).
 //
-// What bounds it: over random operands every tiling ends at 1.2-1.45 PFLOP/s of issued MFMA work (a torch matrix product of
-// the same issued size reaches 1.1-1.47), where the clock gives way to the power limit; below that the waits at the k tiles' seams count.
+// What bounds it: over random operands the best tiling of a large launch ends at 1.3-1.5 PFLOP/s of issued MFMA work (a torch matrix product of
+// the same issued size reaches 1.1-1.47), where the clock gives way to the power limit; smaller launches, a round of the CUs or less, wait at the
+// seams of their k tiles and for their first and last ones (O projection of the 8B shape at 256 rows 0.69, QKV 0.86).
 //
 // A ring of NS LDS slots is filled by direct-to-LDS loads (global_load_lds_dwordx4: every lane's 16 bytes go straight to
 // consecutive LDS addresses, which is exactly a fragment in operand order), and the fragments are double-buffered in registers:
