@@ -459,8 +459,8 @@ struct AcceptArrive {
 // (-inf, 0).  Bound by HBM: every logit is read once (running maximum per thread), and a row is shared out over gridDim.x
 // workgroups, because a block's few rows alone leave most CUs without work.  VEC: V and both pointers allow 16-byte loads.
 // Eight sequences of 16 rows, 151936 columns, both tensors (156 MB): 2 x 99 us as one 1024-thread workgroup per row and
-// two sweeps over it, 28.4 us in this form (the anchors' draft rows left out; 29.4 with a branch per element for masked logits and bounds in
-// every round), the logits being in the memory-side cache from the pass before; 5.3 TB/s whatever the chunks, eight a row or thirty-two.  The
+// two sweeps over it, 27.6 us in this form (the anchors' draft rows left out; 29.4 with a branch per element for masked logits and bounds in
+// every round), the logits being in the memory-side cache from the pass before; 5.5 TB/s whatever the chunks, eight a row or thirty-two.  The
 // rows' log-sum-exp is off by 5.6e-8 rms and 2.6e-7 at worst, as with the library's exponential.
 __device__ __forceinline__ void lse_merge(float& m, float& s, float m2, float s2) {   // union of two sets
   const float M = fmaxf(m, m2);
