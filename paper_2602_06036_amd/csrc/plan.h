@@ -101,7 +101,7 @@ constexpr int prefill_tiles(int chunks) { return chunks > 0 ? (chunks + 1) / 2 :
 //   cached part is short the tiles' lengths differ and even the load out: six of 37 to 311 behind 0 to 600 (296 workgroups, half a round empty) 53 and 37.
 // - Behind longer contexts a block's ramp and merge do not count: 1024 behind 4000 142 and 148, 2000 behind 16000 875 and 900.
 // - A routed-expert target's attention stays with the blocks, also where the knob asks for tiles: another order of sums ahead of its routers (see stream_plan).
-// Over 1600 passes (six head layouts, blocks of 2 to 16, 1 to 32 prompts, up to 4600 tokens) the rule takes 7 % off the attention time of the passes' mean, and 24 are
+// Over 1600 passes (eight head layouts, blocks of 2 to 16, 1 to 32 prompts, up to 4600 tokens) the rule takes 7 % off the attention time of the passes' mean, and 24 are
 // more than 3 % slower by tiles; with 256 workgroups and 4608 tokens as the only conditions 4.5 % and 438.
 inline bool attention_by_tiles(int tiles, int blocks, int head_groups, int cached, int max_tokens, int from, bool routed = false) {
   const int wgs = tiles * head_groups, rounds = (wgs + 255) / 256;
